@@ -297,38 +297,10 @@ __device__ __forceinline__ unsigned long long wave_read(unsigned long long v, in
     return ((unsigned long long)hi << 32) | lo;
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave with data-parallel-primitive moves (no LDS
-// round trips): shifts by 1, 2, 4, 8 inside each row of 16 lanes (zeros shifted in), then lane 15
-// of rows 0 and 2 broadcast to rows 1 and 3, then lane 31 to the upper half.
+// Data-parallel-primitive move: lanes that it does not reach read 0.
 template <int CTRL, int ROW_MASK, bool BOUND>
-__device__ __forceinline__ float dpp_move(float a) {     // lanes the move does not reach read 0
+__device__ __forceinline__ float dpp_move(float a) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), CTRL, ROW_MASK, 0xf, BOUND));
-}
-__device__ __forceinline__ float wave_inclusive_sum(float v) {
-    v += dpp_move<0x111, 0xf, true>(v);    // row_shr:1
-    v += dpp_move<0x112, 0xf, true>(v);    // row_shr:2
-    v += dpp_move<0x114, 0xf, true>(v);    // row_shr:4
-    v += dpp_move<0x118, 0xf, true>(v);    // row_shr:8
-    v += dpp_move<0x142, 0xa, false>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp_move<0x143, 0xc, false>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
-// Sum of the lanes ABOVE each lane (exclusive suffix sum), same moves in the other direction: shifts
-// towards lower lanes inside each row of 16, the totals of the rows above added from scalars, then
-// one shift of the whole wave.  `total` = the sum over all 64 lanes.
-__device__ __forceinline__ float wave_exclusive_suffix_sum(float v, float &total) {
-    v += dpp_move<0x101, 0xf, true>(v);    // row_shl:1
-    v += dpp_move<0x102, 0xf, true>(v);    // row_shl:2
-    v += dpp_move<0x104, 0xf, true>(v);    // row_shl:4
-    v += dpp_move<0x108, 0xf, true>(v);    // row_shl:8
-    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    const int row = (int)(__lane_id() >> 4);
-    v += row == 0 ? r1 + (r2 + r3) : row == 1 ? r2 + r3 : row == 2 ? r3 : 0.f;
-    total = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-    return dpp_move<0x130, 0xf, true>(v);  // wave_shl:1: lane l reads lane l + 1, lane 63 reads 0
 }
 
 // Transposing store of one 16-byte row piece (8 bf16 of row r, columns c8 .. c8+7) into an LDS

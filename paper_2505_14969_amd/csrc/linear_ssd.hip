@@ -1,363 +1,852 @@
 // stree_linear_ssd: the ordinary causal scan of a long token sequence (the lower-triangular case of
 // the tree mask: the paper's remark in Sec. 3 that a chain reduces the method to Mamba2 with an
-// initial state), as one chunked kernel with the state passed from chunk to chunk in registers.
-// This is the prefix pass in front of tree decoding: y for every prefix token and the state after
-// the last one, which then seeds stree_tree_ssd.
+// initial state).  This is the prefix pass in front of tree decoding: y for every prefix token and
+// the state after the last one, which then seeds stree_tree_ssd.
 //
-// One workgroup (4 waves) per (batch, head) walks the sequence in chunks of 64 tokens.  With s_i the
-// inclusive cumulative log-decay inside the chunk and h the state before it,
+// The sequence is walked in chunks of 32 tokens.  With s_i the inclusive cumulative log-decay inside
+// the chunk and h the state before it,
 //
 //   y_i   = exp(s_i) h C_i + sum_{j <= i} exp(s_i - s_j) dt_j <C_i, B_j> x_j + D x_i
 //   h_new = exp(s_last) h + sum_j dt_j exp(s_last - s_j) x_j (outer) B_j
 //
-// The first line is the tree kernel's three products with the causal mask j <= i in place of the
-// ancestor mask (same transposed MFMA tiles, same accumulator layouts).  The state lives in MFMA
-// accumulators as h^T[s][p] for the whole sequence; its update is one more MFMA product
-// B^T (S x 64) times the weighted x (64 x P).  The weights are fp32 and the state must stay fp32
-// accurate over thousands of tokens, so the weighted x is fed as two bf16 terms (value and rounding
-// remainder): each product is then exact to about 2^-17, and because those errors are independent
-// and every chunk's increment is damped by the later decay, the state after 4096 tokens stays
-// within 5e-6 of the fp64 scan (a third term bought nothing measurable against the 1e-4 bound and
-// cost a third more MFMA and conversion work).  Only h as the operand of the y product is rounded
-// to bf16.
+// A wave owns 32 of the P columns of one (sequence, head), with the state h^T[s][p] (S x 32, fp32) in its MFMA
+// accumulators for a whole run of chunks; what a chunk needs beyond that flows through registers and LDS tiles.
+//
+// The three products are chained through registers by choosing which state column or token each
+// accumulator row stands for.  A 32x32 accumulator holds, in lane l, column l%32 and rows
+// 8(r/4) + 4(l/32) + r%4; a 32x32x16 operand wants, in lane l, row l%32 and eight k's at 8(l/32).
+// The k order of a product is free as long as both operands agree, so registers 8kk .. 8kk+7 of an
+// accumulator ARE an operand whose k slot e of half lh stands for row 16kk + 8(e/4) + 4lh + e%4:
+//   * Gt[j][i] = B C^T is turned (decay, causal select, bf16) into the M operand of M x in place;
+//   * h^T becomes the state operand of C h in place (rounded to bf16), its rows standing for the
+//     state columns s so that slot e is column 16kk + 8lh + e: C rows are then read in 16-byte pieces;
+//   * x^T and B^T (tokens along k) come from row-major LDS tiles through the transposing LDS read
+//     (ds_read_b64_tr_b16), which takes the rows in exactly that order.
+//
+// Precision: the weights w_j = dt_j exp(s_last - s_j) are fp32 and the state must stay fp32 accurate
+// over thousands of tokens, so w_j x_j enters as two bf16 terms (value and rounding remainder): each
+// product is then exact to about 2^-17.  Only h and M as operands of the y product are bf16.
+//
+// What bounds it: the length of one chunk's dependent chain (LDS round trips, eight products into one accumulator,
+// the transcendental functions of the decay), not a pipe -- on 8 x 4096 tokens x 80 heads vector units, matrix
+// units and LDS are busy about 30 % of the time each.  So the work is laid out in as many waves as the registers
+// admit, in the form that suits how many columns there are:
+//   * TEAMS (enough heads for every CU): per head one wave for 32 columns each and two more that bring the tiles to
+//     LDS and form M, which the columns share, one chunk ahead;
+//   * SEGMENTS (a few sequences): a workgroup's eight waves are pieces of one sequence for the same 32 columns.  Each
+//     forms the state of its piece alone, the pieces are chained through LDS (h <- exp(sum s) h + local, one wave
+//     after the other), and each wave then runs its piece again, with y, from its true initial state.  The waves
+//     share nothing in the loop: no barrier.  State only (no y): the first half is all there is.
+// Measured (80 heads x 64, S = 128, bf16), before = four waves per head, 64-token chunks, four barriers a chunk:
+// 8 x 4096 tokens 515 -> 302 us, 4 x 3000 235 -> 153 us, 1 x 4096 242 -> 84 us, 1 x 1013 65 -> 28 us; state only
+// 2 x 2000 tokens 60.5 -> 30 us (S = 64: 47 -> 23 us; S = 256, 32 heads: 94 -> 21 us).
 #include "common.hpp"
 #include "launch.hpp"
+#include <type_traits>
 
 namespace stree {
 
 namespace {
 
-constexpr int kChunk = 64;
-constexpr int kCP = kChunk + 8;    // padded row of a [.. x 64] bf16 LDS tile
+constexpr int kQ = 32;             // tokens per chunk
+constexpr int kCols = 32;          // columns of P per wave
 
-// WY = false: state only (no y, no C): a third of the LDS, so more workgroups per CU
-template <int P, int S, bool WY, typename HT>
-__global__ __launch_bounds__(kThreads) void linear_ssd_kernel(
-    int T, int H, int G, const bf16_t *__restrict__ x, long x_sn, const float *__restrict__ dt,
-    const float *__restrict__ dt_bias, const float *__restrict__ A, const bf16_t *__restrict__ Bm, long b_sn, const bf16_t *__restrict__ Cm,
-    long c_sn, const float *__restrict__ D, const HT *__restrict__ h0, bf16_t *__restrict__ y,
-    HT *__restrict__ h_out) {
-    constexpr int SP = S + 8;
-    constexpr int YT = (P / 32) * 2, YQ = YT / 4;            // Yt tiles [p][i], per wave
-    // state tiles h^T[s][p]: a wave owns one p tile and TQ consecutive s tiles, so that the weighted
-    // x fragments (which depend on the p tile only) are formed once per wave
-    constexpr int ST = S / 32, PT = P / 32, WPP = 4 / PT, TQ = ST / WPP;
-    static_assert(PT == 2 || PT == 4, "four waves share 2 or 4 p tiles");
-    constexpr int NC = kChunk * (S / 8) / kThreads;          // 16-byte chunks of C (and B) per thread
-    constexpr int NX = kChunk * (P / 8) / kThreads;          // of x per thread
-    constexpr int kRowsC = kThreads / (S / 8), kRowsX = kThreads / (P / 8);
-    static_assert(YQ >= 1 && TQ >= 1 && NC >= 1 && NX >= 1, "tile too small for 256 threads");
-    __shared__ __align__(16) bf16_t sC[WY ? kChunk * SP : 8]; // C rows; after phase 2 the y staging area
-    __shared__ __align__(16) bf16_t sB[(WY && kChunk * SP > S * kCP) ? kChunk * SP : S * kCP];   // B rows, then B^T
-    __shared__ __align__(16) bf16_t sH[WY ? P * SP : 8];      // state as bf16 operand rows [p][s]
-    __shared__ __align__(16) unsigned short sXT[P * kCP];     // x^T [p][j]
-    __shared__ __align__(16) bf16_t sM[WY ? kChunk * kCP : 8];
-    __shared__ __align__(16) float sS2[kChunk], sU[kChunk], sW[kChunk];
-    __shared__ float sDecay[1];
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
-    const int h = blockIdx.x, b = blockIdx.y, g = h / (H / G);
-    const float A2 = A[h] * 1.44269504088896340736f;          // log2 domain
-    const float bias_h = dt_bias ? dt_bias[h] : 0.f;
-    const float D_h = D ? D[h] : 0.f;
-    const char *xb = reinterpret_cast<const char *>(x + (size_t)b * T * x_sn + (size_t)h * P);
-    const char *Bb = reinterpret_cast<const char *>(Bm + (size_t)b * T * b_sn + (size_t)g * S);
-    const char *Cb = reinterpret_cast<const char *>(Cm + (size_t)b * T * c_sn + (size_t)g * S);
-    const float *dtb = dt + (size_t)b * T * H + h;
+// LDS by byte address: a tile's accesses differ by a few flipped address bits, which is then one
+// instruction (through pointers it is a flip and an addition).
+template <typename V>
+__device__ __forceinline__ __attribute__((address_space(3))) V &lds_at(uint32_t addr) {
+    return *(__attribute__((address_space(3))) V *)(uintptr_t)addr;
+}
+__device__ __forceinline__ uint32_t pack2(float a, float b) {      // bf16 pair, round to nearest even
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
 
-    // register r of lane l of tile (st, pt) is h[p = pt*32 + l%32][s = st*32 + 8(r/4) + 4(l/32) + r%4]
-    floatx16 hacc[TQ];
+// 16-bit transposing read: the 16 lanes of a group each pass the address of 4 elements (lane i: row
+// i/4, column quad i%4 of a 4 x 16 block) and lane i receives column i of the block's four rows.
+__device__ __forceinline__ s16x4 read_transposed(uint32_t addr) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(&lds_at<s16x4>(addr));
+}
+__device__ __forceinline__ bf16x8 join(s16x4 a, s16x4 b) {
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// LDS written by some lanes of this wave is about to be read by others: the LDS pipe serves a wave
+// in order, so this only keeps the compiler from moving accesses across.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The LDS of an independent wave, in bytes from its start: the chunk's B rows, with y its C rows, its x rows (32
+// columns), then per token of two chunks exp(s), s - log dt, the state's weight, s.
+template <int S, bool WY>
+struct WaveLds {
+    static constexpr int c = kQ * S * 2, x = c + (WY ? kQ * S * 2 : 0), e = x + kQ * kCols * 2;
+    static constexpr int u = e + 8 * kQ, w = u + 8 * kQ, s2 = w + 8 * kQ;
+    static constexpr int size = s2 + 8 * kQ;          // a multiple of a row: addresses inside the tile can be flipped
+    static_assert(size % 512 == 0, "");
+};
+
+// B rows keep their 16-byte pieces permuted: the 64-byte block of a row by the row's low bits (the
+// transposing read takes one block of four consecutive rows: all 64 banks once), the piece inside
+// the block by the next two (a row-parallel 16-byte store then touches every bank once as well).
+template <int S>
+__device__ __forceinline__ int b_piece_at(int row, int piece) {
+    const int blk = S == 64 ? (row >> 1) & 1 : row & 3;
+    return row * (S * 2) + ((piece ^ (blk << 2) ^ ((row >> 2) & 3)) << 4);
+}
+
+// LDS addresses differ from a lane's base address by flipped bits or a constant.  This hides the base from the
+// compiler, which would otherwise keep every one of them in a register across the chunk loop (and, having computed
+// it there, not see that the constant fits the instruction).
+__device__ __forceinline__ uint32_t fresh(uint32_t v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// One chunk of rows (B or C), whole rows to consecutive lanes, from a buffer that ends with the sequence's last
+// row: rows past it read as zeros.  (WIDE: token strides for which 64 rows outgrow a 32-bit offset; rows past
+// the sequence are then copies of the last one -- their step size is 0 and their y is not stored.)
+template <int S, bool WIDE>
+__device__ __forceinline__ void load_rows(u32x4 (&r)[S / 16], const bf16_t *base, long sn, int t0, int T, int lane) {
+    constexpr int NK = S / 16, kPieces = S / 8, kRowsAt = kQ / NK;
+    const int row0 = lane / kPieces, piece0 = lane % kPieces;
+    if constexpr (WIDE) {
 #pragma unroll
-    for (int q = 0; q < TQ; ++q) {
-        const int st = (wave % WPP) * TQ + q, pt = wave / WPP;
+        for (int q = 0; q < NK; ++q)
+            r[q] = *reinterpret_cast<const u32x4 *>(base + (size_t)min(t0 + q * kRowsAt + row0, T - 1) * sn + piece0 * 8);
+    } else {
+        const int rows = min(kQ, T - t0);
+        const auto buf = make_buffer(base + (size_t)t0 * sn, rows > 0 ? (size_t)((rows - 1) * (uint32_t)sn + S) * 2 : 0);
+        const uint32_t off = (uint32_t)row0 * (uint32_t)sn * 2 + piece0 * 16;
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (h0) {
-                const HT *src = h0 + ((size_t)b * H + h) * P * S + (size_t)(pt * 32 + l32) * S + st * 32 + 8 * rg + 4 * lh;
-                if constexpr (sizeof(HT) == 4) {
-                    v = *reinterpret_cast<const float4 *>(src);
-                } else {                                  // a bf16 state: widened exactly
-                    const uint2 w = *reinterpret_cast<const uint2 *>(src);
-                    v = make_float4(bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y));
-                }
-            }
-            hacc[q][4 * rg] = v.x; hacc[q][4 * rg + 1] = v.y; hacc[q][4 * rg + 2] = v.z; hacc[q][4 * rg + 3] = v.w;
+        for (int q = 0; q < NK; ++q)
+            r[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off, q * kRowsAt * (uint32_t)sn * 2, 0);
+    }
+}
+// x: 32 columns of two chunks, four lanes a row
+template <bool WIDE>
+__device__ __forceinline__ void load_x_rows(u32x4 (&r)[4], const bf16_t *base, long sn, int t0, int T, int lane) {
+    if constexpr (WIDE) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            r[q] = *reinterpret_cast<const u32x4 *>(base + (size_t)min(t0 + q * 16 + (lane >> 2), T - 1) * sn + (lane & 3) * 8);
+    } else {
+        const int rows = min(2 * kQ, T - t0);
+        const auto buf = make_buffer(base + (size_t)t0 * sn, rows > 0 ? (size_t)((rows - 1) * (uint32_t)sn + kCols) * 2 : 0);
+        const uint32_t off = (uint32_t)(lane >> 2) * (uint32_t)sn * 2 + (lane & 3) * 16;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            r[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off, q * 16 * (uint32_t)sn * 2, 0);
+    }
+}
+template <int S>
+__device__ __forceinline__ void stage_rows(const u32x4 (&r)[S / 16], uint32_t tile, int lane) {
+    constexpr int NK = S / 16, kRowsAt = kQ / NK;
+    const uint32_t at = fresh(tile + b_piece_at<S>(lane / (S / 8), lane % (S / 8)));
+#pragma unroll
+    for (int q = 0; q < NK; ++q)                      // row q kRowsAt + row0: what that adds to b_piece_at
+        lds_at<u32x4>((at ^ (b_piece_at<S>(q * kRowsAt, 0) & (S * 2 - 1))) + q * kRowsAt * S * 2) = r[q];
+}
+// Row operand of k step kk (lane = row, eight state columns) from base tile + b_piece_at(lane % 32, lane / 32).
+__device__ __forceinline__ bf16x8 row_operand(uint32_t at, int kk) { return lds_at<bf16x8>(at ^ (kk << 5)); }
+
+// The addresses of a lane in the transposing reads of an x tile and of a row tile.
+template <int S>
+struct TransposedAt {
+    uint32_t x, b0, b1;
+    __device__ __forceinline__ TransposedAt(uint32_t x_tile, uint32_t row_tile, int lane) {
+        const int row = 4 * (lane >> 5) + ((lane & 15) >> 2), quad = lane & 3, blk = (lane >> 4) & 1;
+        x = x_tile + row * (kCols * 2) + blk * 32 + quad * 8;
+        // B^T: lane row m of a state tile stands for state column 16(m/16) + 8(m/4%2) + 4(m/8%2) + m%4, i.e. column
+        // quads 1 and 2 of each 16 change places: that makes the accumulator an operand (see above)
+        const int bq = ((quad & 1) << 1) | (quad >> 1);
+        b0 = row_tile + b_piece_at<S>(row, blk * 2 + (bq >> 1)) + (bq & 1) * 8;
+        b1 = row_tile + b_piece_at<S>(row + 8, blk * 2 + (bq >> 1)) + (bq & 1) * 8;
+    }
+};
+// x^T operand of tokens 16kk .. 16kk+15: lane = column, slot e = token 16kk + 8(e/4) + 4lh + e%4
+__device__ __forceinline__ bf16x8 x_operand(uint32_t at, int kk) {
+    const uint32_t a = at + 16 * kk * (kCols * 2);
+    return join(read_transposed(a), read_transposed(a + 8 * kCols * 2));
+}
+template <int S>
+__device__ __forceinline__ bf16x8 b_operand(uint32_t at0, uint32_t at1, int st, int kk) {
+    return join(read_transposed((at0 ^ (st << 6)) + 16 * kk * S * 2), read_transposed((at1 ^ (st << 6)) + 16 * kk * S * 2));
+}
+__device__ __forceinline__ void widen(const bf16x8 v, float (&f)[8]) {
+    const u32x4 u = __builtin_bit_cast(u32x4, v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { f[2 * e] = bf16_lo(u[e]); f[2 * e + 1] = bf16_hi(u[e]); }
+}
+
+// Log-decays of two chunks, lane = token: s = inclusive prefix sum inside the token's chunk, behind = the sum of
+// the steps BEHIND it, sum = each chunk's total.  The state's weights dt_j exp(s_last - s_j) take `behind`, a sum
+// of its own: its rounding error is relative to that sum -- small wherever the weight is not negligible -- while
+// s_last - s_j as a difference of prefix sums carries the error of |s_last|.
+__device__ __forceinline__ void chunk_scan(float a, int lane, float &s, float &behind, float (&sum)[2]) {
+    s = a;                                            // row_shr / row_shl 1, 2, 4, 8 in rows of 16, no LDS round trips
+    s += dpp_move<0x111, 0xf, true>(s);
+    s += dpp_move<0x112, 0xf, true>(s);
+    s += dpp_move<0x114, 0xf, true>(s);
+    s += dpp_move<0x118, 0xf, true>(s);
+    s += dpp_move<0x142, 0xa, false>(s);              // row 0 into row 1, row 2 into row 3
+    float t = a;
+    t += dpp_move<0x101, 0xf, true>(t);
+    t += dpp_move<0x102, 0xf, true>(t);
+    t += dpp_move<0x104, 0xf, true>(t);
+    t += dpp_move<0x108, 0xf, true>(t);
+    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 16));
+    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 48));
+    t += (lane & 16) ? 0.f : (lane & 32) ? r3 : r1;
+    behind = dpp_move<0x130, 0xf, true>(t);           // wave_shl:1
+    if ((lane & 31) == 31) behind = 0.f;
+    sum[0] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 0));
+    sum[1] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 32));
+}
+
+// M[i][j] = Gt exp(s_i - s_j) dt_j for j <= i, as the operand of k step kk: lane = i, slot e = token
+// 16kk + 8(e/4) + 4lh + e%4, which is Gt's register 8kk + e.  u_at: this half's first quad of s_j - log2 dt_j.
+__device__ __forceinline__ bf16x8 decay_operand(const floatx16 &gt, int kk, float s2_i, uint32_t u_at, int l32, int lh) {
+    u_at = fresh(u_at);
+    const f32x4 u0 = lds_at<f32x4>(u_at + 16 * kk * 4), u1 = lds_at<f32x4>(u_at + (16 * kk + 8) * 4);
+    const float uv[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+    u32x4 m;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        // select, never 0 * inf: an overflowed weight above the diagonal is dropped
+        const int j = 16 * kk + 8 * (e >> 2) + 4 * lh + (e & 3);
+        const float a = gt[8 * kk + e] * __builtin_amdgcn_exp2f(s2_i - uv[e]);
+        const float b = gt[8 * kk + e + 1] * __builtin_amdgcn_exp2f(s2_i - uv[e + 1]);
+        m[e / 2] = pack2(j <= l32 ? a : 0.f, j + 1 <= l32 ? b : 0.f);
+    }
+    return __builtin_bit_cast(bf16x8, m);
+}
+
+// h^T <- decay h^T + B^T (w x), the weighted x as two bf16 terms.  w_at: this half's first quad of the weights.
+template <int S>
+__device__ __forceinline__ void update_state(floatx16 (&hacc)[S / 32], float decay, const float (&xf)[2][8], uint32_t w_at,
+                                             uint32_t b0, uint32_t b1) {
+    const uint32_t at0 = fresh(b0), at1 = fresh(b1);
+    w_at = fresh(w_at);
+#pragma unroll
+    for (int st = 0; st < S / 32; ++st)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) hacc[st][e] *= decay;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+        const f32x4 w0 = lds_at<f32x4>(w_at + 16 * kk * 4), w1 = lds_at<f32x4>(w_at + (16 * kk + 8) * 4);
+        const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+        u32x4 v0, v1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float a = wv[2 * e] * xf[kk][2 * e], b = wv[2 * e + 1] * xf[kk][2 * e + 1];
+            v0[e] = pack2(a, b);
+            v1[e] = pack2(a - bf16_lo(v0[e]), b - bf16_hi(v0[e]));
+        }
+        const bf16x8 t0 = __builtin_bit_cast(bf16x8, v0), t1 = __builtin_bit_cast(bf16x8, v1);
+#pragma unroll
+        for (int st = 0; st < S / 32; ++st) {
+            const bf16x8 bt = b_operand<S>(at0, at1, st, kk);
+            hacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bt, t0, hacc[st], 0, 0, 0);
+            hacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bt, t1, hacc[st], 0, 0, 0);
         }
     }
-    auto state_to_lds = [&]() {
+}
+// the state tile as the operand of k step kk of C h, rounded to bf16
+template <int ST>
+__device__ __forceinline__ bf16x8 state_operand(const floatx16 (&hacc)[ST], int kk) {
+    u32x4 v;
 #pragma unroll
-        for (int q = 0; q < TQ; ++q) {
-            const int st = (wave % WPP) * TQ + q, pt = wave / WPP;
-#pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                bf16x4 o;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = (bf16_t)hacc[q][4 * rg + e];
-                *reinterpret_cast<bf16x4 *>(&sH[(pt * 32 + l32) * SP + st * 32 + 8 * rg + 4 * lh]) = o;
-            }
-        }
-    };
-    if constexpr (WY) state_to_lds();
+    for (int e = 0; e < 4; ++e) v[e] = pack2(hacc[kk / 2][8 * (kk & 1) + 2 * e], hacc[kk / 2][8 * (kk & 1) + 2 * e + 1]);
+    return __builtin_bit_cast(bf16x8, v);
+}
 
-    // chunk inputs in registers: rows beyond T are read from the last token and zeroed when staged
-    uint4 rc[NC], rb[NC], rx[NX];
+// The chunk's y, turned around in LDS (where its x rows were), to memory in 16-byte pieces of rows; rows past the
+// sequence are dropped.  (The row goes into the vector offset of the store and the scalar offset stays 0: with a
+// scalar register there the compiler sees no hazard in overwriting the data registers right behind the store, but
+// it was seen here -- the first dword of the last lanes came from the next instruction.)
+__device__ __forceinline__ void store_y_rows(uint32_t y_tile, bf16_t *y0, int y_row, int rows, int lane) {
+    const auto yr = make_store_rsrc(y0, rows > 0 ? (uint32_t)((rows - 1) * y_row + kCols * 2) : 0u);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        __builtin_amdgcn_raw_buffer_store_b128(lds_at<u32x4>(y_tile + q * 1024 + lane * 16), yr,
+                                               ((lane >> 2) + q * 16) * y_row + (lane & 3) * 16, 0, 0);
+}
+// One chunk for the wave's 32 columns: y into the LDS tile `ys` (where the chunk's x rows were, which are dead by
+// then), the state advanced.  at_c, at_b0, at_b1, x_at: this lane's addresses in the C, B and x tiles; e_at, w_at:
+// this half's first quad of exp(s) and of the weights; m_operand(kk): the decay-weighted Gt; mid(): called between
+// C h and the rest.
+// AHEAD: the next state tile's B^T operands are read before this tile's are done with (eight registers more).
+// The issue order is set by hand (a wave's matrix instructions run beside the vector instructions behind them, as
+// long as those do not wait for them): first the k steps of C h, each with its share of the weighting of x; then
+// the state tiles, each tile's four products between the scaling of the next tile and the parts of y.
+template <int S, bool AHEAD, typename Mid, typename MOperand>
+__device__ __forceinline__ void chunk_columns(floatx16 (&hacc)[S / 32], uint32_t at_c, uint32_t at_b0, uint32_t at_b1,
+                                              uint32_t x_at, uint32_t ys, uint32_t e_at, uint32_t w_at, float decay,
+                                              float D_h, int lane, Mid &&mid, MOperand &&m_operand) {
+    constexpr int NK = S / 16, ST = S / 32;
+    const int l32 = lane & 31, lh = lane >> 5;
+    x_at = fresh(x_at), e_at = fresh(e_at), w_at = fresh(w_at);
+    const uint32_t y_at = fresh(ys + 4 * lh * (kCols * 2) + l32 * 2);
+    bf16x8 xt[2], c_op[2];
+    f32x4 wv[2];                                      // weights of slots 4q .. 4q+3, one quad ahead
+    c_op[0] = row_operand(at_c, 0);
+    c_op[1] = row_operand(at_c, 1);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) xt[kk] = x_operand(x_at, kk);
+    wv[0] = lds_at<f32x4>(w_at);
+    __builtin_amdgcn_sched_barrier(0);
+    floatx16 yt;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) yt[e] = 0.f;
+    u32x4 t0[2], t1[2];                   // w x as two bf16 terms
+    auto weigh = [&](int i) {             // slots 2i, 2i + 1
+        const uint32_t xw = __builtin_bit_cast(u32x4, xt[i / 4])[i % 4];
+        if ((i & 1) == 0 && i < 6) wv[(i / 2 + 1) & 1] = lds_at<f32x4>(w_at + 8 * (i / 2 + 1) * 4);
+        const f32x4 w4 = wv[(i / 2) & 1];
+        const float a = w4[2 * (i & 1)] * bf16_lo(xw), b2 = w4[2 * (i & 1) + 1] * bf16_hi(xw);
+        const uint32_t hi = pack2(a, b2);
+        t0[i / 4][i % 4] = hi;
+        t1[i / 4][i % 4] = pack2(a - bf16_lo(hi), b2 - bf16_hi(hi));
+    };
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+        yt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c_op[kk & 1], state_operand(hacc, kk), yt, 0, 0, 0);
+        if (kk + 2 < NK) c_op[kk & 1] = row_operand(at_c, kk + 2);
+#pragma unroll
+        for (int i = kk * 8 / NK; i < (kk + 1) * 8 / NK; ++i) weigh(i);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    mid();
+    auto scale = [&](int st, int q) {
+#pragma unroll
+        for (int e = 4 * q; e < 4 * q + 4; ++e) hacc[st][e] *= decay;
+    };
+    bf16x8 bt[2], m[2];
+    f32x4 ev = lds_at<f32x4>(e_at);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) bt[kk] = b_operand<S>(at_b0, at_b1, 0, kk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) scale(0, q);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int st = 0; st < ST; ++st) {
+        bf16x8 bn[2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            hacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                bt[q >> 1], __builtin_bit_cast(bf16x8, (q & 1) ? t1[q >> 1] : t0[q >> 1]), hacc[st], 0, 0, 0);
+            if (st + 1 < ST) {
+                if (AHEAD && (q & 1) == 0) bn[q >> 1] = b_operand<S>(at_b0, at_b1, st + 1, q >> 1);
+                if (!AHEAD && (q & 1) == 1) bt[q >> 1] = b_operand<S>(at_b0, at_b1, st + 1, q >> 1);
+                scale(st + 1, q);
+            }
+            if (st == 0) {                // rows of C h by exp(s_i), then M x
+#pragma unroll
+                for (int e = 0; e < 4; ++e) yt[4 * q + e] *= ev[e];
+                if (q < 3) ev = lds_at<f32x4>(e_at + 8 * (q + 1) * 4);
+                if (q >= 2) m[q - 2] = m_operand(q - 2);
+            }
+            if (st == ST - 1) {           // y = yt + D x (register r of yt and slot r of x are the same token)
+#pragma unroll
+                for (int r = 4 * q; r < 4 * q + 4; r += 2) {
+                    const uint32_t xw = __builtin_bit_cast(u32x4, xt[r / 8])[(r % 8) / 2];
+                    const uint32_t v = pack2(fmaf(D_h, bf16_lo(xw), yt[r]), fmaf(D_h, bf16_hi(xw), yt[r + 1]));
+                    const uint32_t at = y_at + (8 * (r >> 2) + (r & 3)) * (kCols * 2);
+                    lds_at<unsigned short>(at) = (unsigned short)v;
+                    lds_at<unsigned short>(at + kCols * 2) = (unsigned short)(v >> 16);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (st == 0) {
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) yt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m[kk], xt[kk], yt, 0, 0, 0);
+        }
+#pragma unroll
+        for (int kk = 0; kk < 2 && AHEAD; ++kk) bt[kk] = bn[kk];
+    }
+}
+
+// The state between memory and the accumulators: register r of tile st is h[p = l%32][s = st*32 + 16(r/8) + 8lh + r%8];
+// `at` = the lane's row of P, at state column 8lh.
+template <int ST>
+__device__ __forceinline__ void zero_state(floatx16 (&hacc)[ST]) {
+#pragma unroll
+    for (int st = 0; st < ST; ++st)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) hacc[st][e] = 0.f;
+}
+template <int ST, typename HT>
+__device__ __forceinline__ void load_state(floatx16 (&hacc)[ST], const HT *at) {
+#pragma unroll
+    for (int st = 0; st < ST; ++st)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {                 // half of the tile q/2, columns 4(q%2)
+            const float4 v = load_state4(at + st * 32 + 16 * (q >> 1) + 4 * (q & 1));
+            hacc[st][4 * q] = v.x; hacc[st][4 * q + 1] = v.y; hacc[st][4 * q + 2] = v.z; hacc[st][4 * q + 3] = v.w;
+        }
+}
+template <int ST, typename HT>
+__device__ __forceinline__ void store_state(const floatx16 (&hacc)[ST], HT *at) {
+#pragma unroll
+    for (int st = 0; st < ST; ++st)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            store_state4(at + st * 32 + 16 * (q >> 1) + 4 * (q & 1),
+                         make_float4(hacc[st][4 * q], hacc[st][4 * q + 1], hacc[st][4 * q + 2], hacc[st][4 * q + 3]));
+}
+
+// consecutive units (heads, then sequences) stay on one XCD: workgroups are handed out to the eight XCDs in
+// turn, and the heads of a group share their B and C rows through that XCD's L2.  -1: nothing to do.
+__device__ __forceinline__ int unit_of_block(int units) {
+    const int per = (units + 7) / 8, slot = blockIdx.x >> 3, unit = (blockIdx.x & 7) * per + slot;
+    return slot < per && unit < units ? unit : -1;
+}
+
+// ---- independent waves --------------------------------------------------------------------------------------
+// WY: y wanted.  NSEG segments x NP column groups of 32 = the waves of a workgroup.  `SR`: the state's row length;
+// without y nothing couples the state's columns, and S = 256 runs as two parts of S = 128.
+template <int S, bool WY, int NSEG, int NP, bool WIDE, typename HT>
+__global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd_kernel(
+    int T, int H, int G, int P, int SR, int units, const bf16_t *__restrict__ x, long x_sn, const float *__restrict__ dt,
+    const float *__restrict__ dt_bias, const float *__restrict__ A, const bf16_t *__restrict__ Bm, long b_sn,
+    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const HT *__restrict__ h0,
+    bf16_t *__restrict__ y, HT *__restrict__ h_out) {
+    constexpr int NK = S / 16;                        // k steps of a product over the state index
+    constexpr int ST = S / 32;                        // state tiles h^T[32 s][32 p]
+    constexpr size_t kStage = (size_t)WaveLds<S, WY>::size * NSEG * NP;
+    constexpr size_t kChain = NSEG > 1 ? (size_t)NP * S * kCols * 4 : 0;   // overlays the wave tiles
+    __shared__ __align__(512) char lds[kStage > kChain ? kStage : kChain];
+
+    const int unit = unit_of_block(units);
+    if (unit < 0) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+    const int seg = wave / NP;
+    const int pgs = P / (kCols * NP), parts = WY ? 1 : SR / S;   // workgroups per head: column groups x parts
+    const int bh = unit / (pgs * parts), b = bh / H, h = bh % H, g = h / (H / G);
+    const int p0 = ((unit % pgs) * NP + wave % NP) * kCols, s0 = WY ? 0 : unit / pgs % parts * S;
+    using L = WaveLds<S, WY>;
+    const uint32_t tile = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds + wave * L::size;
+
+    const float A2 = A[h] * 1.44269504088896340736f;  // log2 domain
+    const float bias_h = dt_bias ? dt_bias[h] : 0.f;
+    const float D_h = D ? D[h] : 0.f;
+    const bf16_t *xb = x + (size_t)b * T * x_sn + (size_t)h * P + p0;
+    const bf16_t *Bb = Bm + (size_t)b * T * b_sn + (size_t)g * SR + s0;
+    const bf16_t *Cb = Cm + (size_t)b * T * c_sn + (size_t)g * S;
+    const float *dtb = dt + (size_t)b * T * H + h;
+    const size_t state_at = ((size_t)bh * P + p0 + l32) * SR + s0 + 8 * lh;
+    bf16_t *yb = WY ? y + (size_t)b * T * H * P + (size_t)h * P + p0 : nullptr;
+
+    // pairs of chunks [pair0, pair1) of this wave's segment
+    const int pairs = (T + 2 * kQ - 1) / (2 * kQ);
+    const int pair0 = (int)((long)pairs * seg / NSEG), pair1 = (int)((long)pairs * (seg + 1) / NSEG);
+
+    floatx16 hacc[ST];
+    u32x4 rb[NK], rx[4];
+    [[maybe_unused]] u32x4 rc[NK];
     float rdt = 0.f;
-    const int rc0 = tid / (S / 8), cc0 = tid % (S / 8), rx0 = tid / (P / 8), cx0 = tid % (P / 8);
-    // loaders of the three operand groups: each is issued as soon as its registers have been staged,
-    // so that the loads of the next chunk fly for (nearly) a whole chunk period
-    auto load_xc = [&](int c0) {
-#pragma unroll
-        for (int q = 0; q < NX; ++q) {
-            const int tok = min(c0 + rx0 + q * kRowsX, T - 1);
-            rx[q] = load_stream16(xb + ((size_t)tok * x_sn + cx0 * 8) * 2);   // x and y: touched once
-        }
-        if constexpr (WY) {
-#pragma unroll
-            for (int q = 0; q < NC; ++q) {
-                const int tok = min(c0 + rc0 + q * kRowsC, T - 1);
-                rc[q] = *reinterpret_cast<const uint4 *>(Cb + ((size_t)tok * c_sn + cc0 * 8) * 2);
-            }
-        }
-        if (tid < kChunk) rdt = (c0 + tid < T) ? dtb[(size_t)(c0 + tid) * H] : 0.f;
+    auto load_x = [&](int t0) {
+        load_x_rows<WIDE>(rx, xb, x_sn, t0, T, lane);
+        rdt = dtb[(size_t)min(t0 + lane, T - 1) * H];
     };
-    auto load_b = [&](int c0) {
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-            const int tok = min(c0 + rc0 + q * kRowsC, T - 1);
-            rb[q] = *reinterpret_cast<const uint4 *>(Bb + ((size_t)tok * b_sn + cc0 * 8) * 2);
-        }
-    };
-    auto write_bt = [&](int c0) {   // B^T [s][j] from the registers
-        unsigned short *sBT = reinterpret_cast<unsigned short *>(sB);
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-            const int r = rc0 + q * kRowsC;
-            const uint32_t keep = (c0 + r < T) ? 0xffffffffu : 0u;
-            store_transposed_pair<S / 8, true>(sBT, kCP, r, cc0 * 8,
-                                         make_uint4(rb[q].x & keep, rb[q].y & keep, rb[q].z & keep, rb[q].w & keep), lane);
-        }
-    };
-    load_xc(0);
-    load_b(0);
+    const TransposedAt<S> tr(tile + L::x, tile, lane);
+    const uint32_t row_read = tile + b_piece_at<S>(l32, lh);
+    const uint32_t quads = tile + 16 * lh;            // tokens 4 lh .. 4 lh + 3 of a per-token array
 
-    for (int c0 = 0; c0 < T; c0 += kChunk) {
-        // ---- S1: stage C, B (rows), x^T; cumulative log-decay of the chunk --------------------------
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-            const int r = rc0 + q * kRowsC;
-            const uint32_t keep = (c0 + r < T) ? 0xffffffffu : 0u;
-            if constexpr (WY) {
-                *reinterpret_cast<uint4 *>(&sC[r * SP + cc0 * 8]) =
-                    make_uint4(rc[q].x & keep, rc[q].y & keep, rc[q].z & keep, rc[q].w & keep);
-                *reinterpret_cast<uint4 *>(&sB[r * SP + cc0 * 8]) =
-                    make_uint4(rb[q].x & keep, rb[q].y & keep, rb[q].z & keep, rb[q].w & keep);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < NX; ++q) {
-            const int r = rx0 + q * kRowsX;
-            const uint32_t keep = (c0 + r < T) ? 0xffffffffu : 0u;
-            store_transposed_pair<P / 8, true>(sXT, kCP, r, cx0 * 8,
-                                         make_uint4(rx[q].x & keep, rx[q].y & keep, rx[q].z & keep, rx[q].w & keep), lane);
-        }
-        if (tid < kChunk) {   // wave 0: inclusive scan of dt * A over the chunk's tokens (on the
-            // chunk's critical path: every other wave waits for it at the barrier below)
-            if (dt_bias) rdt = (c0 + lane < T) ? softplus_step(rdt + bias_h) : 0.f;   // raw projection -> step size
-            const float s2 = wave_inclusive_sum(rdt * A2);
-            // The state's weights dt_j exp(s_last - s_j) from the sum of the steps BEHIND token j, taken
-            // on its own: its rounding error is relative to that sum -- small wherever the weight is
-            // not negligible -- while s_last - s_j as a difference of prefix sums carries the error of
-            // |s_last| (a strong decay over 64 tokens: 1e-4 in the weight, the whole error budget of
-            // the state).
-            float whole;
-            const float behind = wave_exclusive_suffix_sum(rdt * A2, whole);
-            sS2[lane] = s2;
-            sU[lane] = s2 - __log2f(rdt);                      // dt = 0 -> +inf -> weight 0
-            sW[lane] = rdt * __builtin_amdgcn_exp2f(behind);
-            if (lane == 0) *sDecay = __builtin_amdgcn_exp2f(whole);
-        }
-        if constexpr (!WY) write_bt(c0);                      // no B rows needed: B^T at once
-        if (c0 + kChunk < T) {
-            load_xc(c0 + kChunk);
-            if constexpr (!WY) load_b(c0 + kChunk);
-        }
-        __syncthreads();
-
-        floatx16 acc[YQ];
+    // per-token scalars (lane = token) of two chunks to LDS; the sum of each chunk's log2 decays
+    auto stage_scalars = [&](int t0, float (&sum)[2]) {
+        float d_ = rdt;
+        if (dt_bias) d_ = softplus_step(d_ + bias_h);
+        if (t0 + lane >= T) d_ = 0.f;
+        float s, behind;
+        chunk_scan(d_ * A2, lane, s, behind, sum);
+        const uint32_t at = fresh(tile + lane * 4);
         if constexpr (WY) {
-            // ---- phase 1: Yt = h C^T, *= exp(s_i) ------------------------------------------------
+            lds_at<float>(at + L::e) = __builtin_amdgcn_exp2f(s);
+            lds_at<float>(at + L::s2) = s;
+            lds_at<float>(at + L::u) = s - __log2f(d_);   // dt = 0 -> +inf -> weight 0
+        }
+        lds_at<float>(at + L::w) = d_ * __builtin_amdgcn_exp2f(behind);
+    };
+    auto stage_x = [&](int c) {                       // the x rows of one of the two chunks
+        const uint32_t at = fresh(tile + lane * 16);
 #pragma unroll
-            for (int q = 0; q < YQ; ++q) {
-                const int t = wave + 4 * q, it = t & 1, pt = t >> 1;
+        for (int q = 0; q < 2; ++q) lds_at<u32x4>(at + L::x + q * 1024) = rx[2 * c + q];
+    };
+    auto first_loads = [&]() {
+        // The wait before a use is the least that holds on every way into a loop: the loads ahead of it are
+        // issued in the loop's own order, or every iteration would wait for loads that are meant to stay in flight.
+        load_x(pair0 * 2 * kQ);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (WY) load_rows<S, WIDE>(rc, Cb, c_sn, pair0 * 2 * kQ, T, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows<S, WIDE>(rb, Bb, b_sn, pair0 * 2 * kQ, T, lane);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    first_loads();
+    if ((NSEG == 1 || seg == 0) && h0)
+        load_state(hacc, h0 + state_at);
+    else
+        zero_state(hacc);
+
+    // ---- the state at the end of the segment: of the first one from h0, of the others from a zero state -------
+    if constexpr (NSEG > 1 || !WY) {
+        float sum2 = 0.f;
+#pragma unroll 1
+        for (int pr = pair0; pr < pair1; ++pr) {
+            const int t0 = pr * 2 * kQ;
+            float sum[2];
+            stage_scalars(t0, sum);
+            sum2 += sum[0] + sum[1];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
-                const bf16_t *ap = &sH[(pt * 32 + l32) * SP + 8 * lh];
-                const bf16_t *bp = &sC[(it * 32 + l32) * SP + 8 * lh];
+            for (int c = 0; c < 2; ++c) {
+                stage_x(c);
+                if (c == 1) load_x(t0 + 2 * kQ);      // (past the end: an empty buffer)
+                __builtin_amdgcn_sched_barrier(0);
+                stage_rows<S>(rb, tile, lane);
+                load_rows<S, WIDE>(rb, Bb, b_sn, t0 + (c + 1) * kQ, T, lane);
+                wave_lds_fence();
+                float xf[2][8];
 #pragma unroll
-                for (int k0 = 0; k0 < S; k0 += 16)
-                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(ap + k0),
-                                                                     *reinterpret_cast<const bf16x8 *>(bp + k0), acc[q], 0, 0, 0);
-                const float e2 = __builtin_amdgcn_exp2f(sS2[it * 32 + l32]);
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[q][e] *= e2;
+                for (int kk = 0; kk < 2; ++kk) widen(x_operand(tr.x, kk), xf[kk]);
+                update_state<S>(hacc, __builtin_amdgcn_exp2f(sum[c]), xf, quads + L::w + c * kQ * 4, tr.b0, tr.b1);
+                wave_lds_fence();
             }
-            // ---- phase 2: Gt = B C^T, causal mask and decay -> M (tile jt = 1, it = 0 has j > i) ----
-            {
-                const int it = wave & 1, jt = wave >> 1;
-                if (!(jt == 1 && it == 0)) {
-                    floatx16 gt;
+        }
+        if constexpr (NSEG > 1) {
+            if constexpr (WY) first_loads();          // of the second pass: in flight through the chain
+            float4 *chain = reinterpret_cast<float4 *>(lds) + (size_t)(wave % NP) * (ST * 4) * 64 + lane;
+            const float whole = __builtin_amdgcn_exp2f(sum2);
+#pragma unroll 1
+            for (int k = 0; k < NSEG; ++k) {
+                // h0 is read again before h_out, which may be h0, is written (vmcnt(0))
+                if (WY && k == NSEG - 1 && seg == 0) __builtin_amdgcn_s_waitcnt(0x0f70);
+                __syncthreads();                      // first: the tiles are dead; then: the state is there
+                if (seg != k) continue;
+                auto advance = [&](auto &&put) {      // put(state tile, quarter, state at the segment's end)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) gt[e] = 0.f;
-                    const bf16_t *ap = &sB[(jt * 32 + l32) * SP + 8 * lh];
-                    const bf16_t *bp = &sC[(it * 32 + l32) * SP + 8 * lh];
+                    for (int st = 0; st < ST; ++st)
 #pragma unroll
-                    for (int k0 = 0; k0 < S; k0 += 16)
-                        gt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(ap + k0),
-                                                                     *reinterpret_cast<const bf16x8 *>(bp + k0), gt, 0, 0, 0);
-                    const int il = it * 32 + l32;
-                    const float s2_i = sS2[il];
-#pragma unroll
-                    for (int rg = 0; rg < 4; ++rg) {
-                        const int jl = jt * 32 + 8 * rg + 4 * lh;
-                        const float4 uj = *reinterpret_cast<const float4 *>(&sU[jl]);
-                        const float ujv[4] = {uj.x, uj.y, uj.z, uj.w};
-                        bf16x4 o;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            // select, never 0 * inf: an overflowed weight above the diagonal is dropped
-                            const uint32_t keep = (jl + e <= il) ? 0xffffffffu : 0u;
-                            const float v = gt[4 * rg + e] * __builtin_amdgcn_exp2f(s2_i - ujv[e]);
-                            o[e] = (bf16_t)__uint_as_float(__float_as_uint(v) & keep);
+                        for (int q = 0; q < 4; ++q) {
+                            const float4 v = chain[(st * 4 + q) * 64];
+                            put(st, q, make_float4(fmaf(whole, v.x, hacc[st][4 * q]), fmaf(whole, v.y, hacc[st][4 * q + 1]),
+                                                   fmaf(whole, v.z, hacc[st][4 * q + 2]), fmaf(whole, v.w, hacc[st][4 * q + 3])));
+                            hacc[st][4 * q] = v.x; hacc[st][4 * q + 1] = v.y;    // what this segment's y starts from
+                            hacc[st][4 * q + 2] = v.z; hacc[st][4 * q + 3] = v.w;
                         }
-                        *reinterpret_cast<bf16x4 *>(&sM[il * kCP + jl]) = o;
+                };
+                if (k == NSEG - 1) {
+                    advance([&](int st, int q, float4 n) { store_state4(h_out + state_at + st * 32 + 16 * (q >> 1) + 4 * (q & 1), n); });
+                } else if (k > 0) {
+                    advance([&](int st, int q, float4 n) { chain[(st * 4 + q) * 64] = n; });
+                } else {
+#pragma unroll
+                    for (int st = 0; st < ST; ++st)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            chain[(st * 4 + q) * 64] = make_float4(hacc[st][4 * q], hacc[st][4 * q + 1], hacc[st][4 * q + 2], hacc[st][4 * q + 3]);
+                    if constexpr (WY) {
+                        if (h0)
+                            load_state(hacc, h0 + state_at);
+                        else
+                            zero_state(hacc);
                     }
                 }
             }
+            if constexpr (WY) __syncthreads();        // the chain buffer is the wave tiles' again
         }
-
-        // ---- B^T over the dead B rows (from the registers), then the next chunk's B loads ------------
-        if constexpr (WY) {
-            __syncthreads();
-            write_bt(c0);
-            if (c0 + kChunk < T) load_b(c0 + kChunk);
-        }
-
-        if constexpr (WY) {
-            // ---- phase 3: Yt += Xt M^T over j <= i; y = Yt + D x; 64-byte row pieces via a per-wave
-            //      turn in LDS (the C rows are dead) ------------------------------------------------
-            char *ys = reinterpret_cast<char *>(sC) + wave * 2048;
-            char *yb = reinterpret_cast<char *>(y + ((size_t)b * T + c0) * H * P + (size_t)h * P);
-#pragma unroll
-            for (int q = 0; q < YQ; ++q) {
-                const int t = wave + 4 * q, it = t & 1, pt = t >> 1, il = it * 32 + l32;
-                float xv[16];
-#pragma unroll
-                for (int rg = 0; rg < 4; ++rg)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        xv[4 * rg + e] = __uint_as_float((uint32_t)sXT[transposed_at<true>(kCP, pt * 32 + 8 * rg + 4 * lh + e, il)] << 16);
-                const bf16_t *xt = reinterpret_cast<const bf16_t *>(sXT);
-                const bf16_t *bp = &sM[il * kCP + 8 * lh];
-                const int ksteps = it ? 4 : 2;
-                for (int j = 0; j < ksteps; ++j)
-                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        *reinterpret_cast<const bf16x8 *>(xt + transposed_at<true>(kCP, pt * 32 + l32, 8 * lh + 16 * j)),
-                        *reinterpret_cast<const bf16x8 *>(bp + 16 * j), acc[q], 0, 0, 0);
-                // row r of the wave's tile keeps its 16-byte chunk c at slot c ^ ((r >> 2) & 3)
-#pragma unroll
-                for (int rg = 0; rg < 4; ++rg) {
-                    bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = (bf16_t)fmaf(D_h, xv[4 * rg + e], acc[q][4 * rg + e]);
-                    *reinterpret_cast<bf16x4 *>(ys + l32 * 64 + ((rg ^ ((l32 >> 2) & 3)) * 16) + lh * 8) = o;
-                }
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const int row = half * 16 + (lane >> 2), rcc = lane & 3;
-                    const uint4 v = *reinterpret_cast<const uint4 *>(ys + row * 64 + ((rcc ^ ((row >> 2) & 3)) * 16));
-                    const int tok = it * 32 + row;
-                    if (c0 + tok < T)
-                        store_stream16(yb + ((size_t)tok * H * P + pt * 32 + rcc * 8) * 2, v);
-                }
-            }
-            __syncthreads();   // B^T is complete
-        }
-
-        // ---- state: h^T = exp(s_last) h^T + B^T (w x), the weighted x as two bf16 terms --------------
-        {
-            const float decay = *sDecay;
-            const bf16_t *sBT = sB;
-#pragma unroll
-            for (int q = 0; q < TQ; ++q)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) hacc[q][e] *= decay;
-            const int pt = wave / WPP;
-#pragma unroll
-            for (int k0 = 0; k0 < kChunk; k0 += 16) {
-                const float4 w0 = *reinterpret_cast<const float4 *>(&sW[k0 + 8 * lh]);
-                const float4 w1 = *reinterpret_cast<const float4 *>(&sW[k0 + 8 * lh + 4]);
-                const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-                const uint4 xr = *reinterpret_cast<const uint4 *>(&sXT[transposed_at<true>(kCP, pt * 32 + l32, 8 * lh + k0)]);
-                const float xf[8] = {bf16_lo(xr.x), bf16_hi(xr.x), bf16_lo(xr.y), bf16_hi(xr.y),
-                                     bf16_lo(xr.z), bf16_hi(xr.z), bf16_lo(xr.w), bf16_hi(xr.w)};
-                bf16x8 t0, t1;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float v = wv[e] * xf[e];
-                    t0[e] = (bf16_t)v;
-                    t1[e] = (bf16_t)(v - (float)t0[e]);
-                }
-#pragma unroll
-                for (int q = 0; q < TQ; ++q) {
-                    const int st = (wave % WPP) * TQ + q;
-                    const bf16x8 bt = *reinterpret_cast<const bf16x8 *>(&sBT[transposed_at<true>(kCP, st * 32 + l32, 8 * lh + k0)]);
-                    hacc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bt, t0, hacc[q], 0, 0, 0);
-                    hacc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bt, t1, hacc[q], 0, 0, 0);
-                }
-            }
-        }
-        if (WY && c0 + kChunk < T) state_to_lds();   // the next chunk's phase 1 operand
-        __syncthreads();
     }
-    // ---- final state ------------------------------------------------------------------------------
+
+    // ---- y ---------------------------------------------------------------------------------------
+    if constexpr (WY) {
+        const int y_row = H * P * 2;                  // bytes (32 rows: below 2^31, see the envelope)
+#pragma unroll 1
+        for (int pr = pair0; pr < pair1; ++pr) {
+            const int t0 = pr * 2 * kQ;
+            float sum[2];
+            stage_scalars(t0, sum);
 #pragma unroll
-    for (int q = 0; q < TQ; ++q) {
-        const int st = (wave % WPP) * TQ + q, pt = wave / WPP;
+            for (int c = 0; c < 2; ++c) {
+                const int tc = t0 + c * kQ;
+                stage_x(c);
+                if (c == 1) load_x(t0 + 2 * kQ);
+                __builtin_amdgcn_sched_barrier(0);
+                stage_rows<S>(rc, tile + L::c, lane);
+                load_rows<S, WIDE>(rc, Cb, c_sn, tc + kQ, T, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                stage_rows<S>(rb, tile, lane);
+                load_rows<S, WIDE>(rb, Bb, b_sn, tc + kQ, T, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                wave_lds_fence();
+                // Gt = B C^T (column = token i, rows = tokens j), decay-weighted: the M operand
+                const uint32_t at_b = fresh(row_read), at_c = fresh(row_read + L::c);
+                floatx16 gt;
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-            HT *dst = h_out + ((size_t)b * H + h) * P * S + (size_t)(pt * 32 + l32) * S + st * 32 + 8 * rg + 4 * lh;
-            if constexpr (sizeof(HT) == 4)
-                *reinterpret_cast<float4 *>(dst) =
-                    make_float4(hacc[q][4 * rg], hacc[q][4 * rg + 1], hacc[q][4 * rg + 2], hacc[q][4 * rg + 3]);
-            else                                          // a bf16 state: rounded to nearest even once, here
-                *reinterpret_cast<uint2 *>(dst) =
-                    pack_bf16x4(hacc[q][4 * rg], hacc[q][4 * rg + 1], hacc[q][4 * rg + 2], hacc[q][4 * rg + 3]);
+                for (int e = 0; e < 16; ++e) gt[e] = 0.f;
+#pragma unroll
+                for (int kk = 0; kk < NK; ++kk)
+                    gt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_operand(at_b, kk), row_operand(at_c, kk), gt, 0, 0, 0);
+                const float s2_i = lds_at<float>(tile + L::s2 + (c * kQ + l32) * 4);
+                bf16x8 m[2];
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) m[kk] = decay_operand(gt, kk, s2_i, quads + L::u + c * kQ * 4, l32, lh);
+                __builtin_amdgcn_sched_barrier(0);
+                chunk_columns<S, false>(hacc, at_c, fresh(tr.b0), fresh(tr.b1), tr.x, tile + L::x, quads + L::e + c * kQ * 4,
+                                 quads + L::w + c * kQ * 4, __builtin_amdgcn_exp2f(sum[c]), D_h, lane, [] {},
+                                 [&](int kk) { return m[kk]; });
+                wave_lds_fence();
+                store_y_rows(tile + L::x, yb + (size_t)tc * H * P, y_row, min(kQ, T - tc), lane);
+                wave_lds_fence();
+            }
         }
+    }
+    if constexpr (NSEG == 1) store_state(hacc, h_out + state_at);
+}
+
+// ---- teams ------------------------------------------------------------------------------------------------
+// One workgroup per (sequence, head): NM = P/32 waves that own 32 columns each, and two helpers that work a chunk ahead
+// of them: they bring the rows to LDS (one C and x, the other B and the per-token scalars), and behind a barrier
+// form Gt and from it the M operand (which do not depend on the columns), half of M each.  The tiles are double
+// buffered: two barriers per chunk, which the others meet between C h and the state.  (One helper that does it all
+// is the slowest wave of the team: 1.2 us a chunk with one team on the CU against 1.05 us; with three teams on it,
+// where the issue slots count, it is 5 to 12 % ahead: 296 and 303 us for 8 x 4096 tokens, 144 and 153 for 4 x 3000.)
+template <int S, int NM>
+struct TeamLds {
+    static constexpr int rows = kQ * S * 2;           // bytes of one tile
+    static constexpr int c = 0, b = 2 * rows, x = b + 2 * rows, m = x + NM * 2 * kQ * kCols * 2, e = m + 2 * 2048;
+    static constexpr int w = e + 2 * 2 * kQ * 4, u = w + 2 * 2 * kQ * 4, s2 = u + 2 * kQ * 4, sum = s2 + 2 * kQ * 4, size = sum + 32;
+};
+template <int S, int NM, typename HT>
+__global__ __launch_bounds__(64 * (NM + 2), (S == 256 ? 2 : 3)) void linear_ssd_team_kernel(
+    int T, int H, int G, int units, const bf16_t *__restrict__ x, long x_sn, const float *__restrict__ dt,
+    const float *__restrict__ dt_bias, const float *__restrict__ A, const bf16_t *__restrict__ Bm, long b_sn,
+    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const HT *__restrict__ h0,
+    bf16_t *__restrict__ y, HT *__restrict__ h_out) {
+    constexpr int NK = S / 16, ST = S / 32, P = NM * kCols;
+    using L = TeamLds<S, NM>;
+    __shared__ __align__(512) char lds[L::size];
+    const int unit = unit_of_block(units);
+    if (unit < 0) return;
+    // The waves of a workgroup go to the four SIMDs in turn: every other workgroup of a CU (32 CUs to an XCD) swaps
+    // the roles around, so that the column waves of all of them do not share two SIMDs.
+    const int hw_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = NM == 2 && ((blockIdx.x >> 8) & 1) ? hw_wave ^ 2 : hw_wave;
+    const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+    const int bh = unit, b = bh / H, h = bh % H, g = h / (H / G);
+    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    const int pairs = (T + 2 * kQ - 1) / (2 * kQ);
+
+    if (wave >= NM) {
+        const bool second = wave > NM;                // brings B and the scalars; the first one brings C and x
+        const float A2 = A[h] * 1.44269504088896340736f;
+        const float bias_h = dt_bias ? dt_bias[h] : 0.f;
+        const bf16_t *rows = second ? Bm + (size_t)b * T * b_sn + (size_t)g * S : Cm + (size_t)b * T * c_sn + (size_t)g * S;
+        const long sn = second ? b_sn : c_sn;
+        const float *dtb = dt + (size_t)b * T * H + h;
+        const bf16_t *xb = x + (size_t)b * T * x_sn + (size_t)h * P;
+        // x comes from memory, not from L2 like the others: two chunks ahead
+        constexpr int XR = NM * kCols / 16;
+        u32x4 rr[NK], rx[2][XR];
+        float rdt = 0.f;
+        auto load_x = [&](u32x4 (&r)[XR], int t0) {
+            const int n = min(kQ, T - t0);
+            const auto buf = make_buffer(xb + (size_t)t0 * x_sn, n > 0 ? (size_t)((n - 1) * (uint32_t)x_sn + P) * 2 : 0);
+            const uint32_t off = (uint32_t)(lane / (P / 8)) * (uint32_t)x_sn * 2 + (lane % (P / 8)) * 16;
+#pragma unroll
+            for (int q = 0; q < XR; ++q)
+                r[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off, q * (512 / P) * (uint32_t)x_sn * 2, 0);
+        };
+        // column tiles of [32 tokens][32 columns]
+        const uint32_t x_store = base + L::x + (lane % (P / 8)) / 4 * (2 * kQ * kCols * 2) + (lane / (P / 8)) * (kCols * 2) + (lane & 3) * 16;
+        const uint32_t tile = base + (second ? L::b : L::c), row_read = base + b_piece_at<S>(l32, lh);
+        auto prepare = [&](auto role) {
+            constexpr bool kB = decltype(role)::value;
+            if constexpr (kB) {
+                rdt = dtb[(size_t)min(lane, T - 1) * H];
+            } else {
+                load_x(rx[0], 0);
+                __builtin_amdgcn_sched_barrier(0);
+                load_x(rx[1], kQ);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load_rows<S, false>(rr, rows, sn, 0, T, lane);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+            for (int pr = 0; pr < pairs; ++pr) {
+                const int t0 = pr * 2 * kQ;
+                if constexpr (kB) {
+                    float d_ = rdt, s, behind, sum[2];
+                    if (dt_bias) d_ = softplus_step(d_ + bias_h);
+                    if (t0 + lane >= T) d_ = 0.f;
+                    chunk_scan(d_ * A2, lane, s, behind, sum);
+                    const uint32_t at = base + lane * 4, slot = (pr & 1) * 2 * kQ * 4;     // (read by the others up to a pair later)
+                    lds_at<float>(at + L::e + slot) = __builtin_amdgcn_exp2f(s);
+                    lds_at<float>(at + L::w + slot) = d_ * __builtin_amdgcn_exp2f(behind);
+                    lds_at<float>(at + L::s2) = s;
+                    lds_at<float>(at + L::u) = s - __log2f(d_);   // dt = 0 -> +inf -> weight 0
+                    if (lane < 2) lds_at<float>(at + L::sum + (pr & 1) * 8) = __builtin_amdgcn_exp2f(lane ? sum[1] : sum[0]);
+                    rdt = dtb[(size_t)min(t0 + 2 * kQ + lane, T - 1) * H];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const int tn = t0 + (c + 1) * kQ;
+                    if constexpr (!kB) {
+#pragma unroll
+                        for (int q = 0; q < XR; ++q) lds_at<u32x4>(x_store + c * (kQ * kCols * 2) + q * (512 / P) * (kCols * 2)) = rx[c][q];
+                        load_x(rx[c], tn + kQ);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    stage_rows<S>(rr, tile + c * L::rows, lane);
+                    load_rows<S, false>(rr, rows, sn, tn, T, lane);
+                    __builtin_amdgcn_sched_barrier(0);
+                    __syncthreads();
+                    // both: Gt, and half of M each
+                    const uint32_t at_c = fresh(row_read + L::c + c * L::rows), at_b = fresh(row_read + L::b + c * L::rows);
+                    floatx16 gt;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) gt[e] = 0.f;
+#pragma unroll
+                    for (int kk = 0; kk < NK; ++kk)
+                        gt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_operand(at_b, kk), row_operand(at_c, kk), gt, 0, 0, 0);
+                    const float s2_i = lds_at<float>(base + L::s2 + (c * kQ + l32) * 4);
+                    constexpr int kk = kB;
+                    lds_at<bf16x8>(base + L::m + c * 2048 + kk * 1024 + lane * 16) =
+                        decay_operand(gt, kk, s2_i, base + 16 * lh + L::u + c * kQ * 4, l32, lh);
+                    __syncthreads();
+                }
+            }
+            __syncthreads();                          // (the last chunk is still being worked on)
+            __syncthreads();
+        };
+        if (second)
+            prepare(std::true_type{});
+        else
+            prepare(std::false_type{});
+    } else {
+        const int p0 = wave * kCols;
+        const float D_h = D ? D[h] : 0.f;
+        bf16_t *yb = y + (size_t)b * T * H * P + (size_t)h * P + p0;
+        const size_t state_at = ((size_t)bh * P + p0 + l32) * S + 8 * lh;
+        const uint32_t x_tile = base + L::x + wave * (2 * kQ * kCols * 2);
+        const int y_row = H * P * 2;
+        floatx16 hacc[ST];
+        if (h0)
+            load_state(hacc, h0 + state_at);
+        else
+            zero_state(hacc);
+        const TransposedAt<S> tr(x_tile, base + L::b, lane);
+        const uint32_t row_read = base + L::c + b_piece_at<S>(l32, lh);
+        __syncthreads();                              // the first chunk is being prepared
+        __syncthreads();
+#pragma unroll 1
+        for (int pr = 0; pr < pairs; ++pr) {
+            const int t0 = pr * 2 * kQ;
+            const uint32_t slot = (pr & 1) * 2 * kQ * 4;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int tc = t0 + c * kQ;
+                const uint32_t quads = base + 16 * lh + slot + c * kQ * 4, x_at = tr.x + c * kQ * kCols * 2;
+                chunk_columns<S, true>(
+                    hacc, fresh(row_read + c * L::rows), fresh(tr.b0 + c * L::rows), fresh(tr.b1 + c * L::rows), x_at,
+                    x_tile + c * (kQ * kCols * 2), quads + L::e, quads + L::w,
+                    lds_at<float>(base + L::sum + (pr & 1) * 8 + c * 4), D_h, lane, [] { __syncthreads(); },
+                    [&](int kk) { return lds_at<bf16x8>(base + L::m + c * 2048 + kk * 1024 + lane * 16); });
+                wave_lds_fence();
+                store_y_rows(x_tile + c * (kQ * kCols * 2), yb + (size_t)tc * H * P, y_row, min(kQ, T - tc), lane);
+                __syncthreads();
+            }
+        }
+        store_state(hacc, h_out + state_at);
     }
 }
 
-template <int P, int S, typename HT>
-hipError_t launch_ps(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm,
-                     const void *Cm, const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
-    if (y)
-        hipLaunchKernelGGL((linear_ssd_kernel<P, S, true, HT>), dim3(d.nheads, d.batch), dim3(kThreads), 0, st, d.nnodes,
-                           d.nheads, d.ngroups, (const bf16_t *)x, (long)d.x_stride_n, dt, step_bias(d), A,
-                           (const bf16_t *)Bm, (long)d.b_stride_n, (const bf16_t *)Cm, (long)d.c_stride_n, D,
-                           (const HT *)h0, (bf16_t *)y, (HT *)h_out);
-    else
-        hipLaunchKernelGGL((linear_ssd_kernel<P, S, false, HT>), dim3(d.nheads, d.batch), dim3(kThreads), 0, st, d.nnodes,
-                           d.nheads, d.ngroups, (const bf16_t *)x, (long)d.x_stride_n, dt, step_bias(d), A,
-                           (const bf16_t *)Bm, (long)d.b_stride_n, (const bf16_t *)Cm, (long)d.c_stride_n, D,
-                           (const HT *)h0, (bf16_t *)y, (HT *)h_out);
+template <int S, int NM, typename HT>
+hipError_t launch_team(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm, const void *Cm,
+                       const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
+    const int units = d.batch * d.nheads;
+    hipLaunchKernelGGL((linear_ssd_team_kernel<S, NM, HT>), dim3(8 * ((units + 7) / 8)), dim3(64 * (NM + 2)), 0, st,
+                       d.nnodes, d.nheads, d.ngroups, units, (const bf16_t *)x, (long)d.x_stride_n, dt, step_bias(d), A,
+                       (const bf16_t *)Bm, (long)d.b_stride_n, (const bf16_t *)Cm, (long)d.c_stride_n, D, (const HT *)h0,
+                       (bf16_t *)y, (HT *)h_out);
     return hipGetLastError();
 }
 
-template <int P, int S>
-hipError_t launch_p(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm,
-                    const void *Cm, const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
-    if (d.state_dtype == STREE_BF16) return launch_ps<P, S, bf16_t>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    return launch_ps<P, S, float>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+template <int S, bool WY, int NSEG, int NP, bool WIDE, typename HT>
+hipError_t launch_n(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm, const void *Cm,
+                    const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
+    const int units = d.batch * d.nheads * (d.headdim / (kCols * NP)) * (WY ? 1 : d.dstate / S);
+    hipLaunchKernelGGL((linear_ssd_kernel<S, WY, NSEG, NP, WIDE, HT>), dim3(8 * ((units + 7) / 8)), dim3(64 * NSEG * NP), 0, st,
+                       d.nnodes, d.nheads, d.ngroups, d.headdim, d.dstate, units, (const bf16_t *)x, (long)d.x_stride_n, dt,
+                       step_bias(d), A, (const bf16_t *)Bm, (long)d.b_stride_n, (const bf16_t *)Cm, (long)d.c_stride_n,
+                       D, (const HT *)h0, (bf16_t *)y, (HT *)h_out);
+    return hipGetLastError();
+}
+
+// 64 rows beyond a 32-bit byte offset: never met in earnest, one form of the kernel takes them all
+bool wide_strides(const stree_dims &d) {
+    return d.x_stride_n >= (1L << 25) || d.b_stride_n >= (1L << 25) || d.c_stride_n >= (1L << 25);
+}
+
+// State only: waves without segments, and the chunk pairs each would walk.  From 8 pairs on a workgroup's waves
+// are segments (one row of chunks per wave costs less than the eight steps of the chain; below, and where y is
+// wanted by a team, the state is formed chunk after chunk).  Eight where a round of workgroups holds them all,
+// four of them else: half of a second round idle costs more than segments twice as long (S = 128, 320 column
+// groups x 2000 tokens: 38 us with eight, 30 us with four).
+template <int S, typename HT>
+hipError_t launch_state(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm, const void *Cm,
+                        const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
+    if (wide_strides(d)) return launch_n<S, false, 1, 2, true, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    const long waves = (long)d.batch * d.nheads * (d.headdim / kCols) * (d.dstate / S);
+    const int pairs = (d.nnodes + 2 * kQ - 1) / (2 * kQ);
+    if (pairs < 8) return launch_n<S, false, 1, 2, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    if (waves * 8 > (S == 64 ? 4096 : 2048)) return launch_n<S, false, 4, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    return launch_n<S, false, 8, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+}
+
+// With y: segments where eight times the waves still fit the chip at two a SIMD and each has a chunk pair and a
+// half (80 heads x 64, S = 128: 84 us against the team's 126 us for 4096 tokens; 28 against 36 for 1013; at 700
+// tokens they meet), teams for the rest (160 heads, 1500 tokens: 52 us, two segments each 67 us; 640 heads, 4096
+// tokens: 300 us, independent waves without segments 410 us).  S = 256: the segments' registers do not fit.
+template <int S, typename HT>
+hipError_t launch_y(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm, const void *Cm,
+                    const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
+    if (wide_strides(d)) return launch_n<S, true, 1, 2, true, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    const long waves = (long)d.batch * d.nheads * (d.headdim / kCols);
+    const int pairs = (d.nnodes + 2 * kQ - 1) / (2 * kQ);
+    if constexpr (S != 256) {
+        if (pairs >= 12 && waves * 8 <= 2048) return launch_n<S, true, 8, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    }
+    if constexpr (S == 128) {
+        if (d.headdim == 128) return launch_team<S, 4, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    }
+    return launch_team<S, 2, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+}
+
+template <typename HT>
+hipError_t launch_h(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm, const void *Cm,
+                    const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
+    if (!y) return d.dstate == 64 ? launch_state<64, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st)
+                                  : launch_state<128, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    switch (d.dstate) {
+        case 64: return launch_y<64, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+        case 128: return launch_y<128, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+        case 256: return launch_y<256, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -374,12 +863,8 @@ bool linear_ssd_supported(const stree_dims &d, const void *x, const void *Bm, co
 
 hipError_t launch_linear_ssd(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm,
                              const void *Cm, const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
-    const int P = d.headdim, S = d.dstate;
-    if (P == 64 && S == 128) return launch_p<64, 128>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    if (P == 64 && S == 64) return launch_p<64, 64>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    if (P == 64 && S == 256) return launch_p<64, 256>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    if (P == 128 && S == 128) return launch_p<128, 128>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    return hipErrorInvalidValue;
+    return d.state_dtype == STREE_BF16 ? launch_h<bf16_t>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st)
+                                       : launch_h<float>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
 }
 
 }  // namespace stree
