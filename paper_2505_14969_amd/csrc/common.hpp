@@ -333,6 +333,13 @@ __device__ __forceinline__ void store_transposed_pair(unsigned short *tile, int 
     dst[3 * ldw] = (lo1 >> 16) | (hi1 & 0xffff0000u);
 }
 
+// The unit of work of a workgroup, for grids of 8 ceil(units / 8) workgroups: consecutive units (heads, then sequences) stay on one XCD: workgroups are handed out to the eight XCDs in
+// turn, and the heads of a group share their B and C rows through that XCD's L2.  -1: nothing to do.
+__device__ __forceinline__ int unit_of_block(int units) {
+    const int per = (units + 7) / 8, slot = blockIdx.x >> 3, unit = (blockIdx.x & 7) * per + slot;
+    return slot < per && unit < units ? unit : -1;
+}
+
 // Path of the accepted node k for trees of at most 64 nodes, by one wave with no LDS and no
 // barrier: lane j owns node j; pointer doubling over the parent array with cross-lane reads
 // gives every lane s_j (the paper's A_tree) and its ancestor bit row; lane k's values are then

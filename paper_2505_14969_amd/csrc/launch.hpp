@@ -58,6 +58,12 @@ hipError_t launch_tree_ssd_fma(const stree_dims &d, const int32_t *parent, const
                                const float *A, const void *Bm, const void *Cm, const float *D,
                                const void *h0, void *y, int32_t *status, hipStream_t st);
 
+// fp32 on the fp32 matrix units: at most 64 nodes, dstate 64 / 128 / 256, 16-byte aligned rows
+bool tree_ssd_f32_supported(const stree_dims &d, const void *Bm, const void *Cm, const void *h0);
+hipError_t launch_tree_ssd_f32(const stree_dims &d, const int32_t *parent, const void *x, const float *dt,
+                               const float *A, const void *Bm, const void *Cm, const float *D, const void *h0,
+                               void *y, int32_t *status, hipStream_t st);
+
 // true when the MFMA kernel covers these dims / alignments
 bool tree_ssd_mfma_supported(const stree_dims &d, const void *x, const void *Bm, const void *Cm,
                              const void *h0, const void *y);

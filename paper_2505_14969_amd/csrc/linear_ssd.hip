@@ -407,13 +407,6 @@ __device__ __forceinline__ void store_state(const floatx16 (&hacc)[ST], HT *at) 
                          make_float4(hacc[st][4 * q], hacc[st][4 * q + 1], hacc[st][4 * q + 2], hacc[st][4 * q + 3]));
 }
 
-// consecutive units (heads, then sequences) stay on one XCD: workgroups are handed out to the eight XCDs in
-// turn, and the heads of a group share their B and C rows through that XCD's L2.  -1: nothing to do.
-__device__ __forceinline__ int unit_of_block(int units) {
-    const int per = (units + 7) / 8, slot = blockIdx.x >> 3, unit = (blockIdx.x & 7) * per + slot;
-    return slot < per && unit < units ? unit : -1;
-}
-
 // ---- independent waves --------------------------------------------------------------------------------------
 // WY: y wanted.  NSEG segments x NP column groups of 32 = the waves of a workgroup.  `SR`: the state's row length;
 // without y nothing couples the state's columns, and S = 256 runs as two parts of S = 128.

@@ -164,6 +164,8 @@ hipError_t prepare_tree_ssd_fma() {
 hipError_t launch_tree_ssd_fma(const stree_dims &d, const int32_t *parent, const void *x, const float *dt,
                                const float *A, const void *Bm, const void *Cm, const float *D,
                                const void *h0, void *y, int32_t *status, hipStream_t st) {
+    if (!(d.flags & STREE_FLAG_FORCE_FMA) && tree_ssd_f32_supported(d, Bm, Cm, h0))
+        return launch_tree_ssd_f32(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, st);
     if (d.io_dtype == STREE_BF16) {                 // (a bf16 state goes with bf16 io only)
         if (d.state_dtype == STREE_BF16)
             return launch_fma_t<bf16_t, bf16_t>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, st);

@@ -1,0 +1,27 @@
+"""The fp32 scan on the fp32 matrix units (trees of at most 64 nodes, dstate 64 / 128 / 256): tile edges and
+remainders in nodes and headdim against the oracle, and against the plain FMA kernel, whose fp32 sums it forms in
+another order (2 S + N terms each: S = 256, N = 64 leaves 2^-24 * sqrt(576) < 2e-6 of the rms, and expf's argument
+error 6e-8 |s| on either side; asserted 2e-5)."""
+import numpy as np
+import pytest
+
+from paper_2505_14969_amd import synth
+from helpers import TOL, assert_parity, to_dev, to_host
+from test_gpu_parity import _rand, st  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,H,P,S,G,with_h0", [(1, 2, 64, 64, 1, True), (31, 3, 33, 128, 1, True), (32, 2, 31, 128, 1, False),
+                                               (33, 2, 64, 128, 2, True), (63, 4, 1, 64, 1, True), (64, 2, 100, 256, 1, True),
+                                               (7, 130, 64, 128, 1, True)])
+def test_f32_scan_tiles(st, oracle, N, H, P, S, G, with_h0):
+    B = 2
+    g = np.random.default_rng(N)
+    par = np.stack([synth.gen_tree(N, min(N - 1, 4), 4, g) if N > 1 else np.array([-1]), synth.chain_tree(N)]).astype(np.int32)
+    x, dt, A, Bm, Cm, D, h0 = _rand(40 + N, "f32", B, N, H, P, S, G, h0=with_h0)
+    want = oracle.ssd_paths(par, x, dt, A, Bm, Cm, D, h0)
+    args = (to_dev(par), to_dev(x), to_dev(dt), to_dev(A), to_dev(Bm), to_dev(Cm), to_dev(D), to_dev(h0))
+    y = to_host(st.stree_tree_ssd(*args))
+    assert_parity(y, want, TOL["f32"], "y", kind="y")
+    assert_parity(y, to_host(st.stree_tree_ssd(*args, force_fma=True)), 2e-5, "y against the FMA kernel", kind="y")
