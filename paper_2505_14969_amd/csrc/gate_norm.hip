@@ -6,8 +6,8 @@
 // Streaming kernel: y and z are read once, out is written once.  A norm group spans the heads of a
 // group (all heads when ngroups = 1), i.e. many (batch, head) units of the scan kernels, so the
 // step cannot ride on a unit's y store; fused there it would move the z read into the scan and save
-// no byte.  One workgroup per (node, group) segment; the gated values stay in registers between the
-// sum of squares and the scaling.
+// no byte.  Some lanes of a wave or one workgroup per (node, group) segment, by its size; the gated
+// values stay in registers between the sum of squares and the scaling.
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -44,33 +44,42 @@ struct Pack16<bf16_t> {
 
 __device__ __forceinline__ float gate(float y, float z) { return y * z * __builtin_amdgcn_rcpf(1.f + __expf(-z)); }
 
-// sum over the workgroup (4 waves); every thread gets the result
+// sum over the workgroup (whole waves, at most 16); every thread gets the result
 __device__ __forceinline__ float block_sum(float v) {
-    __shared__ float part[kThreads / 64];
+    __shared__ float part[16];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
     __syncthreads();
     float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) s += part[w];
+    for (int w = 0; w < (int)blockDim.x / 64; ++w) s += part[w];
     return s;
 }
 
-// CPT = 16-byte chunks of a segment per thread (the segment has at most CPT * 256 chunks)
-template <typename T, int CPT>
-__global__ __launch_bounds__(kThreads) void gate_norm_kernel(const T *__restrict__ y, const T *__restrict__ z, long z_sn,
-                                                             const T *__restrict__ w, T *out, int d, int G, int gs,
-                                                             float eps) {
+// TEAM threads per segment: 16, 32 or 64 lanes of a wave (a workgroup of 256 threads then takes 256 / TEAM segments
+// and needs no barrier), or 0 = the whole workgroup, whose size follows the segment's.  CPT = 16-byte chunks of a
+// segment per thread.
+//
+// HBM-bound, and what keeps it from the memory's rate is idle lanes: with one workgroup of 256 threads per segment the
+// 80 chunks of a group of 640 bf16 channels used 80 of 256 threads and one barrier for 2.5 KB of loads.  (Figures: the rule in launch_t.)
+template <typename T, int CPT, int TEAM>
+__global__ __launch_bounds__(TEAM ? kThreads : 1024) void gate_norm_kernel(const T *__restrict__ y,
+                                                                           const T *__restrict__ z, long z_sn,
+                                                                           const T *__restrict__ w, T *out, int d, int G,
+                                                                           int gs, int segs, float eps) {
     constexpr int EPV = Pack16<T>::N;
-    const int row = blockIdx.x / G, g = blockIdx.x % G;
+    const int team = TEAM ? TEAM : (int)blockDim.x;
+    const int t = TEAM ? (int)threadIdx.x & (team - 1) : (int)threadIdx.x;
+    const unsigned own = TEAM ? blockIdx.x * (kThreads / (TEAM ? TEAM : 1)) + threadIdx.x / team : blockIdx.x;
+    const int seg = (int)min(own, (unsigned)segs - 1u);    // (lanes past the last segment follow along and store nothing)
+    const int row = seg / G, g = seg % G;
     const size_t oy = (size_t)row * d + (size_t)g * gs, oz = (size_t)row * z_sn + (size_t)g * gs;
     const int chunks = gs / EPV;
     float v[CPT][EPV];
     uint4 ry[CPT], rz[CPT];
 #pragma unroll
-    for (int q = 0; q < CPT; ++q) {      // every load goes out before anything is waited for
-        const int c = min(q * kThreads + (int)threadIdx.x, chunks - 1);
+    for (int q = 0; q < CPT; ++q) {
+        const int c = min(q * team + t, chunks - 1);
         ry[q] = load_stream16(y + oy + (size_t)c * EPV);
         rz[q] = load_stream16(z + oz + (size_t)c * EPV);
     }
@@ -80,18 +89,24 @@ __global__ __launch_bounds__(kThreads) void gate_norm_kernel(const T *__restrict
         float fy[EPV], fz[EPV];
         Pack16<T>::unpack(ry[q], fy);
         Pack16<T>::unpack(rz[q], fz);
-        const bool live = q * kThreads + (int)threadIdx.x < chunks;
+        const bool live = q * team + t < chunks;
 #pragma unroll
         for (int e = 0; e < EPV; ++e) {
             v[q][e] = live ? gate(fy[e], fz[e]) : 0.f;
             ss = fmaf(v[q][e], v[q][e], ss);
         }
     }
-    const float scale = rsqrtf(block_sum(ss) / (float)gs + eps);
+    if constexpr (TEAM != 0) {
+#pragma unroll
+        for (int o = TEAM / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    } else {
+        ss = block_sum(ss);
+    }
+    const float scale = rsqrtf(ss / (float)gs + eps);
 #pragma unroll
     for (int q = 0; q < CPT; ++q) {
-        const int c = q * kThreads + (int)threadIdx.x;
-        if (c < chunks) {
+        const int c = q * team + t;
+        if (c < chunks && own < (unsigned)segs) {
             float fw[EPV], o[EPV];
             Pack16<T>::unpack(*reinterpret_cast<const uint4 *>(w + (size_t)g * gs + (size_t)c * EPV), fw);
 #pragma unroll
@@ -127,20 +142,41 @@ hipError_t launch_t(const stree_dims &d, const void *y, const void *z, long z_sn
                     hipStream_t st) {
     constexpr int EPV = Pack16<T>::N;
     const int dd = d.nheads * d.headdim, G = d.ngroups, gs = dd / G;
-    const long rows = (long)d.batch * d.nnodes;
-    const dim3 grid((unsigned)(rows * G));
+    const long segs = (long)d.batch * d.nnodes * G;
     const bool vec = gs % EPV == 0 && z_sn % EPV == 0 &&
                      (((uintptr_t)y | (uintptr_t)z | (uintptr_t)w | (uintptr_t)out) % 16) == 0;
-    const int cpt = vec ? (gs / EPV + kThreads - 1) / kThreads : 0;
-#define STREE_GN_LAUNCH(K)                                                                                        \
-    hipLaunchKernelGGL(K, grid, dim3(kThreads), 0, st, (const T *)y, (const T *)z, z_sn, (const T *)w, (T *)out, dd, G, \
-                       gs, eps)
-    if (cpt == 1) STREE_GN_LAUNCH((gate_norm_kernel<T, 1>));
-    else if (cpt == 2) STREE_GN_LAUNCH((gate_norm_kernel<T, 2>));
-    else if (cpt == 3) STREE_GN_LAUNCH((gate_norm_kernel<T, 3>));
-    else if (cpt == 4) STREE_GN_LAUNCH((gate_norm_kernel<T, 4>));
-    else STREE_GN_LAUNCH((gate_norm_plain_kernel<T>));
-#undef STREE_GN_LAUNCH
+    const int chunks = vec ? gs / EPV : 0;
+#define STREE_GN_VEC(CPT, TEAM, GRID, THREADS)                                                                       \
+    hipLaunchKernelGGL((gate_norm_kernel<T, CPT, TEAM>), dim3((unsigned)(GRID)), dim3(THREADS), 0, st, (const T *)y,  \
+                       (const T *)z, z_sn, (const T *)w, (T *)out, dd, G, gs, (int)segs, eps)
+#define STREE_GN_TEAM(TEAM)                                                                                          \
+    do {                                                                                                             \
+        const long grid = (segs + kThreads / TEAM - 1) / (kThreads / TEAM);                                          \
+        const int cpt = (chunks + TEAM - 1) / TEAM;                                                                  \
+        if (cpt == 1) STREE_GN_VEC(1, TEAM, grid, kThreads);                                                         \
+        else if (cpt == 2) STREE_GN_VEC(2, TEAM, grid, kThreads);                                                    \
+        else if (cpt == 3) STREE_GN_VEC(3, TEAM, grid, kThreads);                                                    \
+        else if (cpt == 4) STREE_GN_VEC(4, TEAM, grid, kThreads);                                                    \
+        else STREE_GN_VEC(5, TEAM, grid, kThreads);                                                                  \
+    } while (0)
+    // Lanes of one wave as long as five chunks a lane hold a segment, as few of them as that allows once there are
+    // enough segments to fill the chip that way: 25088 segments of 80 chunks 30.0 us with a workgroup each, 19.6 us
+    // with 16 lanes each (4.9 TB/s, the rate of a plain copy); 8192 of 128 chunks 12.6 -> 9.3 us with 32 lanes.
+    // Larger segments take a workgroup: 256 threads up to four chunks a thread (1024 rows of 640 chunks in a decoding
+    // step: 320 threads of two chunks cost 0.5 us more), then as many as four chunks a thread ask for.  124 rows of
+    // 1280 fp32 chunks took 12.9 us in the two-pass kernel, 4.7 us so.
+    const bool many = segs >= 4096;
+    if (chunks == 0 || chunks > 4096)
+        hipLaunchKernelGGL((gate_norm_plain_kernel<T>), dim3((unsigned)segs), dim3(kThreads), 0, st, (const T *)y,
+                           (const T *)z, z_sn, (const T *)w, (T *)out, dd, G, gs, eps);
+    else if (many && chunks <= 16 * 5) STREE_GN_TEAM(16);
+    else if (many && chunks <= 32 * 5) STREE_GN_TEAM(32);
+    else if (chunks <= 64 * 5) STREE_GN_TEAM(64);
+    else if (chunks <= 2 * kThreads) STREE_GN_VEC(2, 0, segs, kThreads);
+    else if (chunks <= 3 * kThreads) STREE_GN_VEC(3, 0, segs, kThreads);
+    else STREE_GN_VEC(4, 0, segs, (chunks + 255) / 256 * 64);
+#undef STREE_GN_TEAM
+#undef STREE_GN_VEC
     return hipGetLastError();
 }
 
