@@ -41,7 +41,7 @@ constexpr int kB64 = 64;
 constexpr int kNP64 = kB64 + 8;
 constexpr int kT64 = 512;   // 8 waves: 4 Y waves, 3 G waves, 1 tree wave
 
-constexpr int kRC = 8;      // path nodes of the previous tree whose x / B rows are staged in LDS per unit
+constexpr int kRC = 8;      // path nodes of the previous tree whose x / B rows the tree wave requests a half ahead
 constexpr int kYStage = 4 * 2048;   // bytes at the start of the B tile's LDS that the Y waves turn y around in
 
 // static LDS of the kernel below (C, B, h0b tiles, two X^T tiles, M, tree arrays; with replay
@@ -49,8 +49,14 @@ constexpr int kYStage = 4 * 2048;   // bytes at the start of the B tile's LDS th
 template <int P, int S>
 struct Lds64 {
     static constexpr int SP = S + 8;
-    static constexpr size_t replay_rows = (size_t)kRC * (P + S) * 2;
-    static constexpr bool rows_in_b = (size_t)kB64 * SP * 2 >= kYStage + replay_rows;
+    static constexpr size_t row_bytes = (size_t)(P + S) * 2;                      // x row and B row of a path node
+    static constexpr size_t b_bytes = (size_t)kB64 * SP * 2, m_bytes = (size_t)kB64 * kNP64 * 2;
+    static constexpr bool rows_in_b = b_bytes >= kYStage + kRC * row_bytes;
+    // path nodes whose rows LDS has room for: behind the y staging area and (first pass) in the M tile; 24 otherwise
+    static constexpr size_t room_b = (b_bytes > kYStage ? b_bytes - kYStage : 0) / row_bytes, room_m = m_bytes / row_bytes;
+    static constexpr int kRows = rows_in_b ? (int)(room_b < room_m ? room_b : room_m) : 24;
+    static constexpr size_t replay_rows = kRows * row_bytes;
+    static_assert(kRows >= kRC, "the tree wave's rows must fit");
     static constexpr size_t total = (size_t)2 * kB64 * SP * 2 + (size_t)P * SP * 2 + (size_t)2 * P * kNP64 * 2 +
                                     (size_t)kB64 * kNP64 * 2 + 1040;
     static constexpr size_t total_replay = total + 336 + (rows_in_b ? 0 : replay_rows);
@@ -117,8 +123,11 @@ __device__ __forceinline__ int wave_tree_index(int lane, int n, int parent_i, fl
 // it has nothing else to do (same pointer doubling as the tree index, on the previous tree), and
 // asks for the x / B rows of its first kRC nodes; they are in flight until the staging half,
 // where it puts them into LDS; one more barrier per unit (c) separates that from the FMAs of the
-// threads that carry the unit.  Longer paths read the remaining rows from
-// global memory.  Each thread owns one 4-wide piece of the state index and NH consecutive rows.
+// threads that carry the unit.  The rows of nodes kRC .. kRows - 1 of a longer path are fetched by the
+// three G waves, which have nothing to do between barrier 2 and barrier (c): all requested at once, so a
+// long path costs one round trip behind phase 3 and not one per node.  (Deep trees, beams of 3 tokens over 16
+// layers at batch 64 x 80 heads, a bf16 state: 104.8 -> 92.5 us.)  Paths of more than kRows nodes read what is left from
+// global memory row by row.  Each thread owns one 4-wide piece of the state index and NH consecutive rows.
 // HT = type the state is kept in: fp32, or bf16 (then h0 is the MFMA operand as it comes, and the replayed
 // state is rounded once, to the value that is both written back and scanned from).
 template <int P, int S, int WPE, bool RP, bool SPL, typename HT>
@@ -156,7 +165,7 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     __shared__ unsigned char sRnode[RP ? kB64 : 4];
     __shared__ int sRlen[1];
     __shared__ float sRdec[1];
-    __shared__ __align__(16) bf16_t sRrows[(RP && !L::rows_in_b) ? kRC * (P + S) : 8];
+    __shared__ __align__(16) bf16_t sRrows[(RP && !L::rows_in_b) ? L::kRows * (P + S) : 8];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = tid >> 6;
@@ -294,7 +303,8 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
         rdt = dt[(uint32_t)((b * n + node) * H + h)];
     };
     // ---- registers -> LDS -------------------------------------------------------------------------
-    // rbuf: the LDS rows of the replayed path (x rows [kRC][P], then B rows [kRC][S]); b, h: the unit
+    // rbuf: the LDS rows of the replayed path (x rows [kRows][P], then B rows [kRows][S]); b, h: the unit
+    constexpr int kRows = L::kRows;
     auto stage_H = [&]([[maybe_unused]] const char *rbuf, [[maybe_unused]] int b, [[maybe_unused]] int h) {
         const int t = opaque(rt);
         if constexpr (kWide) {
@@ -322,9 +332,9 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                     for (int e = 0; e < 8; ++e) hv[q][e] = fmaf(xv, bv[e], hv[q][e]);
                 }
             };
-            const int nl = min(len, kRC);
+            const int nl = min(len, kRows);
             for (int j = 0; j < nl; ++j) {
-                const uint4 b8 = *reinterpret_cast<const uint4 *>(rbuf + (kRC * P + j * S + s8 * 8) * 2);
+                const uint4 b8 = *reinterpret_cast<const uint4 *>(rbuf + (kRows * P + j * S + s8 * 8) * 2);
                 uint32_t xw[NR / 2];
 #pragma unroll
                 for (int w = 0; w < NR / 2; w += 2) {
@@ -334,11 +344,11 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                 }
                 rank1(sRcoef[j], b8, xw);
             }
-            if (len > kRC) {   // the rest of a long path: rows straight from global memory
+            if (len > kRows) {   // the rest of a very long path: rows straight from global memory
                 const int g = h / hpg;
                 const char *xb = reinterpret_cast<const char *>(R.x + (size_t)b * R.pn * R.x_sn + (size_t)h * P + prow);
                 const char *Bb = reinterpret_cast<const char *>(R.Bm + (size_t)b * R.pn * R.b_sn + (size_t)g * S + s8 * 8);
-                for (int j = kRC; j < len; ++j) {
+                for (int j = kRows; j < len; ++j) {
                     const int node = sRnode[j];
                     const uint4 b8 = *reinterpret_cast<const uint4 *>(Bb + (size_t)node * R.b_sn * 2);
                     uint32_t xw[NR / 2];
@@ -385,9 +395,9 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                     for (int e = 0; e < 4; ++e) hv[q][e] = fmaf(xv, bv[e], hv[q][e]);
                 }
             };
-            const int nl = min(len, kRC);
+            const int nl = min(len, kRows);
             for (int j = 0; j < nl; ++j) {
-                const uint2 b4 = *reinterpret_cast<const uint2 *>(rbuf + (kRC * P + j * S + s4 * 4) * 2);
+                const uint2 b4 = *reinterpret_cast<const uint2 *>(rbuf + (kRows * P + j * S + s4 * 4) * 2);
                 uint32_t xw[NH / 2];
 #pragma unroll
                 for (int w = 0; w < NH / 2; w += 2) {
@@ -397,11 +407,11 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                 }
                 rank1(sRcoef[j], b4, xw);
             }
-            if (len > kRC) {   // the rest of a long path: rows straight from global memory
+            if (len > kRows) {   // the rest of a very long path: rows straight from global memory
                 const int g = h / hpg;
                 const char *xb = reinterpret_cast<const char *>(R.x + (size_t)b * R.pn * R.x_sn + (size_t)h * P + prow);
                 const char *Bb = reinterpret_cast<const char *>(R.Bm + (size_t)b * R.pn * R.b_sn + (size_t)g * S + s4 * 4);
-                for (int j = kRC; j < len; ++j) {
+                for (int j = kRows; j < len; ++j) {
                     const int node = sRnode[j];
                     const uint2 b4 = *reinterpret_cast<const uint2 *>(Bb + (size_t)node * R.b_sn * 2);
                     uint32_t xw[NH / 2];
@@ -468,16 +478,13 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
 
     // ---- replay (tree wave): previous tree's path one unit ahead ----------------------------------
     // Registers that only the tree wave needs live in its copy of acc[0], which it never uses
-    // as an accumulator: 0-3 x row pieces, 4-11 B row pieces, 12 position on the path, 13 weight,
-    // 14 path length, 15 exp(s_k).
+    // as an accumulator: 0-3 x row pieces, 4-11 B row pieces.
     constexpr int PX = P / 8, PB = S / 8;                     // 16-byte pieces per x row, per B row
     constexpr int NXG = (kRC * PX + 63) / 64, NBG = (kRC * PB + 63) / 64;   // pieces per lane
     static_assert(!RP || (NXG <= 1 && NBG <= 2) || WPE < 4, "tree-wave registers exceed its accumulator copy");
     int rpp = -1;
     float rpdt = 0.f;
     uint4 gxw[(RP && WPE < 4) ? NXG : 1], gbw[(RP && WPE < 4) ? NBG : 1];   // roomy variants: plain registers
-    int wpos = -1, wlen = 0;
-    float wcf = 0.f, wdec = 1.f;
     auto load_R = [&](int b, int h) {
         const int node = min(opaque(lane), R.pn - 1);
         rpp = R.parent[(uint32_t)(b * R.pn + node)];
@@ -533,7 +540,6 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             for (int i = 0; i < NXG; ++i) gxw[i] = gx[i];
 #pragma unroll
             for (int i = 0; i < NBG; ++i) gbw[i] = gb[i];
-            wpos = pos; wcf = cf; wlen = len; wdec = dc;
         } else {
             tw[0] = __uint_as_float(gx[0].x); tw[1] = __uint_as_float(gx[0].y);
             tw[2] = __uint_as_float(gx[0].z); tw[3] = __uint_as_float(gx[0].w);
@@ -542,27 +548,31 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                 tw[4 + 4 * i] = __uint_as_float(gb[i].x); tw[5 + 4 * i] = __uint_as_float(gb[i].y);
                 tw[6 + 4 * i] = __uint_as_float(gb[i].z); tw[7 + 4 * i] = __uint_as_float(gb[i].w);
             }
-            tw[12] = __int_as_float(pos); tw[13] = cf; tw[14] = __int_as_float(len); tw[15] = dc;
+        }
+        // the path itself goes to LDS at once: its arrays are read in the staging half only
+        if (pos >= 0) {
+            sRnode[pos] = (unsigned char)ln;
+            sRcoef[pos] = cf;
+        }
+        if (ln == 0) {
+            *sRlen = len;
+            *sRdec = dc;
         }
     };
     auto write_R = [&](const floatx16 &tw, char *rbuf) {
         const int ln = opaque(lane);
         uint4 gx[NXG], gb[NBG];
-        int pos, len;
-        float cf, dc;
         if constexpr (WPE < 4) {
 #pragma unroll
             for (int i = 0; i < NXG; ++i) gx[i] = gxw[i];
 #pragma unroll
             for (int i = 0; i < NBG; ++i) gb[i] = gbw[i];
-            pos = wpos; cf = wcf; len = wlen; dc = wdec;
         } else {
             gx[0] = make_uint4(__float_as_uint(tw[0]), __float_as_uint(tw[1]), __float_as_uint(tw[2]), __float_as_uint(tw[3]));
 #pragma unroll
             for (int i = 0; i < NBG; ++i)
                 gb[i] = make_uint4(__float_as_uint(tw[4 + 4 * i]), __float_as_uint(tw[5 + 4 * i]),
                                    __float_as_uint(tw[6 + 4 * i]), __float_as_uint(tw[7 + 4 * i]));
-            pos = __float_as_int(tw[12]); cf = tw[13]; len = __float_as_int(tw[14]); dc = tw[15];
         }
 #pragma unroll
         for (int i = 0; i < NXG; ++i) {
@@ -573,15 +583,30 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
         for (int i = 0; i < NBG; ++i) {
             const int idx = ln + 64 * i;
             if (idx < kRC * PB)
-                *reinterpret_cast<uint4 *>(rbuf + (kRC * P + (idx / PB) * S + (idx % PB) * 8) * 2) = gb[i];
+                *reinterpret_cast<uint4 *>(rbuf + (kRows * P + (idx / PB) * S + (idx % PB) * 8) * 2) = gb[i];
         }
-        if (pos >= 0) {
-            sRnode[pos] = (unsigned char)ln;
-            sRcoef[pos] = cf;
+    };
+    // rows kRC .. kRows - 1 of a long path (the three G waves, between barrier 2 and barrier (c))
+    auto fetch_R = [&](char *rbuf, int b, int h) {
+        constexpr int PR = PX + PB, NT = 192, NQ = ((kRows - kRC) * PR + NT - 1) / NT;
+        const int total = (min(*sRlen, kRows) - kRC) * PR;
+        if (total <= 0) return;
+        const int t0 = opaque(tid) - kHalf, t = t0 < 128 ? t0 : t0 - 64;     // waves 4, 5, 7
+        const int g = h / hpg;
+        const char *xb = reinterpret_cast<const char *>(R.x + (size_t)b * R.pn * R.x_sn + (size_t)h * P);
+        const char *Bb = reinterpret_cast<const char *>(R.Bm + (size_t)b * R.pn * R.b_sn + (size_t)g * S);
+        uint4 v[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {                 // (clamped: the last piece again past the end)
+            const int idx = min(t + q * NT, total - 1), c = idx % PR;
+            const int node = sRnode[kRC + idx / PR];
+            v[q] = *reinterpret_cast<const uint4 *>(
+                c < PX ? xb + (uint32_t)(node * (int)R.x_sn + c * 8) * 2u : Bb + (uint32_t)(node * (int)R.b_sn + (c - PX) * 8) * 2u);
         }
-        if (ln == 0) {
-            *sRlen = len;
-            *sRdec = dc;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int idx = min(t + q * NT, total - 1), c = idx % PR, j = kRC + idx / PR;
+            *reinterpret_cast<uint4 *>(rbuf + (c < PX ? j * P + c * 8 : kRows * P + j * S + (c - PX) * 8) * 2) = v[q];
         }
     };
     // LDS rows of the replayed path: behind the y staging area of the idle B tile, or their own array
@@ -861,6 +886,8 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                         if (more2) load_R(b2, h2);
                     }
                     write_R(acc[0], rbuf);                 // (waits for the row loads issued in the scan half)
+                } else {
+                    fetch_R(rbuf, b1, h1);
                 }
                 __syncthreads();                           // barrier (c)
             }

@@ -72,6 +72,28 @@ def test_replay_matches_commit_then_scan(st, oracle, io, B, Np, N, H, P, S, G):
     assert np.array_equal(h2, h) and np.array_equal(y2, y)
 
 
+# accepted paths of every length at which the fused kernel changes its way of fetching rows (8 nodes by the tree wave,
+# up to 14 / 18 / 24 by the other waves, the rest from memory) or fills a last group of four nodes only in part
+@pytest.mark.parametrize("P,S,H,state", [(64, 128, 48, "f32"), (64, 128, 48, "bf16"), (64, 64, 40, "f32"),
+                                         (64, 64, 4, "bf16"), (64, 256, 20, "f32"), (64, 256, 4, "bf16"),
+                                         (128, 128, 20, "f32"), (128, 128, 4, "bf16")])
+def test_replay_path_lengths(st, oracle, P, S, H, state):
+    accepted = np.array([0, 2, 3, 4, 7, 8, 9, 11, 13, 14, 17, 18, 23, 24, 27, 63], dtype=np.int32)
+    B, Np, N, G = len(accepted), 64, 5, 2
+    prev, cur, pp, p = _case(750 + P + S, "bf16", B, Np, N, H, P, S, G)
+    pp = np.stack([synth.chain_tree(Np)] * B).astype(np.int32)
+    h0 = synth.round_to_bf16(prev[6]) if state == "bf16" else prev[6]
+    prev = prev[:6] + (h0,)
+    A, D = prev[2], prev[5]
+    want_h, want_y = _expect(oracle, pp, accepted, prev, p, cur, A, D)
+    y, h = _run(st, "bf16", pp, accepted, prev, p, cur, A, D, h_io=to_dev(h0, state))
+    for b in range(B):
+        # fp32 sums of up to 64 terms; a bf16 state is rounded once on top (2^-8 relative)
+        bound = 1e-4 * np.abs(want_h[b]).max() + (2.0 ** -8 * np.abs(want_h[b]) if state == "bf16" else 0.0)
+        assert np.all(np.abs(h[b] - want_h[b]) <= bound), f"replayed state, path of {accepted[b] + 1} nodes"
+        assert_parity(y[b], want_y[b], TOL["bf16"], f"scan after a path of {accepted[b] + 1} nodes", kind="y")
+
+
 def test_replay_edge_cases(st, oracle):
     """Bad previous tree, accepted index out of range, bad current tree: the state passes
     through (or is still replayed) and the scan of the other sequences is untouched."""
