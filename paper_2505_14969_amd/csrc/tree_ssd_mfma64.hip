@@ -127,7 +127,10 @@ __device__ __forceinline__ int wave_tree_index(int lane, int n, int parent_i, fl
 // three G waves, which have nothing to do between barrier 2 and barrier (c): all requested at once, so a
 // long path costs one round trip behind phase 3 and not one per node.  (Deep trees, beams of 3 tokens over 16
 // layers at batch 64 x 80 heads, a bf16 state: 104.8 -> 92.5 us.)  Paths of more than kRows nodes read what is left from
-// global memory row by row.  Each thread owns one 4-wide piece of the state index and NH consecutive rows.
+// global memory, four nodes at a time.  The update itself runs on the fp32 matrix units (16 x 16 x 4: four path
+// nodes an instruction, the fp32 FMAs of the recurrence in the same precision): as vector FMAs it cost the four
+// waves that carry a unit some 56 instructions per path node, while the other four waited (the beams above:
+// 92.5 -> 82.4 us, chains of up to 49 nodes 195 -> 134 us, trees of depth 4 to 8 75.9 -> 72.9 us).
 // HT = type the state is kept in: fp32, or bf16 (then h0 is the MFMA operand as it comes, and the replayed
 // state is rounded once, to the value that is both written back and scanned from).
 template <int P, int S, int WPE, bool RP, bool SPL, typename HT>
@@ -146,7 +149,6 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     constexpr int YT = (P / 32) * 2, YQ = YT / 4;   // Yt tiles, tiles per Y wave
     constexpr int kRowsC = kHalf / (S / 8), kRowsX = kHalf / (P / 8);
     static_assert(NC >= 1 && NX >= 1 && NH >= 1 && YQ >= 1, "tile too small for this thread count");
-    static_assert(!RP || NH % 4 == 0, "replay reads a thread's x values four at a time");
     static_assert(NH % 2 == 0 && S % 8 == 0, "a bf16 state is moved eight values at a time");
     // separate LDS objects (not slices of one array), so that the compiler knows that a write to
     // one tile cannot alias a read of another and does not serialise them
@@ -223,38 +225,33 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     const int it0 = wave & 1;
 
     float rD = 0.f;                  // D[h] of the unit whose h0 is in pre[]
-    // chunk q of a thread: without replay element (t + q*kHalf)*4 of the P x S tile; with replay
-    // row (t / S4) * NH + q, piece t % S4, so that a thread's rows are consecutive
-    constexpr int S4 = S / 4;
-    // replay on a state kept in bf16: a thread owns NH/2 rows of EIGHT columns, so that the state moves in
-    // 16-byte pieces as the fp32 one does (where its x values still come four at a time; otherwise the
-    // fp32 map with 8-byte pieces)
-    constexpr bool kWide = RP && sizeof(HT) == 2 && (NH / 2) % 4 == 0;
+    // The state tile in a thread's registers.  Without replay chunk q is element (t + q*kHalf)*4 of the P x S tile.
+    // With replay it is the accumulator of the fp32 matrix instructions that advance it (16 x 16 x 4, accumulator
+    // row = state row p, column = state column s): a wave owns 16 rows of every 64, lane l the rows 4 (l >> 4) + i of
+    // those and kCW consecutive columns kCW (l & 15) + t -- column t of each lane makes up tile t, so that a lane's
+    // columns are 16-byte pieces in memory (8 bytes for a bf16 state of 64 columns) all the same.
+    constexpr int kCW = (sizeof(HT) == 2 && S % 128 == 0) ? 8 : 4;   // columns per chunk
+    constexpr int kCB = S / (16 * kCW), kPG = P / 64;                // column blocks; 64-row groups
     auto load_H = [&](int b, int h) {       // the role group that carries this unit
         // the lane-dependent zero keeps this a vector load: it then sits in the same in-order
         // queue as the h0 chunks instead of forcing a scalar-cache wait in the hot window
         if (D) rD = D[h + (opaque(lane) & 0)];
         const char *hb = reinterpret_cast<const char *>(h0 + ((size_t)b * H + h) * P * S);
         constexpr uint32_t HB = sizeof(HT);    // a bf16 state: the same four values per chunk, in 8 bytes
-        auto chunk = [&](int q, const char *src) {
-            if constexpr (HB == 4) {
-                pre[q] = load_stream16(src);
-            } else {
-                const uint2 v = load_stream8(src);
-                pre[q].x = v.x;
-                pre[q].y = v.y;
+        if constexpr (RP) {
+            const int t = opaque(rt), row0 = (t >> 6) * 16 + ((t & 63) >> 4) * 4, col0 = (t & 15) * kCW;
+            const uint32_t off = (uint32_t)(row0 * S + col0) * HB;
+#pragma unroll
+            for (int q = 0; q < kPG * kCB * 4; ++q) {     // q = (row group, column block, row)
+                const char *src = hb + off + ((q / (4 * kCB) * 64 + q % 4) * S + (q / 4 % kCB) * 16 * kCW) * HB;
+                if constexpr (kCW * HB == 16) {
+                    pre[q] = load_stream16(src);
+                } else {
+                    const uint2 v = load_stream8(src);
+                    pre[q].x = v.x;
+                    pre[q].y = v.y;
+                }
             }
-        };
-        if constexpr (kWide) {                 // replay on a bf16 state: NH/2 rows of eight columns per thread
-            const int t = opaque(rt);
-            const uint32_t off = (uint32_t)(((t / (S / 8)) * (NH / 2)) * S + (t % (S / 8)) * 8) * 2u;
-#pragma unroll
-            for (int q = 0; q < NH / 2; ++q) pre[q] = load_stream16(hb + off + q * (S * 2));
-        } else if constexpr (RP) {
-            const int t = opaque(rt);
-            const uint32_t off = (uint32_t)(((t / S4) * NH) * S + (t % S4) * 4) * HB;
-#pragma unroll
-            for (int q = 0; q < NH; ++q) chunk(q, hb + off + q * (S * HB));
         } else if constexpr (HB == 4) {
             const uint32_t off = (uint32_t)opaque(rt) * 16u;
 #pragma unroll
@@ -307,136 +304,86 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     constexpr int kRows = L::kRows;
     auto stage_H = [&]([[maybe_unused]] const char *rbuf, [[maybe_unused]] int b, [[maybe_unused]] int h) {
         const int t = opaque(rt);
-        if constexpr (kWide) {
-            constexpr int S8 = S / 8, NR = NH / 2;
-            const int prow = (t / S8) * NR, s8 = t % S8;
+        if constexpr (RP) {
+            const int l = t & 15, kj = (t & 63) >> 4, prow = (t >> 6) * 16;
             const int len = *sRlen;
             const float dec = *sRdec;
-            float hv[NR][8];
+            floatx4 hv[kPG * kCB][kCW];                    // [row group, column block][tile]
 #pragma unroll
-            for (int q = 0; q < NR; ++q) {
+            for (int q = 0; q < kPG * kCB * 4; ++q) {
                 const uint32_t w4[4] = {pre[q].x, pre[q].y, pre[q].z, pre[q].w};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    hv[q][2 * e] = dec * bf16_lo(w4[e]);
-                    hv[q][2 * e + 1] = dec * bf16_hi(w4[e]);
-                }
+                for (int e = 0; e < kCW; ++e)
+                    hv[q / 4][e][q % 4] = dec * (sizeof(HT) == 4 ? __uint_as_float(w4[e % 4])
+                                                 : (e & 1) ? bf16_hi(w4[e / 2]) : bf16_lo(w4[e / 2]));
             }
-            auto rank1 = [&](float cf, uint4 b8, const uint32_t (&xw)[NR / 2]) {
-                const float bv[8] = {cf * bf16_lo(b8.x), cf * bf16_hi(b8.x), cf * bf16_lo(b8.y), cf * bf16_hi(b8.y),
-                                     cf * bf16_lo(b8.z), cf * bf16_hi(b8.z), cf * bf16_lo(b8.w), cf * bf16_hi(b8.w)};
+            // four path nodes: lane group kj holds node j of them, its weight cf (0 past the end of the path),
+            // its x at row (t & 15) of the wave's rows (operand A) and cf * B at the lane's columns (operand B)
+            auto rank4 = [&](bool on, float cf, const char *xr, const char *br) {
+                float av[kPG];
 #pragma unroll
-                for (int q = 0; q < NR; ++q) {
-                    const float xv = (q & 1) ? bf16_hi(xw[q >> 1]) : bf16_lo(xw[q >> 1]);
+                for (int g = 0; g < kPG; ++g) {
+                    const uint32_t xw = *reinterpret_cast<const unsigned short *>(xr + (prow + l + g * 64) * 2);
+                    av[g] = on ? __uint_as_float(xw << 16) : 0.f;
+                }
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) hv[q][e] = fmaf(xv, bv[e], hv[q][e]);
+                for (int c = 0; c < kCB; ++c) {
+                    uint32_t bw[kCW / 2];
+#pragma unroll
+                    for (int w = 0; w < kCW / 2; w += 2) {
+                        const uint2 v = *reinterpret_cast<const uint2 *>(br + ((c * 16 + l) * kCW + 2 * w) * 2);
+                        bw[w] = v.x;
+                        bw[w + 1] = v.y;
+                    }
+#pragma unroll
+                    for (int e = 0; e < kCW; ++e) {
+                        const float bv = on ? cf * ((e & 1) ? bf16_hi(bw[e / 2]) : bf16_lo(bw[e / 2])) : 0.f;
+#pragma unroll
+                        for (int g = 0; g < kPG; ++g)
+                            hv[g * kCB + c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[g], bv, hv[g * kCB + c][e], 0, 0, 0);
+                    }
                 }
             };
             const int nl = min(len, kRows);
-            for (int j = 0; j < nl; ++j) {
-                const uint4 b8 = *reinterpret_cast<const uint4 *>(rbuf + (kRows * P + j * S + s8 * 8) * 2);
-                uint32_t xw[NR / 2];
-#pragma unroll
-                for (int w = 0; w < NR / 2; w += 2) {
-                    const uint2 v = *reinterpret_cast<const uint2 *>(rbuf + (j * P + prow + 2 * w) * 2);
-                    xw[w] = v.x;
-                    xw[w + 1] = v.y;
-                }
-                rank1(sRcoef[j], b8, xw);
+            for (int j0 = 0; j0 < nl; j0 += 4) {
+                const int j = min(j0 + kj, nl - 1);
+                rank4(j0 + kj < nl, sRcoef[j], rbuf + j * P * 2, rbuf + (kRows * P + j * S) * 2);
             }
             if (len > kRows) {   // the rest of a very long path: rows straight from global memory
                 const int g = h / hpg;
-                const char *xb = reinterpret_cast<const char *>(R.x + (size_t)b * R.pn * R.x_sn + (size_t)h * P + prow);
-                const char *Bb = reinterpret_cast<const char *>(R.Bm + (size_t)b * R.pn * R.b_sn + (size_t)g * S + s8 * 8);
-                for (int j = kRows; j < len; ++j) {
-                    const int node = sRnode[j];
-                    const uint4 b8 = *reinterpret_cast<const uint4 *>(Bb + (size_t)node * R.b_sn * 2);
-                    uint32_t xw[NR / 2];
-#pragma unroll
-                    for (int w = 0; w < NR / 2; w += 2) {
-                        const uint2 v = *reinterpret_cast<const uint2 *>(xb + ((size_t)node * R.x_sn + 2 * w) * 2);
-                        xw[w] = v.x;
-                        xw[w + 1] = v.y;
-                    }
-                    rank1(sRcoef[j], b8, xw);
+                const char *xb = reinterpret_cast<const char *>(R.x + (size_t)b * R.pn * R.x_sn + (size_t)h * P);
+                const char *Bb = reinterpret_cast<const char *>(R.Bm + (size_t)b * R.pn * R.b_sn + (size_t)g * S);
+                for (int j0 = kRows; j0 < len; j0 += 4) {
+                    const int j = min(j0 + kj, len - 1), node = sRnode[j];
+                    rank4(j0 + kj < len, sRcoef[j], xb + (size_t)node * R.x_sn * 2, Bb + (size_t)node * R.b_sn * 2);
                 }
             }
-            // the replayed state, rounded once: the value written back (through L2) is the MFMA operand
+            // the replayed state, written once, through L2 (never read again by this kernel); a bf16 state is
+            // rounded once: the value written back is the MFMA operand
             char *ob = reinterpret_cast<char *>(reinterpret_cast<HT *>(R.h_out) + ((size_t)b * H + h) * P * S);
 #pragma unroll
-            for (int q = 0; q < NR; ++q) {
-                const uint2 lo = pack_bf16x4(hv[q][0], hv[q][1], hv[q][2], hv[q][3]);
-                const uint2 hi = pack_bf16x4(hv[q][4], hv[q][5], hv[q][6], hv[q][7]);
-                const uint4 o = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                store_through16(ob + (uint32_t)((prow + q) * S + s8 * 8) * 2u, o);
-                *reinterpret_cast<uint4 *>(&sH[(prow + q) * SP + s8 * 8]) = o;
-            }
-        } else if constexpr (RP) {
-            const int prow = (t / S4) * NH, s4 = t % S4;
-            const int len = *sRlen;
-            const float dec = *sRdec;
-            float hv[NH][4];
+            for (int q = 0; q < kPG * kCB * 4; ++q) {
+                const int at_row = prow + kj * 4 + q / (4 * kCB) * 64 + q % 4, at_col = (q / 4 % kCB * 16 + l) * kCW;
+                uint32_t w[kCW / 2];
 #pragma unroll
-            for (int q = 0; q < NH; ++q) {
-                if constexpr (sizeof(HT) == 4) {
-                    hv[q][0] = dec * __uint_as_float(pre[q].x); hv[q][1] = dec * __uint_as_float(pre[q].y);
-                    hv[q][2] = dec * __uint_as_float(pre[q].z); hv[q][3] = dec * __uint_as_float(pre[q].w);
-                } else {
-                    hv[q][0] = dec * bf16_lo(pre[q].x); hv[q][1] = dec * bf16_hi(pre[q].x);
-                    hv[q][2] = dec * bf16_lo(pre[q].y); hv[q][3] = dec * bf16_hi(pre[q].y);
+                for (int e = 0; e < kCW; e += 4) {
+                    const uint2 v = pack_bf16x4(hv[q / 4][e][q % 4], hv[q / 4][e + 1][q % 4], hv[q / 4][e + 2][q % 4],
+                                                hv[q / 4][e + 3][q % 4]);
+                    w[e / 2] = v.x;
+                    w[e / 2 + 1] = v.y;
                 }
-            }
-            auto rank1 = [&](float cf, uint2 b4, const uint32_t (&xw)[NH / 2]) {
-                const float bv[4] = {cf * bf16_lo(b4.x), cf * bf16_hi(b4.x), cf * bf16_lo(b4.y), cf * bf16_hi(b4.y)};
-#pragma unroll
-                for (int q = 0; q < NH; ++q) {
-                    const float xv = (q & 1) ? bf16_hi(xw[q >> 1]) : bf16_lo(xw[q >> 1]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) hv[q][e] = fmaf(xv, bv[e], hv[q][e]);
-                }
-            };
-            const int nl = min(len, kRows);
-            for (int j = 0; j < nl; ++j) {
-                const uint2 b4 = *reinterpret_cast<const uint2 *>(rbuf + (kRows * P + j * S + s4 * 4) * 2);
-                uint32_t xw[NH / 2];
-#pragma unroll
-                for (int w = 0; w < NH / 2; w += 2) {
-                    const uint2 v = *reinterpret_cast<const uint2 *>(rbuf + (j * P + prow + 2 * w) * 2);
-                    xw[w] = v.x;
-                    xw[w + 1] = v.y;
-                }
-                rank1(sRcoef[j], b4, xw);
-            }
-            if (len > kRows) {   // the rest of a very long path: rows straight from global memory
-                const int g = h / hpg;
-                const char *xb = reinterpret_cast<const char *>(R.x + (size_t)b * R.pn * R.x_sn + (size_t)h * P + prow);
-                const char *Bb = reinterpret_cast<const char *>(R.Bm + (size_t)b * R.pn * R.b_sn + (size_t)g * S + s4 * 4);
-                for (int j = kRows; j < len; ++j) {
-                    const int node = sRnode[j];
-                    const uint2 b4 = *reinterpret_cast<const uint2 *>(Bb + (size_t)node * R.b_sn * 2);
-                    uint32_t xw[NH / 2];
-#pragma unroll
-                    for (int w = 0; w < NH / 2; w += 2) {
-                        const uint2 v = *reinterpret_cast<const uint2 *>(xb + ((size_t)node * R.x_sn + 2 * w) * 2);
-                        xw[w] = v.x;
-                        xw[w + 1] = v.y;
-                    }
-                    rank1(sRcoef[j], b4, xw);
-                }
-            }
-            // the replayed state: written once, through L2 (never read again by this kernel)
-            char *ob = reinterpret_cast<char *>(reinterpret_cast<HT *>(R.h_out) + ((size_t)b * H + h) * P * S);
-#pragma unroll
-            for (int q = 0; q < NH; ++q) {
-                bf16x4 o;
-                o[0] = (bf16_t)hv[q][0]; o[1] = (bf16_t)hv[q][1]; o[2] = (bf16_t)hv[q][2]; o[3] = (bf16_t)hv[q][3];
+                char *dst = ob + (uint32_t)(at_row * S + at_col) * (uint32_t)sizeof(HT);
+                bf16_t *op = &sH[at_row * SP + at_col];
                 if constexpr (sizeof(HT) == 4)
-                    store_through16(ob + (uint32_t)((prow + q) * S + s4 * 4) * 4u,
-                                    make_uint4(__float_as_uint(hv[q][0]), __float_as_uint(hv[q][1]),
-                                               __float_as_uint(hv[q][2]), __float_as_uint(hv[q][3])));
-                else
-                    store_through8(ob + (uint32_t)((prow + q) * S + s4 * 4) * 2u, __builtin_bit_cast(uint2, o));
-                *reinterpret_cast<bf16x4 *>(&sH[(prow + q) * SP + s4 * 4]) = o;
+                    store_through16(dst, make_uint4(__float_as_uint(hv[q / 4][0][q % 4]), __float_as_uint(hv[q / 4][1][q % 4]),
+                                                    __float_as_uint(hv[q / 4][2][q % 4]), __float_as_uint(hv[q / 4][3][q % 4])));
+                if constexpr (kCW == 8) {
+                    store_through16(dst, make_uint4(w[0], w[1], w[2], w[3]));
+                    *reinterpret_cast<uint4 *>(op) = make_uint4(w[0], w[1], w[2], w[3]);
+                } else {
+                    if constexpr (sizeof(HT) == 2) store_through8(dst, make_uint2(w[0], w[1]));
+                    *reinterpret_cast<uint2 *>(op) = make_uint2(w[0], w[1]);
+                }
             }
         } else if constexpr (sizeof(HT) == 4) {
 #pragma unroll
