@@ -82,38 +82,52 @@ def load() -> C.CDLL:
     return _lib
 
 
+# A decoding step on a small tree takes the GPU 15 us, so what a call spends here is what its user waits for: pointers
+# go to ctypes as plain integers (an object for each cost 0.15 us, and a step has 26), the stream handle comes without
+# a Stream object around it, and views are not made for their address alone.  A step with its gate, 15 nodes at batch 1:
+# 33 -> 24 us a pass; verification of 15 fp32 nodes in three calls 38 -> 27 us.
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else _VP(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream() -> _VP:
-    return _VP(torch.cuda.current_stream().cuda_stream)
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    def _stream() -> int:
+        if not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+else:
+    def _stream() -> int:
+        return torch.cuda.current_stream().cuda_stream
+
+_IO_CODE = {torch.float32: F32, torch.bfloat16: BF16}
 
 
 def _io_code(t) -> int:
     dt = t.dtype if isinstance(t, torch.Tensor) else t
-    if dt == torch.float32:
-        return F32
-    if dt == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported dtype {dt}")
+    code = _IO_CODE.get(dt)
+    if code is None:
+        raise TypeError(f"unsupported dtype {dt}")
+    return code
 
 
-def _state_code(*states) -> int:
+def _state_code(h0=None, h_out=None) -> int:
     """Type code of the SSM state from the state tensors of a call (those that are given must agree)."""
-    dts = {t.dtype for t in states if t is not None}
-    assert len(dts) <= 1, "h0 and h_out must have the same dtype"
-    return _io_code(next(iter(dts))) if dts else F32
+    if h0 is None:
+        return F32 if h_out is None else _io_code(h_out.dtype)
+    assert h_out is None or h_out is h0 or h_out.dtype == h0.dtype, "h0 and h_out must have the same dtype"
+    return _io_code(h0.dtype)
 
 
 def _token_stride(t: torch.Tensor, nnodes: int) -> int:
     """Element stride between tokens of a [B,N,a,b] view whose last two dims are
     dense and whose batch stride is N * token stride."""
-    assert t.dim() == 4 and t.stride(3) == 1 and t.stride(2) == t.shape[3], "inner dims must be dense"
-    sn = t.stride(1)
-    if nnodes == 1 and t.shape[0] > 1:
-        sn = t.stride(0)     # (the stride torch keeps for a dimension of size 1 means nothing)
-    assert t.shape[0] == 1 or t.stride(0) == nnodes * sn, "batch stride must be N * token stride"
+    assert t.dim() == 4, "inner dims must be dense"
+    batch, _, _, last = t.shape
+    sb, sn, sa, one = t.stride()
+    assert one == 1 and sa == last, "inner dims must be dense"
+    if nnodes == 1 and batch > 1:
+        sn = sb              # (the stride torch keeps for a dimension of size 1 means nothing)
+    assert batch == 1 or sb == nnodes * sn, "batch stride must be N * token stride"
     return sn
 
 
@@ -186,7 +200,7 @@ def stree_tree_ssd(parent, x, dt, A, Bm, Cm, D=None, h0=None, out: Optional[torc
     B, N, H, P = x.shape
     G, S = Bm.shape[2], Bm.shape[3]
     if out is None:
-        out = torch.empty((B, N, H, P), dtype=x.dtype, device=x.device)
+        out = x.new_empty((B, N, H, P))
     d = make_dims(B, N, H, P, S, G, 0, _io_code(x),
                   (FLAG_FORCE_FMA if force_fma else 0) | (FLAG_GENERAL_MFMA if general_mfma else 0),
                   _token_stride(x, N), _token_stride(Bm, N), _token_stride(Cm, N), dt_bias, _state_code(h0))
@@ -217,7 +231,7 @@ def stree_commit_state(parent, accepted, x, dt, A, Bm, h0=None, h_out: Optional[
     B, N, H, P = x.shape
     G, S = Bm.shape[2], Bm.shape[3]
     if h_out is None:
-        h_out = torch.empty((B, H, P, S), dtype=torch.float32 if h0 is None else h0.dtype, device=x.device)
+        h_out = x.new_empty((B, H, P, S), dtype=torch.float32 if h0 is None else h0.dtype)
     W = 0
     if xbc_pre is not None:
         W = conv_state.shape[1] + 1
@@ -244,7 +258,7 @@ def stree_tree_ssd_replay(prev_parent, prev_accepted, prev_x, prev_dt, prev_Bm, 
     assert prev_dt.is_contiguous() and prev_dt.dtype == torch.float32 and prev_dt.shape == (B, Np, H)
     assert dt.is_contiguous() and dt.dtype == torch.float32 and h0.is_contiguous()
     if out is None:
-        out = torch.empty((B, N, H, P), dtype=x.dtype, device=x.device)
+        out = x.new_empty((B, N, H, P))
     if h_out is None:
         h_out = torch.empty_like(h0)
     d = make_dims(B, N, H, P, S, G, 0, _io_code(x), FLAG_FORCE_FMA if force_fma else 0,
@@ -308,14 +322,14 @@ def stree_tree_step(prev_parent, prev_accepted, prev_xbc_pre, prev_xbc_out, prev
     if h_out is None:
         h_out = torch.empty_like(h0)
     if out is None:
-        out = torch.empty((B, N, H, P), dtype=xbc_pre.dtype, device=xbc_pre.device)
+        out = xbc_pre.new_empty((B, N, H, P))
     assert xbc_out.is_contiguous() and out.is_contiguous() and h_out.is_contiguous()
     assert conv_state_out.data_ptr() != conv_state.data_ptr()
     flags = (FLAG_CONV_SILU if silu else 0) | (FLAG_FORCE_FMA if force_fma else 0)
     d = make_dims(B, N, H, P, S, G, W, _io_code(xbc_pre), flags, dt_bias=dt_bias, state_dtype=_state_code(h0, h_out))
-    prev_B = prev_xbc_out[:, :, H * P:H * P + G * S]
-    r = StreeReplay(Np, 0, prev_parent.data_ptr(), prev_accepted.data_ptr(), prev_xbc_out.data_ptr(),
-                    prev_dt.data_ptr(), prev_B.data_ptr(), Cc, Cc)
+    prev_x = prev_xbc_out.data_ptr()
+    r = StreeReplay(Np, 0, prev_parent.data_ptr(), prev_accepted.data_ptr(), prev_x, prev_dt.data_ptr(),
+                    prev_x + H * P * prev_xbc_out.element_size(), Cc, Cc)     # the B columns behind x's
     _check(load().stree_tree_step(C.byref(d), C.byref(r), _ptr(prev_xbc_pre), _ptr(parent), _ptr(xbc_pre),
                                   _ptr(conv_state), _ptr(conv_w), _ptr(conv_b), _ptr(xbc_out), _ptr(conv_state_out),
                                   _ptr(dt), _ptr(A), _ptr(D), _ptr(h0), _ptr(h_out), _ptr(out), _ptr(status),
@@ -331,7 +345,7 @@ def stree_gate_norm(y, z, norm_w, ngroups: int, eps: float = 1e-5, out: Optional
     if out is None:
         out = torch.empty_like(y)
     d = make_dims(B, N, H, P, 1, ngroups, 0, _io_code(y))
-    _check(load().stree_gate_norm(C.byref(d), _ptr(y), _ptr(z), _token_stride(z, N), _ptr(norm_w), C.c_float(eps),
+    _check(load().stree_gate_norm(C.byref(d), _ptr(y), _ptr(z), _token_stride(z, N), _ptr(norm_w), eps,
                                   _ptr(out), _stream()), "stree_gate_norm")
     return out
 
@@ -345,9 +359,9 @@ def stree_linear_ssd(x, dt, A, Bm, Cm=None, D=None, h0=None, want_y: bool = True
     G, S = Bm.shape[2], Bm.shape[3]
     assert dt.is_contiguous() and dt.dtype == torch.float32 and dt.shape == (B, T, H)
     if want_y and out is None:
-        out = torch.empty((B, T, H, P), dtype=x.dtype, device=x.device)
+        out = x.new_empty((B, T, H, P))
     if h_out is None:
-        h_out = torch.empty((B, H, P, S), dtype=torch.float32 if h0 is None else h0.dtype, device=x.device)
+        h_out = x.new_empty((B, H, P, S), dtype=torch.float32 if h0 is None else h0.dtype)
     d = make_dims(B, T, H, P, S, G, 0, _io_code(x), 0, _token_stride(x, T), _token_stride(Bm, T),
                   _token_stride(Cm, T) if Cm is not None else 0, dt_bias, _state_code(h0, h_out))
     _check(load().stree_linear_ssd(C.byref(d), _ptr(x), _ptr(dt), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(D), _ptr(h0),
