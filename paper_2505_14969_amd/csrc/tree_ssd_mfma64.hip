@@ -30,6 +30,8 @@
 //
 // Template flag RP folds the commit of the previous tree into the state as it is loaded
 // (Alg. 1: replay at the start of the next iteration).
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -41,7 +43,6 @@ constexpr int kB64 = 64;
 constexpr int kNP64 = kB64 + 8;
 constexpr int kT64 = 512;   // 8 waves: 4 Y waves, 3 G waves, 1 tree wave
 
-constexpr int kRC = 8;      // path nodes of the previous tree whose x / B rows the tree wave requests a half ahead
 constexpr int kYStage = 4 * 2048;   // bytes at the start of the B tile's LDS that the Y waves turn y around in
 
 // static LDS of the kernel below (C, B, h0b tiles, two X^T tiles, M, tree arrays; with replay
@@ -51,12 +52,11 @@ struct Lds64 {
     static constexpr int SP = S + 8;
     static constexpr size_t row_bytes = (size_t)(P + S) * 2;                      // x row and B row of a path node
     static constexpr size_t b_bytes = (size_t)kB64 * SP * 2, m_bytes = (size_t)kB64 * kNP64 * 2;
-    static constexpr bool rows_in_b = b_bytes >= kYStage + kRC * row_bytes;
+    static constexpr bool rows_in_b = b_bytes >= kYStage + 8 * row_bytes;
     // path nodes whose rows LDS has room for: behind the y staging area and (first pass) in the M tile; 24 otherwise
     static constexpr size_t room_b = (b_bytes > kYStage ? b_bytes - kYStage : 0) / row_bytes, room_m = m_bytes / row_bytes;
     static constexpr int kRows = rows_in_b ? (int)(room_b < room_m ? room_b : room_m) : 24;
     static constexpr size_t replay_rows = kRows * row_bytes;
-    static_assert(kRows >= kRC, "the tree wave's rows must fit");
     static constexpr size_t total = (size_t)2 * kB64 * SP * 2 + (size_t)P * SP * 2 + (size_t)2 * P * kNP64 * 2 +
                                     (size_t)kB64 * kNP64 * 2 + 1040;
     static constexpr size_t total_replay = total + 336 + (rows_in_b ? 0 : replay_rows);
@@ -120,13 +120,14 @@ __device__ __forceinline__ int wave_tree_index(int lane, int n, int parent_i, fl
 //   h* = exp(s_k) h0 + sum_{j on path(k)} dt_j exp(s_k - s_j) x_j (outer) B_j,
 // in the fp32 registers it arrives in, written back once to h_out, and only then rounded to the
 // bf16 MFMA operand.  The tree wave works the path of the next unit out in the scan half, in which
-// it has nothing else to do (same pointer doubling as the tree index, on the previous tree), and
-// asks for the x / B rows of its first kRC nodes; they are in flight until the staging half,
-// where it puts them into LDS; one more barrier per unit (c) separates that from the FMAs of the
-// threads that carry the unit.  The rows of nodes kRC .. kRows - 1 of a longer path are fetched by the
-// three G waves, which have nothing to do between barrier 2 and barrier (c): all requested at once, so a
-// long path costs one round trip behind phase 3 and not one per node.  (Deep trees, beams of 3 tokens over 16
-// layers at batch 64 x 80 heads, a bf16 state: 104.8 -> 92.5 us.)  Paths of more than kRows nodes read what is left from
+// it has nothing else to do (same pointer doubling as the tree index, on the previous tree).  The x / B
+// rows of the path's first kRows nodes are fetched by the three G waves, which have nothing to do between
+// barrier 2 and barrier (c): all requested at once, put into LDS, one round trip behind phase 3 whatever the
+// length of the path.  (Rows read one by one behind the eighth cost beams of 3 tokens over 16 layers at batch
+// 64 x 80 heads with a bf16 state 104.8 against 92.5 us.  Rows requested by the tree wave a half earlier, into its copy of the
+// accumulator, were in flight for longer, but the compiler does not know the roles: it made every wave's
+// products wait for those registers, i.e. for all of its own prefetches.  Without them: 73.5 -> 69.5 us for trees
+// of depth 4 to 8, 82 -> 78 us for the beams.)  Paths of more than kRows nodes read what is left from
 // global memory, four nodes at a time.  The update itself runs on the fp32 matrix units (16 x 16 x 4: four path
 // nodes an instruction, the fp32 FMAs of the recurrence in the same precision): as vector FMAs it cost the four
 // waves that carry a unit some 56 instructions per path node, while the other four waited (the beams above:
@@ -294,6 +295,12 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             pre[NH + q] = *reinterpret_cast<const uint4 *>(
                 xb + (uint32_t)(min(rx0 + q * kRowsX, n - 1) * (int)x_sn + cx0 * 8) * 2u);
     };
+    // an array element that is the same for the whole wave, by a scalar load: a vector load would be the newest one in
+    // flight, and waiting for it would be waiting for the whole state prefetch
+    auto uniform_load = [](auto *a, int i) {
+        typedef __attribute__((address_space(4))) const typename std::remove_const<typename std::remove_pointer<decltype(a)>::type>::type *ptr_t;
+        return ((ptr_t)(uintptr_t)a)[__builtin_amdgcn_readfirstlane(i)];
+    };
     auto load_T = [&](int b, int h) {       // tree wave
         const int node = min(opaque(lane), n - 1);
         rpar = parent[(uint32_t)(b * n + node)];
@@ -418,34 +425,30 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     auto stage_T = [&](int h) {
         const int ln = opaque(lane);   // LDS addresses re-derived here, not carried across the loop
         float dt_i = rdt;
-        if constexpr (SPL) dt_i = softplus_step(rdt + dt_bias[h]);               // raw projection -> step size
-        const int bad = wave_tree_index(ln, n, rpar, dt_i, A[h], sS2, sU, sMask);
+        const float A_h = uniform_load(A, h);
+        if constexpr (SPL) dt_i = softplus_step(rdt + uniform_load(dt_bias, h));   // raw projection -> step size
+        const int bad = wave_tree_index(ln, n, rpar, dt_i, A_h, sS2, sU, sMask);
         if (ln == 0) *sBad = bad;
     };
 
     // ---- replay (tree wave): previous tree's path one unit ahead ----------------------------------
-    // Registers that only the tree wave needs live in its copy of acc[0], which it never uses
-    // as an accumulator: 0-3 x row pieces, 4-11 B row pieces.
     constexpr int PX = P / 8, PB = S / 8;                     // 16-byte pieces per x row, per B row
-    constexpr int NXG = (kRC * PX + 63) / 64, NBG = (kRC * PB + 63) / 64;   // pieces per lane
-    static_assert(!RP || (NXG <= 1 && NBG <= 2) || WPE < 4, "tree-wave registers exceed its accumulator copy");
     int rpp = -1;
     float rpdt = 0.f;
-    uint4 gxw[(RP && WPE < 4) ? NXG : 1], gbw[(RP && WPE < 4) ? NBG : 1];   // roomy variants: plain registers
     auto load_R = [&](int b, int h) {
         const int node = min(opaque(lane), R.pn - 1);
         rpp = R.parent[(uint32_t)(b * R.pn + node)];
         rpdt = R.dt[(uint32_t)((b * R.pn + node) * H + h)];
     };
-    auto path_R = [&](floatx16 &tw, int b, int h) {
+    auto path_R = [&](int b, int h) {
         const int ln = opaque(lane);
         const int pn = R.pn;
         // uniform values by scalar loads (a vector load here would be the newest one in flight, and
         // waiting for it would wait for the whole h0 prefetch)
-        const int rk = R.accepted[__builtin_amdgcn_readfirstlane(b)];
-        const float rRA = A[__builtin_amdgcn_readfirstlane(h)];
+        const int rk = uniform_load(R.accepted, b);
+        const float rRA = uniform_load(A, h);
         float pdt_i = rpdt;
-        if constexpr (SPL) pdt_i = softplus_step(rpdt + dt_bias[__builtin_amdgcn_readfirstlane(h)]);
+        if constexpr (SPL) pdt_i = softplus_step(rpdt + uniform_load(dt_bias, h));
         const bool kbad = rk < -1 || rk >= pn;
         int pos = -1, len = 0;
         float cf = 0.f, dc = 1.f;
@@ -457,46 +460,7 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             dc = 1.f;
         }
         if (R.status && h == 0 && ln == 0) R.status[b] = st ? st : (kbad ? -1 : 0);
-        // x / B rows of the first kRC path nodes: 16-byte pieces dealt over the lanes
-        const int g = h / hpg;
-        const char *xb = reinterpret_cast<const char *>(R.x + (size_t)b * pn * R.x_sn + (size_t)h * P);
-        const char *Bb = reinterpret_cast<const char *>(R.Bm + (size_t)b * pn * R.b_sn + (size_t)g * S);
-        int nx[NXG], nb[NBG];      // node of the path position each of this lane's pieces belongs to
-#pragma unroll
-        for (int i = 0; i < NXG; ++i) nx[i] = 0;
-#pragma unroll
-        for (int i = 0; i < NBG; ++i) nb[i] = 0;
-#pragma unroll
-        for (int sl = 0; sl < kRC; ++sl) {
-            const unsigned long long m = __ballot(pos == sl);
-            const int nd = m ? (int)__ffsll((long long)m) - 1 : 0;
-#pragma unroll
-            for (int i = 0; i < NXG; ++i) nx[i] = ((ln + 64 * i) / PX == sl) ? nd : nx[i];
-#pragma unroll
-            for (int i = 0; i < NBG; ++i) nb[i] = ((ln + 64 * i) / PB == sl) ? nd : nb[i];
-        }
-        uint4 gx[NXG], gb[NBG];
-#pragma unroll
-        for (int i = 0; i < NXG; ++i)
-            gx[i] = *reinterpret_cast<const uint4 *>(xb + (uint32_t)(nx[i] * (int)R.x_sn + ((ln + 64 * i) % PX) * 8) * 2u);
-#pragma unroll
-        for (int i = 0; i < NBG; ++i)
-            gb[i] = *reinterpret_cast<const uint4 *>(Bb + (uint32_t)(nb[i] * (int)R.b_sn + ((ln + 64 * i) % PB) * 8) * 2u);
-        if constexpr (WPE < 4) {
-#pragma unroll
-            for (int i = 0; i < NXG; ++i) gxw[i] = gx[i];
-#pragma unroll
-            for (int i = 0; i < NBG; ++i) gbw[i] = gb[i];
-        } else {
-            tw[0] = __uint_as_float(gx[0].x); tw[1] = __uint_as_float(gx[0].y);
-            tw[2] = __uint_as_float(gx[0].z); tw[3] = __uint_as_float(gx[0].w);
-#pragma unroll
-            for (int i = 0; i < NBG; ++i) {
-                tw[4 + 4 * i] = __uint_as_float(gb[i].x); tw[5 + 4 * i] = __uint_as_float(gb[i].y);
-                tw[6 + 4 * i] = __uint_as_float(gb[i].z); tw[7 + 4 * i] = __uint_as_float(gb[i].w);
-            }
-        }
-        // the path itself goes to LDS at once: its arrays are read in the staging half only
+        // (the arrays are read in the staging half only)
         if (pos >= 0) {
             sRnode[pos] = (unsigned char)ln;
             sRcoef[pos] = cf;
@@ -506,55 +470,34 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             *sRdec = dc;
         }
     };
-    auto write_R = [&](const floatx16 &tw, char *rbuf) {
-        const int ln = opaque(lane);
-        uint4 gx[NXG], gb[NBG];
-        if constexpr (WPE < 4) {
-#pragma unroll
-            for (int i = 0; i < NXG; ++i) gx[i] = gxw[i];
-#pragma unroll
-            for (int i = 0; i < NBG; ++i) gb[i] = gbw[i];
-        } else {
-            gx[0] = make_uint4(__float_as_uint(tw[0]), __float_as_uint(tw[1]), __float_as_uint(tw[2]), __float_as_uint(tw[3]));
-#pragma unroll
-            for (int i = 0; i < NBG; ++i)
-                gb[i] = make_uint4(__float_as_uint(tw[4 + 4 * i]), __float_as_uint(tw[5 + 4 * i]),
-                                   __float_as_uint(tw[6 + 4 * i]), __float_as_uint(tw[7 + 4 * i]));
-        }
-#pragma unroll
-        for (int i = 0; i < NXG; ++i) {
-            const int idx = ln + 64 * i;
-            if (idx < kRC * PX) *reinterpret_cast<uint4 *>(rbuf + ((idx / PX) * P + (idx % PX) * 8) * 2) = gx[i];
-        }
-#pragma unroll
-        for (int i = 0; i < NBG; ++i) {
-            const int idx = ln + 64 * i;
-            if (idx < kRC * PB)
-                *reinterpret_cast<uint4 *>(rbuf + (kRows * P + (idx / PB) * S + (idx % PB) * 8) * 2) = gb[i];
-        }
-    };
-    // rows kRC .. kRows - 1 of a long path (the three G waves, between barrier 2 and barrier (c))
+    // x / B rows of its first kRows nodes (the three G waves, between barrier 2 and barrier (c))
     auto fetch_R = [&](char *rbuf, int b, int h) {
-        constexpr int PR = PX + PB, NT = 192, NQ = ((kRows - kRC) * PR + NT - 1) / NT;
-        const int total = (min(*sRlen, kRows) - kRC) * PR;
+        constexpr int PR = PX + PB, NT = 192, NQ = (kRows * PR + NT - 1) / NT;
+        const int total = min(*sRlen, kRows) * PR;
         if (total <= 0) return;
         const int t0 = opaque(tid) - kHalf, t = t0 < 128 ? t0 : t0 - 64;     // waves 4, 5, 7
         const int g = h / hpg;
         const char *xb = reinterpret_cast<const char *>(R.x + (size_t)b * R.pn * R.x_sn + (size_t)h * P);
         const char *Bb = reinterpret_cast<const char *>(R.Bm + (size_t)b * R.pn * R.b_sn + (size_t)g * S);
-        uint4 v[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {                 // (clamped: the last piece again past the end)
-            const int idx = min(t + q * NT, total - 1), c = idx % PR;
-            const int node = sRnode[kRC + idx / PR];
-            v[q] = *reinterpret_cast<const uint4 *>(
-                c < PX ? xb + (uint32_t)(node * (int)R.x_sn + c * 8) * 2u : Bb + (uint32_t)(node * (int)R.b_sn + (c - PX) * 8) * 2u);
+        static_assert(NQ <= 3, "pieces of the path rows per thread");
+        auto fetch = [&](int q) {                      // (clamped: the last piece again past the end)
+            const int idx = min(t + q * NT, total - 1), c = idx % PR, node = sRnode[idx / PR];
+            const char *src = c < PX ? xb + (uint32_t)(node * (int)R.x_sn + c * 8) * 2u
+                                     : Bb + (uint32_t)(node * (int)R.b_sn + (c - PX) * 8) * 2u;
+            return *reinterpret_cast<const uint4 *>(src);
+        };
+        auto put = [&](int q, uint4 v) {
+            const int idx = min(t + q * NT, total - 1), c = idx % PR, j = idx / PR;
+            *reinterpret_cast<uint4 *>(rbuf + (c < PX ? j * P + c * 8 : kRows * P + j * S + (c - PX) * 8) * 2) = v;
+        };
+        // (the second and third piece only where the path asks for them: most have at most eight nodes)
+        const uint4 v0 = fetch(0);
+        if (total > NT) {
+            const uint4 v1 = fetch(1), v2 = fetch(2);
+            put(1, v1);
+            put(2, v2);
         }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int idx = min(t + q * NT, total - 1), c = idx % PR, j = kRC + idx / PR;
-            *reinterpret_cast<uint4 *>(rbuf + (c < PX ? j * P + c * 8 : kRows * P + j * S + (c - PX) * 8) * 2) = v[q];
-        }
+        put(0, v0);
     };
     // LDS rows of the replayed path: behind the y staging area of the idle B tile, or their own array
     char *const rrows = L::rows_in_b ? reinterpret_cast<char *>(sB) + kYStage : reinterpret_cast<char *>(sRrows);
@@ -573,12 +516,12 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     // (acc[0]) the G waves' Gt tile of the current (sequence, group), kept across its heads.
     floatx16 acc[YQ];
 
-    // the first loads of every role, before anything is waited for.  With the replay the first
-    // state tile is the exception (kLateH0): it is asked for once the tree wave has requested the
-    // path rows of unit 0.  The replay of unit 0 is two dependent round trips (the previous tree's
-    // parents and step sizes, then the rows of the path), and behind 16 KB of state per thread
-    // group and workgroup each of them takes several times as long, while the first scan waits for
-    // them all the same.
+    // the first loads of every role, before anything is waited for.  With the replay the first state
+    // tile is the exception (kLateH0): it is asked for once the tree wave knows the path of unit 0, and
+    // the state of unit 1 (G threads) behind the rows of that path.  The replay of unit 0 is two
+    // dependent round trips (the previous tree's parents and step sizes, then the rows of the path),
+    // and behind 16 KB of state per thread group and workgroup each of them takes several times as
+    // long, while the first scan waits for them all the same.
     constexpr bool kLateH0 = RP;
     if constexpr (kLateH0) {
 #pragma unroll
@@ -592,11 +535,8 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                 load_R(b1, h1);
             }
         }
-        if (wave == kTreeWave) path_R(acc[0], b1, h1);
-        // the state of unit 1 (carried by the G threads) goes out now, while nothing else uses the
-        // memory system; the tree wave asks for its share after its path rows
-        if (!isY && h0 && nU > 1) load_H(b2, h2);
-        __syncthreads();                                      // the path rows of unit 0 are requested
+        if (wave == kTreeWave) path_R(b1, h1);
+        __syncthreads();                                      // the path of unit 0 is in LDS
         if (isY) {
             if (h0) load_H(b1, h1);
         }
@@ -706,7 +646,7 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             //      half in which this wave has nothing else to do; they are written to LDS at the start
             //      of the staging half.  Then the parent / dt loads for the path of unit k+2.
             if (k + 1 < nU) {
-                path_R(acc[0], b1, h1);
+                path_R(b1, h1);
                 if (k + 2 < nU) load_R(b2, h2);
             }
         }
@@ -777,7 +717,13 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             // tiles come from the G threads, after barrier (a))
             if (!live && fresh_next) restage_CB(b1, h1);
             if (RP && more) __syncthreads();                  // barrier (c): path rows of unit k+1 are in LDS
-            // next unit's state tile (its loads have been in flight for a whole unit period)
+            // next unit's state tile (its loads have been in flight for a whole unit period), and behind it the
+            // request for the state of unit k+3.  Unit 2 is the exception: asked for in the first pass it would
+            // sit in the memory queues in front of the small x / parent / dt loads of units 1 and 2 and make the
+            // last scan wait for them; asked for one pass later, the state of the last unit of a short run is the
+            // last thing to arrive.  (Requested in the same branch that staged, and ahead of the y stores: where
+            // the compiler cannot tell that a register's last load has been waited for, it waits for everything in
+            // front of the next load into it, the stores included.)
             if (more) {
                 if (h0) {
                     if (y_stages) stage_H(rbuf, b1, h1);
@@ -785,6 +731,8 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                     *sDh = D ? D[h1] : 0.f;
                 }
             }
+            if (h0 && more3 && y_stages && live) load_H(b3, h3);
+            if (h0 && more2 && k == 0) load_H(b2, h2);
             // y leaves as 64-byte row pieces: the accumulators give a lane 4 consecutive p of one
             // node, which as direct stores would be 16-byte pieces of 32 different lines per
             // instruction.  Each wave therefore turns its 32x32 tile around in a private 2 KB of LDS
@@ -818,21 +766,11 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                     }
                 }
             }
-            // h0 of unit k+3 after staging unit k+1.  Unit 2 is the exception: asked for in the
-            // first pass it would sit in the memory queues in front of the small x / parent / dt
-            // loads of units 1 and 2 and make the last scan wait for them; asked for one pass
-            // later, the state of the last unit of a short run is the last thing to arrive.
-            if (h0 && more3 && y_stages && live) load_H(b3, h3);
-            if (h0 && more2 && k == 0) load_H(b2, h2);
             if (late_tiles) __syncthreads();                  // barrier (a): scratch use of the B tile is over
         } else if (more) {
             if constexpr (RP) {
                 if (wave == kTreeWave) {
-                    if (!live) {                           // unit 0: path and rows within this pass
-                        if constexpr (!kLateH0) path_R(acc[0], b1, h1);   // (else: done before the loop)
-                        if (more2) load_R(b2, h2);
-                    }
-                    write_R(acc[0], rbuf);                 // (waits for the row loads issued in the scan half)
+                    if (!live && more2) load_R(b2, h2);
                 } else {
                     fetch_R(rbuf, b1, h1);
                 }
@@ -840,6 +778,9 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             }
             if (wave == kTreeWave) {
                 stage_T(h1);
+                // (the path inputs of unit k+2 are waited for here, with the others, and not at the start of the next
+                // scan half, where the state tile requested below would be waited for with them)
+                if constexpr (RP) asm volatile("" : "+v"(rpp), "+v"(rpdt));
             }
             stage_X((k + 1) & 1);                          // the other X^T tile: unit k still reads its own
             // the registers just staged are free: x and parent / dt of unit k+2 go out at once (a
@@ -852,7 +793,7 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                 stage_H(rbuf, b1, h1);
                 if (more3) load_H(b3, h3);
             }
-            if (!kLateH0 && more2 && !live && h0) load_H(b2, h2);      // unit 1: the first odd unit (kLateH0: before the loop)
+            if (more2 && !live && h0) load_H(b2, h2);      // unit 1: the first odd unit
             if (late_tiles) {
                 __syncthreads();                           // barrier (a)
                 restage_CB(b1, h1);
