@@ -44,7 +44,8 @@ struct Pack16<bf16_t> {
 
 __device__ __forceinline__ float gate(float y, float z) { return y * z * __builtin_amdgcn_rcpf(1.f + __expf(-z)); }
 
-// sum over the workgroup (whole waves, at most 16); every thread gets the result
+// sum over the workgroup (whole waves: WAVES of them, or up to 16 where that is 0); every thread gets the result
+template <int WAVES>
 __device__ __forceinline__ float block_sum(float v) {
     __shared__ float part[16];
 #pragma unroll
@@ -52,12 +53,13 @@ __device__ __forceinline__ float block_sum(float v) {
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
     __syncthreads();
     float s = 0.f;
-    for (int w = 0; w < (int)blockDim.x / 64; ++w) s += part[w];
+#pragma unroll
+    for (int w = 0; w < (WAVES ? WAVES : (int)blockDim.x / 64); ++w) s += part[w];
     return s;
 }
 
 // TEAM threads per segment: 16, 32 or 64 lanes of a wave (a workgroup of 256 threads then takes 256 / TEAM segments
-// and needs no barrier), or 0 = the whole workgroup, whose size follows the segment's.  CPT = 16-byte chunks of a
+// and needs no barrier), 256 = that workgroup, or 0 = a workgroup whose size follows the segment's.  CPT = 16-byte chunks of a
 // segment per thread.
 //
 // HBM-bound, and what keeps it from the memory's rate is idle lanes: with one workgroup of 256 threads per segment the
@@ -96,11 +98,11 @@ __global__ __launch_bounds__(TEAM ? kThreads : 1024) void gate_norm_kernel(const
             ss = fmaf(v[q][e], v[q][e], ss);
         }
     }
-    if constexpr (TEAM != 0) {
+    if constexpr (TEAM == kThreads || TEAM == 0) {
+        ss = block_sum<TEAM / 64>(ss);
+    } else {
 #pragma unroll
         for (int o = TEAM / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-    } else {
-        ss = block_sum(ss);
     }
     const float scale = rsqrtf(ss / (float)gs + eps);
 #pragma unroll
@@ -128,7 +130,7 @@ __global__ __launch_bounds__(kThreads) void gate_norm_plain_kernel(const T *__re
         const float v = gate(to_f32(y[oy + c]), to_f32(z[oz + c]));
         ss = fmaf(v, v, ss);
     }
-    const float scale = rsqrtf(block_sum(ss) / (float)gs + eps);
+    const float scale = rsqrtf(block_sum<kThreads / 64>(ss) / (float)gs + eps);
     for (int c = threadIdx.x; c < gs; c += kThreads) {
         const float v = gate(to_f32(y[oy + c]), to_f32(z[oz + c]));
         T o;
@@ -172,8 +174,8 @@ hipError_t launch_t(const stree_dims &d, const void *y, const void *z, long z_sn
     else if (many && chunks <= 16 * 5) STREE_GN_TEAM(16);
     else if (many && chunks <= 32 * 5) STREE_GN_TEAM(32);
     else if (chunks <= 64 * 5) STREE_GN_TEAM(64);
-    else if (chunks <= 2 * kThreads) STREE_GN_VEC(2, 0, segs, kThreads);
-    else if (chunks <= 3 * kThreads) STREE_GN_VEC(3, 0, segs, kThreads);
+    else if (chunks <= 2 * kThreads) STREE_GN_VEC(2, kThreads, segs, kThreads);
+    else if (chunks <= 3 * kThreads) STREE_GN_VEC(3, kThreads, segs, kThreads);
     else STREE_GN_VEC(4, 0, segs, (chunks + 255) / 256 * 64);
 #undef STREE_GN_TEAM
 #undef STREE_GN_VEC
