@@ -721,9 +721,8 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             // request for the state of unit k+3.  Unit 2 is the exception: asked for in the first pass it would
             // sit in the memory queues in front of the small x / parent / dt loads of units 1 and 2 and make the
             // last scan wait for them; asked for one pass later, the state of the last unit of a short run is the
-            // last thing to arrive.  (Requested in the same branch that staged, and ahead of the y stores: where
-            // the compiler cannot tell that a register's last load has been waited for, it waits for everything in
-            // front of the next load into it, the stores included.)
+            // last thing to arrive.  (Ahead of the y stores: the compiler cannot tell that these registers' last
+            // loads have been waited for and waits for everything in front of the next ones, stores included.)
             if (more) {
                 if (h0) {
                     if (y_stages) stage_H(rbuf, b1, h1);
