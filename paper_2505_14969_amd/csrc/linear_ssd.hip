@@ -114,7 +114,10 @@ __device__ __forceinline__ uint32_t fresh(uint32_t v) {
 }
 
 // One chunk of rows (B or C), whole rows to consecutive lanes, from a buffer that ends with the sequence's last
-// row: rows past it read as zeros.  (WIDE: token strides for which 64 rows outgrow a 32-bit offset; rows past
+// row: rows past it read as zeros.  The row goes into the vector offset, which is the one that the buffer's range is
+// checked against: a scalar offset is not part of it, or is subtracted from a range that may be smaller, and rows
+// past the end would then come from whatever lies there (a weight of 0 does not undo a NaN).
+// (WIDE: token strides for which 64 rows outgrow a 32-bit offset; rows past
 // the sequence are then copies of the last one -- their step size is 0 and their y is not stored.)
 template <int S, bool WIDE>
 __device__ __forceinline__ void load_rows(u32x4 (&r)[S / 16], const bf16_t *base, long sn, int t0, int T, int lane) {
@@ -127,10 +130,10 @@ __device__ __forceinline__ void load_rows(u32x4 (&r)[S / 16], const bf16_t *base
     } else {
         const int rows = min(kQ, T - t0);
         const auto buf = make_buffer(base + (size_t)t0 * sn, rows > 0 ? (size_t)((rows - 1) * (uint32_t)sn + S) * 2 : 0);
-        const uint32_t off = (uint32_t)row0 * (uint32_t)sn * 2 + piece0 * 16;
+        const uint32_t off = fresh((uint32_t)row0 * (uint32_t)sn * 2 + piece0 * 16);
 #pragma unroll
         for (int q = 0; q < NK; ++q)
-            r[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off, q * kRowsAt * (uint32_t)sn * 2, 0);
+            r[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off + q * kRowsAt * (uint32_t)sn * 2, 0, 0);
     }
 }
 // x: 32 columns of two chunks, four lanes a row
@@ -143,10 +146,10 @@ __device__ __forceinline__ void load_x_rows(u32x4 (&r)[4], const bf16_t *base, l
     } else {
         const int rows = min(2 * kQ, T - t0);
         const auto buf = make_buffer(base + (size_t)t0 * sn, rows > 0 ? (size_t)((rows - 1) * (uint32_t)sn + kCols) * 2 : 0);
-        const uint32_t off = (uint32_t)(lane >> 2) * (uint32_t)sn * 2 + (lane & 3) * 16;
+        const uint32_t off = fresh((uint32_t)(lane >> 2) * (uint32_t)sn * 2 + (lane & 3) * 16);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            r[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off, q * 16 * (uint32_t)sn * 2, 0);
+            r[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off + q * 16 * (uint32_t)sn * 2, 0, 0);
     }
 }
 template <int S>
@@ -657,10 +660,10 @@ __global__ __launch_bounds__(64 * (NM + 2), (S == 256 ? 2 : 3)) void linear_ssd_
         auto load_x = [&](u32x4 (&r)[XR], int t0) {
             const int n = min(kQ, T - t0);
             const auto buf = make_buffer(xb + (size_t)t0 * x_sn, n > 0 ? (size_t)((n - 1) * (uint32_t)x_sn + P) * 2 : 0);
-            const uint32_t off = (uint32_t)(lane / (P / 8)) * (uint32_t)x_sn * 2 + (lane % (P / 8)) * 16;
+            const uint32_t off = fresh((uint32_t)(lane / (P / 8)) * (uint32_t)x_sn * 2 + (lane % (P / 8)) * 16);
 #pragma unroll
             for (int q = 0; q < XR; ++q)
-                r[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off, q * (512 / P) * (uint32_t)x_sn * 2, 0);
+                r[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off + q * (512 / P) * (uint32_t)x_sn * 2, 0, 0);
         };
         // column tiles of [32 tokens][32 columns]
         const uint32_t x_store = base + L::x + (lane % (P / 8)) / 4 * (2 * kQ * kCols * 2) + (lane / (P / 8)) * (kCols * 2) + (lane & 3) * 16;

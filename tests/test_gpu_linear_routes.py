@@ -48,3 +48,23 @@ def test_prefix_with_huge_token_strides(st, oracle):
     assert_parity(to_host(y), want_y, TOL["bf16"], "y", kind="y")
     _, h2 = st.stree_linear_ssd(views[0], to_dev(dt), to_dev(A), views[1], h0=to_dev(h0), want_y=False)
     assert_parity(to_host(h2), want_h, 1e-4, "state only", kind="state")
+
+
+@pytest.mark.parametrize("P,S", [(64, 64), (64, 128), (64, 256), (128, 128)])
+@pytest.mark.parametrize("T", [1, 31, 33, 65, 449, 705])
+def test_prefix_reads_nothing_behind_the_last_token(st, oracle, T, P, S):
+    """x, B and C are the first T rows of a longer buffer whose other rows are NaN (a weight of 0 would not hide one)."""
+    import torch
+    B, H, G = 1, 2, 1
+    x, dt, A, Bm, Cm, D, h0 = _rand(1300 + T + S, "bf16", B, T, H, P, S, G, h0=True)
+    want_y, want_h = oracle.linear_scan(x, dt, A, Bm, Cm, D, h0)
+    views = []
+    for a, n in ((x, H * P), (Bm, G * S), (Cm, G * S)):
+        rows = torch.full((B, T + 192, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+        rows[:, :T] = to_dev(a, "bf16").reshape(B, T, n)
+        views.append(rows[:, :T].unflatten(2, a.shape[2:]))
+    y, h = st.stree_linear_ssd(views[0], to_dev(dt), to_dev(A), views[1], views[2], to_dev(D), to_dev(h0))
+    assert_parity(to_host(h), want_h, 1e-4, "state", kind="state")
+    assert_parity(to_host(y), want_y, TOL["bf16"], "y", kind="y")
+    _, h2 = st.stree_linear_ssd(views[0], to_dev(dt), to_dev(A), views[1], h0=to_dev(h0), want_y=False)
+    assert_parity(to_host(h2), want_h, 1e-4, "state only", kind="state")
