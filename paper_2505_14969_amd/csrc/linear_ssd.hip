@@ -412,13 +412,14 @@ __device__ __forceinline__ void store_state(const floatx16 (&hacc)[ST], HT *at) 
 
 // ---- independent waves --------------------------------------------------------------------------------------
 // WY: y wanted.  NSEG segments x NP column groups of 32 = the waves of a workgroup.  `SR`: the state's row length;
-// without y nothing couples the state's columns, and S = 256 runs as two parts of S = 128.
+// without y nothing couples the state's columns, and S = 256 runs as two parts of S = 128.  (h_out may be h0: no
+// __restrict__ on either.)
 template <int S, bool WY, int NSEG, int NP, bool WIDE, typename HT>
 __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd_kernel(
     int T, int H, int G, int P, int SR, int units, const bf16_t *__restrict__ x, long x_sn, const float *__restrict__ dt,
     const float *__restrict__ dt_bias, const float *__restrict__ A, const bf16_t *__restrict__ Bm, long b_sn,
-    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const HT *__restrict__ h0,
-    bf16_t *__restrict__ y, HT *__restrict__ h_out) {
+    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const HT *h0,
+    bf16_t *__restrict__ y, HT *h_out) {
     constexpr int NK = S / 16;                        // k steps of a product over the state index
     constexpr int ST = S / 32;                        // state tiles h^T[32 s][32 p]
     constexpr size_t kStage = (size_t)WaveLds<S, WY>::size * NSEG * NP;
@@ -528,8 +529,12 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
             const float whole = __builtin_amdgcn_exp2f(sum2);
 #pragma unroll 1
             for (int k = 0; k < NSEG; ++k) {
-                // h0 is read again before h_out, which may be h0, is written (vmcnt(0))
-                if (WY && k == NSEG - 1 && seg == 0) __builtin_amdgcn_s_waitcnt(0x0f70);
+                // h0, read again below for the first segment's y, is in registers before this barrier lets another wave
+                // write h_out, which may be h0: the empty statement uses the loaded values, so the loads have returned
+                if (WY && k == NSEG - 1 && seg == 0) {
+#pragma unroll
+                    for (int st = 0; st < ST; ++st) asm volatile("" : "+v"(hacc[st])::"memory");
+                }
                 __syncthreads();                      // first: the tiles are dead; then: the state is there
                 if (seg != k) continue;
                 auto advance = [&](auto &&put) {      // put(state tile, quarter, state at the segment's end)
@@ -629,8 +634,8 @@ template <int S, int NM, typename HT>
 __global__ __launch_bounds__(64 * (NM + 2), (S == 256 ? 2 : 3)) void linear_ssd_team_kernel(
     int T, int H, int G, int units, const bf16_t *__restrict__ x, long x_sn, const float *__restrict__ dt,
     const float *__restrict__ dt_bias, const float *__restrict__ A, const bf16_t *__restrict__ Bm, long b_sn,
-    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const HT *__restrict__ h0,
-    bf16_t *__restrict__ y, HT *__restrict__ h_out) {
+    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const HT *h0,
+    bf16_t *__restrict__ y, HT *h_out) {
     constexpr int NK = S / 16, ST = S / 32, P = NM * kCols;
     using L = TeamLds<S, NM>;
     __shared__ __align__(512) char lds[L::size];

@@ -204,3 +204,12 @@ def test_step_rejects_overlapping_conv_outputs(lib):
     assert step(base, base + 4 * nbytes, base - 256) == 6                # B rows run into xbc_out
     assert step(base, None, base) == 1                                   # (NULL is reported first)
     assert step(base, base, base, d=binding.make_dims(**{**ok, "batch": 0})) == 0
+
+
+@pytest.mark.parametrize("source", ["linear_ssd.hip", "commit_state.hip"])
+def test_state_pointers_that_may_alias_are_not_restrict(source):
+    """h_out may be h0, and another wave than the one that reads h0 may write h_out: `__restrict__` on either would let
+    the compiler move or repeat the read behind the barrier between them."""
+    text = open(os.path.join(ROOT, "paper_2505_14969_amd", "csrc", source)).read()
+    params = re.findall(r"HT\s*\*\s*(__restrict__\s+)?(h0|h_out)\b", text)
+    assert len(params) >= 2 and not any(restrict for restrict, _ in params)
