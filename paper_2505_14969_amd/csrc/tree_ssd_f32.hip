@@ -13,6 +13,11 @@
 // j = 8(r/4) + 4(l/32) + r%4, which makes its registers, weighted in place, the M operand of sixteen steps whose x rows
 // are read from memory as they lie; D x uses the same x registers.
 //
+// A matrix instruction multiplies the weight 0 of a node that is no ancestor with that node's x, and 0 times an infinity
+// or NaN would spread one bad node over every row of the tile.  So values of x that are not finite enter the matrix
+// instructions as 0, and a wave that met one adds them to the rows that have a weight for them, one by one: the FMA
+// kernel's results, at the price of two vector instructions per x register otherwise.
+//
 // What bounds it is that chain: the loads (about 2 us), 64 + 64 dependent steps of 64 cycles (S = 128), 16 more per
 // column tile, launch and store.  Measured, against the FMA kernel (one workgroup per head, 16 rows at a time through
 // LDS): batch 4 x 31 nodes x 80 heads, S = 128: 101 -> 13.5 us; 15 nodes x 4 heads, S = 64: 25.2 -> 8.2 us.
@@ -34,6 +39,7 @@ __global__ __launch_bounds__(64, 1) void tree_ssd_f32_kernel(
     constexpr int KC = S < 128 ? S : 128;             // state columns in registers at a time
     constexpr int NG = KC / 8;                        // groups of eight: one 16-byte piece per lane, four steps
     __shared__ __align__(16) float sS[64], sDt[64];
+    __shared__ float sM[32 * 33], sX[32 * 33];        // weights [j][i] and x [j][p] of a tile whose x is not finite throughout
     const int unit = unit_of_block(units);
     if (unit < 0) return;
     const int lane = threadIdx.x, l32 = lane & 31, lh = lane >> 5;
@@ -116,7 +122,7 @@ __global__ __launch_bounds__(64, 1) void tree_ssd_f32_kernel(
         steps(gt, bv, c);
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {                     // rows of C h0 by exp(s_i)
+    for (int q = 0; q < 4 && hrow; ++q) {             // rows of C h0 by exp(s_i)
         const f32x4 sv = *reinterpret_cast<const f32x4 *>(&sS[it * 32 + 8 * q + 4 * lh]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[4 * q + e] *= expf(sv[e]);
@@ -142,16 +148,38 @@ __global__ __launch_bounds__(64, 1) void tree_ssd_f32_kernel(
             const int j = jt * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
             xv[r] = xbase[(size_t)min(j, n - 1) * x_sn];
         }
+        // weight of node j = jt * 32 + 8 (r / 4) + 4 lh + r % 4 for row i (a select: a non-ancestor's weight may overflow)
+        auto weight = [&](int r) {
+            const int j = jt * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
+            const float w = gt[r] * expf(s_i - sS[j]) * sDt[j];
+            return (m_i >> j) & 1ull ? w : 0.f;
+        };
+        bool spoiled = false;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int j0 = jt * 32 + 8 * q + 4 * lh;
-            const f32x4 sv = *reinterpret_cast<const f32x4 *>(&sS[j0]), dv = *reinterpret_cast<const f32x4 *>(&sDt[j0]);
+        for (int r = 0; r < 16; ++r) {
+            const bool fin = __builtin_isfinite(xv[r]);
+            spoiled |= !fin;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(r), fin ? xv[r] : 0.f, acc, 0, 0, 0);
+        }
+        if (__any(spoiled)) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float w = gt[4 * q + e] * expf(s_i - sv[e]) * dv[e];
-                const float mv = (m_i >> (j0 + e)) & 1ull ? w : 0.f;   // select: a non-ancestor's weight may overflow
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(mv, xv[4 * q + e], acc, 0, 0, 0);
+            for (int r = 0; r < 16; ++r) {
+                const int j = 8 * (r >> 2) + 4 * lh + (r & 3);
+                sM[j * 33 + l32] = weight(r);
+                sX[j * 33 + l32] = xv[r];
             }
+            __syncthreads();
+#pragma unroll 1
+            for (int j = 0; j < 32; ++j) {
+                const float xj = sX[j * 33 + l32];
+                if (__builtin_isfinite(xj)) continue;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {        // accumulator rows
+                    const float w = sM[j * 33 + 8 * (r >> 2) + 4 * lh + (r & 3)];
+                    if (w != 0.f) acc[r] = fmaf(w, xj, acc[r]);
+                }
+            }
+            __syncthreads();
         }
     }
 #pragma unroll

@@ -25,3 +25,36 @@ def test_f32_scan_tiles(st, oracle, N, H, P, S, G, with_h0):
     y = to_host(st.stree_tree_ssd(*args))
     assert_parity(y, want, TOL["f32"], "y", kind="y")
     assert_parity(y, to_host(st.stree_tree_ssd(*args, force_fma=True)), 2e-5, "y against the FMA kernel", kind="y")
+
+
+@pytest.mark.parametrize("N,P,bad", [(15, 64, 3), (15, 64, 14), (33, 33, 7), (33, 33, 32), (64, 40, 20), (64, 40, 45)])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_f32_scan_keeps_a_bad_node_to_its_descendants(st, oracle, N, P, bad, value):
+    """x of one node is not finite (all its values, or one of them; in the second sequence its weight is 0 as well): the
+    rows that do not descend from it are what the oracle gives, and the others are the FMA kernel's, which skips
+    products with a weight of 0."""
+    B, H, S, G = 3, 2, 64, 1
+    par = np.stack([synth.full_binary_tree(7)[:N]] * B).astype(np.int32)
+    x, dt, A, Bm, Cm, D, h0 = _rand(70 + N, "f32", B, N, H, P, S, G)
+    dt[1, bad] = 0.0
+    spoilt = x.copy()
+    spoilt[0, bad], spoilt[1, bad], spoilt[2, bad, 1, P - 1] = value, value, value
+    want = oracle.ssd_paths(par, x, dt, A, Bm, Cm, D, h0)
+    below = np.array([bad in _path(par[0], i) for i in range(N)])
+    for h in (h0, None):
+        args = [to_dev(a) for a in (par, spoilt, dt, A, Bm, Cm, D, h)]
+        got, fma = to_host(st.stree_tree_ssd(*args)), to_host(st.stree_tree_ssd(*args, force_fma=True))
+        assert np.isfinite(got[:, ~below]).all() and np.isfinite(got[2, :, 0]).all() and np.isfinite(got[2, :, 1, :P - 1]).all()
+        assert np.isfinite(got[1, np.arange(N) != bad]).all()
+        if h is not None:
+            assert_parity(got[:, ~below], want[:, ~below], TOL["f32"], "rows beside the bad node", kind="y")
+        ok = np.isfinite(fma)
+        assert np.array_equal(np.isfinite(got), ok) and np.array_equal(np.isnan(got), np.isnan(fma))
+        assert np.array_equal(got[~ok & ~np.isnan(fma)], fma[~ok & ~np.isnan(fma)])           # infinities by sign
+        assert_parity(np.where(ok, got, 0), np.where(ok, fma, 0), 2e-5, "finite rows against the FMA kernel", kind="y")
+
+
+def _path(parent, i):
+    while i >= 0:
+        yield i
+        i = parent[i]
