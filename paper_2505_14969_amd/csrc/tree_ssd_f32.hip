@@ -191,11 +191,16 @@ __global__ __launch_bounds__(64, 1) void tree_ssd_f32_kernel(
 
 }  // namespace
 
-// Trees of at most 64 nodes, dstate a tile of the kernel, rows of B, C and the state on 16-byte boundaries.
+static int64_t units_of(const stree_dims &d) {
+    return (int64_t)d.batch * d.nheads * ((d.headdim + 31) / 32) * ((d.nnodes + 31) / 32);
+}
+
+// Trees of at most 64 nodes, dstate a tile of the kernel, rows of B, C and the state on 16-byte boundaries, and no more
+// waves than one grid dimension takes (2^32 work items; the FMA kernel's grid has two).
 bool tree_ssd_f32_supported(const stree_dims &d, const void *Bm, const void *Cm, const void *h0) {
     if (d.io_dtype != STREE_F32 || d.nnodes > 64) return false;
     if (d.dstate != 64 && d.dstate != 128 && d.dstate != 256) return false;
-    if ((d.b_stride_n | d.c_stride_n) % 4 != 0) return false;
+    if ((d.b_stride_n | d.c_stride_n) % 4 != 0 || units_of(d) > (1L << 25)) return false;
     return (((uintptr_t)Bm | (uintptr_t)Cm | (uintptr_t)h0) % 16) == 0;
 }
 
@@ -203,7 +208,7 @@ template <int S>
 static hipError_t launch_f32_s(const stree_dims &d, const int32_t *parent, const void *x, const float *dt, const float *A,
                                const void *Bm, const void *Cm, const float *D, const void *h0, void *y, int32_t *status,
                                hipStream_t st) {
-    const int units = d.batch * d.nheads * ((d.headdim + 31) / 32) * ((d.nnodes + 31) / 32);
+    const int units = (int)units_of(d);
     hipLaunchKernelGGL((tree_ssd_f32_kernel<S>), dim3(8 * ((units + 7) / 8)), dim3(64), 0, st, parent, d.nnodes, d.nheads,
                        d.headdim, d.ngroups, units, (const float *)x, (long)d.x_stride_n, dt, step_bias(d), A,
                        (const float *)Bm, (long)d.b_stride_n, (const float *)Cm, (long)d.c_stride_n, D,

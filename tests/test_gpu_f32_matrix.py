@@ -58,3 +58,16 @@ def _path(parent, i):
     while i >= 0:
         yield i
         i = parent[i]
+
+
+def test_f32_scan_of_more_heads_than_one_grid_dimension_holds(st):
+    """1025 x 65535 heads of one column, one node: as one wave each, 2^32 work items and more in one grid dimension."""
+    import torch
+    B, N, H, P, S, G = 1025, 1, 65535, 1, 64, 1
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
+    x, dt, Bm, Cm, A, D = rand(B, N, H, P), rand(B, N, H).abs(), rand(B, N, G, S), rand(B, N, G, S), -rand(H).abs(), rand(H)
+    y = st.stree_tree_ssd(torch.full((B, N), -1, dtype=torch.int32, device="cuda"), x, dt, A, Bm, Cm, D)
+    want = ((Bm * Cm).sum(-1) * dt + D).unsqueeze(-1) * x
+    # one product of 64 fp32 terms each, in another order
+    assert bool(((y - want).abs() <= 2e-5 * (want.abs() + x.abs() * (dt * 8 + 1).unsqueeze(-1))).all())
