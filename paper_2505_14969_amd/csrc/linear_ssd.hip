@@ -864,8 +864,27 @@ bool linear_ssd_supported(const stree_dims &d, const void *x, const void *Bm, co
 
 hipError_t launch_linear_ssd(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm,
                              const void *Cm, const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
-    return d.state_dtype == STREE_BF16 ? launch_h<bf16_t>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st)
-                                       : launch_h<float>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    // A grid dimension holds 2^32 work items; a head takes at most four workgroups of 512 lanes.  More heads than 2^20
+    // go as several launches, whole sequences each.
+    const int64_t T = d.nnodes, es = d.state_dtype == STREE_BF16 ? 2 : 4;
+    const int per = (1 << 20) / d.nheads;
+    auto at = [](auto *p, int64_t bytes) {
+        typedef typename std::conditional<std::is_const<typename std::remove_pointer<decltype(p)>::type>::value, const char, char>::type byte;
+        return p ? (decltype(p))((byte *)p + bytes) : p;
+    };
+    for (int b = 0; b < d.batch; b += per) {
+        stree_dims s = d;
+        s.batch = d.batch - b < per ? d.batch - b : per;
+        const int64_t state = (int64_t)b * d.nheads * d.headdim * d.dstate * es;
+        const void *xs = at(x, b * T * d.x_stride_n * 2), *Bs = at(Bm, b * T * d.b_stride_n * 2);
+        const void *Cs = at(Cm, b * T * d.c_stride_n * 2), *hs = at(h0, state);
+        const float *ds = at(dt, b * T * d.nheads * 4);
+        void *ys = at(y, b * T * d.nheads * d.headdim * 2), *ho = at(h_out, state);
+        const hipError_t e = d.state_dtype == STREE_BF16 ? launch_h<bf16_t>(s, xs, ds, A, Bs, Cs, D, hs, ys, ho, st)
+                                                         : launch_h<float>(s, xs, ds, A, Bs, Cs, D, hs, ys, ho, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace stree

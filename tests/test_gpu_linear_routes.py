@@ -68,3 +68,33 @@ def test_prefix_reads_nothing_behind_the_last_token(st, oracle, T, P, S):
     assert_parity(to_host(y), want_y, TOL["bf16"], "y", kind="y")
     _, h2 = st.stree_linear_ssd(views[0], to_dev(dt), to_dev(A), views[1], h0=to_dev(h0), want_y=False)
     assert_parity(to_host(h2), want_h, 1e-4, "state only", kind="state")
+
+
+def test_prefix_of_more_heads_than_one_grid_dimension_holds(st):
+    """257 x 65535 heads of one token (a state of 138 GB in bf16): as one workgroup each, more than 2^32 work items; whole
+    sequences go as several launches.  Closed forms at one token: h = dt x (outer) B, y = (dt <B, C> + D) x."""
+    import torch
+    B, T, H, P, S, G = 257, 1, 65535, 64, 64, 1
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        pytest.skip("needs 160 GB of free device memory")
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    x, Bm, Cm = rand(B, T, H, P), rand(B, T, G, S), rand(B, T, G, S)
+    dt = torch.rand((B, T, H), generator=gen, device="cuda")
+    A, D = -torch.rand(H, generator=gen, device="cuda"), torch.randn(H, generator=gen, device="cuda")
+    h = torch.full((B, H, P, S), 7.0, dtype=torch.bfloat16, device="cuda")
+    y = st.stree_linear_ssd(x, dt, A, Bm, Cm, D, h_out=h)[0]
+    wrong = []
+    for b in (0, 14, 15, 16, 17, 128, 255, 256):       # (16 sequences a launch)
+        w = dt[b, 0, :, None] * x[b, 0].float()
+        want_h = w[:, :, None] * Bm[b, 0, 0].float()
+        bc = (Bm[b, 0, 0].float() * Cm[b, 0, 0].float()).sum()
+        want = w * bc + D[:, None] * x[b, 0].float()
+        ok_h = ((h[b].float() - want_h).abs() <= 2.0 ** -8 * want_h.abs() + 1e-4).all()
+        # M = dt <B, C> and the result are rounded to bf16
+        ok_y = ((y[b, 0].float() - want).abs() <= 2.0 ** -8 * (want.abs() + 1.1 * (w * bc).abs()) + 1e-6).all()
+        wrong += [] if bool(ok_h) and bool(ok_y) else [b]
+    del h, want_h
+    torch.cuda.empty_cache()
+    assert not wrong
