@@ -381,8 +381,19 @@ __device__ __forceinline__ void chunk_columns(floatx16 (&hacc)[S / 32], uint32_t
     }
 }
 
-// The state between memory and the accumulators: register r of tile st is h[p = l%32][s = st*32 + 16(r/8) + 8lh + r%8];
-// `at` = the lane's row of P, at state column 8lh.
+// The state between memory and the accumulators: register r of tile st is h[p = l%32][s = st*32 + 16(r/8) + 8lh + r%8],
+// so a lane's pieces of 16 bytes lie 32 bytes apart, in 32 different rows.  Moved like that a state was read and written
+// at 2.6 TB/s, and prompts of a few tokens are little else; so it goes through LDS, 128 bytes of every row at a time
+// (a block: 32 fp32 columns or 64 bf16 ones, 4 KB), and memory sees eight whole lines an instruction.  Each 16-byte
+// piece of a block's row lies at piece ^ (row % 8), which keeps both sides free of bank conflicts.  32 sequences x 80
+// heads x 64, one token, fp32 state, y / state only: S = 128 65 / 64 -> 38 / 31 us, S = 64 38 / 39 -> 22 / 18 us (the
+// four waves per head of the kernel before these forms: 50 / 45 and 32 / 23 us); S = 128, 64 tokens, state only, bf16
+// state 44 -> 24 us.
+constexpr int kStateBlock = 32 * 128;
+template <typename HT>
+struct StateBlock {
+    static constexpr int cols = 128 / (int)sizeof(HT), tiles = cols / 32;
+};
 template <int ST>
 __device__ __forceinline__ void zero_state(floatx16 (&hacc)[ST]) {
 #pragma unroll
@@ -390,24 +401,106 @@ __device__ __forceinline__ void zero_state(floatx16 (&hacc)[ST]) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) hacc[st][e] = 0.f;
 }
+__device__ __forceinline__ f32x4 quad(const floatx16 &v, int q) { return f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}; }
+// Requests the 32 rows at `rows` (sr elements apart); they arrive as they lie in memory, in the registers of each
+// block's first tile, and spread_state brings them where they belong.
 template <int ST, typename HT>
-__device__ __forceinline__ void load_state(floatx16 (&hacc)[ST], const HT *at) {
+__device__ __forceinline__ void request_state(floatx16 (&hacc)[ST], const HT *rows, int sr, int lane) {
+    using Blk = StateBlock<HT>;
+    lane = (int)fresh(lane);
 #pragma unroll
-    for (int st = 0; st < ST; ++st)
+    for (int st = 0; st < ST; st += Blk::tiles)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {                 // half of the tile q/2, columns 4(q%2)
-            const float4 v = load_state4(at + st * 32 + 16 * (q >> 1) + 4 * (q & 1));
-            hacc[st][4 * q] = v.x; hacc[st][4 * q + 1] = v.y; hacc[st][4 * q + 2] = v.z; hacc[st][4 * q + 3] = v.w;
+        for (int q = 0; q < 4; ++q) {                 // rows 8q .. 8q+7, eight lanes each
+            const uint4 v = load_stream16(rows + (8 * q + (lane >> 3)) * sr + st * 32 + (lane & 7) * (Blk::cols / 8));
+            hacc[st][4 * q] = __uint_as_float(v.x); hacc[st][4 * q + 1] = __uint_as_float(v.y);
+            hacc[st][4 * q + 2] = __uint_as_float(v.z); hacc[st][4 * q + 3] = __uint_as_float(v.w);
         }
 }
-template <int ST, typename HT>
-__device__ __forceinline__ void store_state(const floatx16 (&hacc)[ST], HT *at) {
+// the place of a lane's row-wise pieces in a block (+ 1024 for every eight rows), and of its pieces as a column
+__device__ __forceinline__ uint32_t block_row_at(uint32_t block, int lane) { return block + (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 3)) << 4); }
+__device__ __forceinline__ uint32_t block_piece_at(uint32_t block, int piece, int lane) { return block + (lane & 31) * 128 + ((piece ^ (lane & 7)) << 4); }
+
+// ROOM = blocks that the LDS at `room` holds: so many make the trip together.
+template <int ROOM, int ST, typename HT>
+__device__ __forceinline__ void spread_state(floatx16 (&hacc)[ST], uint32_t room, int lane) {
+    using Blk = StateBlock<HT>;
+    lane = (int)fresh(lane);
+    const int lh = lane >> 5;
 #pragma unroll
-    for (int st = 0; st < ST; ++st)
+    for (int st0 = 0; st0 < ST; st0 += ROOM * Blk::tiles) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            store_state4(at + st * 32 + 16 * (q >> 1) + 4 * (q & 1),
-                         make_float4(hacc[st][4 * q], hacc[st][4 * q + 1], hacc[st][4 * q + 2], hacc[st][4 * q + 3]));
+        for (int i = 0; i < ROOM * 4; ++i) {
+            const int st = st0 + i / 4 * Blk::tiles, q = i % 4;
+            if (st < ST) lds_at<f32x4>(block_row_at(room + i / 4 * kStateBlock, lane) + q * 1024) = quad(hacc[st], q);
+        }
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < ROOM * 4; ++i) {
+            const int st = st0 + i / 4 * Blk::tiles, q = i % 4;
+            const uint32_t block = room + i / 4 * kStateBlock;
+            if (st >= ST) continue;
+            if constexpr (sizeof(HT) == 4) {          // columns 16(q/2) + 8lh + 4(q%2)
+                const f32x4 v = lds_at<f32x4>(block_piece_at(block, 4 * (q >> 1) + 2 * lh + (q & 1), lane));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) hacc[st][4 * q + e] = v[e];
+            } else {                                  // tile q/2, columns 16(q%2) + 8lh
+                const u32x4 v = lds_at<u32x4>(block_piece_at(block, 2 * q + lh, lane));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    hacc[st + (q >> 1)][8 * (q & 1) + 2 * e] = bf16_lo(v[e]);
+                    hacc[st + (q >> 1)][8 * (q & 1) + 2 * e + 1] = bf16_hi(v[e]);
+                }
+            }
+        }
+        wave_lds_fence();
+    }
+}
+// The way back, ROOM blocks from tile st0 on: value(st, q) are registers 4q .. 4q+3 of tile st.
+template <int ROOM, int ST, typename HT, typename Value>
+__device__ __forceinline__ void gather_state(Value &&value, int st0, uint32_t room, int lane) {
+    using Blk = StateBlock<HT>;
+    lane = (int)fresh(lane);
+    const int lh = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < ROOM * 4; ++i) {
+        const int st = st0 + i / 4 * Blk::tiles, q = i % 4;
+        const uint32_t block = room + i / 4 * kStateBlock;
+        if (st >= ST) continue;
+        if constexpr (sizeof(HT) == 4) {
+            lds_at<f32x4>(block_piece_at(block, 4 * (q >> 1) + 2 * lh + (q & 1), lane)) = value(st, q);
+        } else {
+            const f32x4 a = value(st + (q >> 1), 2 * (q & 1)), b = value(st + (q >> 1), 2 * (q & 1) + 1);
+            const u32x4 v = {pack2(a[0], a[1]), pack2(a[2], a[3]), pack2(b[0], b[1]), pack2(b[2], b[3])};
+            lds_at<u32x4>(block_piece_at(block, 2 * q + lh, lane)) = v;
+        }
+    }
+    wave_lds_fence();
+}
+template <int ROOM, int ST, typename HT>
+__device__ __forceinline__ void write_state(HT *rows, int sr, int st0, uint32_t room, int lane) {
+    using Blk = StateBlock<HT>;
+    lane = (int)fresh(lane);
+    u32x4 v[ROOM * 4];
+#pragma unroll
+    for (int i = 0; i < ROOM * 4; ++i)
+        if (st0 + i / 4 * Blk::tiles < ST) v[i] = lds_at<u32x4>(block_row_at(room + i / 4 * kStateBlock, lane) + i % 4 * 1024);
+#pragma unroll
+    for (int i = 0; i < ROOM * 4; ++i) {
+        const int st = st0 + i / 4 * Blk::tiles, q = i % 4;
+        if (st < ST)
+            store_stream16(rows + (8 * q + (lane >> 3)) * sr + st * 32 + (lane & 7) * (Blk::cols / 8),
+                           make_uint4(v[i].x, v[i].y, v[i].z, v[i].w));
+    }
+    wave_lds_fence();
+}
+template <int ROOM, int ST, typename HT, typename Value>
+__device__ __forceinline__ void store_state(Value &&value, HT *rows, int sr, uint32_t room, int lane) {
+#pragma unroll
+    for (int st0 = 0; st0 < ST; st0 += ROOM * StateBlock<HT>::tiles) {
+        gather_state<ROOM, ST, HT>(value, st0, room, lane);
+        write_state<ROOM, ST>(rows, sr, st0, room, lane);
+    }
 }
 
 // ---- independent waves --------------------------------------------------------------------------------------
@@ -444,7 +537,9 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
     const bf16_t *Bb = Bm + (size_t)b * T * b_sn + (size_t)g * SR + s0;
     const bf16_t *Cb = Cm + (size_t)b * T * c_sn + (size_t)g * S;
     const float *dtb = dt + (size_t)b * T * H + h;
-    const size_t state_at = ((size_t)bh * P + p0 + l32) * SR + s0 + 8 * lh;
+    const size_t state_at = ((size_t)bh * P + p0) * SR + s0;
+    constexpr int kRoom = L::size / kStateBlock;      // blocks of the state that a wave's tile has room for
+    static_assert(kRoom >= 1, "");
     bf16_t *yb = WY ? y + (size_t)b * T * H * P + (size_t)h * P + p0 : nullptr;
 
     // pairs of chunks [pair0, pair1) of this wave's segment
@@ -493,9 +588,12 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
         load_rows<S, WIDE>(rb, Bb, b_sn, pair0 * 2 * kQ, T, lane);
         __builtin_amdgcn_sched_barrier(0);
     };
+    const bool from_h0 = (NSEG == 1 || seg == 0) && h0;
+    if (from_h0) request_state(hacc, h0 + state_at, SR, lane);
+    __builtin_amdgcn_sched_barrier(0);
     first_loads();
-    if ((NSEG == 1 || seg == 0) && h0)
-        load_state(hacc, h0 + state_at);
+    if (from_h0)
+        spread_state<kRoom, ST, HT>(hacc, tile, lane);
     else
         zero_state(hacc);
 
@@ -525,49 +623,63 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
         }
         if constexpr (NSEG > 1) {
             if constexpr (WY) first_loads();          // of the second pass: in flight through the chain
-            float4 *chain = reinterpret_cast<float4 *>(lds) + (size_t)(wave % NP) * (ST * 4) * 64 + lane;
+            f32x4 *chain = reinterpret_cast<f32x4 *>(lds) + (size_t)(wave % NP) * (ST * 4) * 64 + lane;
             const float whole = __builtin_amdgcn_exp2f(sum2);
 #pragma unroll 1
             for (int k = 0; k < NSEG; ++k) {
-                // h0, read again below for the first segment's y, is in registers before this barrier lets another wave
-                // write h_out, which may be h0: the empty statement uses the loaded values, so the loads have returned
-                if (WY && k == NSEG - 1 && seg == 0) {
-#pragma unroll
-                    for (int st = 0; st < ST; ++st) asm volatile("" : "+v"(hacc[st])::"memory");
-                }
+                // h0, read again below for the first segment's y, has arrived ahead of a barrier behind which another wave
+                // writes h_out, which may be h0 (by way of the next wave's tile, which is dead until the chain ends)
+                if (WY && k == NSEG - 1 && from_h0) spread_state<kRoom, ST, HT>(hacc, tile + NP * L::size, lane);
                 __syncthreads();                      // first: the tiles are dead; then: the state is there
                 if (seg != k) continue;
-                auto advance = [&](auto &&put) {      // put(state tile, quarter, state at the segment's end)
+                // the state at the segment's end, then (what this segment's y starts from) the one before it
+                auto end = [&](int st, int q) {
+                    const f32x4 v = chain[(st * 4 + q) * 64], l = quad(hacc[st], q);
+                    return f32x4{fmaf(whole, v[0], l[0]), fmaf(whole, v[1], l[1]), fmaf(whole, v[2], l[2]), fmaf(whole, v[3], l[3])};
+                };
+                auto begin = [&](int st, int q) {
+                    const f32x4 v = chain[(st * 4 + q) * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) hacc[st][4 * q + e] = v[e];
+                };
+                if (k == NSEG - 1) {
+                    if constexpr (WY) {               // (written behind the chain, which the other waves wait for)
+                        static_assert(kRoom * StateBlock<HT>::tiles >= ST, "");
+                        gather_state<kRoom, ST, HT>(end, 0, tile, lane);
+                    } else {
+                        store_state<kRoom, ST>(end, h_out + state_at, SR, tile, lane);
+                    }
+#pragma unroll
+                    for (int st = 0; st < ST && WY; ++st)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) begin(st, q);
+                } else if (k > 0) {
 #pragma unroll
                     for (int st = 0; st < ST; ++st)
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            const float4 v = chain[(st * 4 + q) * 64];
-                            put(st, q, make_float4(fmaf(whole, v.x, hacc[st][4 * q]), fmaf(whole, v.y, hacc[st][4 * q + 1]),
-                                                   fmaf(whole, v.z, hacc[st][4 * q + 2]), fmaf(whole, v.w, hacc[st][4 * q + 3])));
-                            hacc[st][4 * q] = v.x; hacc[st][4 * q + 1] = v.y;    // what this segment's y starts from
-                            hacc[st][4 * q + 2] = v.z; hacc[st][4 * q + 3] = v.w;
+                            const f32x4 n = end(st, q);
+                            if constexpr (WY) begin(st, q);
+                            chain[(st * 4 + q) * 64] = n;
                         }
-                };
-                if (k == NSEG - 1) {
-                    advance([&](int st, int q, float4 n) { store_state4(h_out + state_at + st * 32 + 16 * (q >> 1) + 4 * (q & 1), n); });
-                } else if (k > 0) {
-                    advance([&](int st, int q, float4 n) { chain[(st * 4 + q) * 64] = n; });
                 } else {
 #pragma unroll
                     for (int st = 0; st < ST; ++st)
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
-                            chain[(st * 4 + q) * 64] = make_float4(hacc[st][4 * q], hacc[st][4 * q + 1], hacc[st][4 * q + 2], hacc[st][4 * q + 3]);
+                            chain[(st * 4 + q) * 64] = quad(hacc[st], q);
                     if constexpr (WY) {
                         if (h0)
-                            load_state(hacc, h0 + state_at);
+                            request_state(hacc, h0 + state_at, SR, lane);
                         else
                             zero_state(hacc);
                     }
                 }
             }
-            if constexpr (WY) __syncthreads();        // the chain buffer is the wave tiles' again
+            if constexpr (WY) {
+                __syncthreads();                      // the chain buffer is the wave tiles' again
+                if (seg == NSEG - 1) write_state<kRoom, ST>(h_out + state_at, SR, 0, tile, lane);
+            }
         }
     }
 
@@ -614,7 +726,7 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
             }
         }
     }
-    if constexpr (NSEG == 1) store_state(hacc, h_out + state_at);
+    if constexpr (NSEG == 1) store_state<kRoom, ST>([&](int st, int q) { return quad(hacc[st], q); }, h_out + state_at, SR, tile, lane);
 }
 
 // ---- teams ------------------------------------------------------------------------------------------------
@@ -741,17 +853,20 @@ __global__ __launch_bounds__(64 * (NM + 2), (S == 256 ? 2 : 3)) void linear_ssd_
         const int p0 = wave * kCols;
         const float D_h = D ? D[h] : 0.f;
         bf16_t *yb = y + (size_t)b * T * H * P + (size_t)h * P + p0;
-        const size_t state_at = ((size_t)bh * P + p0 + l32) * S + 8 * lh;
+        const size_t state_at = ((size_t)bh * P + p0) * S;
         const uint32_t x_tile = base + L::x + wave * (2 * kQ * kCols * 2);
         const int y_row = H * P * 2;
         floatx16 hacc[ST];
         if (h0)
-            load_state(hacc, h0 + state_at);
+            request_state(hacc, h0 + state_at, S, lane);
         else
             zero_state(hacc);
         const TransposedAt<S> tr(x_tile, base + L::b, lane);
         const uint32_t row_read = base + L::c + b_piece_at<S>(l32, lh);
         __syncthreads();                              // the first chunk is being prepared
+        // (through the second chunk's B and C tiles, which the helpers write behind the next barrier)
+        static_assert((NM / 2) * kStateBlock <= L::rows, "");
+        if (h0) spread_state<1, ST, HT>(hacc, base + (wave & 1 ? L::b : L::c) + L::rows + (wave >> 1) * kStateBlock, lane);
         __syncthreads();
 #pragma unroll 1
         for (int pr = 0; pr < pairs; ++pr) {
@@ -771,7 +886,8 @@ __global__ __launch_bounds__(64 * (NM + 2), (S == 256 ? 2 : 3)) void linear_ssd_
                 __syncthreads();
             }
         }
-        store_state(hacc, h_out + state_at);
+        static_assert(kStateBlock <= 2 * kQ * kCols * 2, "");
+        store_state<1, ST>([&](int st, int q) { return quad(hacc[st], q); }, h_out + state_at, S, x_tile, lane);
     }
 }
 

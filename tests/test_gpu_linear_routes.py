@@ -3,6 +3,7 @@ oracle's causal scan (bounds as in test_gpu_linear.py: state 1e-4, y one bf16 pr
 import numpy as np
 import pytest
 
+from paper_2505_14969_amd import synth
 from helpers import TOL, assert_parity, to_dev, to_host
 from test_gpu_parity import _rand, st  # noqa: F401  (fixture)
 
@@ -28,6 +29,26 @@ def test_prefix_routes(st, oracle, B, T, H, P, S, G):
     h = to_dev(h0)
     st.stree_linear_ssd(*args, h0=h, want_y=False, h_out=h)
     assert_parity(to_host(h), want_h, 1e-4, f"state only after {T} tokens", kind="state")
+
+
+@pytest.mark.parametrize("B,T,H,P,S,G", ROUTES)
+def test_prefix_routes_with_a_bf16_state(st, oracle, B, T, H, P, S, G):
+    """The state's way between memory and the accumulators in both types: in place, and from an fp32 state of the same
+    values (which both forms widen exactly: y equal, the bf16 state the rounded fp32 one)."""
+    import torch
+    x, dt, A, Bm, Cm, D, h0 = _rand(1900 + T, "bf16", B, T, H, P, S, G, h0=True)
+    h0 = synth.round_to_bf16(h0)
+    want_y, want_h = oracle.linear_scan(x, dt, A, Bm, Cm, D, h0)
+    args = (to_dev(x, "bf16"), to_dev(dt), to_dev(A), to_dev(Bm, "bf16"))
+    y32, h32 = st.stree_linear_ssd(*args, to_dev(Cm, "bf16"), to_dev(D), to_dev(h0))
+    h = to_dev(h0, "bf16")
+    y, _ = st.stree_linear_ssd(*args, to_dev(Cm, "bf16"), to_dev(D), h, h_out=h)
+    assert_parity(to_host(y), want_y, TOL["bf16"], f"y of {T} tokens", kind="y")
+    assert torch.equal(y, y32) and torch.equal(h, h32.bfloat16())
+    h2 = to_dev(h0, "bf16")
+    st.stree_linear_ssd(*args, h0=h2, want_y=False, h_out=h2)
+    for got in (to_host(h), to_host(h2)):              # one rounding (2^-8 relative) of a state within 1e-4
+        assert np.all(np.abs(got - want_h) <= 2.0 ** -8 * np.abs(want_h) + 1e-4 * np.abs(want_h).max())
 
 
 def test_prefix_with_huge_token_strides(st, oracle):
