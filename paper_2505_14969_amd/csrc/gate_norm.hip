@@ -59,21 +59,24 @@ __device__ __forceinline__ float block_sum(float v) {
 }
 
 // TEAM threads per segment: 16, 32 or 64 lanes of a wave (a workgroup of 256 threads then takes 256 / TEAM segments
-// and needs no barrier), 256 = that workgroup, or 0 = a workgroup whose size follows the segment's.  CPT = 16-byte chunks of a
-// segment per thread.
+// and needs no barrier), 256 = that workgroup, or 0 = a workgroup whose size follows the segment's.  CPT = 16-byte
+// chunks of a segment per thread.
 //
-// HBM-bound, and what keeps it from the memory's rate is idle lanes: with one workgroup of 256 threads per segment the
-// 80 chunks of a group of 640 bf16 channels used 80 of 256 threads and one barrier for 2.5 KB of loads.  (Figures: the rule in launch_t.)
+// HBM-bound, and what keeps many segments from the memory's rate is idle lanes: with one workgroup of 256 threads per
+// segment the 80 chunks of a group of 640 bf16 channels used 80 of 256 threads and one barrier for 2.5 KB of loads.
+// (Figures: the rule in launch_t.)
 template <typename T, int CPT, int TEAM>
 __global__ __launch_bounds__(TEAM ? kThreads : 1024) void gate_norm_kernel(const T *__restrict__ y,
                                                                            const T *__restrict__ z, long z_sn,
                                                                            const T *__restrict__ w, T *out, int d, int G,
-                                                                           int gs, int segs, float eps) {
+                                                                           int gs, float eps, int segs) {
     constexpr int EPV = Pack16<T>::N;
     const int team = TEAM ? TEAM : (int)blockDim.x;
     const int t = TEAM ? (int)threadIdx.x & (team - 1) : (int)threadIdx.x;
-    const unsigned own = TEAM ? blockIdx.x * (kThreads / (TEAM ? TEAM : 1)) + threadIdx.x / team : blockIdx.x;
-    const int seg = (int)min(own, (unsigned)segs - 1u);    // (lanes past the last segment follow along and store nothing)
+    constexpr bool kWhole = TEAM == kThreads || TEAM == 0;     // a workgroup per segment
+    const unsigned own = kWhole ? blockIdx.x : blockIdx.x * (kThreads / (TEAM ? TEAM : 1)) + threadIdx.x / team;
+    // (lanes past the last segment follow along and store nothing)
+    const unsigned seg = kWhole ? own : min(own, (unsigned)segs - 1u);
     const int row = seg / G, g = seg % G;
     const size_t oy = (size_t)row * d + (size_t)g * gs, oz = (size_t)row * z_sn + (size_t)g * gs;
     const int chunks = gs / EPV;
@@ -98,7 +101,7 @@ __global__ __launch_bounds__(TEAM ? kThreads : 1024) void gate_norm_kernel(const
             ss = fmaf(v[q][e], v[q][e], ss);
         }
     }
-    if constexpr (TEAM == kThreads || TEAM == 0) {
+    if constexpr (kWhole) {
         ss = block_sum<TEAM / 64>(ss);
     } else {
 #pragma unroll
@@ -108,7 +111,7 @@ __global__ __launch_bounds__(TEAM ? kThreads : 1024) void gate_norm_kernel(const
 #pragma unroll
     for (int q = 0; q < CPT; ++q) {
         const int c = q * team + t;
-        if (c < chunks && own < (unsigned)segs) {
+        if (c < chunks && (kWhole || own < (unsigned)segs)) {
             float fw[EPV], o[EPV];
             Pack16<T>::unpack(*reinterpret_cast<const uint4 *>(w + (size_t)g * gs + (size_t)c * EPV), fw);
 #pragma unroll
@@ -150,7 +153,7 @@ hipError_t launch_t(const stree_dims &d, const void *y, const void *z, long z_sn
     const int chunks = vec ? gs / EPV : 0;
 #define STREE_GN_VEC(CPT, TEAM, GRID, THREADS)                                                                       \
     hipLaunchKernelGGL((gate_norm_kernel<T, CPT, TEAM>), dim3((unsigned)(GRID)), dim3(THREADS), 0, st, (const T *)y,  \
-                       (const T *)z, z_sn, (const T *)w, (T *)out, dd, G, gs, (int)segs, eps)
+                       (const T *)z, z_sn, (const T *)w, (T *)out, dd, G, gs, eps, (int)segs)
 #define STREE_GN_TEAM(TEAM)                                                                                          \
     do {                                                                                                             \
         const long grid = (segs + kThreads / TEAM - 1) / (kThreads / TEAM);                                          \
@@ -161,21 +164,27 @@ hipError_t launch_t(const stree_dims &d, const void *y, const void *z, long z_sn
         else if (cpt == 4) STREE_GN_VEC(4, TEAM, grid, kThreads);                                                    \
         else STREE_GN_VEC(5, TEAM, grid, kThreads);                                                                  \
     } while (0)
-    // Lanes of one wave as long as five chunks a lane hold a segment, as few of them as that allows once there are
-    // enough segments to fill the chip that way: 25088 segments of 80 chunks 30.0 us with a workgroup each, 19.6 us
-    // with 16 lanes each (4.9 TB/s, the rate of a plain copy); 8192 of 128 chunks 12.6 -> 9.3 us with 32 lanes.
+    // Many segments: lanes of one wave for each, as few as hold it in five chunks a lane, which fills the chip.  25088
+    // segments of 80 chunks 30.0 us with a workgroup each, 19.6 us with 16 lanes each (4.9 TB/s, the rate of a plain
+    // copy); 8192 of 128 chunks 12.6 -> 9.3 us with 32 lanes; 4096 of 256 chunks 10.2 -> 9.4 us with 64; 2048 of 128
+    // chunks 4.5 -> 4.3 us.  Above 256 chunks a wave's loads are more than keeps enough waves on a CU once memory is the
+    // bound: 4096 segments of 320 chunks 12.6 -> 10.7 us, but 16384 of them 40.9 -> 43.1 us.
+    // Few segments are a matter of latency, and every chunk more a lane is more of it, so they get a workgroup: 64
+    // segments of 192 chunks 3.5 us so, 4.2 us with a wave; 500 of 256 chunks 4.2 and 5.5 us, 2048 of them 5.3 and 6.3 us.
     // Larger segments take a workgroup: 256 threads up to four chunks a thread (1024 rows of 640 chunks in a decoding
     // step: 320 threads of two chunks cost 0.5 us more), then as many as four chunks a thread ask for.  124 rows of
     // 1280 fp32 chunks took 12.9 us in the two-pass kernel, 4.7 us so.
-    const bool many = segs >= 4096;
+    const bool some = segs >= 2048, many = segs >= 4096;
     if (chunks == 0 || chunks > 4096)
         hipLaunchKernelGGL((gate_norm_plain_kernel<T>), dim3((unsigned)segs), dim3(kThreads), 0, st, (const T *)y,
                            (const T *)z, z_sn, (const T *)w, (T *)out, dd, G, gs, eps);
     else if (many && chunks <= 16 * 5) STREE_GN_TEAM(16);
     else if (many && chunks <= 32 * 5) STREE_GN_TEAM(32);
-    else if (chunks <= 64 * 5) STREE_GN_TEAM(64);
+    else if ((some && chunks <= 128) || (many && chunks <= (segs < 8192 ? 320 : 256))) STREE_GN_TEAM(64);
+    else if (chunks <= kThreads) STREE_GN_VEC(1, kThreads, segs, kThreads);
     else if (chunks <= 2 * kThreads) STREE_GN_VEC(2, kThreads, segs, kThreads);
     else if (chunks <= 3 * kThreads) STREE_GN_VEC(3, kThreads, segs, kThreads);
+    else if (chunks <= 4 * kThreads) STREE_GN_VEC(4, kThreads, segs, kThreads);
     else STREE_GN_VEC(4, 0, segs, (chunks + 255) / 256 * 64);
 #undef STREE_GN_TEAM
 #undef STREE_GN_VEC

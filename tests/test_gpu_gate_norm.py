@@ -33,13 +33,17 @@ SHAPES = [("bf16", 16, 64, 80, 64, 1), ("bf16", 4, 256, 128, 64, 8), ("bf16", 3,
           ("bf16", 2, 7, 3, 20, 3), ("f32", 2, 9, 5, 3, 1), ("bf16", 1, 3, 160, 64, 1), ("bf16", 1, 2, 320, 64, 1)]
 
 
-# where the split of a segment (16-byte pieces per group) over threads changes: 16 lanes up to 80 pieces, 32 up to 160
-# (both from 4096 segments on, also with a last workgroup that is not full), a wave up to 320, a workgroup of 256
+# where the split of a segment (16-byte pieces per group) over threads changes: from 4096 segments on (also with a last
+# workgroup that is not full) 16 lanes up to 80 pieces, 32 up to 160, a wave up to 320; fewer segments a workgroup: of 256
 # threads up to 1024 pieces, of up to 1024 threads up to 4096, one element at a time beyond; segments of one piece
 SHAPES += [("bf16", 8, 64, 80, 64, 8), ("bf16", 9, 57, 80, 64, 8), ("bf16", 8, 64, 72, 72, 8), ("bf16", 8, 65, 160, 64, 8),
            ("bf16", 2, 3, 7, 184, 1), ("bf16", 1, 5, 40, 64, 1), ("bf16", 1, 3, 12, 214, 1), ("bf16", 1, 3, 64, 64, 1),
            ("f32", 1, 3, 48, 64, 1), ("f32", 1, 3, 64, 64, 1), ("f32", 1, 2, 41, 100, 1), ("f32", 1, 2, 256, 64, 1),
            ("f32", 1, 2, 320, 64, 1), ("bf16", 1, 3, 1, 8, 1), ("f32", 17, 241, 2, 4, 1)]
+
+# from 2048 segments on a wave up to 128 pieces, and from 4096 on up to 320 (256 from 8192 on): both sides of each line
+SHAPES += [("bf16", 8, 256, 16, 64, 1), ("bf16", 23, 89, 16, 64, 1), ("bf16", 8, 256, 17, 64, 1), ("bf16", 16, 256, 40, 64, 1),
+           ("bf16", 16, 256, 41, 64, 1), ("bf16", 32, 256, 33, 64, 1), ("f32", 32, 256, 16, 64, 1), ("f32", 7, 13, 16, 64, 1)]
 
 
 @pytest.mark.parametrize("io,B,N,H,P,G", SHAPES)
