@@ -29,6 +29,26 @@ def test_f32_scan_tiles(st, oracle, N, H, P, S, G, with_h0):
     assert_parity(y, to_host(st.stree_tree_ssd(*args, force_fma=True)), 2e-5, "y against the FMA kernel", kind="y")
 
 
+@pytest.mark.parametrize("N,P,S,G", [(64, 64, 128, 1), (33, 40, 64, 2), (20, 65, 256, 1)])
+def test_f32_scan_reports_bad_trees(st, oracle, N, P, S, G):
+    """A bad parent in either row block: that sequence's y is zero in all rows and columns and its status names the
+    node; the others are untouched."""
+    import torch
+    B, H = 4, 2
+    par = np.stack([synth.gen_tree(N, 5, 4, np.random.default_rng(b)) for b in range(B)]).astype(np.int32)
+    par[1, 4], par[3, N - 1] = 4, N + 7
+    x, dt, A, Bm, Cm, D, h0 = _rand(60 + N, "f32", B, N, H, P, S, G)
+    status = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    out = torch.full((B, N, H, P), 3.0, device="cuda")
+    got = to_host(st.stree_tree_ssd(to_dev(par), to_dev(x), to_dev(dt), to_dev(A), to_dev(Bm), to_dev(Cm), to_dev(D),
+                                    to_dev(h0), out=out, status=status))
+    assert list(to_host(status)) == [0, 5, 0, N]
+    assert not got[1].any() and not got[3].any()
+    keep = [0, 2]
+    want = oracle.ssd_paths(par[keep], x[keep], dt[keep], A, Bm[keep], Cm[keep], D, h0[keep])
+    assert_parity(got[keep], want, TOL["f32"], "sequences beside the bad ones", kind="y")
+
+
 @pytest.mark.parametrize("N,P,bad", [(15, 64, 3), (15, 64, 14), (33, 33, 7), (33, 33, 32), (64, 40, 20), (64, 40, 45)])
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 def test_f32_scan_keeps_a_bad_node_to_its_descendants(st, oracle, N, P, bad, value):

@@ -51,6 +51,47 @@ def test_prefix_routes_with_a_bf16_state(st, oracle, B, T, H, P, S, G):
         assert np.all(np.abs(got - want_h) <= 2.0 ** -8 * np.abs(want_h) + 1e-4 * np.abs(want_h).max())
 
 
+# the routes that walk a sequence in segments: with y from 705 tokens on, state only from 449 on, four segments there
+# once eight waves a column group are more than the chip holds at two a SIMD
+SEGMENTS = [(1, 449, 3, 64, 128, 1), (1, 450, 132, 64, 128, 2), (2, 705, 4, 64, 64, 2), (1, 1013, 2, 64, 128, 1),
+            (2, 705, 2, 128, 128, 2), (1, 460, 260, 64, 64, 1), (1, 1013, 2, 64, 256, 1)]
+
+
+@pytest.mark.parametrize("state", ["f32", "bf16"])
+@pytest.mark.parametrize("B,T,H,P,S,G", SEGMENTS)
+def test_prefix_segments_with_every_option(st, oracle, B, T, H, P, S, G, state):
+    """No initial state, no D, raw step sizes with a bias, and a head whose decay underflows within a few tokens (the
+    chain's factor exp(sum s) is then 0 for every segment)."""
+    import torch
+    x, _, A, Bm, Cm, D, h0 = _rand(2900 + T + H, "bf16", B, T, H, P, S, G, h0=True)
+    h0 = synth.round_to_bf16(h0) if state == "bf16" else h0
+    rng = np.random.default_rng(T)
+    raw, bias = rng.standard_normal((B, T, H)).astype(np.float32), rng.uniform(-3.0, -1.0, H).astype(np.float32)
+    A[H - 1], bias[H - 1] = -100.0, 0.5
+    dt = oracle.step_size(raw, bias)
+    dx, dB, dC = to_dev(x, "bf16"), to_dev(Bm, "bf16"), to_dev(Cm, "bf16")
+    for with_h0, with_D in ((True, False), (False, True)):
+        opt = (D if with_D else None, h0 if with_h0 else None)
+        want_y, want_h = oracle.linear_scan(x, dt, A, Bm, Cm, *opt)
+        # y: the weights M or the state, and the result, are rounded to bf16 (2^-9 relative each) in front of sums of
+        # terms that are no larger than those of the scan of absolute values
+        terms, _ = oracle.linear_scan(abs(x), dt, A, abs(Bm), abs(Cm), *[None if a is None else abs(a) for a in opt])
+        for want in (True, False):
+            h = torch.empty((B, H, P, S), dtype=torch.bfloat16 if state == "bf16" else torch.float32, device="cuda")
+            y, _ = st.stree_linear_ssd(dx, to_dev(raw), to_dev(A), dB, dC if want else None,
+                                       to_dev(D) if with_D and want else None, to_dev(h0, state) if with_h0 else None,
+                                       want_y=want, h_out=h, dt_bias=to_dev(bias))
+            what = f"h0 {with_h0}, D {with_D}, y {want}"
+            if want:
+                err = np.abs(to_host(y) - want_y)
+                assert np.all(err <= 2.0 ** -8 * terms) and np.linalg.norm(err) <= TOL["bf16"] * np.linalg.norm(want_y), what
+            got = to_host(h)
+            assert np.isfinite(got).all()
+            for k in range(H):                         # head by head: the underflowing one has a scale of its own
+                bound = 1e-4 * np.abs(want_h[:, k]).max() + (2.0 ** -8 * np.abs(want_h[:, k]) if state == "bf16" else 0.0)
+                assert np.all(np.abs(got[:, k] - want_h[:, k]) <= bound), f"state of head {k}, {what}"
+
+
 def test_prefix_with_huge_token_strides(st, oracle):
     """Rows 64 MiB apart: beyond the 32-bit offsets of the ordinary form (17 GB, of which three columns are used; up
     to 256 tokens the entry point refuses such strides)."""
