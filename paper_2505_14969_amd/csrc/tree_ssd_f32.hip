@@ -122,51 +122,50 @@ __global__ __launch_bounds__(64, 1) void tree_ssd_f32_kernel(
         steps(gt, bv, c);
     }
 #pragma unroll
-    for (int q = 0; q < 4 && hrow; ++q) {             // rows of C h0 by exp(s_i)
+    for (int q = 0; q < 4; ++q) {                     // rows of C h0 by exp(s_i) (no state: 0 by 1, whatever s_i is)
         const f32x4 sv = *reinterpret_cast<const f32x4 *>(&sS[it * 32 + 8 * q + 4 * lh]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[4 * q + e] *= expf(sv[e]);
+        for (int e = 0; e < 4; ++e) acc[4 * q + e] *= expf(hrow ? sv[e] : 0.f);
     }
     float xv[16];
-    for (int jt = 0; jt <= it; ++jt) {
-        if (jt > 0) {                                 // (n > 32) Gt of the next column tile
-            const float *row = bbase + (size_t)min(jt * 32 + l32, n - 1) * b_sn;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) gt[e] = 0.f;
-#pragma unroll
-            for (int s0 = S - KC; s0 >= 0; s0 -= KC) {
-#pragma unroll
-                for (int q = 0; q < NG; ++q) {
-                    bv[q] = *reinterpret_cast<const f32x4 *>(row + s0 + 8 * q);
-                    if (S > KC) c[q] = *reinterpret_cast<const f32x4 *>(crow + s0 + 8 * q);
-                }
-                steps(gt, bv, c);
-            }
-        }
+    auto column_tile = [&](int jt) {                  // += M x over the nodes 32 jt ..
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int j = jt * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
             xv[r] = xbase[(size_t)min(j, n - 1) * x_sn];
         }
-        // weight of node j = jt * 32 + 8 (r / 4) + 4 lh + r % 4 for row i (a select: a non-ancestor's weight may overflow)
-        auto weight = [&](int r) {
-            const int j = jt * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-            const float w = gt[r] * expf(s_i - sS[j]) * sDt[j];
-            return (m_i >> j) & 1ull ? w : 0.f;
+        // weights of nodes j0 + e, j0 = jt * 32 + 8 q + 4 lh, for row i (a select: a non-ancestor's weight may overflow)
+        auto weights = [&](int q) {
+            const int j0 = jt * 32 + 8 * q + 4 * lh;
+            const f32x4 sv = *reinterpret_cast<const f32x4 *>(&sS[j0]), dv = *reinterpret_cast<const f32x4 *>(&sDt[j0]);
+            f32x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = gt[4 * q + e] * expf(s_i - sv[e]) * dv[e];
+                w[e] = (m_i >> (j0 + e)) & 1ull ? v : 0.f;
+            }
+            return w;
         };
         bool spoiled = false;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const bool fin = __builtin_isfinite(xv[r]);
-            spoiled |= !fin;
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(weight(r), fin ? xv[r] : 0.f, acc, 0, 0, 0);
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 w = weights(q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool fin = __builtin_isfinite(xv[4 * q + e]);
+                spoiled |= !fin;
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], fin ? xv[4 * q + e] : 0.f, acc, 0, 0, 0);
+            }
         }
         if (__any(spoiled)) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int j = 8 * (r >> 2) + 4 * lh + (r & 3);
-                sM[j * 33 + l32] = weight(r);
-                sX[j * 33 + l32] = xv[r];
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 w = weights(q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    sM[(8 * q + 4 * lh + e) * 33 + l32] = w[e];
+                    sX[(8 * q + 4 * lh + e) * 33 + l32] = xv[4 * q + e];
+                }
             }
             __syncthreads();
 #pragma unroll 1
@@ -181,9 +180,25 @@ __global__ __launch_bounds__(64, 1) void tree_ssd_f32_kernel(
             }
             __syncthreads();
         }
+    };
+    column_tile(0);
+    if (it > 0) {                                     // (n > 32) Gt of the other column tile, then the rest of the sum
+        const float *row = bbase + (size_t)min(32 + l32, n - 1) * b_sn;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) gt[e] = 0.f;
+#pragma unroll
+        for (int s0 = S - KC; s0 >= 0; s0 -= KC) {
+#pragma unroll
+            for (int q = 0; q < NG; ++q) {
+                bv[q] = *reinterpret_cast<const f32x4 *>(row + s0 + 8 * q);
+                if (S > KC) c[q] = *reinterpret_cast<const f32x4 *>(crow + s0 + 8 * q);
+            }
+            steps(gt, bv, c);
+        }
+        column_tile(1);
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {                    // xv: the x rows of this row block (jt == it came last)
+    for (int r = 0; r < 16; ++r) {                    // xv: the x rows of this row block (its own column tile came last)
         const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
         if (it * 32 + row < n && p < P) yrow[(size_t)row * H * P] = fmaf(D_h, xv[r], acc[r]);
     }
