@@ -26,14 +26,20 @@
  *     == 0, 1 <= headdim <= 256, 1 <= dstate <= 256, conv_width in {2,3,4};
  *     batch * nnodes * nheads < 2^31 and nnodes * (token stride) <= 2^29 elements
  *     (32-bit offsets inside the kernels).
- *     An MFMA kernel is used when io_dtype is bf16, headdim in {32,64,128},
- *     dstate % 16 == 0 and pointers/strides are 16-byte aligned; every other
- *     case in the envelope runs a plain fp32-FMA kernel.  Among the MFMA
+ *     A bf16 MFMA kernel is used when io_dtype is bf16, headdim in {32,64,128},
+ *     dstate % 16 == 0 and pointers/strides are 16-byte aligned; a kernel on the
+ *     fp32 matrix instructions when io_dtype is fp32, the tree has at most 64 nodes,
+ *     dstate is 64, 128 or 256 and B, C and the state are 16-byte aligned (bar a
+ *     few nodes of wide heads without a state); every other case in the envelope
+ *     runs a plain fp32-FMA kernel.  Among the bf16 MFMA
  *     shapes, the persistent kernels (the ones the benchmark prices) take
  *     headdim 64 with dstate 64, 128 or 256, and headdim 128 with dstate 128,
  *     at any node count; the remaining MFMA shapes (headdim 32, other dstates,
  *     ...) run one workgroup per (sequence, head) and are several times slower
- *     per node.  Results are the same to rounding on every route.
+ *     per node.  Results are the same to rounding on every route.  Infinities and
+ *     NaN in x: the fp32 routes keep a node's to the nodes that descend from it; the
+ *     bf16 MFMA routes multiply the whole tile (0 times NaN), so that they reach
+ *     other nodes of the same head too.
  */
 #ifndef STREE_H
 #define STREE_H
@@ -63,7 +69,7 @@ enum stree_flags {
     STREE_FLAG_CONV_SILU = 1,    /* tree_conv applies z * sigmoid(z) */
     STREE_FLAG_DT_SOFTPLUS = 2,  /* every `dt` argument (and prev->dt) holds the RAW projection; the kernels use
                                     softplus(dt + dt_bias[h]) as the step size (see stree_dims.dt_bias) */
-    STREE_FLAG_FORCE_FMA = 256,    /* tree_ssd: use the plain fp32-FMA kernel even where MFMA applies */
+    STREE_FLAG_FORCE_FMA = 256,    /* tree_ssd: use the plain fp32-FMA kernel even where a matrix kernel applies */
     STREE_FLAG_GENERAL_MFMA = 1024 /* tree_ssd: trees of more than 64 nodes take the one-workgroup-per-(b,h) MFMA
                                       kernel even where the persistent one applies (same results to rounding) */
 };
@@ -294,7 +300,7 @@ int stree_tree_step(const stree_dims *dims, const stree_replay *prev, const void
  *   out    io [B,N,H,P] dense, MAY alias y
  * fp32 arithmetic, one rounding of the result.  16-byte aligned pointers, a stride and a
  * group size that are multiples of 8 (bf16) or 4 (fp32) elements, and groups of at most
- * 8192 (bf16) / 4096 (fp32) channels take the single-pass kernel (y and z read once);
+ * 32768 (bf16) / 16384 (fp32) channels take the single-pass kernel (y and z read once);
  * anything else a plain two-pass kernel with the same result.  No tree is involved, so
  * there is no tree_status.
  */

@@ -333,8 +333,9 @@ __device__ __forceinline__ void store_transposed_pair(unsigned short *tile, int 
     dst[3 * ldw] = (lo1 >> 16) | (hi1 & 0xffff0000u);
 }
 
-// The unit of work of a workgroup, for grids of 8 ceil(units / 8) workgroups: consecutive units (heads, then sequences) stay on one XCD: workgroups are handed out to the eight XCDs in
-// turn, and the heads of a group share their B and C rows through that XCD's L2.  -1: nothing to do.
+// The unit of work of a workgroup, for grids of 8 ceil(units / 8) workgroups.  Workgroups are handed out to the eight
+// XCDs in turn; consecutive units (heads, then sequences) go to the same XCD, so that the heads of a group share their B
+// and C rows through its L2.  -1: nothing to do.
 __device__ __forceinline__ int unit_of_block(int units) {
     const int per = (units + 7) / 8, slot = blockIdx.x >> 3, unit = (blockIdx.x & 7) * per + slot;
     return slot < per && unit < units ? unit : -1;

@@ -72,8 +72,9 @@ def test_replay_matches_commit_then_scan(st, oracle, io, B, Np, N, H, P, S, G):
     assert np.array_equal(h2, h) and np.array_equal(y2, y)
 
 
-# accepted paths of every length at which the fused kernel changes its way of fetching rows (8 nodes by the tree wave,
-# up to 14 / 18 / 24 by the other waves, the rest from memory) or fills a last group of four nodes only in part
+# accepted paths of every length at which the fused kernel changes its way of fetching rows (one 16-byte piece a thread
+# up to 4 / 6 / 8 / 12 nodes, three pieces up to the 14 / 18 / 24 that LDS has room for, the rest straight from memory) or
+# fills a last group of four nodes only in part
 @pytest.mark.parametrize("P,S,H,state", [(64, 128, 48, "f32"), (64, 128, 48, "bf16"), (64, 64, 40, "f32"),
                                          (64, 64, 4, "bf16"), (64, 256, 20, "f32"), (64, 256, 4, "bf16"),
                                          (128, 128, 20, "f32"), (128, 128, 4, "bf16")])
