@@ -171,16 +171,19 @@ hipError_t launch_t(const stree_dims &d, const void *y, const void *z, long z_sn
     // bound: 4096 segments of 320 chunks 12.6 -> 10.7 us, but 16384 of them 40.9 -> 43.1 us.
     // Few segments are a matter of latency, and every chunk more a lane is more of it, so they get a workgroup: 64
     // segments of 192 chunks 3.5 us so, 4.2 us with a wave; 500 of 256 chunks 4.2 and 5.5 us, 2048 of them 5.3 and 6.3 us.
+    // With one chunk a lane a wave waits no longer: 2000 segments of 16 chunks 3.7 us with a workgroup, 3.0 us with a wave,
+    // 250 of 32 or 64 the same, 120 of 16 2.7 and 2.9 us.
     // Larger segments take a workgroup: 256 threads up to four chunks a thread (1024 rows of 640 chunks in a decoding
     // step: 320 threads of two chunks cost 0.5 us more), then as many as four chunks a thread ask for.  124 rows of
     // 1280 fp32 chunks took 12.9 us in the two-pass kernel, 4.7 us so.
-    const bool some = segs >= 2048, many = segs >= 4096;
+    const int wave_chunks = segs < 256 ? 0 : segs < 2048 ? 64 : segs < 4096 ? 128 : segs < 8192 ? 320 : 256;
+    const bool many = segs >= 4096;
     if (chunks == 0 || chunks > 4096)
         hipLaunchKernelGGL((gate_norm_plain_kernel<T>), dim3((unsigned)segs), dim3(kThreads), 0, st, (const T *)y,
                            (const T *)z, z_sn, (const T *)w, (T *)out, dd, G, gs, eps);
     else if (many && chunks <= 16 * 5) STREE_GN_TEAM(16);
     else if (many && chunks <= 32 * 5) STREE_GN_TEAM(32);
-    else if ((some && chunks <= 128) || (many && chunks <= (segs < 8192 ? 320 : 256))) STREE_GN_TEAM(64);
+    else if (chunks <= wave_chunks) STREE_GN_TEAM(64);
     else if (chunks <= kThreads) STREE_GN_VEC(1, kThreads, segs, kThreads);
     else if (chunks <= 2 * kThreads) STREE_GN_VEC(2, kThreads, segs, kThreads);
     else if (chunks <= 3 * kThreads) STREE_GN_VEC(3, kThreads, segs, kThreads);

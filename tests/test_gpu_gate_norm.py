@@ -41,8 +41,10 @@ SHAPES += [("bf16", 8, 64, 80, 64, 8), ("bf16", 9, 57, 80, 64, 8), ("bf16", 8, 6
            ("f32", 1, 3, 48, 64, 1), ("f32", 1, 3, 64, 64, 1), ("f32", 1, 2, 41, 100, 1), ("f32", 1, 2, 256, 64, 1),
            ("f32", 1, 2, 320, 64, 1), ("bf16", 1, 3, 1, 8, 1), ("f32", 17, 241, 2, 4, 1)]
 
-# from 2048 segments on a wave up to 128 pieces, and from 4096 on up to 320 (256 from 8192 on): both sides of each line
-SHAPES += [("bf16", 8, 256, 16, 64, 1), ("bf16", 23, 89, 16, 64, 1), ("bf16", 8, 256, 17, 64, 1), ("bf16", 16, 256, 40, 64, 1),
+# a wave from 256 segments on up to 64 pieces, from 2048 on up to 128 and from 4096 on up to 320 (256 from 8192 on): both
+# sides of each line
+SHAPES += [("bf16", 1, 255, 8, 64, 1), ("bf16", 1, 256, 8, 64, 1), ("f32", 2, 129, 1, 256, 1), ("bf16", 3, 100, 9, 64, 1),
+           ("bf16", 8, 256, 16, 64, 1), ("bf16", 23, 89, 16, 64, 1), ("bf16", 8, 256, 17, 64, 1), ("bf16", 16, 256, 40, 64, 1),
            ("bf16", 16, 256, 41, 64, 1), ("bf16", 32, 256, 33, 64, 1), ("f32", 32, 256, 16, 64, 1), ("f32", 7, 13, 16, 64, 1)]
 
 
