@@ -214,13 +214,13 @@ static int64_t units_of(const stree_dims &d) {
 // waves than one grid dimension takes (2^32 work items; the FMA kernel's grid has two).  Without a state, a few nodes
 // of a wide head stay with the FMA kernel too: every 32 columns have a wave of their own here, which forms <B, C> for 32
 // rows again.  64 sequences, S = 128: 40 heads of 128 columns, one node 47.9 us, FMA kernel 38.8 us, two 48.8 and 42.0 us,
-// four 50.3 and 50.9 us; 20 heads of 192, four nodes 38.5 and 32.1 us, five 39.0 and 38.0 us; 80 heads of 64, one node 47.8
-// and 52.6 us.
+// four 50.3 and 50.9 us; 20 heads of 192, four nodes 38.5 and 32.1 us, five 40.6 and 37.9 us; 80 heads of 64, one node 47.8
+// and 52.6 us.  S = 64, 40 heads of 96, two nodes 28.3 and 24.0 us.
 bool tree_ssd_f32_supported(const stree_dims &d, const void *Bm, const void *Cm, const void *h0) {
     if (d.io_dtype != STREE_F32 || d.nnodes > 64) return false;
     if (d.dstate != 64 && d.dstate != 128 && d.dstate != 256) return false;
     const int tiles = (d.headdim + 31) / 32;
-    if (!h0 && d.nnodes <= (tiles < 5 ? tiles - 2 : 4)) return false;
+    if (!h0 && d.nnodes <= (tiles < 3 ? 0 : tiles < 5 ? 2 : 4)) return false;
     if ((d.b_stride_n | d.c_stride_n) % 4 != 0 || units_of(d) > (1L << 25)) return false;
     return (((uintptr_t)Bm | (uintptr_t)Cm | (uintptr_t)h0) % 16) == 0;
 }

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("N,H,P,S,G,with_h0", [(1, 2, 64, 64, 1, True), (31, 3, 33, 128, 1, True), (32, 2, 31, 128, 1, False),
                                                (33, 2, 64, 128, 2, True), (63, 4, 1, 64, 1, True), (64, 2, 100, 256, 1, True),
                                                (7, 130, 64, 128, 1, True), (1, 2, 65, 128, 1, False),
-                                               (2, 2, 96, 64, 1, False), (3, 2, 128, 64, 1, False), (4, 2, 129, 64, 1, False),
+                                               (2, 2, 96, 64, 1, False), (3, 2, 96, 64, 1, False), (3, 2, 128, 64, 1, False), (4, 2, 129, 64, 1, False),
                                                (5, 2, 256, 64, 1, False)])
 def test_f32_scan_tiles(st, oracle, N, H, P, S, G, with_h0):
     B = 2
