@@ -114,14 +114,11 @@ __global__ __launch_bounds__(kThreads) void commit_h_kernel(
     const size_t sbase = ((size_t)b * H + h) * P * S + (size_t)s4 * 4;
     const size_t ubase = ((size_t)b * H + h) * P * S;              // FAST: the head's state, uniform
     const uint32_t loff = (uint32_t)(p0 * S + s4 * 4) * (uint32_t)sizeof(HT);   // and this thread's place in it, bytes
-    // n <= 64: every wave asks for the parents and step sizes (wave 0 uses them), ahead of the state
-    int par_j = -1;
-    float dt_j = 0.f;
-    if constexpr (WAVE) {
-        const int node = min(lane, n - 1);
-        par_j = parent[(size_t)b * n + node];
-        dt_j = dt[((size_t)b * n + node) * H + h];
-    }
+    // The parents and step sizes, ahead of the state: what waits for them does not wait for the state.
+    // n <= 64: every wave asks for all of them (wave 0 uses them); else thread i owns node i.
+    const int node = min(WAVE ? lane : tid, n - 1);
+    int par_j = parent[(size_t)b * n + node];
+    float dt_j = dt[((size_t)b * n + node) * H + h];
     // the state rows: these loads fly while the path is worked out (read once: streaming hint,
     // as for the store of the result below)
     float4 acc[kQ];
@@ -162,23 +159,57 @@ __global__ __launch_bounds__(kThreads) void commit_h_kernel(
         }
         __syncthreads();
     } else {
-        __shared__ TreeLds tree;
-        __shared__ uint32_t mask[kMaxNodes * kMaxWords];
-        const int words = (n + 31) / 32;
-        const float dt_raw = tid < n ? dt[((size_t)b * n + tid) * H + h] : 0.f;
-        const float dt_i = (SPL && tid < n) ? softplus_step(dt_raw + bias_h) : dt_raw;
-        bad = build_tree_index(tree, mask, parent + (size_t)b * n, n, n, words, dt_i, A_h);
-        len = 0;
-        if (!bad && k >= 0 && !k_bad) {
-            // compact path(k) (ancestors have smaller labels, so ascending label = root first)
-            if (tid < n && mask_bit(mask, words, k, tid)) {
-                int pos = 0;
-                for (int w = 0; w < (tid >> 5); ++w) pos += __popc(mask[k * words + w]);
-                pos += __popc(mask[k * words + (tid >> 5)] & ((1u << (tid & 31)) - 1u));
-                path[pos] = tid;
-                coef[pos] = tree.dt[tid];              // the step size for now, the weight below
+        // One path is all that is needed of the tree: a wave finds, for each of its 64 nodes, the ancestors among
+        // those 64 and the first one below them (pointer doubling in registers, no barrier); the path of k is then
+        // at most four hops from one wave's nodes to a lower one's.  Before, every workgroup built the whole tree's index
+        // (decay sums and eight-word ancestor rows through LDS, two barriers a round), from parents and steps that were
+        // requested behind the state: 8 x 128 nodes x 80 heads 13.1 -> 10.1 us, 4 x 256 nodes x 128 heads 14.9 -> 10.0 us.
+        __shared__ __align__(16) uint4 up[kMaxNodes];      // ancestors among the wave's nodes (64 bits), the first below
+        __shared__ int bad_w[kThreads / 64];               // first bad node + 1 per wave, or INT_MAX
+        if constexpr (SPL) dt_j = softplus_step(dt_j + bias_h);      // raw projection -> step size
+        {
+            const int base = tid & ~63;
+            const bool ok = tid >= n || ((tid == 0) ? (par_j == -1) : (par_j >= 0 && par_j < tid));
+            const unsigned long long bm = __ballot(!ok);
+            if (lane == 0) bad_w[tid >> 6] = bm ? base + (int)__ffsll((long long)bm) : 0x7fffffff;
+            int j = (tid < n && ok) ? par_j : -1;
+            unsigned long long m = tid < n ? 1ull << lane : 0ull;
+            for (int round = 0; round < 6; ++round) {      // chains of at most 64 nodes
+                const bool in = j >= base;
+                if (!__any(in)) break;
+                const int q = in ? j - base : lane;
+                const int rj = wave_read(j, q);
+                const unsigned long long rm = wave_read(m, q);
+                if (in) {
+                    m |= rm;
+                    j = rj;
+                }
             }
-            len = tree.cnt[k];
+            up[tid] = make_uint4((uint32_t)m, (uint32_t)(m >> 32), (uint32_t)j, 0u);
+        }
+        __syncthreads();
+        bad = 0x7fffffff;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) bad = min(bad, bad_w[w]);
+        bad = bad == 0x7fffffff ? 0 : bad;
+        if (!bad && k >= 0 && !k_bad) {
+            unsigned long long mine = 0;
+            int before = 0;                                // path nodes in the waves below this one
+            for (int cur = k; cur >= 0;) {                 // (a step's jump goes to a lower wave's node: at most four)
+                const uint4 v = up[cur];
+                const unsigned long long m = ((unsigned long long)v.y << 32) | v.x;
+                const int cnt = __popcll(m);
+                len += cnt;
+                if ((cur >> 6) < (tid >> 6)) before += cnt;
+                if ((cur >> 6) == (tid >> 6)) mine = m;
+                cur = (int)v.z;
+            }
+            // (ancestors have smaller labels, so ascending label = root first)
+            if ((mine >> lane) & 1ull) {
+                const int pos = before + __popcll(mine & ((1ull << lane) - 1ull));
+                path[pos] = tid;
+                coef[pos] = dt_j;                          // the step size for now, the weight below
+            }
         }
         __syncthreads();
         // exp(s_k - s_j) as the exponential of the sum of dt_m A over the path nodes BEHIND j, summed
