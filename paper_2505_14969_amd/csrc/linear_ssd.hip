@@ -42,6 +42,7 @@
 // 2 x 2000 tokens 60.5 -> 30 us (S = 64: 47 -> 23 us; S = 256, 32 heads: 94 -> 21 us).
 #include "common.hpp"
 #include "launch.hpp"
+#include "tiles.hpp"
 #include <type_traits>
 
 namespace stree {
@@ -50,41 +51,6 @@ namespace {
 
 constexpr int kQ = 32;             // tokens per chunk
 constexpr int kCols = 32;          // columns of P per wave
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// LDS by byte address: a tile's accesses differ by a few flipped address bits, which is then one
-// instruction (through pointers it is a flip and an addition).
-template <typename V>
-__device__ __forceinline__ __attribute__((address_space(3))) V &lds_at(uint32_t addr) {
-    return *(__attribute__((address_space(3))) V *)(uintptr_t)addr;
-}
-__device__ __forceinline__ uint32_t pack2(float a, float b) {      // bf16 pair, round to nearest even
-    const f32x2 v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-// 16-bit transposing read: the 16 lanes of a group each pass the address of 4 elements (lane i: row
-// i/4, column quad i%4 of a 4 x 16 block) and lane i receives column i of the block's four rows.
-__device__ __forceinline__ s16x4 read_transposed(uint32_t addr) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(&lds_at<s16x4>(addr));
-}
-__device__ __forceinline__ bf16x8 join(s16x4 a, s16x4 b) {
-    typedef short s16x8 __attribute__((ext_vector_type(8)));
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-// LDS written by some lanes of this wave is about to be read by others: the LDS pipe serves a wave
-// in order, so this only keeps the compiler from moving accesses across.
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // The LDS of an independent wave, in bytes from its start: the chunk's B rows, with y its C rows, its x rows (32
 // columns), then per token of two chunks exp(s), s - log dt, the state's weight, s.
@@ -103,14 +69,6 @@ template <int S>
 __device__ __forceinline__ int b_piece_at(int row, int piece) {
     const int blk = S == 64 ? (row >> 1) & 1 : row & 3;
     return row * (S * 2) + ((piece ^ (blk << 2) ^ ((row >> 2) & 3)) << 4);
-}
-
-// LDS addresses differ from a lane's base address by flipped bits or a constant.  This hides the base from the
-// compiler, which would otherwise keep every one of them in a register across the chunk loop (and, having computed
-// it there, not see that the constant fits the instruction).
-__device__ __forceinline__ uint32_t fresh(uint32_t v) {
-    asm volatile("" : "+v"(v));
-    return v;
 }
 
 // One chunk of rows (B or C), whole rows to consecutive lanes, from a buffer that ends with the sequence's last
