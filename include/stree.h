@@ -32,7 +32,7 @@
  *     dstate is 64, 128 or 256 and B, C and the state are 16-byte aligned (bar a
  *     few nodes of wide heads without a state); every other case in the envelope
  *     runs a plain fp32-FMA kernel.  Among the bf16 MFMA
- *     shapes, the persistent kernels (the ones the benchmark prices) take
+ *     shapes, the tuned kernels (the ones the benchmark prices) take
  *     headdim 64 with dstate 64, 128 or 256, and headdim 128 with dstate 128,
  *     at any node count; the remaining MFMA shapes (headdim 32, other dstates,
  *     ...) run one workgroup per (sequence, head) and are several times slower
@@ -71,7 +71,7 @@ enum stree_flags {
                                     softplus(dt + dt_bias[h]) as the step size (see stree_dims.dt_bias) */
     STREE_FLAG_FORCE_FMA = 256,    /* tree_ssd: use the plain fp32-FMA kernel even where a matrix kernel applies */
     STREE_FLAG_GENERAL_MFMA = 1024 /* tree_ssd: trees of more than 64 nodes take the one-workgroup-per-(b,h) MFMA
-                                      kernel even where the persistent one applies (same results to rounding) */
+                                      kernel even where the tuned one applies (same results to rounding) */
 };
 
 /* Problem sizes.  POD, host memory. */
@@ -229,8 +229,9 @@ typedef struct stree_replay {
  *                 or -1 for an accepted index outside [-1, prev->nnodes); in the
  *                 last two cases the state passes through unchanged
  *   every other argument as in stree_tree_ssd; A is shared by both trees.
- * The single-pass kernel covers the shapes of a decoding step (both trees of at
- * most 64 nodes, bf16, the MFMA head shapes); every other shape in the envelope
+ * The single-pass kernels cover the shapes of a decoding step (bf16, the tuned
+ * head shapes; both trees of at most 64 nodes, or the current one of 65 to 128
+ * nodes behind any previous one); every other shape in the envelope
  * runs the two separate kernels back to back on the stream, with the same result.
  * dstate must be a multiple of 4.
  */

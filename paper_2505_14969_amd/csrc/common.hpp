@@ -333,6 +333,19 @@ __device__ __forceinline__ void store_transposed_pair(unsigned short *tile, int 
     dst[3 * ldw] = (lo1 >> 16) | (hi1 & 0xffff0000u);
 }
 
+// A divisor known on the host: quotients of values below 2^31 by one multiplication (m = ceil(2^(32+s) / d), s the
+// position of d's top bit; the error m d - 2^(32+s) is below 2^(s+1)).  A division by a kernel argument takes some forty
+// dependent instructions, and a workgroup's chain began with three of them.
+struct Divisor {
+    int d;
+    uint32_t m = 0, s = 0;             // m = 0: d is a power of two
+    explicit Divisor(int div) : d(div) {
+        while (s < 31 && (1u << (s + 1)) <= (uint32_t)d) ++s;
+        if (d & (d - 1)) m = (uint32_t)(((1ull << (32 + s)) + (uint32_t)d - 1) / (uint32_t)d);
+    }
+    __device__ __forceinline__ int quotient(int v) const { return (int)((m ? __umulhi((uint32_t)v, m) : (uint32_t)v) >> s); }
+};
+
 // The unit of work of a workgroup, for grids of 8 ceil(units / 8) workgroups.  Workgroups are handed out to the eight
 // XCDs in turn; consecutive units (heads, then sequences) go to the same XCD, so that the heads of a group share their B
 // and C rows through its L2.  -1: nothing to do.

@@ -83,7 +83,17 @@ hipError_t launch_tree_ssd_rows(const stree_dims &d, const int32_t *parent, cons
                                 const float *A, const void *Bm, const void *Cm, const float *D, const void *h0,
                                 void *y, int32_t *status, hipStream_t st);
 
-// fused replay + scan: `dp` describes the previous tree (its node count and strides)
+// ... with the replay, trees of at most 128 nodes; `dp` describes the previous tree (its node count and strides)
+bool tree_ssd_replay_rows_supported(const stree_dims &d, const stree_dims &dp, const void *px, const void *pB,
+                                     const void *x, const void *Bm, const void *Cm, const void *y, const void *h0,
+                                     const void *h_out);
+hipError_t launch_tree_ssd_replay_rows(const stree_dims &d, const stree_dims &dp, const int32_t *pparent,
+                                        const int32_t *paccepted, const void *px, const float *pdt, const void *pB,
+                                        const int32_t *parent, const void *x, const float *dt, const float *A,
+                                        const void *Bm, const void *Cm, const float *D, const void *h0,
+                                        void *h_out, void *y, int32_t *status, int32_t *rstatus, hipStream_t st);
+
+// fused replay + scan of trees of at most 64 nodes
 bool tree_ssd_replay_fused_supported(const stree_dims &d, const stree_dims &dp, const void *px, const void *pB,
                                      const void *x, const void *Bm, const void *Cm, const void *y, const void *h0,
                                      const void *h_out);
