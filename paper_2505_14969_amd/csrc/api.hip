@@ -185,11 +185,6 @@ int stree_tree_ssd_replay(const stree_dims *dims, const stree_replay *prev, cons
     if (rc) return rc;
     if (d.batch == 0) return STREE_OK;
     hipStream_t st = (hipStream_t)hip_stream;
-    if (!(d.flags & (STREE_FLAG_FORCE_FMA | STREE_FLAG_GENERAL_MFMA)) &&
-        stree::tree_ssd_replay_rows_supported(d, dp, prev->x, prev->Bm, x, Bm, Cm, y, h0, h_out))
-        return hip_status(stree::launch_tree_ssd_replay_rows(d, dp, prev->parent, prev->accepted, prev->x, prev->dt,
-                                                              prev->Bm, parent, x, dt, A, Bm, Cm, D, h0, h_out, y,
-                                                              tree_status, replay_status, st));
     if (!(d.flags & STREE_FLAG_FORCE_FMA) && stree::tree_ssd_replay_fused_supported(d, dp, prev->x, prev->Bm, x, Bm, Cm, y, h0, h_out))
         return hip_status(stree::launch_tree_ssd_replay_fused(d, dp, prev->parent, prev->accepted, prev->x, prev->dt,
                                                               prev->Bm, parent, x, dt, A, Bm, Cm, D, h0, h_out, y,

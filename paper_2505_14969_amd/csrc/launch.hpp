@@ -93,7 +93,7 @@ hipError_t launch_tree_ssd_replay_rows(const stree_dims &d, const stree_dims &dp
                                         const void *Bm, const void *Cm, const float *D, const void *h0,
                                         void *h_out, void *y, int32_t *status, int32_t *rstatus, hipStream_t st);
 
-// fused replay + scan of trees of at most 64 nodes
+// fused replay + scan, on either kernel; `dp` describes the previous tree
 bool tree_ssd_replay_fused_supported(const stree_dims &d, const stree_dims &dp, const void *px, const void *pB,
                                      const void *x, const void *Bm, const void *Cm, const void *y, const void *h0,
                                      const void *h_out);

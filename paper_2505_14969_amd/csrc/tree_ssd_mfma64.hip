@@ -872,6 +872,7 @@ bool tree_ssd_mfma64_supported(const stree_dims &d) {
 bool tree_ssd_replay_fused_supported(const stree_dims &d, const stree_dims &dp, const void *px, const void *pB,
                                      const void *x, const void *Bm, const void *Cm, const void *y, const void *h0,
                                      const void *h_out) {
+    if (d.nnodes > kB64) return tree_ssd_replay_rows_supported(d, dp, px, pB, x, Bm, Cm, y, h0, h_out);
     if (d.io_dtype != STREE_BF16 || !tree_ssd_mfma64_supported(d) || dp.nnodes > kB64) return false;
     if ((d.x_stride_n | d.b_stride_n | d.c_stride_n | dp.x_stride_n | dp.b_stride_n) % 8 != 0) return false;
     const uintptr_t bits = (uintptr_t)x | (uintptr_t)Bm | (uintptr_t)Cm | (uintptr_t)y | (uintptr_t)px | (uintptr_t)pB |
@@ -884,6 +885,9 @@ hipError_t launch_tree_ssd_replay_fused(const stree_dims &d, const stree_dims &d
                                         const int32_t *parent, const void *x, const float *dt, const float *A,
                                         const void *Bm, const void *Cm, const float *D, const void *h0,
                                         void *h_out, void *y, int32_t *status, int32_t *rstatus, hipStream_t st) {
+    if (d.nnodes > kB64)
+        return launch_tree_ssd_replay_rows(d, dp, pparent, paccepted, px, pdt, pB, parent, x, dt, A, Bm, Cm, D, h0, h_out, y,
+                                           status, rstatus, st);
     const ReplayArgs R = {pparent, paccepted, (const bf16_t *)px, (const bf16_t *)pB, pdt,
                           (long)dp.x_stride_n, (long)dp.b_stride_n, dp.nnodes, h_out, rstatus};
     return launch64<true>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);

@@ -659,7 +659,8 @@ hipError_t launch_tree_ssd_rows(const stree_dims &d, const int32_t *parent, cons
 bool tree_ssd_replay_rows_supported(const stree_dims &d, const stree_dims &dp, const void *px, const void *pB,
                                      const void *x, const void *Bm, const void *Cm, const void *y, const void *h0,
                                      const void *h_out) {
-    if (d.io_dtype != STREE_BF16 || !tree_ssd_rows_supported(d) || d.nnodes > 128) return false;
+    if (d.io_dtype != STREE_BF16 || !tree_ssd_rows_supported(d) || d.nnodes > 128 || (d.flags & STREE_FLAG_GENERAL_MFMA))
+        return false;
     if ((d.x_stride_n | d.b_stride_n | d.c_stride_n | dp.x_stride_n | dp.b_stride_n) % 8 != 0) return false;
     const uintptr_t bits = (uintptr_t)x | (uintptr_t)Bm | (uintptr_t)Cm | (uintptr_t)y | (uintptr_t)px | (uintptr_t)pB |
                            (uintptr_t)h0 | (uintptr_t)h_out;   // (the state is read and written 16 bytes at a time)
