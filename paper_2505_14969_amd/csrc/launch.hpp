@@ -36,6 +36,25 @@ struct LdsLimit {
     }
 };
 
+// A grid dimension holds 2^32 work items: kernels with a workgroup of up to 512 lanes per head (or two) take at most 2^22
+// heads a launch, whole sequences each.  launch(dims of the part, its first sequence)
+template <typename Launch>
+inline hipError_t launch_in_parts(const stree_dims &d, Launch &&launch) {
+    const int per = d.nheads < (1 << 22) ? (1 << 22) / d.nheads : 1;
+    for (int b = 0; b < d.batch; b += per) {
+        stree_dims part = d;
+        part.batch = d.batch - b < per ? d.batch - b : per;
+        const hipError_t e = launch(part, b);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+// `p` moved on by `n` elements; null stays null
+template <typename T>
+inline T *advance(T *p, int64_t n) { return p ? p + n : p; }
+inline const void *advance(const void *p, int64_t bytes) { return p ? static_cast<const char *>(p) + bytes : p; }
+inline void *advance(void *p, int64_t bytes) { return p ? static_cast<char *>(p) + bytes : p; }
+
 // raise, on the current device, every limit that a launcher below would otherwise raise at its first launch
 hipError_t prepare_tree_ssd_mfma();
 hipError_t prepare_tree_ssd_fma();
@@ -76,6 +95,16 @@ bool tree_ssd_mfma64_supported(const stree_dims &d);
 hipError_t launch_tree_ssd_mfma64(const stree_dims &d, const int32_t *parent, const void *x, const float *dt,
                                   const float *A, const void *Bm, const void *Cm, const float *D,
                                   const void *h0, void *y, int32_t *status, hipStream_t st);
+
+// at most 64 nodes: four waves per head, five workgroups a CU
+hipError_t launch_tree_ssd_unit(const stree_dims &d, const int32_t *parent, const void *x, const float *dt,
+                                const float *A, const void *Bm, const void *Cm, const float *D, const void *h0,
+                                void *y, int32_t *status, hipStream_t st);
+hipError_t launch_tree_ssd_replay_unit(const stree_dims &d, const stree_dims &dp, const int32_t *pparent,
+                                       const int32_t *paccepted, const void *px, const float *pdt, const void *pB,
+                                       const int32_t *parent, const void *x, const float *dt, const float *A,
+                                       const void *Bm, const void *Cm, const float *D, const void *h0,
+                                       void *h_out, void *y, int32_t *status, int32_t *rstatus, hipStream_t st);
 
 // 65 .. 256 nodes: a workgroup per head, waves that own 32 nodes each
 bool tree_ssd_rows_supported(const stree_dims &d);

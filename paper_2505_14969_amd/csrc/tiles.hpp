@@ -50,6 +50,41 @@ __device__ __forceinline__ uint32_t fresh(uint32_t v) {
     return v;
 }
 
+// ---- tree scans whose waves own blocks of 32 nodes ------------------------------------------------------------------
+constexpr int kRB = 32;            // nodes per row (and column) block
+constexpr int kPC = 64;            // columns of a head that a workgroup takes
+// Where no |s2| of a head's tree reaches this, exp(s_i - s_j) dt_j is the product of a factor per row and one per
+// column instead of an exponential per pair (16 of a lane's some 100 instructions a tile, each four times as long).
+constexpr float kNarrow = 64.f;
+
+// Rows of S bf16 in LDS: the 16-byte pieces of a row are permuted by the row, so that 16 rows' reads of one piece touch
+// every bank once.
+template <int S>
+__device__ __forceinline__ uint32_t piece_at(int row, int piece) {
+    return row * (S * 2) + ((piece ^ (S == 64 ? (row >> 1) & 7 : row & 15)) << 4);
+}
+
+// bit `b` of w as a mask (the compiler would compare and select, an instruction more)
+__device__ __forceinline__ uint32_t bit_as_mask(uint32_t w, int b) {
+    uint32_t m;
+    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(w), "i"(b));
+    return m;
+}
+// x as tiles of 32 columns, 64 bytes a row: its four pieces permuted by the row's quad, for the lanes that read one
+// piece of 32 rows (the transposing read takes whole quads of rows).
+__device__ __forceinline__ uint32_t x_piece_at(int row, int piece) { return row * 64 + ((piece ^ ((row >> 2) & 3)) << 4); }
+
+// The previous iteration's tree and cached activations (replay).
+struct ReplayArgs {
+    const int32_t *parent, *accepted;   // [B, pn], [B]
+    const bf16_t *x, *Bm;               // [B, pn, H, P], [B, pn, G, S] with token strides x_sn, b_sn
+    const float *dt;                    // [B, pn, H]
+    long x_sn, b_sn;
+    int pn;
+    void *h_out;                        // [B, H, P, S]: the replayed state, in the type the state is kept in
+    int32_t *status;                    // [B] or null
+};
+
 }  // namespace
 
 }  // namespace stree

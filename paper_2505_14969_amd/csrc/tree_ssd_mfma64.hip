@@ -1,7 +1,6 @@
-// Tree scan for trees of at most 64 nodes (one node block), the shape of a
-// speculative-decoding step: persistent, software-pipelined, wave-specialised
-// variant of the MFMA kernel in tree_ssd_mfma.hip (same products, same
-// accumulator layouts).
+// Tree scan for trees of at most 64 nodes with an fp32 state, headdim 64 and some three to six heads a CU, the band in
+// which it is ahead of the workgroup per head of tree_ssd_unit.hip (see unit_is_slower): persistent, software-pipelined,
+// wave-specialised (products and accumulator layouts as in tree_ssd_mfma.hip).
 //
 // A workgroup of 8 waves walks a list of (batch, head) units.  Units are dealt
 // out so that all heads of one sequence land on the same XCD (workgroup id % 8),
@@ -34,6 +33,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "tiles.hpp"
 
 namespace stree {
 
@@ -45,32 +45,18 @@ constexpr int kT64 = 512;   // 8 waves: 4 Y waves, 3 G waves, 1 tree wave
 
 constexpr int kYStage = 4 * 2048;   // bytes at the start of the B tile's LDS that the Y waves turn y around in
 
-// static LDS of the kernel below (C, B, h0b tiles, two X^T tiles, M, tree arrays; with replay
-// the path arrays and, where the B tile has no room behind the y staging area, the path rows)
+// static LDS of the kernel below (C, B, h0b tiles, two X^T tiles, M, tree arrays; with replay the path arrays)
 template <int P, int S>
 struct Lds64 {
     static constexpr int SP = S + 8;
     static constexpr size_t row_bytes = (size_t)(P + S) * 2;                      // x row and B row of a path node
     static constexpr size_t b_bytes = (size_t)kB64 * SP * 2, m_bytes = (size_t)kB64 * kNP64 * 2;
-    static constexpr bool rows_in_b = b_bytes >= kYStage + 8 * row_bytes;
-    // path nodes whose rows LDS has room for: behind the y staging area and (first pass) in the M tile; 24 otherwise
+    // path nodes whose rows LDS has room for: behind the y staging area of the B tile and (first pass) in the M tile
     static constexpr size_t room_b = (b_bytes > kYStage ? b_bytes - kYStage : 0) / row_bytes, room_m = m_bytes / row_bytes;
-    static constexpr int kRows = rows_in_b ? (int)(room_b < room_m ? room_b : room_m) : 24;
-    static constexpr size_t replay_rows = kRows * row_bytes;
+    static constexpr int kRows = (int)(room_b < room_m ? room_b : room_m);
     static constexpr size_t total = (size_t)2 * kB64 * SP * 2 + (size_t)P * SP * 2 + (size_t)2 * P * kNP64 * 2 +
                                     (size_t)kB64 * kNP64 * 2 + 1040;
-    static constexpr size_t total_replay = total + 336 + (rows_in_b ? 0 : replay_rows);
-};
-
-// The previous iteration's tree and cached activations (fused replay variant only).
-struct ReplayArgs {
-    const int32_t *parent, *accepted;   // [B, pn], [B]
-    const bf16_t *x, *Bm;               // [B, pn, H, P], [B, pn, G, S] with token strides x_sn, b_sn
-    const float *dt;                    // [B, pn, H]
-    long x_sn, b_sn;
-    int pn;
-    void *h_out;                        // [B, H, P, S]: the replayed state, in the type the state is kept in
-    int32_t *status;                    // [B] or null
+    static constexpr size_t total_replay = total + 336;
 };
 
 // Wave-level tree index for n <= 64: lane i owns node i; pointer doubling with
@@ -132,14 +118,12 @@ __device__ __forceinline__ int wave_tree_index(int lane, int n, int parent_i, fl
 // nodes an instruction, the fp32 FMAs of the recurrence in the same precision): as vector FMAs it cost the four
 // waves that carry a unit some 56 instructions per path node, while the other four waited (the beams above:
 // 92.5 -> 82.4 us, chains of up to 49 nodes 195 -> 134 us, trees of depth 4 to 8 75.9 -> 72.9 us).
-// HT = type the state is kept in: fp32, or bf16 (then h0 is the MFMA operand as it comes, and the replayed
-// state is rounded once, to the value that is both written back and scanned from).
-template <int P, int S, int WPE, bool RP, bool SPL, typename HT>
+template <int P, int S, int WPE, bool RP, bool SPL>
 __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void tree_ssd_mfma64_kernel(
     const int32_t *__restrict__ parent, int n, int nbatch, int H, int G, const bf16_t *__restrict__ x, long x_sn,
     const float *__restrict__ dt, const float *__restrict__ dt_bias, const float *__restrict__ A,
     const bf16_t *__restrict__ Bm, long b_sn,
-    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const HT *__restrict__ h0,
+    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const float *__restrict__ h0,
     bf16_t *__restrict__ y, int32_t *__restrict__ status, ReplayArgs R) {
     using L = Lds64<P, S>;
     constexpr int SP = L::SP;
@@ -150,7 +134,6 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     constexpr int YT = (P / 32) * 2, YQ = YT / 4;   // Yt tiles, tiles per Y wave
     constexpr int kRowsC = kHalf / (S / 8), kRowsX = kHalf / (P / 8);
     static_assert(NC >= 1 && NX >= 1 && NH >= 1 && YQ >= 1, "tile too small for this thread count");
-    static_assert(NH % 2 == 0 && S % 8 == 0, "a bf16 state is moved eight values at a time");
     // separate LDS objects (not slices of one array), so that the compiler knows that a write to
     // one tile cannot alias a read of another and does not serialise them
     __shared__ __align__(16) bf16_t sC[kB64 * SP];
@@ -168,7 +151,6 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     __shared__ unsigned char sRnode[RP ? kB64 : 4];
     __shared__ int sRlen[1];
     __shared__ float sRdec[1];
-    __shared__ __align__(16) bf16_t sRrows[(RP && !L::rows_in_b) ? L::kRows * (P + S) : 8];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = tid >> 6;
@@ -228,39 +210,26 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     float rD = 0.f;                  // D[h] of the unit whose h0 is in pre[]
     // The state tile in a thread's registers.  Without replay chunk q is element (t + q*kHalf)*4 of the P x S tile.
     // With replay it is the accumulator of the fp32 matrix instructions that advance it (16 x 16 x 4, accumulator
-    // row = state row p, column = state column s): a wave owns 16 rows of every 64, lane l the rows 4 (l >> 4) + i of
-    // those and kCW consecutive columns kCW (l & 15) + t -- column t of each lane makes up tile t, so that a lane's
-    // columns are 16-byte pieces in memory (8 bytes for a bf16 state of 64 columns) all the same.
-    constexpr int kCW = (sizeof(HT) == 2 && S % 128 == 0) ? 8 : 4;   // columns per chunk
-    constexpr int kCB = S / (16 * kCW), kPG = P / 64;                // column blocks; 64-row groups
+    // row = state row p, column = state column s): a wave owns 16 rows, lane l the rows 4 (l >> 4) + i of those and
+    // kCW consecutive columns kCW (l & 15) + t -- column t of each lane makes up tile t, so that a lane's columns are
+    // 16-byte pieces in memory all the same.
+    constexpr int kCW = 4, kCB = S / (16 * kCW);                     // columns per chunk; column blocks
+    static_assert(P == 64, "a wave of each role owns 16 rows of the state");
     auto load_H = [&](int b, int h) {       // the role group that carries this unit
         // the lane-dependent zero keeps this a vector load: it then sits in the same in-order
         // queue as the h0 chunks instead of forcing a scalar-cache wait in the hot window
         if (D) rD = D[h + (opaque(lane) & 0)];
         const char *hb = reinterpret_cast<const char *>(h0 + ((size_t)b * H + h) * P * S);
-        constexpr uint32_t HB = sizeof(HT);    // a bf16 state: the same four values per chunk, in 8 bytes
         if constexpr (RP) {
             const int t = opaque(rt), row0 = (t >> 6) * 16 + ((t & 63) >> 4) * 4, col0 = (t & 15) * kCW;
-            const uint32_t off = (uint32_t)(row0 * S + col0) * HB;
+            const uint32_t off = (uint32_t)(row0 * S + col0) * 4u;
 #pragma unroll
-            for (int q = 0; q < kPG * kCB * 4; ++q) {     // q = (row group, column block, row)
-                const char *src = hb + off + ((q / (4 * kCB) * 64 + q % 4) * S + (q / 4 % kCB) * 16 * kCW) * HB;
-                if constexpr (kCW * HB == 16) {
-                    pre[q] = load_stream16(src);
-                } else {
-                    const uint2 v = load_stream8(src);
-                    pre[q].x = v.x;
-                    pre[q].y = v.y;
-                }
-            }
-        } else if constexpr (HB == 4) {
+            for (int q = 0; q < kCB * 4; ++q)         // q = (column block, row)
+                pre[q] = load_stream16(hb + off + (q % 4 * S + q / 4 * 16 * kCW) * 4);
+        } else {
             const uint32_t off = (uint32_t)opaque(rt) * 16u;
 #pragma unroll
             for (int q = 0; q < NH; ++q) pre[q] = load_stream16(hb + q * (kHalf * 16) + off);
-        } else {                               // no replay, bf16 state: eight values per 16-byte chunk, half as many chunks
-            const uint32_t off = (uint32_t)opaque(rt) * 16u;
-#pragma unroll
-            for (int q = 0; q < NH / 2; ++q) pre[q] = load_stream16(hb + q * (kHalf * 16) + off);
         }
     };
     // C and B tiles of a unit: global -> registers -> LDS in one go (G threads).  Runs only when
@@ -315,40 +284,25 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             const int l = t & 15, kj = (t & 63) >> 4, prow = (t >> 6) * 16;
             const int len = *sRlen;
             const float dec = *sRdec;
-            floatx4 hv[kPG * kCB][kCW];                    // [row group, column block][tile]
+            floatx4 hv[kCB][kCW];                          // [column block][tile]
 #pragma unroll
-            for (int q = 0; q < kPG * kCB * 4; ++q) {
+            for (int q = 0; q < kCB * 4; ++q) {
                 const uint32_t w4[4] = {pre[q].x, pre[q].y, pre[q].z, pre[q].w};
 #pragma unroll
-                for (int e = 0; e < kCW; ++e)
-                    hv[q / 4][e][q % 4] = dec * (sizeof(HT) == 4 ? __uint_as_float(w4[e % 4])
-                                                 : (e & 1) ? bf16_hi(w4[e / 2]) : bf16_lo(w4[e / 2]));
+                for (int e = 0; e < kCW; ++e) hv[q / 4][e][q % 4] = dec * __uint_as_float(w4[e]);
             }
             // four path nodes: lane group kj holds node j of them, its weight cf (0 past the end of the path),
             // its x at row (t & 15) of the wave's rows (operand A) and cf * B at the lane's columns (operand B)
             auto rank4 = [&](bool on, float cf, const char *xr, const char *br) {
-                float av[kPG];
-#pragma unroll
-                for (int g = 0; g < kPG; ++g) {
-                    const uint32_t xw = *reinterpret_cast<const unsigned short *>(xr + (prow + l + g * 64) * 2);
-                    av[g] = on ? __uint_as_float(xw << 16) : 0.f;
-                }
+                const uint32_t xw = *reinterpret_cast<const unsigned short *>(xr + (prow + l) * 2);
+                const float av = on ? __uint_as_float(xw << 16) : 0.f;
 #pragma unroll
                 for (int c = 0; c < kCB; ++c) {
-                    uint32_t bw[kCW / 2];
+                    const uint2 bw = *reinterpret_cast<const uint2 *>(br + (c * 16 + l) * kCW * 2);
+                    const float bf[4] = {bf16_lo(bw.x), bf16_hi(bw.x), bf16_lo(bw.y), bf16_hi(bw.y)};
 #pragma unroll
-                    for (int w = 0; w < kCW / 2; w += 2) {
-                        const uint2 v = *reinterpret_cast<const uint2 *>(br + ((c * 16 + l) * kCW + 2 * w) * 2);
-                        bw[w] = v.x;
-                        bw[w + 1] = v.y;
-                    }
-#pragma unroll
-                    for (int e = 0; e < kCW; ++e) {
-                        const float bv = on ? cf * ((e & 1) ? bf16_hi(bw[e / 2]) : bf16_lo(bw[e / 2])) : 0.f;
-#pragma unroll
-                        for (int g = 0; g < kPG; ++g)
-                            hv[g * kCB + c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[g], bv, hv[g * kCB + c][e], 0, 0, 0);
-                    }
+                    for (int e = 0; e < kCW; ++e)
+                        hv[c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, on ? cf * bf[e] : 0.f, hv[c][e], 0, 0, 0);
                 }
             };
             const int nl = min(len, kRows);
@@ -365,34 +319,17 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                     rank4(j0 + kj < len, sRcoef[j], xb + (size_t)node * R.x_sn * 2, Bb + (size_t)node * R.b_sn * 2);
                 }
             }
-            // the replayed state, written once, through L2 (never read again by this kernel); a bf16 state is
-            // rounded once: the value written back is the MFMA operand
-            char *ob = reinterpret_cast<char *>(reinterpret_cast<HT *>(R.h_out) + ((size_t)b * H + h) * P * S);
+            // the replayed state, written once, through L2 (never read again by this kernel)
+            char *ob = reinterpret_cast<char *>(reinterpret_cast<float *>(R.h_out) + ((size_t)b * H + h) * P * S);
 #pragma unroll
-            for (int q = 0; q < kPG * kCB * 4; ++q) {
-                const int at_row = prow + kj * 4 + q / (4 * kCB) * 64 + q % 4, at_col = (q / 4 % kCB * 16 + l) * kCW;
-                uint32_t w[kCW / 2];
-#pragma unroll
-                for (int e = 0; e < kCW; e += 4) {
-                    const uint2 v = pack_bf16x4(hv[q / 4][e][q % 4], hv[q / 4][e + 1][q % 4], hv[q / 4][e + 2][q % 4],
-                                                hv[q / 4][e + 3][q % 4]);
-                    w[e / 2] = v.x;
-                    w[e / 2 + 1] = v.y;
-                }
-                char *dst = ob + (uint32_t)(at_row * S + at_col) * (uint32_t)sizeof(HT);
-                bf16_t *op = &sH[at_row * SP + at_col];
-                if constexpr (sizeof(HT) == 4)
-                    store_through16(dst, make_uint4(__float_as_uint(hv[q / 4][0][q % 4]), __float_as_uint(hv[q / 4][1][q % 4]),
-                                                    __float_as_uint(hv[q / 4][2][q % 4]), __float_as_uint(hv[q / 4][3][q % 4])));
-                if constexpr (kCW == 8) {
-                    store_through16(dst, make_uint4(w[0], w[1], w[2], w[3]));
-                    *reinterpret_cast<uint4 *>(op) = make_uint4(w[0], w[1], w[2], w[3]);
-                } else {
-                    if constexpr (sizeof(HT) == 2) store_through8(dst, make_uint2(w[0], w[1]));
-                    *reinterpret_cast<uint2 *>(op) = make_uint2(w[0], w[1]);
-                }
+            for (int q = 0; q < kCB * 4; ++q) {
+                const int at_row = prow + kj * 4 + q % 4, at_col = (q / 4 * 16 + l) * kCW;
+                const float v[4] = {hv[q / 4][0][q % 4], hv[q / 4][1][q % 4], hv[q / 4][2][q % 4], hv[q / 4][3][q % 4]};
+                store_through16(ob + (uint32_t)(at_row * S + at_col) * 4u,
+                                make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
+                *reinterpret_cast<uint2 *>(&sH[at_row * SP + at_col]) = pack_bf16x4(v[0], v[1], v[2], v[3]);
             }
-        } else if constexpr (sizeof(HT) == 4) {
+        } else {
 #pragma unroll
             for (int q = 0; q < NH; ++q) {
                 const int e = (t + q * kHalf) * 4, p = e / S, sidx = e % S;
@@ -400,12 +337,6 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                 o[0] = (bf16_t)__uint_as_float(pre[q].x); o[1] = (bf16_t)__uint_as_float(pre[q].y);
                 o[2] = (bf16_t)__uint_as_float(pre[q].z); o[3] = (bf16_t)__uint_as_float(pre[q].w);
                 *reinterpret_cast<bf16x4 *>(&sH[p * SP + sidx]) = o;
-            }
-        } else {                                   // already the MFMA operand: copied as it came
-#pragma unroll
-            for (int q = 0; q < NH / 2; ++q) {
-                const int e = (t + q * kHalf) * 8, p = e / S, sidx = e % S;
-                *reinterpret_cast<uint4 *>(&sH[p * SP + sidx]) = pre[q];
             }
         }
         if (rt == 0) *sDh = rD;      // D of that unit, for the Y waves
@@ -505,8 +436,8 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
         }
         put(0, v0);
     };
-    // LDS rows of the replayed path: behind the y staging area of the idle B tile, or their own array
-    char *const rrows = L::rows_in_b ? reinterpret_cast<char *>(sB) + kYStage : reinterpret_cast<char *>(sRrows);
+    // LDS rows of the replayed path: behind the y staging area of the idle B tile
+    char *const rrows = reinterpret_cast<char *>(sB) + kYStage;
 
     if (nU <= 0) return;
     // (b, h) of the current unit and of the next three.  The loop starts one unit early (k = -1):
@@ -671,7 +602,7 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
         const bool late_tiles = live && fresh_next;
         // replayed path rows of unit k+1: in the first pass the M tile's LDS (the B tile is being
         // written), later the B tile's
-        [[maybe_unused]] char *rbuf = (L::rows_in_b && !live) ? reinterpret_cast<char *>(sM) : rrows;
+        [[maybe_unused]] char *rbuf = !live ? reinterpret_cast<char *>(sM) : rrows;
         if (isY) {
             // ---- phase 3: Yt += Xt M^T over j <= i only (nodes i < 32 have no ancestor j >= 32:
             //      that quadrant of M is never written or read); y = Yt + D x ---------------------------
@@ -820,45 +751,38 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     }
 }
 
-template <int P, int S, bool RP>
-hipError_t launch64_ps(const stree_dims &d, const int32_t *parent, const void *x, const float *dt, const float *A,
-                       const void *Bm, const void *Cm, const float *D, const void *h0, void *y,
-                       int32_t *status, const ReplayArgs &R, hipStream_t st) {
-    constexpr size_t lds = RP ? Lds64<P, S>::total_replay : Lds64<P, S>::total;   // static LDS (upper bound)
-    constexpr int WPE = (2 * (lds + 64) <= 160 * 1024) ? 4 : 2;
+template <int S, bool RP>
+hipError_t launch64(const stree_dims &d, const int32_t *parent, const void *x, const float *dt, const float *A,
+                    const void *Bm, const void *Cm, const float *D, const void *h0, void *y,
+                    int32_t *status, const ReplayArgs &R, hipStream_t st) {
+    constexpr size_t lds = RP ? Lds64<64, S>::total_replay : Lds64<64, S>::total;   // static LDS (upper bound)
+    static_assert(2 * (lds + 64) <= 160 * 1024, "two workgroups a CU");
     const int n_units = d.batch * d.nheads;
-    const int per_cu = (int)((160 * 1024) / (lds + 64));      // resident workgroups per CU by LDS
-    int grid = (n_units + 7) / 8 * 8;
-    const int cap = 256 * (per_cu < 1 ? 1 : (per_cu > 2 ? 2 : per_cu));
-    if (grid > cap) grid = cap;
+    const int grid = n_units > 512 ? 512 : (n_units + 7) / 8 * 8;
     // (the in-kernel softplus is a variant of its own: compiled into the common one, even unused, it costs time)
-#define STREE_LAUNCH64(SPL, HT)                                                                                     \
-    hipLaunchKernelGGL((tree_ssd_mfma64_kernel<P, S, WPE, RP, SPL, HT>), dim3(grid), dim3(kT64), 0, st, parent,     \
+#define STREE_LAUNCH64(SPL)                                                                                         \
+    hipLaunchKernelGGL((tree_ssd_mfma64_kernel<64, S, 4, RP, SPL>), dim3(grid), dim3(kT64), 0, st, parent,          \
                        d.nnodes, d.batch, d.nheads, d.ngroups, (const bf16_t *)x, (long)d.x_stride_n, dt,           \
                        step_bias(d), A, (const bf16_t *)Bm, (long)d.b_stride_n, (const bf16_t *)Cm,                 \
-                       (long)d.c_stride_n, D, (const HT *)h0, (bf16_t *)y, status, R)
-    const bool hb = d.state_dtype == STREE_BF16;
-    if (step_bias(d)) {
-        if (hb) STREE_LAUNCH64(true, bf16_t);
-        else STREE_LAUNCH64(true, float);
-    } else {
-        if (hb) STREE_LAUNCH64(false, bf16_t);
-        else STREE_LAUNCH64(false, float);
-    }
+                       (long)d.c_stride_n, D, (const float *)h0, (bf16_t *)y, status, R)
+    if (step_bias(d)) STREE_LAUNCH64(true);
+    else STREE_LAUNCH64(false);
 #undef STREE_LAUNCH64
     return hipGetLastError();
 }
 
-template <bool RP>
-hipError_t launch64(const stree_dims &d, const int32_t *parent, const void *x, const float *dt, const float *A,
-                    const void *Bm, const void *Cm, const float *D, const void *h0, void *y, int32_t *status,
-                    const ReplayArgs &R, hipStream_t st) {
-    const int P = d.headdim, S = d.dstate;
-    if (P == 64 && S == 128) return launch64_ps<64, 128, RP>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
-    if (P == 64 && S == 64) return launch64_ps<64, 64, RP>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
-    if (P == 64 && S == 256) return launch64_ps<64, 256, RP>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
-    if (P == 128 && S == 128) return launch64_ps<128, 128, RP>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
-    return hipErrorInvalidValue;
+// The band in which the persistent kernel is ahead of a workgroup per head: an fp32 state, and so many heads that all of
+// them enter the workgroup-per-head kernel at once (five a CU, 1280) and read their C and B rows at once, where a
+// persistent workgroup reads them once for the two or three heads it walks.  80 heads, S = 128, persistent / per head:
+// replay + scan, 64 nodes, batch 8 15.1 / 15.5, 12 20.0 / 21.9, 16 24.0 / 25.6, 18 28.6 / 28.4 us, 40 nodes, batch 8 14.7 /
+// 13.7, 12 19.0 / 20.2, 32 nodes, batch 12 18.9 / 18.9, 16 22.8 / 21.9; scan, 64 nodes, batch 12 13.8 / 13.7, 16 15.5 / 16.8,
+// 20 19.7 / 20.6, 26 25.6 / 24.9, 48 nodes, batch 16 15.0 / 14.8; S = 64, scan, 64 nodes, batch 16 12.1 / 12.4.  Beyond it (few
+// heads, more than a round of them, a state in bf16, S = 256, headdim 128) the workgroup per head is ahead by 3 to 30 %.
+bool unit_is_slower(const stree_dims &d, bool replay) {
+    if (d.state_dtype != STREE_F32 || d.headdim != 64) return false;
+    const int units = d.batch * d.nheads;
+    if (replay) return d.dstate == 128 && d.nnodes > 32 && units > 640 && units <= 1408;
+    return (d.dstate == 128 || d.dstate == 64) && d.nnodes > 48 && units > 1024 && units <= 1700;
 }
 
 }  // namespace
@@ -888,15 +812,20 @@ hipError_t launch_tree_ssd_replay_fused(const stree_dims &d, const stree_dims &d
     if (d.nnodes > kB64)
         return launch_tree_ssd_replay_rows(d, dp, pparent, paccepted, px, pdt, pB, parent, x, dt, A, Bm, Cm, D, h0, h_out, y,
                                            status, rstatus, st);
+    if (!unit_is_slower(d, true))
+        return launch_tree_ssd_replay_unit(d, dp, pparent, paccepted, px, pdt, pB, parent, x, dt, A, Bm, Cm, D, h0, h_out, y,
+                                           status, rstatus, st);
     const ReplayArgs R = {pparent, paccepted, (const bf16_t *)px, (const bf16_t *)pB, pdt,
                           (long)dp.x_stride_n, (long)dp.b_stride_n, dp.nnodes, h_out, rstatus};
-    return launch64<true>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
+    return launch64<128, true>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
 }
 
 hipError_t launch_tree_ssd_mfma64(const stree_dims &d, const int32_t *parent, const void *x, const float *dt,
                                   const float *A, const void *Bm, const void *Cm, const float *D,
                                   const void *h0, void *y, int32_t *status, hipStream_t st) {
-    return launch64<false>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, ReplayArgs{}, st);
+    if (!unit_is_slower(d, false)) return launch_tree_ssd_unit(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, st);
+    return d.dstate == 128 ? launch64<128, false>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, ReplayArgs{}, st)
+                           : launch64<64, false>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, ReplayArgs{}, st);
 }
 
 }  // namespace stree

@@ -34,29 +34,6 @@ namespace stree {
 
 namespace {
 
-constexpr int kRB = 32;            // nodes per row (and column) block
-constexpr int kPC = 64;            // columns of a head that a workgroup takes
-// Where no |s2| of a head's tree reaches this, exp(s_i - s_j) dt_j is the product of a factor per row and one per
-// column instead of an exponential per pair (16 of a lane's some 100 instructions a tile, each four times as long).
-constexpr float kNarrow = 64.f;
-
-// Rows of S bf16 in LDS: the 16-byte pieces of a row are permuted by the row, so that 16 rows' reads of one piece touch
-// every bank once.
-template <int S>
-__device__ __forceinline__ uint32_t piece_at(int row, int piece) {
-    return row * (S * 2) + ((piece ^ (S == 64 ? (row >> 1) & 7 : row & 15)) << 4);
-}
-
-// bit `b` of w as a mask (the compiler would compare and select, an instruction more)
-__device__ __forceinline__ uint32_t bit_as_mask(uint32_t w, int b) {
-    uint32_t m;
-    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(w), "i"(b));
-    return m;
-}
-// x as tiles of 32 columns, 64 bytes a row: its four pieces permuted by the row's quad, for the lanes that read one
-// piece of 32 rows (the transposing read takes whole quads of rows).
-__device__ __forceinline__ uint32_t x_piece_at(int row, int piece) { return row * 64 + ((piece ^ ((row >> 2) & 3)) << 4); }
-
 // LDS of a workgroup for NR node blocks, in bytes: the rows of B for one phase (behind the last one the state tile),
 // x, which y takes the place of, and the tree.  C passes through the B and x tiles on its way in.
 template <int S, int NR, bool RP>
@@ -79,17 +56,6 @@ struct RowsLds {
     static constexpr int per_cu = 160 * 1024 / size;
 };
 
-// The previous iteration's tree and cached activations (replay).
-struct ReplayArgs {
-    const int32_t *parent, *accepted;   // [B, pn], [B]
-    const bf16_t *x, *Bm;               // [B, pn, H, P], [B, pn, G, S] with token strides x_sn, b_sn
-    const float *dt;                    // [B, pn, H]
-    long x_sn, b_sn;
-    int pn;
-    void *h_out;                        // [B, H, P, S]: the replayed state, in the type the state is kept in
-    int32_t *status;                    // [B] or null
-};
-
 template <int S, int NR, int WPE, bool RP, typename HT>
 __global__ __launch_bounds__(64 * NR) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void tree_ssd_rows_kernel(
     const int32_t *__restrict__ parent, int n, int units, Divisor H, Divisor per_group, int P, const bf16_t *__restrict__ x, long x_sn,
@@ -102,7 +68,7 @@ __global__ __launch_bounds__(64 * NR) __attribute__((amdgpu_waves_per_eu(WPE, WP
     constexpr int kCB = L::kCB, NB = kCB * kRB * kPieces / T;                   // of the B rows of a phase
     constexpr int kRowsX = T / 8, NX = kNodes / kRowsX;         // rows of x per round; rounds
     constexpr bool kTight = NR == 8;                            // little room in the registers
-    constexpr int kAhead = kTight ? 2 : 4;
+    constexpr int kAhead = kTight ? 3 : 4;
     constexpr int kSlots = NR / 2;                              // groups of 64 nodes, a wave each for the index
     static_assert(NH >= 1 && NB >= 1 && NX == 4 && (!RP || NR == 4), "");
     __shared__ __align__(512) char lds[L::size];
@@ -467,7 +433,8 @@ __global__ __launch_bounds__(64 * NR) __attribute__((amdgpu_waves_per_eu(WPE, WP
                     v[e] = __uint_as_float(__float_as_uint(gt[4 * q + e] * f[e]) & bit_as_mask(word, 8 * q + e));
                 m[q / 2][2 * (q % 2)] = pack2(v[0], v[1]);
                 m[q / 2][2 * (q % 2) + 1] = pack2(v[2], v[3]);
-                if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);     // (register budget)
+                // (formed here: the compiler would put all of this off to the end, behind the branches, and keep f until then)
+                asm volatile("" : "+v"(m[q / 2][2 * (q % 2)]), "+v"(m[q / 2][2 * (q % 2) + 1]));
             }
             const uint32_t x_at = fresh(x_lane + J * (kRB * 64));
 #pragma unroll
@@ -477,7 +444,6 @@ __global__ __launch_bounds__(64 * NR) __attribute__((amdgpu_waves_per_eu(WPE, WP
                     const uint32_t at = x_at + pt * (kNodes * 64) + kk * (16 * 64);
                     acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(join(read_transposed(at), read_transposed((at ^ 32) + 8 * 64)),
                                                                       __builtin_bit_cast(bf16x8, m[kk]), acc[pt], 0, 0, 0);
-                    if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
                 }
         }
     }
@@ -631,12 +597,20 @@ template <int NR, bool RP>
 hipError_t launch_rows(const stree_dims &d, const int32_t *parent, const void *x, const float *dt, const float *A,
                        const void *Bm, const void *Cm, const float *D, const void *h0, void *y, int32_t *status,
                        const ReplayArgs &R, hipStream_t st) {
-    switch (d.dstate) {
-        case 64: return launch_rows_s<64, NR, RP>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
-        case 128: return launch_rows_s<128, NR, RP>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
-        case 256: return launch_rows_s<256, NR, RP>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
-    }
-    return hipErrorInvalidValue;
+    return launch_in_parts(d, [&](const stree_dims &s, int b) {
+        const int64_t nodes = (int64_t)b * s.nnodes, d_inner = (int64_t)s.nheads * s.headdim, es = s.state_dtype == STREE_BF16 ? 2 : 4;
+        const int64_t state = b * d_inner * s.dstate * es;
+        ReplayArgs r = R;
+        if (RP) {
+            const int64_t pnodes = (int64_t)b * r.pn;
+            r.parent += pnodes, r.accepted += b, r.x += pnodes * r.x_sn, r.Bm += pnodes * r.b_sn, r.dt += pnodes * s.nheads;
+            r.h_out = advance(r.h_out, state), r.status = advance(r.status, b);
+        }
+        const auto launch = s.dstate == 64 ? launch_rows_s<64, NR, RP> : s.dstate == 128 ? launch_rows_s<128, NR, RP> : launch_rows_s<256, NR, RP>;
+        return launch(s, parent + nodes, advance(x, nodes * s.x_stride_n * 2), dt + nodes * s.nheads, A,
+                      advance(Bm, nodes * s.b_stride_n * 2), advance(Cm, nodes * s.c_stride_n * 2), D, advance(h0, state),
+                      advance(y, nodes * d_inner * 2), advance(status, b), r, st);
+    });
 }
 
 }  // namespace
