@@ -1,4 +1,5 @@
-"""Build libstree.so (the C-ABI HIP library) for gfx950 with hipcc, in-tree."""
+"""Build libstree.so (the C-ABI HIP library) for gfx950 with hipcc, and _host.so (the binding's native half) with the
+host compiler against the installed torch, both in-tree."""
 from __future__ import annotations
 
 import glob
@@ -11,6 +12,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libstree.so")
+HOST = os.path.join(HERE, "_host.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-gpu-rdc",
@@ -35,16 +37,34 @@ def _run(cmd, verbose):
         print(err, file=sys.stderr)
 
 
+def host_command():
+    """The host compiler's line for _host.so: no device code, the installed torch's headers and libraries."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(os.path.abspath(torch.__file__))
+    rocm = os.path.dirname(os.path.dirname(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")))
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DNDEBUG", "-D__HIP_PLATFORM_AMD__=1",
+            "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-Wno-deprecated-declarations",
+            "-isystem", os.path.join(root, "include"), "-isystem", sysconfig.get_paths()["include"],
+            "-isystem", os.path.join(rocm, "include"), os.path.join(CSRC, "host.cpp"), "-L" + os.path.join(root, "lib"),
+            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source to an object file (side by side, a few at a time) and link them."""
+    """Compile every source to an object file (side by side, a few at a time) and link them; the native half of the
+    binding beside them."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     flags = [f for f in HIPCC_FLAGS if f != "-shared"]
     jobs = max(1, min(8, os.cpu_count() or 1))
     with tempfile.TemporaryDirectory(prefix="stree_build_") as tmp:
         objs = [os.path.join(tmp, os.path.basename(src) + ".o") for src in sources()]
         with ThreadPoolExecutor(max_workers=jobs) as pool:
+            host = pool.submit(_run, host_command() + ["-o", HOST + ".tmp"], verbose)
             list(pool.map(lambda so: _run([hipcc] + flags + ["-c", so[0], "-o", so[1]], verbose), zip(sources(), objs)))
+            host.result()
         _run([hipcc] + HIPCC_FLAGS + objs + ["-o", LIB + ".tmp"], verbose)
+    os.replace(HOST + ".tmp", HOST)
     os.replace(LIB + ".tmp", LIB)
     return LIB
 

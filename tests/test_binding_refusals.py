@@ -1,0 +1,100 @@
+"""What the binding refuses before anything is launched, on the CPU: wrong shapes, types, strides and objects, entry point by
+entry point, and that no argument of a call is lost on its way to the native half."""
+import inspect
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2505_14969_amd import binding as st
+
+B, N, H, P, S, G, W, NP = 2, 6, 4, 64, 128, 2, 4, 5
+CC = H * P + 2 * G * S
+BF = torch.bfloat16
+
+
+def _good():
+    z = torch.zeros
+    rows, prev = z(B, N, CC, dtype=BF), z(B, NP, CC, dtype=BF)
+    x, Bm, Cm = z(B, N, H, P, dtype=BF), z(B, N, G, S, dtype=BF), z(B, N, G, S, dtype=BF)
+    px, pB = z(B, NP, H, P, dtype=BF), z(B, NP, G, S, dtype=BF)
+    par, ppar, acc = z(B, N, dtype=torch.int32), z(B, NP, dtype=torch.int32), z(B, dtype=torch.int32)
+    dt, pdt, A, D, h0 = z(B, N, H), z(B, NP, H), z(H), z(H), z(B, H, P, S)
+    cs, w, b = z(B, W - 1, CC, dtype=BF), z(CC, W, dtype=BF), z(CC, dtype=BF)
+    heads = dict(nheads=H, headdim=P, dstate=S, ngroups=G)
+    return {
+        "stree_tree_conv": dict(parent=par, xbc_pre=rows, conv_state=cs, conv_w=w, conv_b=b, **heads),
+        "stree_tree_ssd": dict(parent=par, x=x, dt=dt, A=A, Bm=Bm, Cm=Cm, D=D, h0=h0),
+        "stree_commit_state": dict(parent=par, accepted=acc, x=x, dt=dt, A=A, Bm=Bm, h0=h0, xbc_pre=rows, conv_state=cs),
+        "stree_tree_ssd_replay": dict(prev_parent=ppar, prev_accepted=acc, prev_x=px, prev_dt=pdt, prev_Bm=pB, parent=par, x=x,
+                                      dt=dt, A=A, Bm=Bm, Cm=Cm, D=D, h0=h0),
+        "stree_tree_conv_replay": dict(prev_parent=ppar, prev_accepted=acc, prev_xbc_pre=prev, parent=par, xbc_pre=rows,
+                                       conv_state=cs, conv_w=w, conv_b=b, **heads),
+        "stree_tree_step": dict(prev_parent=ppar, prev_accepted=acc, prev_xbc_pre=prev, prev_xbc_out=prev.clone(), prev_dt=pdt,
+                                parent=par, xbc_pre=rows, conv_state=cs, conv_w=w, conv_b=b, dt=dt, A=A, D=D, h0=h0, **heads),
+        "stree_gate_norm": dict(y=x, z=x.clone(), norm_w=torch.ones(H * P, dtype=BF), ngroups=G),
+        "stree_linear_ssd": dict(x=x, dt=dt, A=A, Bm=Bm, Cm=Cm, D=D, h0=h0),
+    }
+
+
+def _strided(*shape, dtype=BF):                          # the right shape, rows twice as far apart
+    return torch.zeros(*shape[:-1], 2 * shape[-1], dtype=dtype)[..., :shape[-1]]
+
+
+REFUSED = [
+    ("stree_tree_conv", "xbc_pre", lambda t: t[0], ValueError), ("stree_tree_conv", "xbc_pre", lambda t: t[..., :-8], AssertionError),
+    ("stree_tree_conv", "xbc_pre", lambda t: t.double(), TypeError), ("stree_tree_conv", "nheads", lambda v: v + 1, AssertionError),
+    ("stree_tree_conv", "nheads", lambda v: float(v), TypeError), ("stree_tree_conv", "conv_w", lambda t: _strided(CC, W), AssertionError),
+    ("stree_tree_conv", "conv_state", lambda t: _strided(B, W - 1, CC), AssertionError),
+    ("stree_tree_conv", "conv_state", lambda t: None, AttributeError),
+    ("stree_tree_ssd", "x", lambda t: t[0], ValueError), ("stree_tree_ssd", "x", lambda t: t.double(), TypeError),
+    ("stree_tree_ssd", "x", lambda t: t.float().numpy(), AttributeError), ("stree_tree_ssd", "Bm", lambda t: _strided(B, N, G, S), AssertionError),
+    ("stree_tree_ssd", "Cm", lambda t: torch.zeros(B, 2 * N, G, S, dtype=BF)[:, :N], AssertionError),
+    ("stree_tree_ssd", "dt", lambda t: t.double(), AssertionError), ("stree_tree_ssd", "dt", lambda t: _strided(B, N, H, dtype=torch.float32), AssertionError),
+    ("stree_tree_ssd", "h0", lambda t: t.double(), TypeError), ("stree_tree_ssd", "out", lambda t: _strided(B, N, H, P), AssertionError),
+    ("stree_tree_ssd", "dt_bias", lambda t: torch.zeros(H + 1), AssertionError), ("stree_tree_ssd", "dt_bias", lambda t: torch.zeros(H, dtype=BF), AssertionError),
+    ("stree_tree_ssd", "parent", lambda t: [0], AttributeError),
+    ("stree_commit_state", "x", lambda t: t[0], ValueError), ("stree_commit_state", "h_out", lambda t: torch.zeros(B, H, P, S, dtype=BF), AssertionError),
+    ("stree_commit_state", "conv_state", lambda t: None, AttributeError), ("stree_commit_state", "accepted", lambda t: 0, AttributeError),
+    ("stree_tree_ssd_replay", "prev_x", lambda t: t[:, :, :-1], AssertionError), ("stree_tree_ssd_replay", "prev_x", lambda t: t.float(), AssertionError),
+    ("stree_tree_ssd_replay", "prev_dt", lambda t: t[:, :-1], AssertionError), ("stree_tree_ssd_replay", "prev_Bm", lambda t: t[:, :-1], AssertionError),
+    ("stree_tree_ssd_replay", "h0", lambda t: _strided(B, H, P, S, dtype=torch.float32), AssertionError),
+    ("stree_tree_ssd_replay", "h_out", lambda t: torch.zeros(B, H, P, S, dtype=BF), AssertionError),
+    ("stree_tree_conv_replay", "prev_xbc_pre", lambda t: t[..., :-8], AssertionError),
+    ("stree_tree_conv_replay", "conv_state_out", "conv_state", AssertionError),
+    ("stree_tree_step", "prev_xbc_out", lambda t: t[:, :-1], AssertionError), ("stree_tree_step", "prev_dt", lambda t: t.double(), AssertionError),
+    ("stree_tree_step", "dt", lambda t: _strided(B, N, H, dtype=torch.float32), AssertionError), ("stree_tree_step", "h0", lambda t: None, AttributeError),
+    ("stree_tree_step", "conv_state_out", "conv_state", AssertionError), ("stree_tree_step", "dstate", lambda v: S // 2, AssertionError),
+    ("stree_tree_step", "out", lambda t: _strided(B, N, H, P), AssertionError),
+    ("stree_tree_step", "ngroups", lambda v: np.int64(v + 1), AssertionError),             # (numpy's integers are integers)
+    ("stree_gate_norm", "z", lambda t: t.float(), AssertionError), ("stree_gate_norm", "z", lambda t: t[:, :-1], AssertionError),
+    ("stree_gate_norm", "norm_w", lambda t: t[:-1], AssertionError), ("stree_gate_norm", "y", lambda t: _strided(B, N, H, P), AssertionError),
+    ("stree_gate_norm", "y", lambda t: t[0], ValueError),
+    ("stree_linear_ssd", "dt", lambda t: t[:, :-1], AssertionError), ("stree_linear_ssd", "h_out", lambda t: torch.zeros(B, H, P, S, dtype=BF), AssertionError),
+    ("stree_linear_ssd", "x", lambda t: t.half(), TypeError), ("stree_linear_ssd", "Cm", lambda t: _strided(B, N, G, S), AssertionError),
+]
+
+
+@pytest.mark.parametrize("name,arg,change,error", REFUSED)
+def test_refused_before_anything_is_launched(name, arg, change, error):
+    call = _good()[name]
+    call[arg] = call[change] if isinstance(change, str) else change(call.get(arg))
+    with pytest.raises(error):
+        getattr(st, name)(**call)
+
+
+def test_every_argument_reaches_the_native_half():
+    """The functions pass their arguments by position: each by its own name, none twice, as many as the other side takes."""
+    class Seen:
+        def __getattr__(self, entry):
+            return lambda *args: args
+    st.load()
+    kept, st._host = st._host, Seen()
+    try:
+        for name in _good():
+            f = getattr(st, name)
+            names = list(inspect.signature(f).parameters)
+            passed = f(**{n: n for n in names})
+            assert sorted(passed) == sorted(names), name
+    finally:
+        st._host = kept
