@@ -693,7 +693,21 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
 // form Gt and from it the M operand (which do not depend on the columns), half of M each.  The tiles are double
 // buffered: two barriers per chunk, which the others meet between C h and the state.  (One helper that does it all
 // is the slowest wave of the team: 1.2 us a chunk with one team on the CU against 1.05 us; with three teams on it,
-// where the issue slots count, it is 5 to 12 % ahead: 296 and 303 us for 8 x 4096 tokens, 144 and 153 for 4 x 3000.)
+// where the issue slots count, it is 5 to 12 % ahead: 297 and 304 us for 8 x 4096 tokens, 144 and 153 for 4 x 3000.)
+// What bounds a team is the chunk after chunk of its head beside the others of its CU, with no unit of its own full:
+// without the x loads 8 x 4096 tokens (640 heads) take 272 of 291 us, without the y stores 267, without the MFMAs of
+// C h 275, with neither memory nor MFMAs 157.  So a launch lasts as long as the CU with the most teams, and the heads
+// left over from a multiple of the CUs are split where that evens it out: into halves, a team of one column wave each
+// (the rows and Gt are made twice).
+constexpr int kCUs = 256;
+template <int S>
+constexpr int kTeams = S == 256 ? 2 : 3;              // of a CU
+// The unit of a workgroup behind those of the whole heads (its XCD's share in a row, as unit_of_block); -1: none.
+__device__ __forceinline__ int half_of_block(int whole, int units) {
+    const int n = units - whole, at = (int)blockIdx.x - 8 * ((whole + 7) / 8), per = (n + 7) / 8;
+    const int slot = at >> 3, i = (at & 7) * per + slot;
+    return slot < per && i < n ? whole + i : -1;
+}
 template <int S, int NM>
 struct TeamLds {
     static constexpr int rows = kQ * S * 2;           // bytes of one tile
@@ -701,22 +715,24 @@ struct TeamLds {
     static constexpr int w = e + 2 * 2 * kQ * 4, u = w + 2 * 2 * kQ * 4, s2 = u + 2 * kQ * 4, sum = s2 + 2 * kQ * 4, size = sum + 32;
 };
 template <int S, int NM, typename HT>
-__global__ __launch_bounds__(64 * (NM + 2), (S == 256 ? 2 : 3)) void linear_ssd_team_kernel(
-    int T, int H, int G, int units, const bf16_t *__restrict__ x, long x_sn, const float *__restrict__ dt,
+__global__ __launch_bounds__(64 * (NM + 2), kTeams<S>) void linear_ssd_team_kernel(
+    int T, int H, int G, int units, int whole, const bf16_t *__restrict__ x, long x_sn, const float *__restrict__ dt,
     const float *__restrict__ dt_bias, const float *__restrict__ A, const bf16_t *__restrict__ Bm, long b_sn,
     const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const HT *h0,
     bf16_t *__restrict__ y, HT *h_out) {
     constexpr int NK = S / 16, ST = S / 32, P = NM * kCols;
     using L = TeamLds<S, NM>;
     __shared__ __align__(512) char lds[L::size];
-    const int unit = unit_of_block(units);
+    // The first `whole` units are heads, the others halves of heads: the second column wave has nothing to do there.
+    const int unit = (int)blockIdx.x < 8 * ((whole + 7) / 8) ? unit_of_block(whole) : half_of_block(whole, units);
     if (unit < 0) return;
+    const bool half = NM == 2 && unit >= whole;
     // The waves of a workgroup go to the four SIMDs in turn: every other workgroup of a CU (32 CUs to an XCD) swaps
     // the roles around, so that the column waves of all of them do not share two SIMDs.
     const int hw_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wave = NM == 2 && ((blockIdx.x >> 8) & 1) ? hw_wave ^ 2 : hw_wave;
     const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
-    const int bh = unit, b = bh / H, h = bh % H, g = h / (H / G);
+    const int bh = half ? whole + ((unit - whole) >> 1) : unit, b = bh / H, h = bh % H, g = h / (H / G);
     const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const int pairs = (T + 2 * kQ - 1) / (2 * kQ);
 
@@ -808,11 +824,15 @@ __global__ __launch_bounds__(64 * (NM + 2), (S == 256 ? 2 : 3)) void linear_ssd_
         else
             prepare(std::false_type{});
     } else {
-        const int p0 = wave * kCols;
+        if (half && wave > 0) {                       // the others' barriers
+            for (int c = 0; c < 4 * pairs + 2; ++c) __syncthreads();
+            return;
+        }
+        const int column = half ? (unit - whole) & 1 : wave, p0 = column * kCols;
         const float D_h = D ? D[h] : 0.f;
         bf16_t *yb = y + (size_t)b * T * H * P + (size_t)h * P + p0;
         const size_t state_at = ((size_t)bh * P + p0) * S;
-        const uint32_t x_tile = base + L::x + wave * (2 * kQ * kCols * 2);
+        const uint32_t x_tile = base + L::x + column * (2 * kQ * kCols * 2);
         const int y_row = H * P * 2;
         floatx16 hacc[ST];
         if (h0)
@@ -852,9 +872,17 @@ __global__ __launch_bounds__(64 * (NM + 2), (S == 256 ? 2 : 3)) void linear_ssd_
 template <int S, int NM, typename HT>
 hipError_t launch_team(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm, const void *Cm,
                        const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
-    const int units = d.batch * d.nheads;
-    hipLaunchKernelGGL((linear_ssd_team_kernel<S, NM, HT>), dim3(8 * ((units + 7) / 8)), dim3(64 * (NM + 2)), 0, st,
-                       d.nnodes, d.nheads, d.ngroups, units, (const bf16_t *)x, (long)d.x_stride_n, dt, step_bias(d), A,
+    // Halves where every CU has a team and at most half of them would get one more, and all are there at once: S = 128,
+    // 640 heads x 4096 tokens 305 -> 291 us, 320 x 2000 104 -> 95, 288 x 1500 77 -> 71; S = 64, 640 x 1500 92 -> 84;
+    // S = 256, 288 x 1000 80 -> 71.  Where they are not, the order evens itself out (S = 128, 880 heads 90.2 and 89.8
+    // us, 1920 heads 78.9 and 79.6; S = 256, 640 heads 187 and 189), and with fewer than 256 heads a CU's one team
+    // pays for a second (160 heads 96.3 and 99.9 us).
+    const long heads = (long)d.batch * d.nheads, rest = heads % kCUs;
+    const bool split = NM == 2 && heads > kCUs && 2 * rest <= kCUs && heads + rest <= kTeams<S> * kCUs;
+    const int whole = (int)(split ? heads - rest : heads), units = (int)(split ? heads + rest : heads);
+    hipLaunchKernelGGL((linear_ssd_team_kernel<S, NM, HT>), dim3(8 * ((whole + 7) / 8 + (units - whole + 7) / 8)),
+                       dim3(64 * (NM + 2)), 0, st, d.nnodes, d.nheads, d.ngroups, units, whole,
+                       (const bf16_t *)x, (long)d.x_stride_n, dt, step_bias(d), A,
                        (const bf16_t *)Bm, (long)d.b_stride_n, (const bf16_t *)Cm, (long)d.c_stride_n, D, (const HT *)h0,
                        (bf16_t *)y, (HT *)h_out);
     return hipGetLastError();
