@@ -36,10 +36,10 @@
 //   * SEGMENTS (a few sequences): a workgroup's eight waves are pieces of one sequence for the same 32 columns.  Each
 //     forms the state of its piece alone, the pieces are chained through LDS (h <- exp(sum s) h + local, one wave
 //     after the other), and each wave then runs its piece again, with y, from its true initial state.  The waves
-//     share nothing in the loop: no barrier.  State only (no y): the first half is all there is.
+//     share nothing in the loop: no barrier.  State only (no y): the first half is all there is;
+//   * STATE ONLY, long or with many columns: segments whose states are added up, by waves of one or two column groups.
 // Measured (80 heads x 64, S = 128, bf16), before = four waves per head, 64-token chunks, four barriers a chunk:
-// 8 x 4096 tokens 515 -> 302 us, 4 x 3000 235 -> 153 us, 1 x 4096 242 -> 84 us, 1 x 1013 65 -> 28 us; state only
-// 2 x 2000 tokens 60.5 -> 30 us (S = 64: 47 -> 23 us; S = 256, 32 heads: 94 -> 21 us).
+// 8 x 4096 tokens 515 -> 302 us, 4 x 3000 235 -> 153 us, 1 x 4096 242 -> 84 us, 1 x 1013 65 -> 28 us.
 #include "common.hpp"
 #include "launch.hpp"
 #include "tiles.hpp"
@@ -51,6 +51,7 @@ namespace {
 
 constexpr int kQ = 32;             // tokens per chunk
 constexpr int kCols = 32;          // columns of P per wave
+constexpr int kCUs = 256;
 
 // The LDS of an independent wave, in bytes from its start: the chunk's B rows, with y its C rows, its x rows (32
 // columns), then per token of two chunks exp(s), s - log dt, the state's weight, s.
@@ -687,6 +688,188 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
     if constexpr (NSEG == 1) store_state<kRoom, ST>([&](int st, int q) { return quad(hacc[st], q); }, h_out + state_at, SR, tile, lane);
 }
 
+// ---- state only -----------------------------------------------------------------------------------------------
+// Without y nothing couples the state's columns along S (S = 256 runs as two parts of S = 128) and a chunk is one product,
+// h^T <- decay h^T + B^T (w x): NC column groups of 32 to a wave share the B tile, its transposed operands and the steps.
+// `SR`: the state's row length.  (h_out may be h0: no __restrict__ on either.)
+//
+// What bounds it: the rows' way from memory and L2 into LDS, not the products (S = 64, 480 groups x 2050 tokens, of 33 us
+// with 32 columns a wave: without x from memory 23, without B's rows 28, without half of the products 32; every second
+// request more for the same rows costs 5 %).  So a wave takes 64 columns, whole 128-byte lines of x, where enough of them are
+// left; and the segments' states, which one wave after the other takes up in the form above (1 to 2 us a segment), are
+// scaled to the end of them all and added up in pairs.  Before (32 columns, chained) -> now, HBM cold: S = 64, 480 x 2050,
+// bf16 state 33 -> 24 us, 1280 x 4000 121 -> 103; S = 128, 320 x 2000 37 -> 29, 1280 x 4000 161 -> 136, 160 x 600 14.6 -> 10.9,
+// 1280 x 250 20.7 -> 18.8.
+template <int S, int NC>
+struct StateLds {
+    static constexpr int x = kQ * S * 2, w = x + NC * kQ * kCols * 2, size = w + 512;   // (a multiple of a row, see WaveLds)
+    static_assert(size % 512 == 0 && 2 * kQ * 4 <= 512, "");
+};
+template <int S, int NSEG, int NC, typename HT>
+__global__ __launch_bounds__(64 * NSEG, 2) void linear_state_kernel(
+    int T, int H, int G, int P, int SR, int units, const bf16_t *__restrict__ x, long x_sn, const float *__restrict__ dt,
+    const float *__restrict__ dt_bias, const float *__restrict__ A, const bf16_t *__restrict__ Bm, long b_sn,
+    const HT *h0, HT *h_out) {
+    constexpr int NK = S / 16, ST = S / 32, XR = 2 * NC, kRow = 4 * NC;     // 16-byte pieces: of x a lane holds, of an x row
+    using L = StateLds<S, NC>;
+    constexpr size_t kStage = (size_t)L::size * NSEG, kChain = (size_t)(NSEG / 2) * NC * S * kCols * 4;   // overlays the tiles
+    __shared__ float sums[NSEG];
+    __shared__ __align__(512) char lds[kStage > kChain ? kStage : kChain];
+
+    const int unit = unit_of_block(units);
+    if (unit < 0) return;
+    const int seg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, lh = lane >> 5;
+    const int pgs = P / (kCols * NC), parts = SR / S;              // workgroups per head: column groups x parts
+    const int bh = unit / (pgs * parts), b = bh / H, h = bh % H, g = h / (H / G);
+    const int p0 = unit % pgs * NC * kCols, s0 = unit / pgs % parts * S;
+    const uint32_t tile = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds + seg * L::size;
+    const float A2 = A[h] * 1.44269504088896340736f;  // log2 domain
+    const float bias_h = dt_bias ? dt_bias[h] : 0.f;
+    const bf16_t *xb = x + (size_t)b * T * x_sn + (size_t)h * P + p0;
+    const bf16_t *Bb = Bm + (size_t)b * T * b_sn + (size_t)g * SR + s0;
+    const float *dtb = dt + (size_t)b * T * H + h;
+    const size_t state_at = ((size_t)bh * P + p0) * SR + s0;
+    constexpr int kRoom = L::size / kStateBlock;      // blocks of the state that a wave's tile has room for
+    static_assert(kRoom >= 1, "");
+
+    // pairs of chunks [pair0, pair1) of this wave's segment
+    const int pairs = (T + 2 * kQ - 1) / (2 * kQ);
+    const int pair0 = (int)((long)pairs * seg / NSEG), pair1 = (int)((long)pairs * (seg + 1) / NSEG);
+
+    floatx16 hacc[NC][ST];
+    u32x4 rb[NK], rx[XR];
+    float rdt = 0.f;
+    auto load_dt = [&](int t0) { rdt = dtb[(size_t)min(t0 + lane, T - 1) * H]; };
+    auto load_x = [&](int t0) {                       // a chunk's rows (past the end: an empty buffer)
+        const int n = min(kQ, T - t0);
+        const auto buf = make_buffer(xb + (size_t)t0 * x_sn, n > 0 ? (size_t)((n - 1) * (uint32_t)x_sn + NC * kCols) * 2 : 0);
+        const uint32_t off = fresh((uint32_t)(lane / kRow) * (uint32_t)x_sn * 2 + (lane % kRow) * 16);
+#pragma unroll
+        for (int q = 0; q < XR; ++q)
+            rx[q] = __builtin_amdgcn_raw_buffer_load_b128(buf, off + q * (64 / kRow) * (uint32_t)x_sn * 2, 0, 0);
+    };
+    const TransposedAt<S> tr(tile + L::x, tile, lane);
+    const uint32_t quads = tile + L::w + 16 * lh;     // this half's first quad of the weights
+
+    const bool from_h0 = seg == 0 && h0;
+#pragma unroll
+    for (int n = 0; n < NC; ++n)
+        if (from_h0) request_state(hacc[n], h0 + state_at + (size_t)n * kCols * SR, SR, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    // (in the loop's own order: the wait before a use is the least that holds on every way into a loop)
+    load_dt(pair0 * 2 * kQ);
+    load_x(pair0 * 2 * kQ);
+    __builtin_amdgcn_sched_barrier(0);
+    load_rows<S, false>(rb, Bb, b_sn, pair0 * 2 * kQ, T, lane);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        if (from_h0) spread_state<kRoom, ST, HT>(hacc[n], tile, lane);
+        else zero_state(hacc[n]);
+    }
+
+    // the state at the end of the segment: of the first one from h0, of the others from a zero state
+    float sum2 = 0.f;
+#pragma unroll 1
+    for (int pr = pair0; pr < pair1; ++pr) {
+        const int t0 = pr * 2 * kQ;
+        float d_ = rdt, s, behind, sum[2];
+        if (dt_bias) d_ = softplus_step(d_ + bias_h);
+        if (t0 + lane >= T) d_ = 0.f;
+        chunk_scan(d_ * A2, lane, s, behind, sum);
+        lds_at<float>(fresh(tile + L::w + lane * 4)) = d_ * __builtin_amdgcn_exp2f(behind);   // (lane = token)
+        sum2 += sum[0] + sum[1];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const uint32_t at_x = fresh(tile + L::x + (lane % kRow) / 4 * (kQ * kCols * 2) + (lane / kRow) * (kCols * 2) + (lane & 3) * 16);
+#pragma unroll
+            for (int q = 0; q < XR; ++q) lds_at<u32x4>(at_x + q * (64 / kRow) * (kCols * 2)) = rx[q];
+            if (c == 1) load_dt(t0 + 2 * kQ);
+            load_x(t0 + (c + 1) * kQ);
+            __builtin_amdgcn_sched_barrier(0);
+            stage_rows<S>(rb, tile, lane);
+            load_rows<S, false>(rb, Bb, b_sn, t0 + (c + 1) * kQ, T, lane);
+            wave_lds_fence();
+            const uint32_t at0 = fresh(tr.b0), at1 = fresh(tr.b1), x_at = fresh(tr.x), w_at = fresh(quads + c * kQ * 4);
+            const float decay = __builtin_amdgcn_exp2f(sum[c]);
+#pragma unroll
+            for (int n = 0; n < NC; ++n)
+#pragma unroll
+                for (int st = 0; st < ST; ++st)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) hacc[n][st][e] *= decay;
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                const f32x4 w0 = lds_at<f32x4>(w_at + 16 * kk * 4), w1 = lds_at<f32x4>(w_at + (16 * kk + 8) * 4);
+                const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+                bf16x8 term[NC][2];                   // w x as two bf16 terms
+#pragma unroll
+                for (int n = 0; n < NC; ++n) {
+                    float xf[8];
+                    widen(x_operand(x_at + n * (kQ * kCols * 2), kk), xf);
+                    u32x4 v0, v1;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float a = wv[2 * e] * xf[2 * e], b2 = wv[2 * e + 1] * xf[2 * e + 1];
+                        v0[e] = pack2(a, b2);
+                        v1[e] = pack2(a - bf16_lo(v0[e]), b2 - bf16_hi(v0[e]));
+                    }
+                    term[n][0] = __builtin_bit_cast(bf16x8, v0), term[n][1] = __builtin_bit_cast(bf16x8, v1);
+                }
+#pragma unroll
+                for (int st = 0; st < ST; ++st) {
+                    const bf16x8 bt = b_operand<S>(at0, at1, st, kk);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int n = 0; n < NC; ++n)
+                            hacc[n][st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bt, term[n][i], hacc[n][st], 0, 0, 0);
+                }
+            }
+            wave_lds_fence();
+        }
+    }
+    // Each segment's share of the state at the end of them all, added up in pairs, then pairs of pairs.  A wave hands its
+    // sum on in the slot that it took the first one from (nobody else reads that).
+    if constexpr (NSEG > 1) {
+        if (lane == 0) sums[seg] = sum2;
+        __syncthreads();                              // (and the tiles are dead)
+        float later = 0.f;
+        for (int k = seg + 1; k < NSEG; ++k) later += sums[k];
+        const float share = __builtin_amdgcn_exp2f(later);
+#pragma unroll
+        for (int n = 0; n < NC; ++n)
+#pragma unroll
+            for (int st = 0; st < ST; ++st)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) hacc[n][st][e] *= share;
+        constexpr int kSlot = NC * ST * 4 * 64;
+        f32x4 *slots = reinterpret_cast<f32x4 *>(lds) + lane;
+#pragma unroll 1
+        for (int step = 1; step < NSEG; step *= 2) {
+            const bool gives = (seg & (2 * step - 1)) == step, takes = (seg & (2 * step - 1)) == 0;
+            if (gives) {
+#pragma unroll
+                for (int i = 0; i < NC * ST * 4; ++i) slots[(seg >> 1) * kSlot + i * 64] = quad(hacc[i / 4 / ST][i / 4 % ST], i % 4);
+            }
+            __syncthreads();
+            if (takes) {
+#pragma unroll
+                for (int i = 0; i < NC * ST * 4; ++i) {
+                    const f32x4 v = slots[((seg + step) >> 1) * kSlot + i * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) hacc[i / 4 / ST][i / 4 % ST][4 * (i % 4) + e] += v[e];
+                }
+            }
+        }
+        if (seg > 0) return;
+    }
+#pragma unroll
+    for (int n = 0; n < NC; ++n)
+        store_state<kRoom, ST>([&](int st, int q) { return quad(hacc[n][st], q); }, h_out + state_at + (size_t)n * kCols * SR, SR, tile, lane);
+}
+
 // ---- teams ------------------------------------------------------------------------------------------------
 // One workgroup per (sequence, head): NM = P/32 waves that own 32 columns each, and two helpers that work a chunk ahead
 // of them: they bring the rows to LDS (one C and x, the other B and the per-token scalars), and behind a barrier
@@ -699,7 +882,6 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
 // C h 275, with neither memory nor MFMAs 157.  So a launch lasts as long as the CU with the most teams, and the heads
 // left over from a multiple of the CUs are split where that evens it out: into halves, a team of one column wave each
 // (the rows and Gt are made twice).
-constexpr int kCUs = 256;
 template <int S>
 constexpr int kTeams = S == 256 ? 2 : 3;              // of a CU
 // The unit of a workgroup behind those of the whole heads (its XCD's share in a row, as unit_of_block); -1: none.
@@ -899,39 +1081,64 @@ hipError_t launch_n(const stree_dims &d, const void *x, const float *dt, const f
     return hipGetLastError();
 }
 
+template <int S, int NSEG, int NC, typename HT>
+hipError_t launch_s(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm, const void *h0, void *h_out,
+                    hipStream_t st) {
+    const int units = d.batch * d.nheads * (d.headdim / (kCols * NC)) * (d.dstate / S);
+    hipLaunchKernelGGL((linear_state_kernel<S, NSEG, NC, HT>), dim3(8 * ((units + 7) / 8)), dim3(64 * NSEG), 0, st, d.nnodes,
+                       d.nheads, d.ngroups, d.headdim, d.dstate, units, (const bf16_t *)x, (long)d.x_stride_n, dt, step_bias(d), A,
+                       (const bf16_t *)Bm, (long)d.b_stride_n, (const HT *)h0, (HT *)h_out);
+    return hipGetLastError();
+}
+
 // 64 rows beyond a 32-bit byte offset: never met in earnest, one form of the kernel takes them all
 bool wide_strides(const stree_dims &d) {
     return d.x_stride_n >= (1L << 25) || d.b_stride_n >= (1L << 25) || d.c_stride_n >= (1L << 25);
 }
 
-// State only: waves without segments, and the chunk pairs each would walk.  From 8 pairs on a workgroup's waves
-// are segments (one row of chunks per wave costs less than the eight steps of the chain; below, and where y is
-// wanted by a team, the state is formed chunk after chunk).  Eight where a round of workgroups holds them all,
-// four of them else: half of a second round idle costs more than segments twice as long (S = 128, 320 column
-// groups x 2000 tokens: 38 us with eight, 30 us with four).
+// With y: eight segments of a sequence where their waves still fit the chip at two a SIMD and each has a chunk pair and a
+// half (80 heads x 64, S = 128: 84 us against the team's 126 us for 4096 tokens; 28 against 36 for 1013; at 700 tokens they
+// meet).  S = 256: the segments' registers do not fit.
+bool y_in_segments(const stree_dims &d) {
+    const long waves = (long)d.batch * d.nheads * (d.headdim / kCols);
+    return d.dstate != 256 && (d.nnodes + 2 * kQ - 1) / (2 * kQ) >= 12 && waves * 8 <= 2048;
+}
+
+// State only: segments NSEG and 32-column groups NC a wave, by the column groups (of 32, with S = 256 two parts each) and
+// the chunk pairs there are.  Below 8 pairs the state is formed chunk after chunk, and where y would take segments in
+// those: the two give the same bits.  Else the segments' states are added up:
+//   * from 10 pairs on, where the waves of 64 columns still fill half of the CUs: four segments of those (S = 64, 480 groups
+//     x 2050 tokens 24 us, 32 columns 32 us; S = 128, 320 x 2000 29 and 37 us, 1280 x 4000 136 and 162 us; 320 x 520, 9 pairs,
+//     15.7 and, two segments of 32, 15.1 us);
+//   * fewer pairs: two segments of 32 columns (640 x 520 19.9 us, four 22.1 us), none with many groups (1280 x 520, S = 64
+//     23.4 and 24.5 us);
+//   * few groups: four segments of 32 columns (160 x 600, S = 128 10.9 us, two 12.5, eight 12.5 us).
+// One segment: workgroups of one wave; where they are few, or a wave has one pair only, of two waves that ask for a
+// pair's x at once (S = 64, 320 x 400: 11.8 and, one wave, 13.1 us; S = 128 15.5 and 15.9 us; 1280 x 60 11.0 and 11.5 us;
+// but 1280 x 400 29.2 and 26.4 us; S = 64 20.9 and 19.6 us, 1280 x 60 7.9 and 7.4 us).
 template <int S, typename HT>
 hipError_t launch_state(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm, const void *Cm,
                         const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
     if (wide_strides(d)) return launch_n<S, false, 1, 2, true, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    const long waves = (long)d.batch * d.nheads * (d.headdim / kCols) * (d.dstate / S);
+    const long groups = (long)d.batch * d.nheads * (d.headdim / kCols) * (d.dstate / S);
     const int pairs = (d.nnodes + 2 * kQ - 1) / (2 * kQ);
-    if (pairs < 8) return launch_n<S, false, 1, 2, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    if (waves * 8 > (S == 64 ? 4096 : 2048)) return launch_n<S, false, 4, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    return launch_n<S, false, 8, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    if (pairs < 8 && (groups < 2 * kCUs || (S == 128 && pairs < 2)))
+        return launch_n<S, false, 1, 2, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    if (pairs < 8 || (pairs < 10 && groups >= 4 * kCUs)) return launch_s<S, 1, 1, HT>(d, x, dt, A, Bm, h0, h_out, st);
+    if (y_in_segments(d)) return launch_n<S, false, 8, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    if (groups <= kCUs) return launch_s<S, 4, 1, HT>(d, x, dt, A, Bm, h0, h_out, st);
+    if (pairs >= 10) return launch_s<S, 4, 2, HT>(d, x, dt, A, Bm, h0, h_out, st);
+    return launch_s<S, 2, 1, HT>(d, x, dt, A, Bm, h0, h_out, st);
 }
 
-// With y: segments where eight times the waves still fit the chip at two a SIMD and each has a chunk pair and a
-// half (80 heads x 64, S = 128: 84 us against the team's 126 us for 4096 tokens; 28 against 36 for 1013; at 700
-// tokens they meet), teams for the rest (160 heads, 1500 tokens: 52 us, two segments each 67 us; 640 heads, 4096
-// tokens: 300 us, independent waves without segments 410 us).  S = 256: the segments' registers do not fit.
+// With y: segments (see above) or teams (160 heads, 1500 tokens: 52 us, two segments each 67 us; 640 heads, 4096 tokens: 300
+// us, independent waves without segments 410 us).
 template <int S, typename HT>
 hipError_t launch_y(const stree_dims &d, const void *x, const float *dt, const float *A, const void *Bm, const void *Cm,
                     const float *D, const void *h0, void *y, void *h_out, hipStream_t st) {
     if (wide_strides(d)) return launch_n<S, true, 1, 2, true, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    const long waves = (long)d.batch * d.nheads * (d.headdim / kCols);
-    const int pairs = (d.nnodes + 2 * kQ - 1) / (2 * kQ);
     if constexpr (S != 256) {
-        if (pairs >= 12 && waves * 8 <= 2048) return launch_n<S, true, 8, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+        if (y_in_segments(d)) return launch_n<S, true, 8, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
     }
     if constexpr (S == 128) {
         if (d.headdim == 128) return launch_team<S, 4, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
