@@ -34,8 +34,8 @@
 //   * TEAMS (enough heads for every CU): per head one wave for 32 columns each and two more that bring the tiles to
 //     LDS and form M, which the columns share, one chunk ahead;
 //   * SEGMENTS (a few sequences): a workgroup's eight waves are pieces of one sequence for the same 32 columns.  Each
-//     forms the state of its piece alone, the pieces are chained through LDS (h <- exp(sum s) h + local, one wave
-//     after the other), and each wave then runs its piece again, with y, from its true initial state.  The waves
+//     forms the state of its piece alone, the pieces are chained through LDS (h <- exp(sum s) h + local, each wave
+//     an eighth of the elements), and each wave then runs its piece again, with y, from its true initial state.  The waves
 //     share nothing in the loop: no barrier.  State only (no y): the first half is all there is;
 //   * STATE ONLY, long or with many columns: segments whose states are added up, by waves of one or two column groups.
 // Measured (80 heads x 64, S = 128, bf16), before = four waves per head, 64-token chunks, four barriers a chunk:
@@ -475,7 +475,8 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
     constexpr int NK = S / 16;                        // k steps of a product over the state index
     constexpr int ST = S / 32;                        // state tiles h^T[32 s][32 p]
     constexpr size_t kStage = (size_t)WaveLds<S, WY>::size * NSEG * NP;
-    constexpr size_t kChain = NSEG > 1 ? (size_t)NP * S * kCols * 4 : 0;   // overlays the wave tiles
+    constexpr size_t kChain = NSEG > 1 ? (size_t)NSEG * S * kCols * 4 : 0;   // overlays the wave tiles
+    [[maybe_unused]] __shared__ float sums[NSEG];
     __shared__ __align__(512) char lds[kStage > kChain ? kStage : kChain];
 
     const int unit = unit_of_block(units);
@@ -582,62 +583,64 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
         }
         if constexpr (NSEG > 1) {
             if constexpr (WY) first_loads();          // of the second pass: in flight through the chain
-            f32x4 *chain = reinterpret_cast<f32x4 *>(lds) + (size_t)(wave % NP) * (ST * 4) * 64 + lane;
-            const float whole = __builtin_amdgcn_exp2f(sum2);
-#pragma unroll 1
+            // The segments' states to LDS; each wave chains its share of the elements through all of them, h <- exp(sum s) h +
+            // local (the k-th state <- what segment k's y starts from, the first one <- the end of them all).  One wave after the
+            // other with a whole state each, the same sums, took (S = 128, 160 column groups, HBM cold): 1013 tokens with y 31.4
+            // us, now 30.4; state only 2000 tokens 24.9 -> 22.4; 256 groups x 900 18.1 -> 15.6 and, with y, 35.3 -> 33.8.
+            constexpr int kQuads = ST * 4, kShare = kQuads / NSEG;
+            static_assert(NP == 1 && kQuads % NSEG == 0, "");
+            f32x4 *states = reinterpret_cast<f32x4 *>(lds) + lane;
+            if (lane == 0) sums[seg] = sum2;
+            __syncthreads();                          // the tiles are dead
+#pragma unroll
+            for (int i = 0; i < kQuads; ++i) states[(seg * kQuads + i) * 64] = quad(hacc[i / 4], i % 4);
+            if constexpr (WY) {
+                if (from_h0) request_state(hacc, h0 + state_at, SR, lane);
+            }
+            __syncthreads();
+            f32x4 v[kShare];
+#pragma unroll
             for (int k = 0; k < NSEG; ++k) {
-                // h0, read again below for the first segment's y, has arrived ahead of a barrier behind which another wave
-                // writes h_out, which may be h0 (by way of the next wave's tile, which is dead until the chain ends)
-                if (WY && k == NSEG - 1 && from_h0) spread_state<kRoom, ST, HT>(hacc, tile + NP * L::size, lane);
-                __syncthreads();                      // first: the tiles are dead; then: the state is there
-                if (seg != k) continue;
-                // the state at the segment's end, then (what this segment's y starts from) the one before it
-                auto end = [&](int st, int q) {
-                    const f32x4 v = chain[(st * 4 + q) * 64], l = quad(hacc[st], q);
-                    return f32x4{fmaf(whole, v[0], l[0]), fmaf(whole, v[1], l[1]), fmaf(whole, v[2], l[2]), fmaf(whole, v[3], l[3])};
-                };
-                auto begin = [&](int st, int q) {
-                    const f32x4 v = chain[(st * 4 + q) * 64];
+                const float whole = __builtin_amdgcn_exp2f(sums[k]);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) hacc[st][4 * q + e] = v[e];
-                };
-                if (k == NSEG - 1) {
-                    if constexpr (WY) {               // (written behind the chain, which the other waves wait for)
-                        static_assert(kRoom * StateBlock<HT>::tiles >= ST, "");
-                        gather_state<kRoom, ST, HT>(end, 0, tile, lane);
-                    } else {
-                        store_state<kRoom, ST>(end, h_out + state_at, SR, tile, lane);
+                for (int j = 0; j < kShare; ++j) {
+                    f32x4 *at = states + (k * kQuads + seg * kShare + j) * 64;
+                    f32x4 l = *at;
+                    if (k > 0) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) l[e] = fmaf(whole, v[j][e], l[e]);
+                        if constexpr (WY) *at = v[j];
                     }
-#pragma unroll
-                    for (int st = 0; st < ST && WY; ++st)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) begin(st, q);
-                } else if (k > 0) {
-#pragma unroll
-                    for (int st = 0; st < ST; ++st)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const f32x4 n = end(st, q);
-                            if constexpr (WY) begin(st, q);
-                            chain[(st * 4 + q) * 64] = n;
-                        }
-                } else {
-#pragma unroll
-                    for (int st = 0; st < ST; ++st)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            chain[(st * 4 + q) * 64] = quad(hacc[st], q);
-                    if constexpr (WY) {
-                        if (h0)
-                            request_state(hacc, h0 + state_at, SR, lane);
-                        else
-                            zero_state(hacc);
-                    }
+                    v[j] = l;
                 }
             }
+#pragma unroll
+            for (int j = 0; j < kShare; ++j) states[(seg * kShare + j) * 64] = v[j];
+            auto end = [&](int st, int q) { return states[(st * 4 + q) * 64]; };
             if constexpr (WY) {
-                __syncthreads();                      // the chain buffer is the wave tiles' again
+                // h0, read again for the first segment's y, has arrived ahead of a barrier behind which another wave writes
+                // h_out, which may be h0 (by way of the last wave's tile, which lies behind the states)
+                static_assert(kChain <= (size_t)L::size * (NSEG - 1), "");
+                if (from_h0)
+                    spread_state<kRoom, ST, HT>(hacc, tile + (NSEG - 1) * L::size, lane);
+                else if (seg == 0)
+                    zero_state(hacc);
+                __syncthreads();
+                if (seg > 0) {
+#pragma unroll
+                    for (int i = 0; i < kQuads; ++i) {
+                        const f32x4 s = states[(seg * kQuads + i) * 64];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) hacc[i / 4][4 * (i % 4) + e] = s[e];
+                    }
+                }
+                static_assert(kRoom * StateBlock<HT>::tiles >= ST, "");
+                if (seg == NSEG - 1) gather_state<kRoom, ST, HT>(end, 0, tile, lane);
+                __syncthreads();                      // the states are the wave tiles' again
                 if (seg == NSEG - 1) write_state<kRoom, ST>(h_out + state_at, SR, 0, tile, lane);
+            } else {
+                __syncthreads();
+                if (seg == NSEG - 1) store_state<kRoom, ST>(end, h_out + state_at, SR, tile, lane);
             }
         }
     }
@@ -696,7 +699,7 @@ __global__ __launch_bounds__(64 * NSEG * NP, (S == 256 ? 1 : 2)) void linear_ssd
 // What bounds it: the rows' way from memory and L2 into LDS, not the products (S = 64, 480 groups x 2050 tokens, of 33 us
 // with 32 columns a wave: without x from memory 23, without B's rows 28, without half of the products 32; every second
 // request more for the same rows costs 5 %).  So a wave takes 64 columns, whole 128-byte lines of x, where enough of them are
-// left; and the segments' states, which one wave after the other takes up in the form above (1 to 2 us a segment), are
+// left; and the segments' states, which one wave after the other took up before (1 to 2 us a segment), are
 // scaled to the end of them all and added up in pairs.  Before (32 columns, chained) -> now, HBM cold: S = 64, 480 x 2050,
 // bf16 state 33 -> 24 us, 1280 x 4000 121 -> 103; S = 128, 320 x 2000 37 -> 29, 1280 x 4000 161 -> 136, 160 x 600 14.6 -> 10.9,
 // 1280 x 250 20.7 -> 18.8.
