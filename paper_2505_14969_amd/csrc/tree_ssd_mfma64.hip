@@ -1,4 +1,4 @@
-// Tree scan for trees of at most 64 nodes with an fp32 state, headdim 64 and some three to six heads a CU, the band in
+// Tree scan for trees of at most 64 nodes with headdim 64 and some three to six heads a CU, the band in
 // which it is ahead of the workgroup per head of tree_ssd_unit.hip (see unit_is_slower): persistent, software-pipelined,
 // wave-specialised (products and accumulator layouts as in tree_ssd_mfma.hip).
 //
@@ -118,12 +118,14 @@ __device__ __forceinline__ int wave_tree_index(int lane, int n, int parent_i, fl
 // nodes an instruction, the fp32 FMAs of the recurrence in the same precision): as vector FMAs it cost the four
 // waves that carry a unit some 56 instructions per path node, while the other four waited (the beams above:
 // 92.5 -> 82.4 us, chains of up to 49 nodes 195 -> 134 us, trees of depth 4 to 8 75.9 -> 72.9 us).
-template <int P, int S, int WPE, bool RP, bool SPL>
+// HT = type the state is kept in: fp32, or bf16 (then h0 is the MFMA operand as it comes, and the replayed
+// state is rounded once, to the value that is both written back and scanned from).
+template <int P, int S, int WPE, bool RP, bool SPL, typename HT>
 __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void tree_ssd_mfma64_kernel(
     const int32_t *__restrict__ parent, int n, int nbatch, int H, int G, const bf16_t *__restrict__ x, long x_sn,
     const float *__restrict__ dt, const float *__restrict__ dt_bias, const float *__restrict__ A,
     const bf16_t *__restrict__ Bm, long b_sn,
-    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const float *__restrict__ h0,
+    const bf16_t *__restrict__ Cm, long c_sn, const float *__restrict__ D, const HT *__restrict__ h0,
     bf16_t *__restrict__ y, int32_t *__restrict__ status, ReplayArgs R) {
     using L = Lds64<P, S>;
     constexpr int SP = L::SP;
@@ -213,7 +215,9 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     // row = state row p, column = state column s): a wave owns 16 rows, lane l the rows 4 (l >> 4) + i of those and
     // kCW consecutive columns kCW (l & 15) + t -- column t of each lane makes up tile t, so that a lane's columns are
     // 16-byte pieces in memory all the same.
-    constexpr int kCW = 4, kCB = S / (16 * kCW);                     // columns per chunk; column blocks
+    constexpr uint32_t HB = sizeof(HT);
+    constexpr int kCW = 16 / HB, kCB = S / (16 * kCW);               // columns per chunk; column blocks
+    static_assert(kCB >= 1 && NH % 2 == 0, "a state is moved 16 bytes at a time");
     static_assert(P == 64, "a wave of each role owns 16 rows of the state");
     auto load_H = [&](int b, int h) {       // the role group that carries this unit
         // the lane-dependent zero keeps this a vector load: it then sits in the same in-order
@@ -222,14 +226,14 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
         const char *hb = reinterpret_cast<const char *>(h0 + ((size_t)b * H + h) * P * S);
         if constexpr (RP) {
             const int t = opaque(rt), row0 = (t >> 6) * 16 + ((t & 63) >> 4) * 4, col0 = (t & 15) * kCW;
-            const uint32_t off = (uint32_t)(row0 * S + col0) * 4u;
+            const uint32_t off = (uint32_t)(row0 * S + col0) * HB;
 #pragma unroll
             for (int q = 0; q < kCB * 4; ++q)         // q = (column block, row)
-                pre[q] = load_stream16(hb + off + (q % 4 * S + q / 4 * 16 * kCW) * 4);
+                pre[q] = load_stream16(hb + off + (q % 4 * S + q / 4 * 16 * kCW) * HB);
         } else {
             const uint32_t off = (uint32_t)opaque(rt) * 16u;
 #pragma unroll
-            for (int q = 0; q < NH; ++q) pre[q] = load_stream16(hb + q * (kHalf * 16) + off);
+            for (int q = 0; q < NH * (int)HB / 4; ++q) pre[q] = load_stream16(hb + q * (kHalf * 16) + off);
         }
     };
     // C and B tiles of a unit: global -> registers -> LDS in one go (G threads).  Runs only when
@@ -289,7 +293,8 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             for (int q = 0; q < kCB * 4; ++q) {
                 const uint32_t w4[4] = {pre[q].x, pre[q].y, pre[q].z, pre[q].w};
 #pragma unroll
-                for (int e = 0; e < kCW; ++e) hv[q / 4][e][q % 4] = dec * __uint_as_float(w4[e]);
+                for (int e = 0; e < kCW; ++e)
+                    hv[q / 4][e][q % 4] = dec * (HB == 4 ? __uint_as_float(w4[e % 4]) : (e & 1) ? bf16_hi(w4[e / 2]) : bf16_lo(w4[e / 2]));
             }
             // four path nodes: lane group kj holds node j of them, its weight cf (0 past the end of the path),
             // its x at row (t & 15) of the wave's rows (operand A) and cf * B at the lane's columns (operand B)
@@ -298,8 +303,13 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                 const float av = on ? __uint_as_float(xw << 16) : 0.f;
 #pragma unroll
                 for (int c = 0; c < kCB; ++c) {
-                    const uint2 bw = *reinterpret_cast<const uint2 *>(br + (c * 16 + l) * kCW * 2);
-                    const float bf[4] = {bf16_lo(bw.x), bf16_hi(bw.x), bf16_lo(bw.y), bf16_hi(bw.y)};
+                    const char *at = br + (c * 16 + l) * kCW * 2;
+                    float bf[kCW];
+#pragma unroll
+                    for (int e = 0; e < kCW; e += 4) {
+                        const uint2 bw = *reinterpret_cast<const uint2 *>(at + e * 2);
+                        bf[e] = bf16_lo(bw.x), bf[e + 1] = bf16_hi(bw.x), bf[e + 2] = bf16_lo(bw.y), bf[e + 3] = bf16_hi(bw.y);
+                    }
 #pragma unroll
                     for (int e = 0; e < kCW; ++e)
                         hv[c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, on ? cf * bf[e] : 0.f, hv[c][e], 0, 0, 0);
@@ -320,16 +330,25 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                 }
             }
             // the replayed state, written once, through L2 (never read again by this kernel)
-            char *ob = reinterpret_cast<char *>(reinterpret_cast<float *>(R.h_out) + ((size_t)b * H + h) * P * S);
+            char *ob = reinterpret_cast<char *>(reinterpret_cast<HT *>(R.h_out) + ((size_t)b * H + h) * P * S);
 #pragma unroll
             for (int q = 0; q < kCB * 4; ++q) {
                 const int at_row = prow + kj * 4 + q % 4, at_col = (q / 4 * 16 + l) * kCW;
-                const float v[4] = {hv[q / 4][0][q % 4], hv[q / 4][1][q % 4], hv[q / 4][2][q % 4], hv[q / 4][3][q % 4]};
-                store_through16(ob + (uint32_t)(at_row * S + at_col) * 4u,
-                                make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
-                *reinterpret_cast<uint2 *>(&sH[at_row * SP + at_col]) = pack_bf16x4(v[0], v[1], v[2], v[3]);
+                float v[kCW];
+#pragma unroll
+                for (int e = 0; e < kCW; ++e) v[e] = hv[q / 4][e][q % 4];
+                char *dst = ob + (uint32_t)(at_row * S + at_col) * HB;
+                bf16_t *op = &sH[at_row * SP + at_col];
+                if constexpr (HB == 4) {
+                    store_through16(dst, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
+                    *reinterpret_cast<uint2 *>(op) = pack_bf16x4(v[0], v[1], v[2], v[3]);
+                } else {
+                    const uint2 lo = pack_bf16x4(v[0], v[1], v[2], v[3]), hi = pack_bf16x4(v[kCW - 4], v[kCW - 3], v[kCW - 2], v[kCW - 1]);
+                    store_through16(dst, make_uint4(lo.x, lo.y, hi.x, hi.y));
+                    *reinterpret_cast<uint4 *>(op) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                }
             }
-        } else {
+        } else if constexpr (HB == 4) {
 #pragma unroll
             for (int q = 0; q < NH; ++q) {
                 const int e = (t + q * kHalf) * 4, p = e / S, sidx = e % S;
@@ -337,6 +356,12 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                 o[0] = (bf16_t)__uint_as_float(pre[q].x); o[1] = (bf16_t)__uint_as_float(pre[q].y);
                 o[2] = (bf16_t)__uint_as_float(pre[q].z); o[3] = (bf16_t)__uint_as_float(pre[q].w);
                 *reinterpret_cast<bf16x4 *>(&sH[p * SP + sidx]) = o;
+            }
+        } else {                                   // already the MFMA operand: copied as it came
+#pragma unroll
+            for (int q = 0; q < NH / 2; ++q) {
+                const int e = (t + q * kHalf) * 8, p = e / S, sidx = e % S;
+                *reinterpret_cast<uint4 *>(&sH[p * SP + sidx]) = pre[q];
             }
         }
         if (rt == 0) *sDh = rD;      // D of that unit, for the Y waves
@@ -751,7 +776,7 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     }
 }
 
-template <int S, bool RP>
+template <int S, bool RP, typename HT>
 hipError_t launch64(const stree_dims &d, const int32_t *parent, const void *x, const float *dt, const float *A,
                     const void *Bm, const void *Cm, const float *D, const void *h0, void *y,
                     int32_t *status, const ReplayArgs &R, hipStream_t st) {
@@ -761,26 +786,31 @@ hipError_t launch64(const stree_dims &d, const int32_t *parent, const void *x, c
     const int grid = n_units > 512 ? 512 : (n_units + 7) / 8 * 8;
     // (the in-kernel softplus is a variant of its own: compiled into the common one, even unused, it costs time)
 #define STREE_LAUNCH64(SPL)                                                                                         \
-    hipLaunchKernelGGL((tree_ssd_mfma64_kernel<64, S, 4, RP, SPL>), dim3(grid), dim3(kT64), 0, st, parent,          \
+    hipLaunchKernelGGL((tree_ssd_mfma64_kernel<64, S, 4, RP, SPL, HT>), dim3(grid), dim3(kT64), 0, st, parent,          \
                        d.nnodes, d.batch, d.nheads, d.ngroups, (const bf16_t *)x, (long)d.x_stride_n, dt,           \
                        step_bias(d), A, (const bf16_t *)Bm, (long)d.b_stride_n, (const bf16_t *)Cm,                 \
-                       (long)d.c_stride_n, D, (const float *)h0, (bf16_t *)y, status, R)
+                       (long)d.c_stride_n, D, (const HT *)h0, (bf16_t *)y, status, R)
     if (step_bias(d)) STREE_LAUNCH64(true);
     else STREE_LAUNCH64(false);
 #undef STREE_LAUNCH64
     return hipGetLastError();
 }
 
-// The band in which the persistent kernel is ahead of a workgroup per head: an fp32 state, and so many heads that all of
+// The band in which the persistent kernel is ahead of a workgroup per head: so many heads that all of
 // them enter the workgroup-per-head kernel at once (five a CU, 1280) and read their C and B rows at once, where a
 // persistent workgroup reads them once for the two or three heads it walks.  80 heads, S = 128, persistent / per head:
 // replay + scan, 64 nodes, batch 8 15.1 / 15.5, 12 20.0 / 21.9, 16 24.0 / 25.6, 18 28.6 / 28.4 us, 40 nodes, batch 8 14.7 /
 // 13.7, 12 19.0 / 20.2, 32 nodes, batch 12 18.9 / 18.9, 16 22.8 / 21.9; scan, 64 nodes, batch 12 13.8 / 13.7, 16 15.5 / 16.8,
 // 20 19.7 / 20.6, 26 25.6 / 24.9, 48 nodes, batch 16 15.0 / 14.8; S = 64, scan, 64 nodes, batch 16 12.1 / 12.4.  Beyond it (few
-// heads, more than a round of them, a state in bf16, S = 256, headdim 128) the workgroup per head is ahead by 3 to 30 %.
+// heads, more than a round of them, S = 256, headdim 128) the workgroup per head is ahead by 3 to 30 %.  A state in bf16, half
+// the bytes: only between four and five workgroups a CU, where a few CUs have the fifth (64 nodes, batch 13 17.3 / 18.5, 15 18.4 /
+// 19.9 us, 44 nodes, 13 16.5 / 17.1, 40 nodes, 13 16.6 / 16.7; batch 16 18.6 / 18.6; scan, 64 nodes, 14 12.6 / 13.7, 57, 14
+// 12.4 / 12.6, 56, 15 13.0 / 12.6).
 bool unit_is_slower(const stree_dims &d, bool replay) {
-    if (d.state_dtype != STREE_F32 || d.headdim != 64) return false;
+    if (d.headdim != 64) return false;
     const int units = d.batch * d.nheads;
+    if (d.state_dtype != STREE_F32)
+        return d.dstate == 128 && units > 1024 && units < 1280 && d.nnodes > (replay ? 40 : 56);
     if (replay) return d.dstate == 128 && d.nnodes > 32 && units > 640 && units <= 1408;
     return (d.dstate == 128 || d.dstate == 64) && d.nnodes > 48 && units > 1024 && units <= 1700;
 }
@@ -817,15 +847,16 @@ hipError_t launch_tree_ssd_replay_fused(const stree_dims &d, const stree_dims &d
                                            status, rstatus, st);
     const ReplayArgs R = {pparent, paccepted, (const bf16_t *)px, (const bf16_t *)pB, pdt,
                           (long)dp.x_stride_n, (long)dp.b_stride_n, dp.nnodes, h_out, rstatus};
-    return launch64<128, true>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
+    return (d.state_dtype == STREE_F32 ? launch64<128, true, float> : launch64<128, true, bf16_t>)(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
 }
 
 hipError_t launch_tree_ssd_mfma64(const stree_dims &d, const int32_t *parent, const void *x, const float *dt,
                                   const float *A, const void *Bm, const void *Cm, const float *D,
                                   const void *h0, void *y, int32_t *status, hipStream_t st) {
     if (!unit_is_slower(d, false)) return launch_tree_ssd_unit(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, st);
-    return d.dstate == 128 ? launch64<128, false>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, ReplayArgs{}, st)
-                           : launch64<64, false>(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, ReplayArgs{}, st);
+    const auto launch = d.dstate == 64 ? launch64<64, false, float>
+                        : d.state_dtype == STREE_F32 ? launch64<128, false, float> : launch64<128, false, bf16_t>;
+    return launch(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, ReplayArgs{}, st);
 }
 
 }  // namespace stree

@@ -75,7 +75,9 @@ def test_unit_kernel_replay(st, oracle, N, Np, P, S, G, state):
 # the state requested late (more heads than are resident at once), and the persistent kernel's band on either side
 @pytest.mark.parametrize("B,N,H,P,S,state", [(89, 34, 16, 64, 64, "f32"), (89, 33, 16, 64, 64, "bf16"), (88, 33, 16, 64, 128, "f32"),
                                              (41, 33, 16, 64, 128, "f32"), (40, 33, 16, 64, 128, "f32"), (41, 32, 16, 64, 128, "f32"),
-                                             (89, 33, 16, 64, 128, "f32"), (89, 20, 16, 64, 128, "bf16"), (90, 20, 8, 128, 128, "f32")])
+                                             (89, 33, 16, 64, 128, "f32"), (89, 20, 16, 64, 128, "bf16"), (90, 20, 8, 128, 128, "f32"),
+                                             (65, 41, 16, 64, 128, "bf16"), (65, 40, 16, 64, 128, "bf16"), (79, 64, 16, 64, 128, "bf16"),
+                                             (80, 64, 16, 64, 128, "bf16")])
 def test_unit_kernel_replay_at_the_lines_between_its_forms(st, oracle, B, N, H, P, S, state):
     _replay(st, oracle, B, N, 21, H, P, S, 1, state, 190 + B + N)
 
@@ -86,3 +88,14 @@ def test_unit_kernel_scan_at_the_lines_between_its_forms(st, oracle, B, N, H, S)
     x, dt, A, Bm, Cm, D, h0 = _rand(231 + B, "bf16", B, N, H, 64, S, 1)
     want = oracle.ssd_paths(parent, x, dt, A, Bm, Cm, D, h0)
     assert_parity(_run_ssd(st, "bf16", parent, x, dt, A, Bm, Cm, D, h0), want, TOL["bf16"], f"scan B={B} N={N} S={S}", kind="y")
+
+
+@pytest.mark.parametrize("B,N,H", [(65, 57, 16), (65, 56, 16), (79, 64, 16), (80, 64, 16)])
+def test_scan_of_a_bf16_state_at_the_lines_between_its_forms(st, oracle, B, N, H):
+    parent = _trees(260 + B, B, N)
+    x, dt, A, Bm, Cm, D, h0 = _rand(261 + B + N, "bf16", B, N, H, 64, 128, 1)
+    h0 = synth.round_to_bf16(h0)
+    want = oracle.ssd_paths(parent, x, dt, A, Bm, Cm, D, h0)
+    y = st.stree_tree_ssd(to_dev(parent), to_dev(x, "bf16"), to_dev(dt), to_dev(A), to_dev(Bm, "bf16"), to_dev(Cm, "bf16"),
+                          to_dev(D), to_dev(h0, "bf16"))
+    assert_parity(to_host(y), want, TOL["bf16"], f"scan of a bf16 state B={B} N={N}", kind="y")
