@@ -355,13 +355,13 @@ def main():
     ms_best = steps[best]
     tr_scan, src_scan = read_traffic("tree_ssd_mfma_cfg2")
     tr_fused, src_fused = read_traffic("tree_ssd_replay_cfg2")
-    roof_scan = {"bound": "hbm", "kernel": "tree_ssd_mfma64_kernel<64,128,4,false,false>", "achieved": achieved,
+    roof_scan = {"bound": "hbm", "kernel": "tree_ssd_mfma64_kernel<64,128,4,false,false,float>", "achieved": achieved,
                  "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                  "traffic": tr_scan, "traffic_source": src_scan,
                  "algorithmic_bytes": alg_bytes, "avg_launch_us": ms_ssd * 1e3,
                  "cache_warm_us": ms_ssd_warm * 1e3,
                  "mfma_tflops": alg_flops / (ms_ssd * 1e-3) / 1e12}
-    roof_fused = {"bound": "hbm", "kernel": "tree_ssd_mfma64_kernel<64,128,4,true,false>", "achieved": achieved_f,
+    roof_fused = {"bound": "hbm", "kernel": "tree_ssd_mfma64_kernel<64,128,4,true,false,float>", "achieved": achieved_f,
                   "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved_f / HBM_PEAK_GBS,
                   "traffic": tr_fused, "traffic_source": src_fused,
                   "algorithmic_bytes": alg_bytes_f, "avg_launch_us": ms_fused * 1e3}
@@ -512,7 +512,7 @@ def measure_config(cid, st, synth, torch, dev, use_graph):
         if name == "tree_ssd":
             row[name]["nodes_per_s"] = B * N / (cold * 1e-6)
             if N > 64:
-                row[name]["traffic"], row[name]["traffic_source"] = read_traffic(f"tree_ssd_blocks_cfg{cid}")
+                row[name]["traffic"], row[name]["traffic_source"] = read_traffic(f"tree_ssd_rows_cfg{cid}")
         log(f"[bench] {wl.name}: {name:12s} {cold:7.2f} us cold ({nbytes/cold/1e3:5.0f} GB/s = "
             f"{nbytes/cold/8e4:4.1f}% of 8 TB/s), {warm:7.2f} us warm; {nbytes/1e6:.2f} MB algorithmic")
     del sets

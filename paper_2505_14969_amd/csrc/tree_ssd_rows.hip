@@ -16,10 +16,10 @@
 // What bounds it: the chain of a workgroup -- requests, index, products, state, stores -- of which two or three are
 // resident on a CU.  The state, half of all bytes, is requested last and used last: it streams in while the products are
 // formed, and nothing small waits behind it.  Operands read from memory as a product wants them (a lane its own row, 32
-// bytes of 32 rows an instruction) cost an L1 look-up a row: 27 us for 4 x 256 nodes where whole rows through LDS take 24.
+// bytes of 32 rows an instruction) cost an L1 look-up a row: 27 us for 4 x 256 nodes where whole rows through LDS took 24.
 // Before, persistent workgroups of alternating roles with two barriers per pair of 64-node blocks (fp32 state, cold):
-// 8 x 128 nodes x 80 heads 19.8 -> 14.7 us, 16 x 128 30.7 -> 23.3, 16 x 81 29.9 -> 20.0, 4 x 256 x 128 heads 33.6 -> 23.7,
-// 16 x 256 x 80 68.7 -> 50.4; 16 x 128 x 40 heads of 128 42.0 -> 23.3; 16 x 128 x 32 heads, S = 256, 24.1 -> 18.0.
+// 8 x 128 nodes x 80 heads 19.8 -> 14.5 us, 16 x 128 29.9 -> 22.2, 16 x 81 28.5 -> 18.7, 4 x 256 x 128 heads 33 -> 19.1,
+// 16 x 256 x 80 70 -> 42; 16 x 128 x 40 heads of 128 42 -> 23; 16 x 128 x 32 heads, S = 256, 24 -> 18.
 //
 // RP: the commit of the previous tree (Alg. 1: replay at the start of the next iteration) on the state while it passes
 // through the registers, for trees of at most 128 nodes; the path is worked out beside the tree's index, its rows are
