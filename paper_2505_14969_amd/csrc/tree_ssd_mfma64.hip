@@ -805,12 +805,12 @@ hipError_t launch64(const stree_dims &d, const int32_t *parent, const void *x, c
 // heads, more than a round of them, S = 256, headdim 128) the workgroup per head is ahead by 3 to 30 %.  A state in bf16, half
 // the bytes: only between four and five workgroups a CU, where a few CUs have the fifth (64 nodes, batch 13 17.3 / 18.5, 15 18.4 /
 // 19.9 us, 44 nodes, 13 16.5 / 17.1, 40 nodes, 13 16.6 / 16.7; batch 16 18.6 / 18.6; scan, 64 nodes, 14 12.6 / 13.7, 57, 14
-// 12.4 / 12.6, 56, 15 13.0 / 12.6).
+// 12.4 / 12.6, 56, 15 13.0 / 12.6; 64, 16 12.2 / 13.1).
 bool unit_is_slower(const stree_dims &d, bool replay) {
     if (d.headdim != 64) return false;
     const int units = d.batch * d.nheads;
     if (d.state_dtype != STREE_F32)
-        return d.dstate == 128 && units > 1024 && units < 1280 && d.nnodes > (replay ? 40 : 56);
+        return d.dstate == 128 && units > 1024 && (replay ? units < 1280 && d.nnodes > 40 : units <= 1280 && d.nnodes > 56);
     if (replay) return d.dstate == 128 && d.nnodes > 32 && units > 640 && units <= 1408;
     return (d.dstate == 128 || d.dstate == 64) && d.nnodes > 48 && units > 1024 && units <= 1700;
 }

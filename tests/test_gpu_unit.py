@@ -90,7 +90,7 @@ def test_unit_kernel_scan_at_the_lines_between_its_forms(st, oracle, B, N, H, S)
     assert_parity(_run_ssd(st, "bf16", parent, x, dt, A, Bm, Cm, D, h0), want, TOL["bf16"], f"scan B={B} N={N} S={S}", kind="y")
 
 
-@pytest.mark.parametrize("B,N,H", [(65, 57, 16), (65, 56, 16), (79, 64, 16), (80, 64, 16)])
+@pytest.mark.parametrize("B,N,H", [(65, 57, 16), (65, 56, 16), (80, 64, 16), (81, 64, 16)])
 def test_scan_of_a_bf16_state_at_the_lines_between_its_forms(st, oracle, B, N, H):
     parent = _trees(260 + B, B, N)
     x, dt, A, Bm, Cm, D, h0 = _rand(261 + B + N, "bf16", B, N, H, 64, 128, 1)
