@@ -34,7 +34,7 @@
  *     runs a plain fp32-FMA kernel.  Among the bf16 MFMA
  *     shapes, the tuned kernels (the ones the benchmark prices) take
  *     headdim 64 with dstate 64, 128 or 256, and headdim 128 with dstate 128,
- *     at any node count; the remaining MFMA shapes (headdim 32, other dstates,
+ *     at any node count (token strides below 2^25 elements); the remaining MFMA shapes (headdim 32, other dstates,
  *     ...) run one workgroup per (sequence, head) and are several times slower
  *     per node.  Results are the same to rounding on every route.  Infinities and
  *     NaN in x: the fp32 routes keep a node's to the nodes that descend from it; the

@@ -817,8 +817,11 @@ bool unit_is_slower(const stree_dims &d, bool replay) {
 
 }  // namespace
 
+// (Rows past a small tree are addressed as well, with 32-bit byte offsets that have to lie behind its last row: token strides
+// for which 64 rows outgrow those, never met in earnest, go to the kernel for every head shape.)
 bool tree_ssd_mfma64_supported(const stree_dims &d) {
     if (d.nnodes > kB64) return false;
+    if (d.x_stride_n >= (1L << 25) || d.b_stride_n >= (1L << 25) || d.c_stride_n >= (1L << 25)) return false;
     const int P = d.headdim, S = d.dstate;
     return (P == 64 && (S == 128 || S == 64 || S == 256)) || (P == 128 && S == 128);
 }

@@ -99,3 +99,28 @@ def test_scan_of_a_bf16_state_at_the_lines_between_its_forms(st, oracle, B, N, H
     y = st.stree_tree_ssd(to_dev(parent), to_dev(x, "bf16"), to_dev(dt), to_dev(A), to_dev(Bm, "bf16"), to_dev(Cm, "bf16"),
                           to_dev(D), to_dev(h0, "bf16"))
     assert_parity(to_host(y), want, TOL["bf16"], f"scan of a bf16 state B={B} N={N}", kind="y")
+
+
+@pytest.mark.parametrize("P,S,G", SHAPES)
+def test_few_nodes_with_huge_token_strides(st, oracle, P, S, G):
+    """Rows 256 MiB apart, NaN between them: sixteen rows on, a 32-bit byte offset is back between the tree's rows (and a
+    weight of 0 does not undo a NaN)."""
+    import torch
+    B, N, H, stride = 1, 3, 2, (1 << 27) + 64
+    parent, pparent = _trees(180, B, N), _trees(181, B, 5)
+    x, dt, A, Bm, Cm, D, h0 = _rand(182, "bf16", B, N, H, P, S, G)
+    px, pdt, _, pB, _, _, _ = _rand(183, "bf16", B, 5, H, P, S, G)
+    room = torch.full((N * stride,), float("nan"), dtype=torch.bfloat16, device="cuda").view(1, N, stride)
+    views = []
+    for k, a in enumerate((x, Bm, Cm)):
+        rows = room[:, :, 4096 * k:4096 * k + a.shape[2] * a.shape[3]]
+        rows.copy_(to_dev(a, "bf16").reshape(1, N, -1))
+        views.append(rows.unflatten(2, a.shape[2:]))
+    now = (to_dev(parent), views[0], to_dev(dt), to_dev(A), views[1], views[2], to_dev(D), to_dev(h0))
+    want = oracle.ssd_paths(parent, x, dt, A, Bm, Cm, D, h0)
+    assert_parity(to_host(st.stree_tree_ssd(*now)), want, TOL["bf16"], "scan", kind="y")
+    acc = np.array([4], dtype=np.int32)
+    want_h, _ = oracle.commit(pparent, acc, px, pdt, A, pB, h0)
+    y, h = st.stree_tree_ssd_replay(to_dev(pparent), to_dev(acc), to_dev(px, "bf16"), to_dev(pdt), to_dev(pB, "bf16"), *now)
+    assert_parity(to_host(h), want_h, 1e-4, "replayed state", kind="state")
+    assert_parity(to_host(y), oracle.ssd_paths(parent, x, dt, A, Bm, Cm, D, want_h), TOL["bf16"], "scan behind the replay", kind="y")
