@@ -36,11 +36,12 @@ struct LdsLimit {
     }
 };
 
-// A grid dimension holds 2^32 work items: kernels with a workgroup of up to 512 lanes per head (or two) take at most 2^22
-// heads a launch, whole sequences each.  launch(dims of the part, its first sequence)
+// A grid dimension holds fewer than 2^32 work items: kernels with a workgroup of up to 512 lanes per head, or two of them
+// (headdim 128), take at most 2^21 heads a launch, whole sequences each.  launch(dims of the part, its first sequence)
+constexpr int kHeadsPerLaunch = 1 << 21;
 template <typename Launch>
 inline hipError_t launch_in_parts(const stree_dims &d, Launch &&launch) {
-    const int per = d.nheads < (1 << 22) ? (1 << 22) / d.nheads : 1;
+    const int per = kHeadsPerLaunch / d.nheads;      // (nheads is at most 65535)
     for (int b = 0; b < d.batch; b += per) {
         stree_dims part = d;
         part.batch = d.batch - b < per ? d.batch - b : per;
