@@ -47,12 +47,20 @@ const at::Tensor &tensor(PyObject *o) {
     return THPVariable_Unpack(o);
 }
 void *pointer(PyObject *o) { return o == Py_None ? nullptr : tensor(o).data_ptr(); }
-int32_t integer(PyObject *o) {                        // an int, or what gives one as an index (numpy's)
+// An int, or what gives one as an index (numpy's), as far as 64 bits reach: the checks see the whole value.
+int64_t integer(PyObject *o) {
     PyObject *i = PyNumber_Index(o);
     if (!i) throw Raised{};
-    const auto v = (int32_t)PyLong_AsUnsignedLongMask(i);
+    int beyond = 0;
+    const long long v = PyLong_AsLongLongAndOverflow(i, &beyond);
     Py_DECREF(i);
-    return v;
+    return beyond > 0 ? INT64_MAX : beyond < 0 ? INT64_MIN : v;
+}
+// channels of a row: x, then B and C of every group
+bool channels_are(int64_t channels, int64_t heads, int64_t headdim, int64_t dstate, int64_t groups) {
+    int64_t x, bc;
+    return !__builtin_mul_overflow(heads, headdim, &x) && !__builtin_mul_overflow(groups, dstate, &bc) &&
+           !__builtin_mul_overflow(bc, (int64_t)2, &bc) && !__builtin_add_overflow(x, bc, &x) && x == channels;
 }
 bool truth(PyObject *o) {
     const int t = PyObject_IsTrue(o);
@@ -194,7 +202,7 @@ PyObject *conv(PyObject *const *a) {
     dimensions(x, 3);
     const int64_t B = x.size(0), N = x.size(1), Cc = x.size(2), W = w.size(1);
     const int64_t H = integer(a[nheads]), P = integer(a[headdim]), S = integer(a[dstate]), G = integer(a[ngroups]);
-    require(Cc == H * P + 2 * G * S, "channels of xbc_pre");
+    require(channels_are(Cc, H, P, S, G), "channels of xbc_pre");
     require(x.is_contiguous() && tensor(a[conv_state]).is_contiguous() && w.is_contiguous(), "contiguous rows");
     Result y;
     like(y, a[out], a[xbc_pre]);
@@ -236,7 +244,7 @@ PyObject *commit(PyObject *const *a) {
     if (a[x] == Py_None) {                            // the conv tail alone; `dims` names the head shapes
         const at::Tensor &tp = tensor(a[parent]);
         dimensions(tp, 2);
-        int shape[4];
+        int64_t shape[4];
         Result s;
         s.o = PySequence_Fast(a[dims], "dims = (H, P, S, G)");
         if (!s.o) throw Raised{};
@@ -314,7 +322,7 @@ PyObject *conv_replay(PyObject *const *a) {
     require(px.dim() >= 2, "rows of the previous tree");
     const int64_t B = x.size(0), N = x.size(1), Cc = x.size(2), W = w.size(1), Np = px.size(1);
     const int64_t H = integer(a[nheads]), P = integer(a[headdim]), S = integer(a[dstate]), G = integer(a[ngroups]);
-    require(Cc == H * P + 2 * G * S && shaped(px, {B, Np, Cc}), "channels of xbc_pre and prev_xbc_pre");
+    require(channels_are(Cc, H, P, S, G) && shaped(px, {B, Np, Cc}), "channels of xbc_pre and prev_xbc_pre");
     require(x.is_contiguous() && cs.is_contiguous() && w.is_contiguous() && px.is_contiguous(), "contiguous rows");
     Result y, c;
     like(y, a[out], a[xbc_pre]);
@@ -341,7 +349,7 @@ PyObject *step(PyObject *const *a) {
     require(px.dim() >= 2, "rows of the previous tree");
     const int64_t B = x.size(0), N = x.size(1), Cc = x.size(2), W = w.size(1), Np = px.size(1);
     const int64_t H = integer(a[nheads]), P = integer(a[headdim]), S = integer(a[dstate]), G = integer(a[ngroups]);
-    require(Cc == H * P + 2 * G * S && shaped(px, {B, Np, Cc}) && shaped(po, {B, Np, Cc}), "channels of the rows of both trees");
+    require(channels_are(Cc, H, P, S, G) && shaped(px, {B, Np, Cc}) && shaped(po, {B, Np, Cc}), "channels of the rows of both trees");
     for (const at::Tensor *t : {&x, &cs, &w, &px, &po, &tpd, &td, &th}) require(t->is_contiguous(), "dense tensors");
     require(td.scalar_type() == at::kFloat && tpd.scalar_type() == at::kFloat && shaped(tpd, {B, Np, H}), "dt fp32, prev_dt fp32 [B,Np,H]");
     Result xo, c, h, y;

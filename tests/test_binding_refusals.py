@@ -45,6 +45,9 @@ REFUSED = [
     ("stree_tree_conv", "xbc_pre", lambda t: t[0], ValueError), ("stree_tree_conv", "xbc_pre", lambda t: t[..., :-8], AssertionError),
     ("stree_tree_conv", "xbc_pre", lambda t: t.double(), TypeError), ("stree_tree_conv", "nheads", lambda v: v + 1, AssertionError),
     ("stree_tree_conv", "nheads", lambda v: float(v), TypeError), ("stree_tree_conv", "conv_w", lambda t: _strided(CC, W), AssertionError),
+    ("stree_tree_conv", "nheads", lambda v: v + 2 ** 32, AssertionError),                  # (not its low 32 bits)
+    ("stree_tree_conv", "headdim", lambda v: v + 2 ** 64, AssertionError), ("stree_tree_conv_replay", "ngroups", lambda v: v - 2 ** 32, AssertionError),
+    ("stree_tree_step", "dstate", lambda v: v + 2 ** 32, AssertionError),
     ("stree_tree_conv", "conv_state", lambda t: _strided(B, W - 1, CC), AssertionError),
     ("stree_tree_conv", "conv_state", lambda t: None, AttributeError),
     ("stree_tree_ssd", "x", lambda t: t[0], ValueError), ("stree_tree_ssd", "x", lambda t: t.double(), TypeError),
