@@ -11,8 +11,11 @@
 #include <ATen/ops/empty.h>
 #include <ATen/ops/empty_like.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <vector>
 
 #include "../../include/stree.h"
 
@@ -39,14 +42,84 @@ void require(bool ok, const char *text) {
     if (!ok) raise(PyExc_AssertionError, text);
 }
 
-const at::Tensor &tensor(PyObject *o) {
-    if (!THPVariable_Check(o)) {
-        PyErr_Format(PyExc_AttributeError, "'%s' object has no attribute 'data_ptr'", Py_TYPE(o)->tp_name);
-        throw Raised{};
-    }
-    return THPVariable_Unpack(o);
+bool truth(PyObject *o) {
+    const int t = PyObject_IsTrue(o);
+    if (t < 0) throw Raised{};
+    return t != 0;
 }
-void *pointer(PyObject *o) { return o == Py_None ? nullptr : tensor(o).data_ptr(); }
+// A Python object of our own.
+struct Owned {
+    PyObject *o;
+    explicit Owned(PyObject *made) : o(made) {
+        if (!o) throw Raised{};
+    }
+    Owned(const Owned &) = delete;
+    ~Owned() { Py_DECREF(o); }
+};
+// A tensor that is read, and results made like it, without a detour through Python: no subclass, whose methods may be
+// somebody's own, and nobody listens to what is called on tensors.
+bool plain(PyObject *o) { return THPVariable_CheckExact(o) && !at::impl::torch_function_mode_enabled(); }
+
+// An array argument: a plain tensor, or whatever its Python attributes say it is (shape, stride(), dtype, is_contiguous(),
+// numel(), element_size(), data_ptr()).
+class Array {
+  public:
+    explicit Array(PyObject *object) : o(object), t(plain(object) ? &THPVariable_Unpack(object) : nullptr) {}
+    at::IntArrayRef sizes() const {
+        if (t) return t->sizes();
+        if (!known_size) size_ = numbers(Owned(PyObject_GetAttrString(o, "shape")).o), known_size = true;
+        return size_;
+    }
+    at::IntArrayRef strides() const {
+        if (t) return t->strides();
+        if (!known_stride) stride_ = numbers(Owned(PyObject_CallMethod(o, "stride", nullptr)).o), known_stride = true;
+        return stride_;
+    }
+    int64_t dim() const { return (int64_t)sizes().size(); }
+    int64_t size(int64_t i) const {
+        if (i >= dim()) raise(PyExc_IndexError, "tuple index out of range");
+        return sizes()[i];
+    }
+    bool shaped(std::initializer_list<int64_t> size) const { return sizes() == at::IntArrayRef(size); }
+    bool is_contiguous() const { return t ? t->is_contiguous() : truth(Owned(PyObject_CallMethod(o, "is_contiguous", nullptr)).o); }
+    int64_t numel() const { return t ? t->numel() : number("numel"); }
+    int64_t element_size() const { return t ? t->element_size() : number("element_size"); }
+    void *data_ptr() const {
+        if (t) return t->data_ptr();
+        const Owned p(PyObject_CallMethod(o, "data_ptr", nullptr));
+        void *v = p.o == Py_None ? nullptr : PyLong_AsVoidPtr(p.o);
+        if (!v && PyErr_Occurred()) throw Raised{};
+        return v;
+    }
+    // (Undefined: a type that torch does not know)
+    at::ScalarType type() const {
+        if (t) return t->scalar_type();
+        const Owned d(PyObject_GetAttrString(o, "dtype"));
+        return THPDtype_Check(d.o) ? reinterpret_cast<THPDtype *>(d.o)->scalar_type : at::ScalarType::Undefined;
+    }
+    bool same_type(const Array &b) const { return type() == b.type() && type() != at::ScalarType::Undefined; }
+
+  private:
+    static std::vector<int64_t> numbers(PyObject *sequence) {
+        const Owned f(PySequence_Fast(sequence, "a sequence of sizes"));
+        std::vector<int64_t> v(PySequence_Fast_GET_SIZE(f.o));
+        for (size_t i = 0; i < v.size(); ++i) {
+            v[i] = PyLong_AsLongLong(PySequence_Fast_GET_ITEM(f.o, (Py_ssize_t)i));
+            if (v[i] == -1 && PyErr_Occurred()) throw Raised{};
+        }
+        return v;
+    }
+    int64_t number(const char *method) const {
+        const int64_t v = PyLong_AsLongLong(Owned(PyObject_CallMethod(o, method, nullptr)).o);
+        if (v == -1 && PyErr_Occurred()) throw Raised{};
+        return v;
+    }
+    PyObject *o;
+    const at::Tensor *t;
+    mutable std::vector<int64_t> size_, stride_;
+    mutable bool known_size = false, known_stride = false;
+};
+void *pointer(PyObject *o) { return o == Py_None ? nullptr : Array(o).data_ptr(); }
 // An int, or what gives one as an index (numpy's), as far as 64 bits reach: the checks see the whole value.
 int64_t integer(PyObject *o) {
     PyObject *i = PyNumber_Index(o);
@@ -62,41 +135,42 @@ bool channels_are(int64_t channels, int64_t heads, int64_t headdim, int64_t dsta
     return !__builtin_mul_overflow(heads, headdim, &x) && !__builtin_mul_overflow(groups, dstate, &bc) &&
            !__builtin_mul_overflow(bc, (int64_t)2, &bc) && !__builtin_add_overflow(x, bc, &x) && x == channels;
 }
-bool truth(PyObject *o) {
-    const int t = PyObject_IsTrue(o);
-    if (t < 0) throw Raised{};
-    return t != 0;
-}
-void dimensions(const at::Tensor &t, int n) {
+void dimensions(const Array &t, int n) {
     if (t.dim() != n) {
         PyErr_Format(PyExc_ValueError, "a tensor of %d dimensions is expected, not %d", n, (int)t.dim());
         throw Raised{};
     }
 }
-int type_code(const at::Tensor &t) {
-    if (t.scalar_type() == at::kFloat) return STREE_F32;
-    if (t.scalar_type() == at::kBFloat16) return STREE_BF16;
+int type_code(const Array &t) {
+    const auto type = t.type();
+    if (type == at::kFloat) return STREE_F32;
+    if (type == at::kBFloat16) return STREE_BF16;
     raise(PyExc_TypeError, "unsupported dtype");
+}
+// ... of the rows, which are torch's
+int rows_code(PyObject *o) {
+    if (!THPVariable_Check(o)) raise(PyExc_TypeError, "unsupported dtype");
+    return type_code(Array(o));
 }
 // type of the SSM state from the state tensors of a call (those that are given must agree)
 int state_code(PyObject *h0, PyObject *h_out) {
-    if (h0 == Py_None) return h_out == Py_None ? STREE_F32 : type_code(tensor(h_out));
-    const at::Tensor &h = tensor(h0);
-    require(h_out == Py_None || tensor(h_out).scalar_type() == h.scalar_type(), "h0 and h_out must have the same dtype");
+    if (h0 == Py_None) return h_out == Py_None ? STREE_F32 : type_code(Array(h_out));
+    const Array h(h0);
+    require(h_out == Py_None || h_out == h0 || Array(h_out).same_type(h), "h0 and h_out must have the same dtype");
     return type_code(h);
 }
 // Element stride between tokens of a [B,N,a,b] view whose last two dims are dense and whose batch stride is N * token
 // stride.
-int64_t token_stride(const at::Tensor &t, int64_t nnodes) {
+int64_t token_stride(const Array &t, int64_t nnodes) {
     require(t.dim() == 4, "inner dims must be dense");
-    const auto size = t.sizes(), stride = t.strides();
+    const at::IntArrayRef size = t.sizes(), stride = t.strides();
+    require(stride.size() == 4, "inner dims must be dense");
     require(stride[3] == 1 && stride[2] == size[3], "inner dims must be dense");
     // (the stride torch keeps for a dimension of size 1 means nothing)
     const int64_t sn = nnodes == 1 && size[0] > 1 ? stride[0] : stride[1];
     require(size[0] == 1 || stride[0] == nnodes * sn, "batch stride must be N * token stride");
     return sn;
 }
-bool shaped(const at::Tensor &t, std::initializer_list<int64_t> size) { return t.sizes() == at::IntArrayRef(size); }
 
 stree_dims make_dims(int64_t batch, int64_t nnodes, int64_t heads, int64_t headdim, int64_t dstate, int64_t groups, int64_t width,
                      int io, int state, int flags, PyObject *dt_bias) {
@@ -105,8 +179,8 @@ stree_dims make_dims(int64_t batch, int64_t nnodes, int64_t heads, int64_t headd
     d.dstate = (int32_t)dstate, d.ngroups = (int32_t)groups, d.conv_width = (int32_t)width;
     d.io_dtype = io, d.state_dtype = state, d.flags = flags;
     if (dt_bias != Py_None) {
-        const at::Tensor &b = tensor(dt_bias);
-        require(b.scalar_type() == at::kFloat && b.is_contiguous() && b.numel() == heads, "dt_bias must be fp32 [H], contiguous");
+        const Array b(dt_bias);
+        require(b.type() == at::kFloat && b.is_contiguous() && b.numel() == heads, "dt_bias must be fp32 [H], contiguous");
         d.flags |= STREE_FLAG_DT_SOFTPLUS;
         d.dt_bias = static_cast<const float *>(b.data_ptr());
     }
@@ -117,7 +191,7 @@ stree_dims make_dims(int64_t batch, int64_t nnodes, int64_t heads, int64_t headd
 struct Result {
     PyObject *o = nullptr;
     ~Result() { Py_XDECREF(o); }
-    const at::Tensor &t() const { return tensor(o); }
+    Array t() const { return Array(o); }
     void *ptr() const { return pointer(o); }
     bool keep(PyObject *given) {
         if (given == Py_None) return false;
@@ -138,10 +212,8 @@ struct Result {
         o = Py_None;
     }
 };
-bool plain(PyObject *o) { return THPVariable_CheckExact(o) && !at::impl::torch_function_mode_enabled(); }
 void like(Result &r, PyObject *given, PyObject *model) {
     if (r.keep(given)) return;
-    tensor(model);
     if (plain(model)) {
         r.o = THPVariable_Wrap(at::empty_like(THPVariable_Unpack(model)));
     } else {
@@ -154,9 +226,9 @@ void like(Result &r, PyObject *given, PyObject *model) {
 // ... what model.new_empty(size) makes, in the type of `typed` (fp32 where that is None)
 void sized(Result &r, PyObject *given, PyObject *model, std::initializer_list<int64_t> size, PyObject *typed) {
     if (r.keep(given)) return;
-    const auto type = typed == Py_None ? at::kFloat : tensor(typed).scalar_type();
-    if (plain(model)) {
-        r.o = THPVariable_Wrap(at::empty(at::IntArrayRef(size), tensor(model).options().dtype(type).requires_grad(false)));
+    const auto type = typed == Py_None ? at::kFloat : Array(typed).type();
+    if (plain(model) && type != at::ScalarType::Undefined) {
+        r.o = THPVariable_Wrap(at::empty(at::IntArrayRef(size), THPVariable_Unpack(model).options().dtype(type).requires_grad(false)));
     } else {
         PyObject *torch = PyImport_ImportModule("torch"), *dtype = nullptr, *shape = nullptr, *kw = nullptr, *args = nullptr, *f = nullptr;
         if (torch) dtype = typed == Py_None ? PyObject_GetAttrString(torch, "float32") : PyObject_GetAttrString(typed, "dtype");
@@ -198,15 +270,15 @@ PyObject *pair(Result &a, Result &b) {
 
 PyObject *conv(PyObject *const *a) {
     enum { parent, xbc_pre, conv_state, conv_w, conv_b, nheads, headdim, dstate, ngroups, silu, out, status };
-    const at::Tensor &x = tensor(a[xbc_pre]), &w = tensor(a[conv_w]);
+    const Array x(a[xbc_pre]), w(a[conv_w]);
     dimensions(x, 3);
     const int64_t B = x.size(0), N = x.size(1), Cc = x.size(2), W = w.size(1);
     const int64_t H = integer(a[nheads]), P = integer(a[headdim]), S = integer(a[dstate]), G = integer(a[ngroups]);
     require(channels_are(Cc, H, P, S, G), "channels of xbc_pre");
-    require(x.is_contiguous() && tensor(a[conv_state]).is_contiguous() && w.is_contiguous(), "contiguous rows");
+    require(x.is_contiguous() && Array(a[conv_state]).is_contiguous() && w.is_contiguous(), "contiguous rows");
     Result y;
     like(y, a[out], a[xbc_pre]);
-    const stree_dims d = make_dims(B, N, H, P, S, G, W, type_code(x), STREE_F32, truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0, Py_None);
+    const stree_dims d = make_dims(B, N, H, P, S, G, W, rows_code(a[xbc_pre]), STREE_F32, truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0, Py_None);
     const auto p0 = (const int32_t *)pointer(a[parent]);
     const void *p1 = pointer(a[xbc_pre]), *p2 = pointer(a[conv_state]), *p3 = pointer(a[conv_w]), *p4 = pointer(a[conv_b]);
     void *p5 = y.ptr(), *st = stream();
@@ -217,17 +289,17 @@ PyObject *conv(PyObject *const *a) {
 
 PyObject *ssd(PyObject *const *a) {
     enum { parent, x, dt, A, Bm, Cm, D, h0, out, status, force_fma, general_mfma, dt_bias };
-    const at::Tensor &tx = tensor(a[x]), &tb = tensor(a[Bm]), &tc = tensor(a[Cm]);
+    const Array tx(a[x]), tb(a[Bm]), tc(a[Cm]);
     dimensions(tx, 4);
     require(tb.dim() == 4, "inner dims must be dense");
     const int64_t B = tx.size(0), N = tx.size(1), H = tx.size(2), P = tx.size(3), G = tb.size(2), S = tb.size(3);
     Result y;
     sized(y, a[out], a[x], {B, N, H, P}, a[x]);
-    stree_dims d = make_dims(B, N, H, P, S, G, 0, type_code(tx), state_code(a[h0], Py_None),
+    stree_dims d = make_dims(B, N, H, P, S, G, 0, rows_code(a[x]), state_code(a[h0], Py_None),
                              (truth(a[force_fma]) ? STREE_FLAG_FORCE_FMA : 0) | (truth(a[general_mfma]) ? STREE_FLAG_GENERAL_MFMA : 0), a[dt_bias]);
     d.x_stride_n = token_stride(tx, N), d.b_stride_n = token_stride(tb, N), d.c_stride_n = token_stride(tc, N);
-    const at::Tensor &td = tensor(a[dt]);
-    require(td.is_contiguous() && td.scalar_type() == at::kFloat && y.t().is_contiguous(), "dt fp32, dense; out dense");
+    const Array td(a[dt]);
+    require(td.is_contiguous() && td.type() == at::kFloat && y.t().is_contiguous(), "dt fp32, dense; out dense");
     const auto p0 = (const int32_t *)pointer(a[parent]);
     const void *p1 = pointer(a[x]), *p4 = pointer(a[Bm]), *p5 = pointer(a[Cm]), *p7 = pointer(a[h0]);
     const auto p2 = (const float *)pointer(a[dt]), p3 = (const float *)pointer(a[A]), p6 = (const float *)pointer(a[D]);
@@ -242,7 +314,7 @@ PyObject *commit(PyObject *const *a) {
     Result h, cs;
     stree_dims d;
     if (a[x] == Py_None) {                            // the conv tail alone; `dims` names the head shapes
-        const at::Tensor &tp = tensor(a[parent]);
+        const Array tp(a[parent]);
         dimensions(tp, 2);
         int64_t shape[4];
         Result s;
@@ -251,8 +323,8 @@ PyObject *commit(PyObject *const *a) {
         if (PySequence_Fast_GET_SIZE(s.o) != 4) raise(PyExc_ValueError, "dims = (H, P, S, G)");
         for (int i = 0; i < 4; ++i) shape[i] = integer(PySequence_Fast_GET_ITEM(s.o, i));
         like(cs, a[conv_state_out], a[conv_state]);
-        d = make_dims(tp.size(0), tp.size(1), shape[0], shape[1], shape[2], shape[3], tensor(a[conv_state]).size(1) + 1,
-                      type_code(tensor(a[xbc_pre])), STREE_F32, 0, Py_None);
+        d = make_dims(tp.size(0), tp.size(1), shape[0], shape[1], shape[2], shape[3], Array(a[conv_state]).size(1) + 1,
+                      rows_code(a[xbc_pre]), STREE_F32, 0, Py_None);
         h.none();
         const auto p0 = (const int32_t *)pointer(a[parent]), p1 = (const int32_t *)pointer(a[accepted]);
         const void *p2 = pointer(a[xbc_pre]), *p3 = pointer(a[conv_state]);
@@ -263,19 +335,19 @@ PyObject *commit(PyObject *const *a) {
         });
         return pair(h, cs);
     }
-    const at::Tensor &tx = tensor(a[x]), &tb = tensor(a[Bm]);
+    const Array tx(a[x]), tb(a[Bm]);
     dimensions(tx, 4);
     require(tb.dim() == 4, "inner dims must be dense");
     const int64_t B = tx.size(0), N = tx.size(1), H = tx.size(2), P = tx.size(3), G = tb.size(2), S = tb.size(3);
     sized(h, a[h_out], a[x], {B, H, P, S}, a[h0]);
     int64_t W = 0;
     if (a[xbc_pre] != Py_None) {
-        W = tensor(a[conv_state]).size(1) + 1;
+        W = Array(a[conv_state]).size(1) + 1;
         like(cs, a[conv_state_out], a[conv_state]);
     } else if (!cs.keep(a[conv_state_out])) {
         cs.none();
     }
-    d = make_dims(B, N, H, P, S, G, W, type_code(tx), state_code(a[h0], h.o), 0, a[dt_bias]);
+    d = make_dims(B, N, H, P, S, G, W, rows_code(a[x]), state_code(a[h0], h.o), 0, a[dt_bias]);
     d.x_stride_n = token_stride(tx, N), d.b_stride_n = token_stride(tb, N);
     const auto p0 = (const int32_t *)pointer(a[parent]), p1 = (const int32_t *)pointer(a[accepted]);
     const void *p2 = pointer(a[x]), *p5 = pointer(a[Bm]), *p6 = pointer(a[h0]), *p8 = pointer(a[xbc_pre]), *p9 = pointer(a[conv_state]);
@@ -288,22 +360,22 @@ PyObject *commit(PyObject *const *a) {
 
 PyObject *ssd_replay(PyObject *const *a) {
     enum { pparent, paccepted, px, pdt, pBm, parent, x, dt, A, Bm, Cm, D, h0, h_out, out, status, rstatus, force_fma, dt_bias };
-    const at::Tensor &tx = tensor(a[x]), &tb = tensor(a[Bm]), &tc = tensor(a[Cm]), &tpx = tensor(a[px]), &tpb = tensor(a[pBm]);
-    const at::Tensor &tpd = tensor(a[pdt]), &td = tensor(a[dt]), &th = tensor(a[h0]);
+    const Array tx(a[x]), tb(a[Bm]), tc(a[Cm]), tpx(a[px]), tpb(a[pBm]);
+    const Array tpd(a[pdt]), td(a[dt]), th(a[h0]);
     dimensions(tx, 4);
     require(tb.dim() == 4 && tpx.dim() == 4, "inner dims must be dense");
     const int64_t B = tx.size(0), N = tx.size(1), H = tx.size(2), P = tx.size(3), G = tb.size(2), S = tb.size(3), Np = tpx.size(1);
-    require(shaped(tpx, {B, Np, H, P}) && shaped(tpb, {B, Np, G, S}) && tpx.scalar_type() == tx.scalar_type(), "rows of the previous tree");
-    require(tpd.is_contiguous() && tpd.scalar_type() == at::kFloat && shaped(tpd, {B, Np, H}), "prev_dt fp32 [B,Np,H], dense");
-    require(td.is_contiguous() && td.scalar_type() == at::kFloat && th.is_contiguous(), "dt fp32, dense; h0 dense");
+    require(tpx.shaped({B, Np, H, P}) && tpb.shaped({B, Np, G, S}) && tpx.same_type(tx), "rows of the previous tree");
+    require(tpd.is_contiguous() && tpd.type() == at::kFloat && tpd.shaped({B, Np, H}), "prev_dt fp32 [B,Np,H], dense");
+    require(td.is_contiguous() && td.type() == at::kFloat && th.is_contiguous(), "dt fp32, dense; h0 dense");
     Result y, h;
     sized(y, a[out], a[x], {B, N, H, P}, a[x]);
     like(h, a[h_out], a[h0]);
-    stree_dims d = make_dims(B, N, H, P, S, G, 0, type_code(tx), state_code(a[h0], h.o), truth(a[force_fma]) ? STREE_FLAG_FORCE_FMA : 0, a[dt_bias]);
+    stree_dims d = make_dims(B, N, H, P, S, G, 0, rows_code(a[x]), state_code(a[h0], h.o), truth(a[force_fma]) ? STREE_FLAG_FORCE_FMA : 0, a[dt_bias]);
     d.x_stride_n = token_stride(tx, N), d.b_stride_n = token_stride(tb, N), d.c_stride_n = token_stride(tc, N);
     stree_replay r = {};
-    r.nnodes = (int32_t)Np, r.parent = (const int32_t *)tensor(a[pparent]).data_ptr();
-    r.accepted = (const int32_t *)tensor(a[paccepted]).data_ptr(), r.x = tpx.data_ptr(), r.dt = (const float *)tpd.data_ptr();
+    r.nnodes = (int32_t)Np, r.parent = (const int32_t *)Array(a[pparent]).data_ptr();
+    r.accepted = (const int32_t *)Array(a[paccepted]).data_ptr(), r.x = tpx.data_ptr(), r.dt = (const float *)tpd.data_ptr();
     r.Bm = tpb.data_ptr(), r.x_stride_n = token_stride(tpx, Np), r.b_stride_n = token_stride(tpb, Np);
     const auto p0 = (const int32_t *)pointer(a[parent]);
     const void *p1 = pointer(a[x]), *p4 = pointer(a[Bm]), *p5 = pointer(a[Cm]), *p7 = pointer(a[h0]);
@@ -317,21 +389,21 @@ PyObject *ssd_replay(PyObject *const *a) {
 PyObject *conv_replay(PyObject *const *a) {
     enum { pparent, paccepted, pxbc_pre, parent, xbc_pre, conv_state, conv_w, conv_b, nheads, headdim, dstate, ngroups, silu, out,
            conv_state_out, status, rstatus };
-    const at::Tensor &x = tensor(a[xbc_pre]), &w = tensor(a[conv_w]), &px = tensor(a[pxbc_pre]), &cs = tensor(a[conv_state]);
+    const Array x(a[xbc_pre]), w(a[conv_w]), px(a[pxbc_pre]), cs(a[conv_state]);
     dimensions(x, 3);
     require(px.dim() >= 2, "rows of the previous tree");
     const int64_t B = x.size(0), N = x.size(1), Cc = x.size(2), W = w.size(1), Np = px.size(1);
     const int64_t H = integer(a[nheads]), P = integer(a[headdim]), S = integer(a[dstate]), G = integer(a[ngroups]);
-    require(channels_are(Cc, H, P, S, G) && shaped(px, {B, Np, Cc}), "channels of xbc_pre and prev_xbc_pre");
+    require(channels_are(Cc, H, P, S, G) && px.shaped({B, Np, Cc}), "channels of xbc_pre and prev_xbc_pre");
     require(x.is_contiguous() && cs.is_contiguous() && w.is_contiguous() && px.is_contiguous(), "contiguous rows");
     Result y, c;
     like(y, a[out], a[xbc_pre]);
     like(c, a[conv_state_out], a[conv_state]);
     require(c.t().data_ptr() != cs.data_ptr(), "conv_state_out must not be conv_state");
-    const stree_dims d = make_dims(B, N, H, P, S, G, W, type_code(x), STREE_F32, truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0, Py_None);
+    const stree_dims d = make_dims(B, N, H, P, S, G, W, rows_code(a[xbc_pre]), STREE_F32, truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0, Py_None);
     stree_replay r = {};
-    r.nnodes = (int32_t)Np, r.parent = (const int32_t *)tensor(a[pparent]).data_ptr();
-    r.accepted = (const int32_t *)tensor(a[paccepted]).data_ptr();
+    r.nnodes = (int32_t)Np, r.parent = (const int32_t *)Array(a[pparent]).data_ptr();
+    r.accepted = (const int32_t *)Array(a[paccepted]).data_ptr();
     const void *p0 = pointer(a[pxbc_pre]), *p2 = pointer(a[xbc_pre]), *p3 = pointer(a[conv_state]), *p4 = pointer(a[conv_w]), *p5 = pointer(a[conv_b]);
     const auto p1 = (const int32_t *)pointer(a[parent]);
     void *p6 = y.ptr(), *p7 = c.ptr(), *st = stream();
@@ -343,15 +415,15 @@ PyObject *conv_replay(PyObject *const *a) {
 PyObject *step(PyObject *const *a) {
     enum { pparent, paccepted, pxbc_pre, pxbc_out, pdt, parent, xbc_pre, conv_state, conv_w, conv_b, dt, A, D, h0, nheads, headdim, dstate,
            ngroups, silu, xbc_out, conv_state_out, h_out, out, status, rstatus, force_fma, dt_bias };
-    const at::Tensor &x = tensor(a[xbc_pre]), &w = tensor(a[conv_w]), &px = tensor(a[pxbc_pre]), &po = tensor(a[pxbc_out]);
-    const at::Tensor &cs = tensor(a[conv_state]), &tpd = tensor(a[pdt]), &td = tensor(a[dt]), &th = tensor(a[h0]);
+    const Array x(a[xbc_pre]), w(a[conv_w]), px(a[pxbc_pre]), po(a[pxbc_out]);
+    const Array cs(a[conv_state]), tpd(a[pdt]), td(a[dt]), th(a[h0]);
     dimensions(x, 3);
     require(px.dim() >= 2, "rows of the previous tree");
     const int64_t B = x.size(0), N = x.size(1), Cc = x.size(2), W = w.size(1), Np = px.size(1);
     const int64_t H = integer(a[nheads]), P = integer(a[headdim]), S = integer(a[dstate]), G = integer(a[ngroups]);
-    require(channels_are(Cc, H, P, S, G) && shaped(px, {B, Np, Cc}) && shaped(po, {B, Np, Cc}), "channels of the rows of both trees");
-    for (const at::Tensor *t : {&x, &cs, &w, &px, &po, &tpd, &td, &th}) require(t->is_contiguous(), "dense tensors");
-    require(td.scalar_type() == at::kFloat && tpd.scalar_type() == at::kFloat && shaped(tpd, {B, Np, H}), "dt fp32, prev_dt fp32 [B,Np,H]");
+    require(channels_are(Cc, H, P, S, G) && px.shaped({B, Np, Cc}) && po.shaped({B, Np, Cc}), "channels of the rows of both trees");
+    for (const Array *t : {&x, &cs, &w, &px, &po, &tpd, &td, &th}) require(t->is_contiguous(), "dense tensors");
+    require(td.type() == at::kFloat && tpd.type() == at::kFloat && tpd.shaped({B, Np, H}), "dt fp32, prev_dt fp32 [B,Np,H]");
     Result xo, c, h, y;
     like(xo, a[xbc_out], a[xbc_pre]);
     like(c, a[conv_state_out], a[conv_state]);
@@ -359,19 +431,20 @@ PyObject *step(PyObject *const *a) {
     sized(y, a[out], a[xbc_pre], {B, N, H, P}, a[xbc_pre]);
     require(xo.t().is_contiguous() && y.t().is_contiguous() && h.t().is_contiguous(), "dense results");
     require(c.t().data_ptr() != cs.data_ptr(), "conv_state_out must not be conv_state");
-    const stree_dims d = make_dims(B, N, H, P, S, G, W, type_code(x), state_code(a[h0], h.o),
+    const stree_dims d = make_dims(B, N, H, P, S, G, W, rows_code(a[xbc_pre]), state_code(a[h0], h.o),
                                    (truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0) | (truth(a[force_fma]) ? STREE_FLAG_FORCE_FMA : 0), a[dt_bias]);
     stree_replay r = {};
-    r.nnodes = (int32_t)Np, r.parent = (const int32_t *)tensor(a[pparent]).data_ptr();
-    r.accepted = (const int32_t *)tensor(a[paccepted]).data_ptr(), r.x = po.data_ptr(), r.dt = (const float *)tpd.data_ptr();
-    r.Bm = static_cast<const char *>(po.data_ptr()) + H * P * (int64_t)po.element_size();             // the B columns behind x's
+    r.nnodes = (int32_t)Np, r.parent = (const int32_t *)Array(a[pparent]).data_ptr();
+    r.accepted = (const int32_t *)Array(a[paccepted]).data_ptr(), r.x = po.data_ptr(), r.dt = (const float *)tpd.data_ptr();
+    r.Bm = static_cast<const char *>(po.data_ptr()) + H * P * po.element_size();             // the B columns behind x's
     r.x_stride_n = r.b_stride_n = Cc;
     const void *p0 = pointer(a[pxbc_pre]), *p2 = pointer(a[xbc_pre]), *p3 = pointer(a[conv_state]), *p4 = pointer(a[conv_w]), *p5 = pointer(a[conv_b]);
     const auto p1 = (const int32_t *)pointer(a[parent]);
-    void *p6 = xo.ptr(), *p7 = c.ptr(), *p12 = h.ptr(), *p13 = y.ptr(), *st = stream();
+    void *p6 = xo.ptr(), *p7 = c.ptr(), *p12 = h.ptr(), *p13 = y.ptr();
     const auto p8 = (const float *)pointer(a[dt]), p9 = (const float *)pointer(a[A]), p10 = (const float *)pointer(a[D]);
     const void *p11 = pointer(a[h0]);
     const auto p14 = (int32_t *)pointer(a[status]), p15 = (int32_t *)pointer(a[rstatus]);
+    void *st = stream();
     run("stree_tree_step", [&] {
         return g_entry.tree_step(&d, &r, p0, p1, p2, p3, p4, p5, p6, p7, p8, p9, p10, p11, p12, p13, p14, p15, st);
     });
@@ -380,13 +453,13 @@ PyObject *step(PyObject *const *a) {
 
 PyObject *gate(PyObject *const *a) {
     enum { y, z, norm_w, ngroups, eps, out };
-    const at::Tensor &ty = tensor(a[y]), &tz = tensor(a[z]), &tw = tensor(a[norm_w]);
+    const Array ty(a[y]), tz(a[z]), tw(a[norm_w]);
     dimensions(ty, 4);
     const int64_t B = ty.size(0), N = ty.size(1), H = ty.size(2), P = ty.size(3);
-    require(ty.is_contiguous() && tz.sizes() == ty.sizes() && tz.scalar_type() == ty.scalar_type() && tw.numel() == H * P, "y, z and norm_w agree");
+    require(ty.is_contiguous() && tz.sizes() == ty.sizes() && tz.same_type(ty) && tw.numel() == H * P, "y, z and norm_w agree");
     Result o;
     like(o, a[out], a[y]);
-    const stree_dims d = make_dims(B, N, H, P, 1, integer(a[ngroups]), 0, type_code(ty), STREE_F32, 0, Py_None);
+    const stree_dims d = make_dims(B, N, H, P, 1, integer(a[ngroups]), 0, rows_code(a[y]), STREE_F32, 0, Py_None);
     const int64_t zs = token_stride(tz, N);
     const float e = (float)PyFloat_AsDouble(a[eps]);
     if (PyErr_Occurred()) throw Raised{};
@@ -398,19 +471,19 @@ PyObject *gate(PyObject *const *a) {
 
 PyObject *linear(PyObject *const *a) {
     enum { x, dt, A, Bm, Cm, D, h0, want_y, out, h_out, dt_bias };
-    const at::Tensor &tx = tensor(a[x]), &tb = tensor(a[Bm]), &td = tensor(a[dt]);
+    const Array tx(a[x]), tb(a[Bm]), td(a[dt]);
     dimensions(tx, 4);
     require(tb.dim() == 4, "inner dims must be dense");
     const int64_t B = tx.size(0), T = tx.size(1), H = tx.size(2), P = tx.size(3), G = tb.size(2), S = tb.size(3);
-    require(td.is_contiguous() && td.scalar_type() == at::kFloat && shaped(td, {B, T, H}), "dt fp32 [B,T,H], dense");
+    require(td.is_contiguous() && td.type() == at::kFloat && td.shaped({B, T, H}), "dt fp32 [B,T,H], dense");
     const bool wanted = truth(a[want_y]);
     Result y, h;
     if (wanted) sized(y, a[out], a[x], {B, T, H, P}, a[x]);
     else y.none();
     sized(h, a[h_out], a[x], {B, H, P, S}, a[h0]);
-    stree_dims d = make_dims(B, T, H, P, S, G, 0, type_code(tx), state_code(a[h0], h.o), 0, a[dt_bias]);
+    stree_dims d = make_dims(B, T, H, P, S, G, 0, rows_code(a[x]), state_code(a[h0], h.o), 0, a[dt_bias]);
     d.x_stride_n = token_stride(tx, T), d.b_stride_n = token_stride(tb, T);
-    d.c_stride_n = a[Cm] == Py_None ? 0 : token_stride(tensor(a[Cm]), T);
+    d.c_stride_n = a[Cm] == Py_None ? 0 : token_stride(Array(a[Cm]), T);
     const void *p0 = pointer(a[x]), *p3 = pointer(a[Bm]), *p4 = pointer(a[Cm]), *p6 = pointer(a[h0]);
     const auto p1 = (const float *)pointer(a[dt]), p2 = (const float *)pointer(a[A]), p5 = (const float *)pointer(a[D]);
     void *p7 = y.ptr(), *p8 = h.ptr(), *st = stream();

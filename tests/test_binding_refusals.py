@@ -1,5 +1,6 @@
 """What the binding refuses before anything is launched, on the CPU: wrong shapes, types, strides and objects, entry point by
 entry point, and that no argument of a call is lost on its way to the native half."""
+import ctypes as C
 import inspect
 
 import numpy as np
@@ -84,6 +85,88 @@ def test_refused_before_anything_is_launched(name, arg, change, error):
     call[arg] = call[change] if isinstance(change, str) else change(call.get(arg))
     with pytest.raises(error):
         getattr(st, name)(**call)
+
+
+class _Like:
+    """An array that is no tensor: the attributes of one that the binding asks for."""
+
+    def __init__(self, t):
+        self.t, self.shape, self.dtype = t, tuple(t.shape), t.dtype
+
+    dim = lambda self: len(self.shape)
+    stride = lambda self: self.t.stride()
+    is_contiguous = lambda self: self.t.is_contiguous()
+    numel = lambda self: self.t.numel()
+    element_size = lambda self: self.t.element_size()
+    data_ptr = lambda self: self.t.data_ptr()
+
+
+class _Own(torch.Tensor):
+    """A tensor whose address and density are its own methods'."""
+    asked = []
+
+    def data_ptr(self):
+        self.asked.append("data_ptr")
+        return super().data_ptr()
+
+    def is_contiguous(self):
+        return True
+
+
+@pytest.fixture
+def nothing_launched():
+    """The entry points replaced by one that returns at once, so that no call goes further than that on any machine."""
+    entry = C.CFUNCTYPE(C.c_int, C.c_void_p)(lambda dims: 0)
+    st.load()
+    st._native().bind(st.StreeError, *[C.cast(entry, C.c_void_p).value] * len(st._ENTRIES))
+    yield
+    st._bind(st.load())
+
+
+def _outcome(name, call):
+    try:
+        getattr(st, name)(**call)
+    except RuntimeError as e:                            # no GPU here: the checks are passed, the stream is asked for
+        return str(e).splitlines()[0]
+    return "launched"
+
+
+# (the rows themselves, whose type decides the kernels, are tensors)
+ROWS = {"stree_tree_conv": "xbc_pre", "stree_tree_ssd": "x", "stree_commit_state": "x", "stree_tree_ssd_replay": "x",
+        "stree_tree_conv_replay": "xbc_pre", "stree_tree_step": "xbc_pre", "stree_gate_norm": "y", "stree_linear_ssd": "x"}
+
+
+@pytest.mark.parametrize("name", sorted(ROWS))
+def test_arrays_that_are_no_tensors_are_taken(name, nothing_launched):
+    call = _good()[name]
+    want = _outcome(name, call)
+    for arg, value in call.items():
+        if not isinstance(value, torch.Tensor):
+            continue
+        changed = dict(call)
+        if arg != ROWS[name]:
+            changed[arg] = _Like(value)
+            result = {"h0": "h_out", "conv_state": "conv_state_out"}.get(arg)
+            if result in inspect.signature(getattr(st, name)).parameters:        # (nothing can be made like them)
+                changed[result] = torch.empty_like(value)
+            assert _outcome(name, changed) == want, arg
+        changed[arg] = value.as_subclass(_Own)
+        _Own.asked.clear()
+        assert _outcome(name, changed) == want and "data_ptr" in _Own.asked, arg
+
+
+def test_a_torch_function_mode_sees_the_calls(nothing_launched):
+    from torch.overrides import TorchFunctionMode
+    seen = set()
+
+    class Listener(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            seen.add(getattr(func, "__name__", str(func)))
+            return func(*args, **(kwargs or {}))
+    call = _good()["stree_gate_norm"]
+    with Listener():
+        _outcome("stree_gate_norm", call)
+    assert {"data_ptr", "empty_like", "is_contiguous"} <= seen
 
 
 def test_every_argument_reaches_the_native_half():
