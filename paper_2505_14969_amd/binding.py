@@ -5,7 +5,8 @@ device pointers and the current HIP stream through the C ABI declared in
 ``include/stree.h`` and returns the output tensors.  The checks, the results'
 allocation and the marshalling of a call are native code (``csrc/host.cpp``,
 ``_host.so``).  No step of the path is computed here, and there is no CPU
-fallback: if either library is missing, ``load()`` raises.
+fallback: if the library is missing ``load()`` raises, and every call on tensors
+does if either is.
 """
 from __future__ import annotations
 
@@ -66,14 +67,14 @@ def _bind(lib: C.CDLL) -> None:
 
 def _native():
     if _host is None:
-        load()
+        _bind(load())
     return _host
 
 
 def load() -> C.CDLL:
     """Load libstree.so (build it first with ``python -m paper_2505_14969_amd.build``
     or ``__graft_entry__.build()``).  Raises if it is not there."""
-    global _lib
+    global _lib, _host
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(f"{LIB_PATH} is not built; run paper_2505_14969_amd/build.py")
@@ -100,8 +101,7 @@ def load() -> C.CDLL:
         for f in (lib.stree_tree_index, lib.stree_tree_conv, lib.stree_tree_ssd, lib.stree_commit_state,
                   lib.stree_tree_ssd_replay, lib.stree_tree_conv_replay, lib.stree_tree_step):
             f.restype = C.c_int
-        _bind(lib)
-        _lib = lib
+        _lib, _host = lib, None            # (the native half is bound to this library at the first call that needs it)
     return _lib
 
 
