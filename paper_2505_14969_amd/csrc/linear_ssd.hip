@@ -899,7 +899,7 @@ struct TeamLds {
     static constexpr int c = 0, b = 2 * rows, x = b + 2 * rows, m = x + NM * 2 * kQ * kCols * 2, e = m + 2 * 2048;
     static constexpr int w = e + 2 * 2 * kQ * 4, u = w + 2 * 2 * kQ * 4, s2 = u + 2 * kQ * 4, sum = s2 + 2 * kQ * 4, size = sum + 32;
 };
-template <int S, int NM, typename HT>
+template <int S, int NM, bool HALVES, typename HT>
 __global__ __launch_bounds__(64 * (NM + 2), kTeams<S>) void linear_ssd_team_kernel(
     int T, int H, int G, int units, int whole, const bf16_t *__restrict__ x, long x_sn, const float *__restrict__ dt,
     const float *__restrict__ dt_bias, const float *__restrict__ A, const bf16_t *__restrict__ Bm, long b_sn,
@@ -908,10 +908,10 @@ __global__ __launch_bounds__(64 * (NM + 2), kTeams<S>) void linear_ssd_team_kern
     constexpr int NK = S / 16, ST = S / 32, P = NM * kCols;
     using L = TeamLds<S, NM>;
     __shared__ __align__(512) char lds[L::size];
-    // The first `whole` units are heads, the others halves of heads: the second column wave has nothing to do there.
-    const int unit = (int)blockIdx.x < 8 * ((whole + 7) / 8) ? unit_of_block(whole) : half_of_block(whole, units);
+    // HALVES: the first `whole` units are heads, the others halves of heads, whose second column wave has nothing to do.
+    const int unit = !HALVES || (int)blockIdx.x < 8 * ((whole + 7) / 8) ? unit_of_block(whole) : half_of_block(whole, units);
     if (unit < 0) return;
-    const bool half = NM == 2 && unit >= whole;
+    const bool half = HALVES && unit >= whole;
     // The waves of a workgroup go to the four SIMDs in turn: every other workgroup of a CU (32 CUs to an XCD) swaps
     // the roles around, so that the column waves of all of them do not share two SIMDs.
     const int hw_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1063,10 +1063,13 @@ hipError_t launch_team(const stree_dims &d, const void *x, const float *dt, cons
     // us, 1920 heads 78.9 and 79.6; S = 256, 640 heads 187 and 189), and with fewer than 256 heads a CU's one team
     // pays for a second (160 heads 96.3 and 99.9 us).
     const long heads = (long)d.batch * d.nheads, rest = heads % kCUs;
-    const bool split = NM == 2 && heads > kCUs && 2 * rest <= kCUs && heads + rest <= kTeams<S> * kCUs;
+    const bool split = NM == 2 && rest > 0 && heads > kCUs && 2 * rest <= kCUs && heads + rest <= kTeams<S> * kCUs;
     const int whole = (int)(split ? heads - rest : heads), units = (int)(split ? heads + rest : heads);
-    hipLaunchKernelGGL((linear_ssd_team_kernel<S, NM, HT>), dim3(8 * ((whole + 7) / 8 + (units - whole + 7) / 8)),
-                       dim3(64 * (NM + 2)), 0, st, d.nnodes, d.nheads, d.ngroups, units, whole,
+    // (Without halves a kernel of its own: the arithmetic of halves costs a launch that has none 2 to 5 %; S = 128, 160 heads x
+    // 1013 tokens 37.7 and 36.7 us, 240 x 2050 72.5 and 68.6, 24 x 700 25.8 and 25.3.)
+    const auto kernel = split ? linear_ssd_team_kernel<S, NM, NM == 2, HT> : linear_ssd_team_kernel<S, NM, false, HT>;
+    hipLaunchKernelGGL(kernel, dim3(8 * ((whole + 7) / 8 + (units - whole + 7) / 8)), dim3(64 * (NM + 2)), 0, st, d.nnodes,
+                       d.nheads, d.ngroups, units, whole,
                        (const bf16_t *)x, (long)d.x_stride_n, dt, step_bias(d), A,
                        (const bf16_t *)Bm, (long)d.b_stride_n, (const bf16_t *)Cm, (long)d.c_stride_n, D, (const HT *)h0,
                        (bf16_t *)y, (HT *)h_out);
