@@ -1110,15 +1110,42 @@ bool y_in_segments(const stree_dims &d) {
     return d.dstate != 256 && (d.nnodes + 2 * kQ - 1) / (2 * kQ) >= 12 && waves * 8 <= 2048;
 }
 
-// State only: segments NSEG and 32-column groups NC a wave, by the column groups (of 32, with S = 256 two parts each) and
-// the chunk pairs there are.  Below 8 pairs the state is formed chunk after chunk, and where y would take segments in
-// those: the two give the same bits.  Else the segments' states are added up:
-//   * from 10 pairs on, where the waves of 64 columns still fill half of the CUs: four segments of those (S = 64, 480 groups
-//     x 2050 tokens 24 us, 32 columns 32 us; S = 128, 320 x 2000 29 and 37 us, 1280 x 4000 136 and 162 us; 320 x 520, 9 pairs,
-//     15.7 and, two segments of 32, 15.1 us);
-//   * fewer pairs: two segments of 32 columns (640 x 520 19.9 us, four 22.1 us), none with many groups (1280 x 520, S = 64
-//     23.4 and 24.5 us);
-//   * few groups: four segments of 32 columns (160 x 600, S = 128 10.9 us, two 12.5, eight 12.5 us).
+// State only, from 8 chunk pairs on: where four segments of 64 columns a wave (whole lines of x, half as many workgroups) are
+// ahead of 32 columns, as the pairs from which they are, by the column groups (of 32, with S = 256 two parts each).  A group
+// of 64 columns is worth it where the CUs that get one more of them are many, or the prompt is long.  In us, 64 / 32 columns
+// (the better of two and four segments):
+//   up to 2 groups a CU: S = 64, 400 x 460 10.0 / 11.3, 320 x 2050 22.5 / 25.0; S = 128, 400 x 700 16.3 / 16.4, 460 14.1 / 13.6,
+//     4096 50.8 / 65.5, 264 x 1100 21.1 / 20.2, 4096 49.5 / 50.9; S = 256, 400 x 1100 21.4 / 20.9, 4096 51.4 / 54.5
+//   up to 3: S = 64, 520 x 2050 36.4 / 33.9, 640 x 4096 66.6 / 74.9; S = 128, 640 x 700 23.6 / 20.8, 4096 88.6 / 95.9, 520 x 4096
+//     80.5 / 77.4; S = 256, 640 x 1500 37.1 / 34.7
+//   up to 4: S = 64, 800 x 900 21.1 / 25.3; S = 128, 800 x 700 24.6 / 25.2, 2050 55.0 / 65.2; S = 256, 800 x 900 28.1 / 28.4
+//   up to 5: S = 64, 1280 x 4096 104 / 129; S = 128, 1280 x 700 35.7 / 31.9, 1500 61.4 / 68.1; S = 256, 1280 x 700 34.7 / 31.0
+//   above: S = 128, 1800 x 1000 56.5 / 65.6; S = 256, 1800 x 1200 61.7 / 65.9, 700 40.0 / 38.8.
+int pairs_for_64_columns(int dstate, long groups) {
+    constexpr int kNever = 1 << 30;
+    const int k = dstate == 64 ? 0 : dstate == 128 ? 1 : 2;
+    if (groups <= kCUs) return kNever;
+    if (groups <= 2 * kCUs) {
+        const int from[] = {8, groups >= 272 ? 11 : 20, 24};
+        return from[k];
+    }
+    const int from[4][3] = {{20, 28, kNever}, {10, 11, 11}, {10, 16, 33}, {10, 12, 16}};
+    if (groups < 528) return kNever;
+    if (groups <= 3 * kCUs) return from[0][k];
+    if (groups <= 4 * kCUs) return from[1][k];
+    if (groups < 1312) return from[2][k];
+    if (groups < 1792) return from[3][k];
+    return k == 2 ? 12 : 10;
+}
+
+// State only: segments NSEG and 32-column groups NC a wave.  Below 8 pairs the state is formed chunk after chunk, and where
+// y would take segments in those: the two give the same bits.  Else the segments' states are added up:
+//   * four segments of 64 columns (see above);
+//   * up to two groups a CU four segments of 32 columns (160 x 600, S = 128 10.9 us, two 12.5, eight 12.5), but long prompts of
+//     few groups with S = 256 eight, chained (64 x 4096 30.4 and 33.0 us, 200 x 2050 21.2 and 22.2; at 1500 tokens they meet);
+//   * beyond, two of 32 columns (S = 128, 640 x 520 18.9 us, four 20.8; 520 x 700 20.0 and 20.7; 1280 x 700 31.9 and 34.0), four
+//     for long prompts up to three a CU (520 x 1500 33.1 us, two 35.6; S = 256, 640 x 900 25.0 and 25.3);
+//   * none with many groups and fewer than 10 pairs (1280 x 520, S = 64 23.4 us, two 24.5).
 // One segment: workgroups of one wave; where they are few, or a wave has one pair only, of two waves that ask for a
 // pair's x at once (S = 64, 320 x 400: 11.8 and, one wave, 13.1 us; S = 128 15.5 and 15.9 us; 1280 x 60 11.0 and 11.5 us;
 // but 1280 x 400 29.2 and 26.4 us; S = 64 20.9 and 19.6 us, 1280 x 60 7.9 and 7.4 us).
@@ -1132,8 +1159,11 @@ hipError_t launch_state(const stree_dims &d, const void *x, const float *dt, con
         return launch_n<S, false, 1, 2, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
     if (pairs < 8 || (pairs < 10 && groups >= 4 * kCUs)) return launch_s<S, 1, 1, HT>(d, x, dt, A, Bm, h0, h_out, st);
     if (y_in_segments(d)) return launch_n<S, false, 8, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
-    if (groups <= kCUs) return launch_s<S, 4, 1, HT>(d, x, dt, A, Bm, h0, h_out, st);
-    if (pairs >= 10) return launch_s<S, 4, 2, HT>(d, x, dt, A, Bm, h0, h_out, st);
+    if (groups <= kCUs && d.dstate == 256 && pairs >= 28)
+        return launch_n<S, false, 8, 1, false, HT>(d, x, dt, A, Bm, Cm, D, h0, y, h_out, st);
+    if (pairs >= pairs_for_64_columns(d.dstate, groups)) return launch_s<S, 4, 2, HT>(d, x, dt, A, Bm, h0, h_out, st);
+    if (groups <= 2 * kCUs || (groups <= 3 * kCUs && S != 64 && pairs >= (d.dstate == 256 ? 12 : 20)))
+        return launch_s<S, 4, 1, HT>(d, x, dt, A, Bm, h0, h_out, st);
     return launch_s<S, 2, 1, HT>(d, x, dt, A, Bm, h0, h_out, st);
 }
 

@@ -15,7 +15,12 @@ LINES = [(1, 1, 3, 64, 128, 1), (2, 65, 3, 128, 128, 1), (1, 448, 4, 64, 128, 2)
          (1, 449, 4, 64, 128, 2), (1, 700, 128, 64, 64, 1), (1, 1013, 64, 64, 256, 2), (2, 512, 3, 128, 128, 1),  # few groups
          (1, 449, 129, 64, 128, 3), (2, 576, 128, 64, 64, 1), (1, 550, 65, 64, 256, 1),                        # 8 and 9 pairs
          (4, 576, 128, 64, 64, 2), (4, 449, 128, 64, 128, 1),
-         (1, 577, 129, 64, 128, 1), (2, 640, 65, 64, 64, 1), (1, 609, 65, 128, 128, 1), (1, 1025, 65, 64, 256, 1)]
+         (1, 577, 129, 64, 128, 1), (2, 640, 65, 64, 64, 1), (1, 609, 65, 128, 128, 1), (1, 1025, 65, 64, 256, 1),
+         (1, 1729, 3, 64, 256, 1), (1, 1728, 3, 64, 256, 1), (2, 449, 65, 64, 64, 5), (2, 641, 72, 64, 128, 1),  # both sides of each line
+         (2, 640, 72, 64, 128, 1), (1, 1217, 129, 64, 128, 3), (2, 1473, 33, 64, 256, 1), (2, 1472, 33, 64, 256, 1),
+         (2, 640, 130, 64, 128, 2), (2, 705, 130, 64, 128, 1), (2, 1217, 152, 64, 64, 1), (2, 1216, 152, 64, 64, 1),
+         (1, 3009, 152, 64, 256, 1), (3, 641, 128, 64, 128, 1), (3, 577, 128, 64, 64, 1), (4, 1217, 130, 64, 128, 1),
+         (4, 1216, 65, 128, 128, 1), (5, 449, 26, 64, 256, 1), (8, 705, 82, 64, 128, 1), (8, 641, 112, 64, 128, 1)]
 
 
 @pytest.mark.parametrize("state", ["f32", "bf16"])
