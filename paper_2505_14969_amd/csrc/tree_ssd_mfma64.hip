@@ -1,4 +1,4 @@
-// Tree scan for trees of at most 64 nodes with headdim 64 and some three to six heads a CU, the band in
+// Tree scan for trees of at most 64 nodes, most of them with two to six heads a CU, the bands in
 // which it is ahead of the workgroup per head of tree_ssd_unit.hip (see unit_is_slower): persistent, software-pipelined,
 // wave-specialised (products and accumulator layouts as in tree_ssd_mfma.hip).
 //
@@ -212,13 +212,12 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     float rD = 0.f;                  // D[h] of the unit whose h0 is in pre[]
     // The state tile in a thread's registers.  Without replay chunk q is element (t + q*kHalf)*4 of the P x S tile.
     // With replay it is the accumulator of the fp32 matrix instructions that advance it (16 x 16 x 4, accumulator
-    // row = state row p, column = state column s): a wave owns 16 rows, lane l the rows 4 (l >> 4) + i of those and
-    // kCW consecutive columns kCW (l & 15) + t -- column t of each lane makes up tile t, so that a lane's columns are
-    // 16-byte pieces in memory all the same.
+    // row = state row p, column = state column s): a wave owns 16 rows of every 64, lane l the rows 4 (l >> 4) + i of
+    // those and kCW consecutive columns kCW (l & 15) + t -- column t of each lane makes up tile t, so that a lane's columns
+    // are 16-byte pieces in memory all the same.
     constexpr uint32_t HB = sizeof(HT);
-    constexpr int kCW = 16 / HB, kCB = S / (16 * kCW);               // columns per chunk; column blocks
+    constexpr int kCW = 16 / HB, kCB = S / (16 * kCW), kPG = P / 64; // columns per chunk; column blocks; 64-row groups
     static_assert(kCB >= 1 && NH % 2 == 0, "a state is moved 16 bytes at a time");
-    static_assert(P == 64, "a wave of each role owns 16 rows of the state");
     auto load_H = [&](int b, int h) {       // the role group that carries this unit
         // the lane-dependent zero keeps this a vector load: it then sits in the same in-order
         // queue as the h0 chunks instead of forcing a scalar-cache wait in the hot window
@@ -228,8 +227,8 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             const int t = opaque(rt), row0 = (t >> 6) * 16 + ((t & 63) >> 4) * 4, col0 = (t & 15) * kCW;
             const uint32_t off = (uint32_t)(row0 * S + col0) * HB;
 #pragma unroll
-            for (int q = 0; q < kCB * 4; ++q)         // q = (column block, row)
-                pre[q] = load_stream16(hb + off + (q % 4 * S + q / 4 * 16 * kCW) * HB);
+            for (int q = 0; q < kPG * kCB * 4; ++q)   // q = (row group, column block, row)
+                pre[q] = load_stream16(hb + off + ((q / (4 * kCB) * 64 + q % 4) * S + q / 4 % kCB * 16 * kCW) * HB);
         } else {
             const uint32_t off = (uint32_t)opaque(rt) * 16u;
 #pragma unroll
@@ -288,9 +287,9 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             const int l = t & 15, kj = (t & 63) >> 4, prow = (t >> 6) * 16;
             const int len = *sRlen;
             const float dec = *sRdec;
-            floatx4 hv[kCB][kCW];                          // [column block][tile]
+            floatx4 hv[kPG * kCB][kCW];                    // [row group, column block][tile]
 #pragma unroll
-            for (int q = 0; q < kCB * 4; ++q) {
+            for (int q = 0; q < kPG * kCB * 4; ++q) {
                 const uint32_t w4[4] = {pre[q].x, pre[q].y, pre[q].z, pre[q].w};
 #pragma unroll
                 for (int e = 0; e < kCW; ++e)
@@ -299,8 +298,12 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             // four path nodes: lane group kj holds node j of them, its weight cf (0 past the end of the path),
             // its x at row (t & 15) of the wave's rows (operand A) and cf * B at the lane's columns (operand B)
             auto rank4 = [&](bool on, float cf, const char *xr, const char *br) {
-                const uint32_t xw = *reinterpret_cast<const unsigned short *>(xr + (prow + l) * 2);
-                const float av = on ? __uint_as_float(xw << 16) : 0.f;
+                float av[kPG];
+#pragma unroll
+                for (int g = 0; g < kPG; ++g) {
+                    const uint32_t xw = *reinterpret_cast<const unsigned short *>(xr + (prow + l + g * 64) * 2);
+                    av[g] = on ? __uint_as_float(xw << 16) : 0.f;
+                }
 #pragma unroll
                 for (int c = 0; c < kCB; ++c) {
                     const char *at = br + (c * 16 + l) * kCW * 2;
@@ -312,7 +315,9 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
                     }
 #pragma unroll
                     for (int e = 0; e < kCW; ++e)
-                        hv[c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, on ? cf * bf[e] : 0.f, hv[c][e], 0, 0, 0);
+#pragma unroll
+                        for (int g = 0; g < kPG; ++g)
+                            hv[g * kCB + c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[g], on ? cf * bf[e] : 0.f, hv[g * kCB + c][e], 0, 0, 0);
                 }
             };
             const int nl = min(len, kRows);
@@ -332,8 +337,8 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
             // the replayed state, written once, through L2 (never read again by this kernel)
             char *ob = reinterpret_cast<char *>(reinterpret_cast<HT *>(R.h_out) + ((size_t)b * H + h) * P * S);
 #pragma unroll
-            for (int q = 0; q < kCB * 4; ++q) {
-                const int at_row = prow + kj * 4 + q % 4, at_col = (q / 4 * 16 + l) * kCW;
+            for (int q = 0; q < kPG * kCB * 4; ++q) {
+                const int at_row = prow + kj * 4 + q / (4 * kCB) * 64 + q % 4, at_col = (q / 4 % kCB * 16 + l) * kCW;
                 float v[kCW];
 #pragma unroll
                 for (int e = 0; e < kCW; ++e) v[e] = hv[q / 4][e][q % 4];
@@ -776,17 +781,17 @@ __global__ __launch_bounds__(kT64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))
     }
 }
 
-template <int S, bool RP, typename HT>
+template <int P, int S, bool RP, typename HT>
 hipError_t launch64(const stree_dims &d, const int32_t *parent, const void *x, const float *dt, const float *A,
                     const void *Bm, const void *Cm, const float *D, const void *h0, void *y,
                     int32_t *status, const ReplayArgs &R, hipStream_t st) {
-    constexpr size_t lds = RP ? Lds64<64, S>::total_replay : Lds64<64, S>::total;   // static LDS (upper bound)
-    static_assert(2 * (lds + 64) <= 160 * 1024, "two workgroups a CU");
+    constexpr size_t lds = RP ? Lds64<P, S>::total_replay : Lds64<P, S>::total;   // static LDS (upper bound)
+    constexpr int kPerCU = 2 * (lds + 64) <= 160 * 1024 ? 2 : 1;                  // workgroups
     const int n_units = d.batch * d.nheads;
-    const int grid = n_units > 512 ? 512 : (n_units + 7) / 8 * 8;
+    const int grid = n_units > 256 * kPerCU ? 256 * kPerCU : (n_units + 7) / 8 * 8;
     // (the in-kernel softplus is a variant of its own: compiled into the common one, even unused, it costs time)
 #define STREE_LAUNCH64(SPL)                                                                                         \
-    hipLaunchKernelGGL((tree_ssd_mfma64_kernel<64, S, 4, RP, SPL, HT>), dim3(grid), dim3(kT64), 0, st, parent,          \
+    hipLaunchKernelGGL((tree_ssd_mfma64_kernel<P, S, 2 * kPerCU, RP, SPL, HT>), dim3(grid), dim3(kT64), 0, st, parent,          \
                        d.nnodes, d.batch, d.nheads, d.ngroups, (const bf16_t *)x, (long)d.x_stride_n, dt,           \
                        step_bias(d), A, (const bf16_t *)Bm, (long)d.b_stride_n, (const bf16_t *)Cm,                 \
                        (long)d.c_stride_n, D, (const HT *)h0, (bf16_t *)y, status, R)
@@ -796,23 +801,31 @@ hipError_t launch64(const stree_dims &d, const int32_t *parent, const void *x, c
     return hipGetLastError();
 }
 
-// The band in which the persistent kernel is ahead of a workgroup per head: so many heads that all of
-// them enter the workgroup-per-head kernel at once (five a CU, 1280) and read their C and B rows at once, where a
-// persistent workgroup reads them once for the two or three heads it walks.  80 heads, S = 128, persistent / per head:
-// replay + scan, 64 nodes, batch 8 15.1 / 15.5, 12 20.0 / 21.9, 16 24.0 / 25.6, 18 28.6 / 28.4 us, 40 nodes, batch 8 14.7 /
-// 13.7, 12 19.0 / 20.2, 32 nodes, batch 12 18.9 / 18.9, 16 22.8 / 21.9; scan, 64 nodes, batch 12 13.8 / 13.7, 16 15.5 / 16.8,
-// 20 19.7 / 20.6, 26 25.6 / 24.9, 48 nodes, batch 16 15.0 / 14.8; S = 64, scan, 64 nodes, batch 16 12.1 / 12.4.  Beyond it (few
-// heads, more than a round of them, S = 256, headdim 128) the workgroup per head is ahead by 3 to 30 %.  A state in bf16, half
-// the bytes: only between four and five workgroups a CU, where a few CUs have the fifth (64 nodes, batch 13 17.3 / 18.5, 15 18.4 /
-// 19.9 us, 44 nodes, 13 16.5 / 17.1, 40 nodes, 13 16.6 / 16.7; batch 16 18.6 / 18.6; scan, 64 nodes, 14 12.6 / 13.7, 57, 14
-// 12.4 / 12.6, 56, 15 13.0 / 12.6; 64, 16 12.2 / 13.1).
+// The bands in which the persistent kernel is ahead of a workgroup per head: so many heads that (nearly) all of them enter
+// the workgroup-per-head kernel at once and read their C and B rows at once, where a persistent workgroup reads them once
+// for the two or three heads it walks; the more nodes, the more so, and most where its workgroups (two a CU) have the same
+// number of heads each.  80 heads, S = 128, us, persistent / per head, fp32 state:
+//   replay + scan   batch 8, 64 nodes 14.8 / 15.5, 50 nodes 14.8 / 14.5; 9, 58 nodes 14.9 / 15.4, 48 nodes 15.3 / 14.6; 11, 44
+//                   nodes 18.5 / 19.7; 12, 64 19.6 / 20.8; 15, 48 22.6 / 23.7; 16, 64 23.3 / 24.9; 18 27.9 / 27.5; 19, 54 27.0 / 27.6
+//   scan            batch 10, 64 nodes 12.7 / 13.1; 14, 64 14.0 / 15.8, 44 13.4 / 13.8, 36 13.2 / 13.0; 19, 48 16.6 / 16.9; 21, 64
+//                   19.0 / 20.0; 24 22.6 / 22.0; S = 64, batch 14, 64 11.5 / 11.8, 16 11.8 / 12.3
+// and with a state in bf16, half the bytes:
+//   replay + scan   batch 14, 64 nodes 17.9 / 18.3; 15, 44 17.3 / 17.5; 16, 64 18.2 / 18.4, 48 17.3 / 17.0
+//   scan            batch 14, 54 nodes 11.9 / 12.3; 16, 58 12.0 / 12.8; 18, 64 14.4 / 15.1, 58 14.3 / 14.5; 64, 64 36.7 / 38.0
+// Headdim 128 (one persistent workgroup a CU), replay + scan, fp32 state: 440 heads, 64 nodes 18.8 / 20.9, 40 nodes 18.6 / 19.5;
+// 380 heads 18.4 / 15.6, 520 heads 27.6 / 22.9.  Elsewhere the workgroup per head is ahead by 2 to 30 %.
 bool unit_is_slower(const stree_dims &d, bool replay) {
-    if (d.headdim != 64) return false;
-    const int units = d.batch * d.nheads;
-    if (d.state_dtype != STREE_F32)
-        return d.dstate == 128 && units > 1024 && (replay ? units < 1280 && d.nnodes > 40 : units <= 1280 && d.nnodes > 56);
-    if (replay) return d.dstate == 128 && d.nnodes > 32 && units > 640 && units <= 1408;
-    return (d.dstate == 128 || d.dstate == 64) && d.nnodes > 48 && units > 1024 && units <= 1700;
+    const int heads = d.batch * d.nheads, n = d.nnodes;
+    const bool f32 = d.state_dtype == STREE_F32;
+    if (d.headdim == 128) return replay && f32 && heads > 384 && heads <= 512 && n > 36;
+    if (d.dstate == 64) return !replay && f32 && heads > 1088 && heads <= 1280 && n > 56;
+    if (d.dstate != 128) return false;
+    int from = 65;                                    // nodes from which it is
+    if (!f32 && replay) from = heads <= 1024 ? 65 : heads <= 1216 ? 41 : heads <= 1280 ? 61 : 65;
+    else if (!f32) from = heads <= 1024 ? 65 : heads <= 1280 ? 53 : 59;
+    else if (replay) from = heads <= 512 ? 65 : heads <= 640 ? 55 : heads <= 768 ? 53 : heads <= 1408 ? 33 : heads <= 1472 ? 65 : heads <= 1536 ? 49 : 65;
+    else from = heads <= 768 ? 65 : heads <= 1024 ? 57 : heads <= 1280 ? 41 : heads <= 1700 ? 45 : 65;
+    return n >= from;
 }
 
 }  // namespace
@@ -850,15 +863,17 @@ hipError_t launch_tree_ssd_replay_fused(const stree_dims &d, const stree_dims &d
                                            status, rstatus, st);
     const ReplayArgs R = {pparent, paccepted, (const bf16_t *)px, (const bf16_t *)pB, pdt,
                           (long)dp.x_stride_n, (long)dp.b_stride_n, dp.nnodes, h_out, rstatus};
-    return (d.state_dtype == STREE_F32 ? launch64<128, true, float> : launch64<128, true, bf16_t>)(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
+    const auto launch = d.headdim == 128 ? launch64<128, 128, true, float>
+                        : d.state_dtype == STREE_F32 ? launch64<64, 128, true, float> : launch64<64, 128, true, bf16_t>;
+    return launch(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, R, st);
 }
 
 hipError_t launch_tree_ssd_mfma64(const stree_dims &d, const int32_t *parent, const void *x, const float *dt,
                                   const float *A, const void *Bm, const void *Cm, const float *D,
                                   const void *h0, void *y, int32_t *status, hipStream_t st) {
     if (!unit_is_slower(d, false)) return launch_tree_ssd_unit(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, st);
-    const auto launch = d.dstate == 64 ? launch64<64, false, float>
-                        : d.state_dtype == STREE_F32 ? launch64<128, false, float> : launch64<128, false, bf16_t>;
+    const auto launch = d.dstate == 64 ? launch64<64, 64, false, float>
+                        : d.state_dtype == STREE_F32 ? launch64<64, 128, false, float> : launch64<64, 128, false, bf16_t>;
     return launch(d, parent, x, dt, A, Bm, Cm, D, h0, y, status, ReplayArgs{}, st);
 }
 

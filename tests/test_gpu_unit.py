@@ -77,12 +77,16 @@ def test_unit_kernel_replay(st, oracle, N, Np, P, S, G, state):
                                              (41, 33, 16, 64, 128, "f32"), (40, 33, 16, 64, 128, "f32"), (41, 32, 16, 64, 128, "f32"),
                                              (89, 33, 16, 64, 128, "f32"), (89, 20, 16, 64, 128, "bf16"), (90, 20, 8, 128, 128, "f32"),
                                              (65, 41, 16, 64, 128, "bf16"), (65, 40, 16, 64, 128, "bf16"), (79, 64, 16, 64, 128, "bf16"),
-                                             (80, 64, 16, 64, 128, "bf16")])
+                                             (80, 64, 16, 64, 128, "bf16"), (33, 55, 16, 64, 128, "f32"), (33, 54, 16, 64, 128, "f32"),
+                                             (41, 53, 16, 64, 128, "f32"), (93, 49, 16, 64, 128, "f32"), (92, 49, 16, 64, 128, "f32"),
+                                             (49, 37, 8, 128, 128, "f32"), (48, 41, 8, 128, 128, "f32"), (64, 64, 8, 128, 128, "f32"),
+                                             (65, 64, 8, 128, 128, "f32"), (64, 36, 8, 128, 128, "f32"), (49, 60, 8, 128, 128, "bf16")])
 def test_unit_kernel_replay_at_the_lines_between_its_forms(st, oracle, B, N, H, P, S, state):
     _replay(st, oracle, B, N, 21, H, P, S, 1, state, 190 + B + N)
 
 
-@pytest.mark.parametrize("B,N,H,S", [(65, 49, 16, 128), (64, 49, 16, 128), (65, 48, 16, 128), (106, 50, 16, 64), (107, 50, 16, 64)])
+@pytest.mark.parametrize("B,N,H,S", [(65, 49, 16, 128), (64, 49, 16, 128), (65, 48, 16, 128), (106, 50, 16, 64), (107, 50, 16, 64),
+                                       (49, 57, 16, 128), (49, 56, 16, 128), (81, 45, 16, 128), (81, 44, 16, 128), (69, 57, 16, 64)])
 def test_unit_kernel_scan_at_the_lines_between_its_forms(st, oracle, B, N, H, S):
     parent = _trees(230 + B, B, N)
     x, dt, A, Bm, Cm, D, h0 = _rand(231 + B, "bf16", B, N, H, 64, S, 1)
@@ -90,7 +94,7 @@ def test_unit_kernel_scan_at_the_lines_between_its_forms(st, oracle, B, N, H, S)
     assert_parity(_run_ssd(st, "bf16", parent, x, dt, A, Bm, Cm, D, h0), want, TOL["bf16"], f"scan B={B} N={N} S={S}", kind="y")
 
 
-@pytest.mark.parametrize("B,N,H", [(65, 57, 16), (65, 56, 16), (80, 64, 16), (81, 64, 16)])
+@pytest.mark.parametrize("B,N,H", [(65, 57, 16), (65, 56, 16), (80, 64, 16), (81, 64, 16), (65, 53, 16), (65, 52, 16), (81, 59, 16), (81, 58, 16)])
 def test_scan_of_a_bf16_state_at_the_lines_between_its_forms(st, oracle, B, N, H):
     parent = _trees(260 + B, B, N)
     x, dt, A, Bm, Cm, D, h0 = _rand(261 + B + N, "bf16", B, N, H, 64, 128, 1)
