@@ -487,10 +487,12 @@ hipError_t launch_unit_s(const stree_dims &d, const int32_t *parent, const void 
     using L = UnitLds<S, RP>;
     constexpr int kMost = S == 256 ? 3 : 5, WPE = L::per_cu < kMost ? L::per_cu : kMost;   // waves per SIMD
     const int units = d.batch * d.nheads * (d.headdim / kPC);
-    // More heads than are resident at once: the workgroups of a CU are then at different places of their chains, and the
-    // small requests of one need not stand behind the state of another (64 x 64 nodes x 80 heads, fp32 state, 81.6 -> 79.0 us,
-    // bf16 56.9 -> 55.3; 16 x 64 25.6 either way; few heads wait for the state: 4 x 29 nodes 8.9 -> 10.0 us).
-    const bool late = RP && units > 1408;
+    // More heads than are resident at once (five a CU, 1280) and two blocks of nodes: the workgroups of a CU are then at
+    // different places of their chains, and the small requests of one need not stand behind the state of another.  Early /
+    // late, us, fp32 state, S = 128: 64 nodes x 5120 heads 81.6 / 79.0 (bf16 56.9 / 55.3), 40 x 1440 26.7 / 25.8, 1280 22.9 / 23.3;
+    // one block waits for the state alone: 16 x 1440 23.3 / 23.7, S = 64 14.2 / 15.8, bf16, S = 128, 16 x 1600 17.0 / 18.6; few heads
+    // do at any size (4 x 29 nodes x 80 heads 8.9 / 10.0).  S = 256, where three are resident: even from 1280 to 2560 heads.
+    const bool late = RP && units > 1408 && d.nnodes > kRB;
 #define STREE_LAUNCH_UNIT(LATE, HT)                                                                                       \
     hipLaunchKernelGGL((tree_ssd_unit_kernel<S, WPE, RP, RP && LATE, HT>), dim3(8 * ((units + 7) / 8)), dim3(256), 0, st,       \
                        parent, d.nnodes, units, Divisor(d.nheads), Divisor(d.nheads / d.ngroups), d.headdim,        \

@@ -80,7 +80,9 @@ def test_unit_kernel_replay(st, oracle, N, Np, P, S, G, state):
                                              (80, 64, 16, 64, 128, "bf16"), (33, 55, 16, 64, 128, "f32"), (33, 54, 16, 64, 128, "f32"),
                                              (41, 53, 16, 64, 128, "f32"), (93, 49, 16, 64, 128, "f32"), (92, 49, 16, 64, 128, "f32"),
                                              (49, 37, 8, 128, 128, "f32"), (48, 41, 8, 128, 128, "f32"), (64, 64, 8, 128, 128, "f32"),
-                                             (65, 64, 8, 128, 128, "f32"), (64, 36, 8, 128, 128, "f32"), (49, 60, 8, 128, 128, "bf16")])
+                                             (65, 64, 8, 128, 128, "f32"), (64, 36, 8, 128, 128, "f32"), (49, 60, 8, 128, 128, "bf16"), (89, 32, 16, 64, 64, "f32"),
+                                             (89, 33, 16, 64, 256, "f32"), (89, 33, 16, 64, 256, "bf16"), (89, 33, 8, 128, 128, "bf16"),
+                                             (90, 34, 8, 128, 128, "f32")])
 def test_unit_kernel_replay_at_the_lines_between_its_forms(st, oracle, B, N, H, P, S, state):
     _replay(st, oracle, B, N, 21, H, P, S, 1, state, 190 + B + N)
 
