@@ -2,6 +2,8 @@
 entry point, and that no argument of a call is lost on its way to the native half."""
 import ctypes as C
 import inspect
+import os
+import re
 
 import numpy as np
 import pytest
@@ -168,17 +170,34 @@ def test_a_torch_function_mode_sees_the_calls(nothing_launched):
     assert {"data_ptr", "empty_like", "is_contiguous"} <= seen
 
 
+# host.cpp's short names of arguments
+SHORT = {"pparent": "prev_parent", "paccepted": "prev_accepted", "px": "prev_x", "pdt": "prev_dt", "pBm": "prev_Bm",
+         "pxbc_pre": "prev_xbc_pre", "pxbc_out": "prev_xbc_out", "rstatus": "replay_status"}
+
+
+def _native_order():
+    """Per entry point the arguments in the order in which host.cpp numbers them, and how many it says it takes."""
+    with open(os.path.join(os.path.dirname(os.path.abspath(st.__file__)), "csrc", "host.cpp")) as f:
+        text = f.read()
+    order = {}
+    for name, function, count in re.findall(r'STREE_METHOD\("(\w+)", (\w+), (\d+)\)', text):
+        body = re.search(r"PyObject \*%s\(PyObject \*const \*a\) \{\s*enum \{([^}]*)\}" % function, text).group(1)
+        order["stree_" + name] = ([SHORT.get(n, n) for n in re.findall(r"\w+", body)], int(count))
+    return order
+
+
 def test_every_argument_reaches_the_native_half():
-    """The functions pass their arguments by position: each by its own name, none twice, as many as the other side takes."""
+    """The functions pass their arguments by position: each at the place, and as many, as the other side reads."""
     class Seen:
         def __getattr__(self, entry):
             return lambda *args: args
+    order = _native_order()
+    assert sorted(order) == sorted(_good())
     kept, st._host = st._native(), Seen()
     try:
-        for name in _good():
+        for name, (names, count) in order.items():
             f = getattr(st, name)
-            names = list(inspect.signature(f).parameters)
-            passed = f(**{n: n for n in names})
-            assert sorted(passed) == sorted(names), name
+            passed = f(**{n: n for n in inspect.signature(f).parameters})
+            assert list(passed) == names and len(passed) == count, name
     finally:
         st._host = kept

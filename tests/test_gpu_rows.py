@@ -48,7 +48,7 @@ def test_rows_kernel_large_values_and_positive_exponents(st, oracle, N):
 
 @pytest.mark.parametrize("N,Np", [(65, 1), (66, 64), (96, 65), (100, 17), (128, 128), (128, 256), (81, 200)])
 @pytest.mark.parametrize("P,S,G,state", [(64, 128, 1, "f32"), (64, 64, 2, "bf16"), (64, 256, 1, "f32"), (128, 128, 2, "bf16"),
-                                         (64, 64, 1, "f32"), (64, 128, 2, "bf16")])
+                                         (64, 64, 1, "f32"), (64, 128, 2, "bf16"), (64, 256, 1, "bf16"), (128, 128, 2, "f32")])
 def test_replay_inside_the_rows_kernel(st, oracle, N, Np, P, S, G, state):
     """The state advanced inside the scan of a tree of 65 .. 128 nodes: accepted paths of one node, of more rows than are
     held at once (16), of more than a wave's lanes (64), none, and a previous tree that is refused."""
