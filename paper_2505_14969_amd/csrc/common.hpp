@@ -208,13 +208,6 @@ __device__ __forceinline__ void store_through16(void *p, uint4 v) {
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" ::"v"(p), "v"(vv) : "memory");
 }
 
-// The 8-byte form (a state kept in bf16).  A store of at most 8 bytes needs no wait states behind it.
-__device__ __forceinline__ void store_through8(void *p, uint2 v) {
-    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-    const u32x2 vv = {v.x, v.y};
-    asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1 nt" ::"v"(p), "v"(vv) : "memory");
-}
-
 // The same store as a raw buffer store, the cache bits riding on an instruction the compiler knows.
 // (The compiler's wait-count pass treats the operand registers of inline assembly as if a memory
 // operation of unknown age still read them: the next write to any of them -- they are ordinary

@@ -132,30 +132,18 @@ __global__ __launch_bounds__(64 * NR) __attribute__((amdgpu_waves_per_eu(WPE, WP
     request(xr, xb, (int)x_sn, tid / 8, tid % 8, kRowsX);
     __builtin_amdgcn_sched_barrier(0);
     // The state, used behind the last phase: it streams in while the products are formed.  With the replay it lies in
-    // the registers as the accumulators of the fp32 matrix instructions that advance it (16 x 16 x 4, accumulator row =
-    // state row p, column = state column s): a wave owns 16 rows, lane l the rows 4 (l >> 4) + i of those and kCW
-    // consecutive columns kCW (l & 15) + t -- column t of each lane makes up tile t, so that a lane's columns are
-    // 16-byte pieces in memory (8 bytes for a bf16 state of 64 columns).
-    constexpr int kCW = (sizeof(HT) == 2 && S % 128 == 0) ? 8 : 4, kCols = S / (16 * kCW);      // columns per piece; column blocks
-    constexpr int kHB = kCW * (int)sizeof(HT), NHR = RP ? 4 * kCols : NH;
+    // the registers as the tiles that advance it, else as whole rows.
+    using Tiles = StateTiles<S, HT>;
+    constexpr int NHR = RP ? Tiles::kPieces : NH;
     u32x4 hr[NHR];
     auto request_state = [&]() {   // (a buffer, empty without a state: no branch that the registers would have to agree behind)
         const auto hbuf = make_buffer(h0 + ((size_t)bh * P + p0) * S, h0 ? (size_t)kPC * S * sizeof(HT) : 0);
         const int t = (int)fresh(tid);
+        if constexpr (RP) {
+            Tiles::request(hr, hbuf, (t >> 6) * 16 + ((t & 63) >> 4) * 4, t & 15);
+        } else {
 #pragma unroll
-        for (int q = 0; q < NHR; ++q) {
-            if constexpr (!RP) {
-                hr[q] = __builtin_amdgcn_raw_buffer_load_b128(hbuf, (q * T + t) * 16, 0, 2);   // nt
-            } else {
-                const int at = (((t >> 6) * 16 + ((t & 63) >> 4) * 4 + q % 4) * S + (q / 4 * 16 + (t & 15)) * kCW) * (int)sizeof(HT);
-                if constexpr (kHB == 16) {
-                    hr[q] = __builtin_amdgcn_raw_buffer_load_b128(hbuf, at, 0, 2);
-                } else {
-                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(hbuf, at, 0, 2);
-                    hr[q].x = v.x;
-                    hr[q].y = v.y;
-                }
-            }
+            for (int q = 0; q < NHR; ++q) hr[q] = __builtin_amdgcn_raw_buffer_load_b128(hbuf, (q * T + t) * 16, 0, 2);   // nt
         }
     };
     // ---- the tree's index (Sec. 3: depth-ordered packing, Eq. a_tree), in log2 units ---------------------------
@@ -317,30 +305,14 @@ __global__ __launch_bounds__(64 * NR) __attribute__((amdgpu_waves_per_eu(WPE, WP
     __syncthreads();
 
     // ---- replay: the first rows of the path --------------------------------------------------------------------
-    constexpr int PX = kPC / 8, PR = PX + kPieces;    // 16-byte pieces of a path node's x row; of both
-    constexpr int NP = (L::kPath * PR + T - 1) / T;
-    u32x4 pr[NP];
+    using Path = PathRows<S, T, L::kPath, false>;
+    u32x4 pr[Path::kPieces];
     [[maybe_unused]] auto request_path = [&](int first) {
-        const int total = min(plen - first, L::kPath) * PR;
         const char *xb = reinterpret_cast<const char *>(R.x + (size_t)b * R.pn * R.x_sn + (size_t)h * P + p0);
         const char *Bp = reinterpret_cast<const char *>(R.Bm + (size_t)b * R.pn * R.b_sn + (size_t)g * S);
-        const int t = (int)fresh(tid);
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {                // (clamped: the last piece again past the end)
-            const int idx = min(q * T + t, total - 1), c = idx % PR, node = lds_at<unsigned char>(base + L::node + first + idx / PR);
-            pr[q] = *reinterpret_cast<const u32x4 *>(c < PX ? xb + (uint32_t)(node * (int)R.x_sn + c * 8) * 2u
-                                                            : Bp + (uint32_t)(node * (int)R.b_sn + (c - PX) * 8) * 2u);
-        }
+        Path::request(pr, R, xb, Bp, base + L::node + first, plen - first, fresh(tid));
     };
-    [[maybe_unused]] auto stage_path = [&](int first) {
-        const int total = min(plen - first, L::kPath) * PR;
-        const int t = (int)fresh(tid);
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            const int idx = q * T + t, c = idx % PR, at = idx / PR;
-            if (idx < total) lds_at<u32x4>(base + L::rows + (c < PX ? at * kPC + c * 8 : L::kPath * kPC + at * S + (c - PX) * 8) * 2) = pr[q];
-        }
-    };
+    [[maybe_unused]] auto stage_path = [&](int first) { Path::stage(pr, base + L::rows, plen - first, fresh(tid)); };
     if constexpr (RP) {
         if (plen > 0) request_path(0);
     }
@@ -413,29 +385,9 @@ __global__ __launch_bounds__(64 * NR) __attribute__((amdgpu_waves_per_eu(WPE, WP
                 if (kk + kAhead < NK) bo[kk % kAhead] = lds_at<bf16x8>(b_at ^ ((kk + kAhead) << 5));
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // bit 8(r/4) + r%4 of `word` <-> Gt's register r
             const uint32_t word = lds_at<uint32_t>(mask_at + J * (kNodes * 4)) >> (4 * lh), u_at = fresh(base + L::u + 16 * lh + J * (kRB * 4));
             u32x4 m[2];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 u = lds_at<f32x4>(u_at + 8 * q * 4);
-                float v[4];
-                f32x4 f;
-                if (wide) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) f[e] = __builtin_amdgcn_exp2f(s2_i - u[e]);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) f[e] = e_i * u[e];
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e)           // bitwise select: an overflow under a cleared mask bit never reaches M
-                    v[e] = __uint_as_float(__float_as_uint(gt[4 * q + e] * f[e]) & bit_as_mask(word, 8 * q + e));
-                m[q / 2][2 * (q % 2)] = pack2(v[0], v[1]);
-                m[q / 2][2 * (q % 2) + 1] = pack2(v[2], v[3]);
-                // (formed here: the compiler would put all of this off to the end, behind the branches, and keep f until then)
-                asm volatile("" : "+v"(m[q / 2][2 * (q % 2)]), "+v"(m[q / 2][2 * (q % 2) + 1]));
-            }
+            weigh(m, gt, word, u_at, s2_i, e_i, wide);
             const uint32_t x_at = fresh(x_lane + J * (kRB * 64));
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
@@ -456,13 +408,8 @@ __global__ __launch_bounds__(64 * NR) __attribute__((amdgpu_waves_per_eu(WPE, WP
     if constexpr (RP) {
         const int l = ft & 15, kj = (ft & 63) >> 4, prow = (ft >> 6) * 16;
         if (plen > 0) dec = lds_at<float>(base + L::pbad + 16);
-        floatx4 hv[kCols][kCW];                       // [column block][tile]
-#pragma unroll
-        for (int q = 0; q < NHR; ++q)
-#pragma unroll
-            for (int e = 0; e < kCW; ++e)
-                hv[q / 4][e][q % 4] = dec * (sizeof(HT) == 4 ? __uint_as_float(hr[q][e % 4])
-                                             : (e & 1) ? bf16_hi(hr[q][e / 2]) : bf16_lo(hr[q][e / 2]));
+        typename Tiles::Values hv;
+        Tiles::widen(hv, hr, dec);
         for (int first = 0; first < plen; first += L::kPath) {
             if (first > 0) {                          // longer paths: the next rows, one round trip for sixteen
                 request_path(first);
@@ -470,66 +417,12 @@ __global__ __launch_bounds__(64 * NR) __attribute__((amdgpu_waves_per_eu(WPE, WP
                 stage_path(first);
                 __syncthreads();
             }
-            // four path nodes a turn: lane group kj holds node j of them, its weight (0 past the end of the path), its x
-            // at row l of the wave's rows (operand A) and weight * B at the lane's columns (operand B)
-            const int nl = min(plen - first, L::kPath);
-            for (int j0 = 0; j0 < nl; j0 += 4) {
-                const bool on = j0 + kj < nl;
-                const int j = min(j0 + kj, nl - 1);
-                const float cf_j = lds_at<float>(base + L::weight + (first + j) * 4);
-                const uint32_t xw = lds_at<unsigned short>(base + L::rows + (j * kPC + prow + l) * 2);
-                const float av = on ? __uint_as_float(xw << 16) : 0.f;
-#pragma unroll
-                for (int c = 0; c < kCols; ++c) {
-                    uint32_t bw[kCW / 2];
-#pragma unroll
-                    for (int w = 0; w < kCW / 2; w += 2) {
-                        const u32x2 v = lds_at<u32x2>(base + L::rows + (L::kPath * kPC + j * S + (c * 16 + l) * kCW + 2 * w) * 2);
-                        bw[w] = v.x;
-                        bw[w + 1] = v.y;
-                    }
-#pragma unroll
-                    for (int e = 0; e < kCW; ++e) {
-                        const float bv = on ? cf_j * ((e & 1) ? bf16_hi(bw[e / 2]) : bf16_lo(bw[e / 2])) : 0.f;
-                        hv[c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, hv[c][e], 0, 0, 0);
-                    }
-                }
-            }
+            Tiles::template advance<false>(hv, base + L::rows, L::kPath, base + L::weight + first * 4, min(plen - first, L::kPath), prow, l, kj);
         }
-        // the replayed state, written once (never read again by this kernel); a bf16 state is rounded once: the value
-        // written back is the operand
         const auto ho = make_store_rsrc(reinterpret_cast<HT *>(R.h_out) + ((size_t)bh * P + p0) * S, (uint32_t)(kPC * S * sizeof(HT)));
-#pragma unroll
-        for (int q = 0; q < NHR; ++q) {
-            const int row = prow + kj * 4 + q % 4, col = (q / 4 * 16 + l) * kCW;
-            uint32_t w[kCW / 2];
-#pragma unroll
-            for (int e = 0; e < kCW; e += 2) w[e / 2] = pack2(hv[q / 4][e][q % 4], hv[q / 4][e + 1][q % 4]);
-            const uint32_t dst = (uint32_t)(row * S + col) * (uint32_t)sizeof(HT);
-            const uint32_t op = base + L::bm + piece_at<S>(row, col / 8);
-            if constexpr (sizeof(HT) == 4)
-                buffer_store_through16(ho, dst, make_uint4(__float_as_uint(hv[q / 4][0][q % 4]), __float_as_uint(hv[q / 4][1][q % 4]),
-                                                           __float_as_uint(hv[q / 4][2][q % 4]), __float_as_uint(hv[q / 4][3][q % 4])));
-            if constexpr (kCW == 8) {
-                buffer_store_through16(ho, dst, make_uint4(w[0], w[1], w[2], w[3]));
-                lds_at<u32x4>(op) = u32x4{w[0], w[1], w[2], w[3]};
-            } else {
-                if constexpr (sizeof(HT) == 2)
-                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{w[0], w[1]}, ho, (int)dst, 0, 1 | 2 | 16);
-                lds_at<u32x2>(op + (col & 4) * 2) = u32x2{w[0], w[1]};
-            }
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < (RP ? 0 : NH); ++q) {
-        if constexpr (sizeof(HT) == 4) {
-            const int e = (q * T + ft) * 4;
-            lds_at<u32x2>(base + L::bm + piece_at<S>(e / S, e % S / 8) + (e & 4) * 2) =
-                u32x2{pack2(__uint_as_float(hr[q].x), __uint_as_float(hr[q].y)), pack2(__uint_as_float(hr[q].z), __uint_as_float(hr[q].w))};
-        } else {                                      // a bf16 state is the operand as it comes
-            const int e = (q * T + ft) * 8;
-            lds_at<u32x4>(base + L::bm + piece_at<S>(e / S, e % S / 8)) = hr[q];
-        }
+        Tiles::store(hv, ho, base + L::bm, prow + kj * 4, l);
+    } else {
+        stage_state<S, T, HT>(hr, base + L::bm, ft);
     }
     __syncthreads();
     if (RP && bad) {

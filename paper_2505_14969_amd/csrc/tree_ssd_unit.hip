@@ -97,29 +97,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
     request(rr, rows_of(Cm + (size_t)g * S, c_sn, S), (int)c_sn, t_row, t_piece, kStep);      // whole rows to consecutive lanes
     request(xr, rows_of(x + (size_t)h * P + p0, x_sn, kPC), (int)x_sn, tid / 8, tid % 8, 32);
     __builtin_amdgcn_sched_barrier(0);
-    // The state.  With the replay it lies in the registers as the accumulators of the fp32 matrix instructions that advance
-    // it (16 x 16 x 4, accumulator row = state row p, column = state column s): a wave owns 16 rows, lane l the rows
-    // 4 (l >> 4) + i of those and kCW consecutive columns kCW (l & 15) + t -- column t of each lane makes up tile t, so
-    // that a lane's columns are 16-byte pieces in memory (8 bytes for a bf16 state of 64 columns).
-    constexpr int kCW = (sizeof(HT) == 2 && S % 128 == 0) ? 8 : 4, kCols = S / (16 * kCW);      // columns per piece; column blocks
-    constexpr int kHB = kCW * (int)sizeof(HT), NHR = RP ? 4 * kCols : NH;
+    // The state: with the replay as the tiles that advance it, else as whole rows.
+    using Tiles = StateTiles<S, HT>;
+    constexpr int NHR = RP ? Tiles::kPieces : NH;
     u32x4 hr[NHR];
     auto request_state = [&]() {   // (a buffer, empty without a state: no branch that the registers would have to agree behind)
         const auto hbuf = make_buffer(h0 + (uint64_t)(uint32_t)bh * (uint32_t)(P * S) + (uint32_t)(p0 * S), h0 ? (size_t)kPC * S * sizeof(HT) : 0);
+        if constexpr (RP) {
+            Tiles::request(hr, hbuf, wave * 16 + (lane >> 4) * 4, lane & 15);
+        } else {
 #pragma unroll
-        for (int q = 0; q < NHR; ++q) {
-            if constexpr (!RP) {
-                hr[q] = __builtin_amdgcn_raw_buffer_load_b128(hbuf, (q * 256 + tid) * 16, 0, 2);   // nt
-            } else {
-                const int at = ((wave * 16 + (lane >> 4) * 4 + q % 4) * S + (q / 4 * 16 + (lane & 15)) * kCW) * (int)sizeof(HT);
-                if constexpr (kHB == 16) {
-                    hr[q] = __builtin_amdgcn_raw_buffer_load_b128(hbuf, at, 0, 2);
-                } else {
-                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(hbuf, at, 0, 2);
-                    hr[q].x = v.x;
-                    hr[q].y = v.y;
-                }
-            }
+            for (int q = 0; q < NHR; ++q) hr[q] = __builtin_amdgcn_raw_buffer_load_b128(hbuf, (q * 256 + tid) * 16, 0, 2);   // nt
         }
     };
     if constexpr (!LATE) request_state();
@@ -241,30 +229,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
         for (int kk = 0; kk < NK; ++kk) cf[kk] = lds_at<bf16x8>(c_at ^ (kk << 5));
     }
     const int bad = __builtin_amdgcn_readfirstlane(lds_at<int>(base + L::flags));
-    constexpr int PX = kPC / 8, PR = PX + kPieces, NP = (L::kPath * PR + 255) / 256;   // 16-byte pieces of a path node's x row; of both
+    using Path = PathRows<S, 256, L::kPath, true>;
     [[maybe_unused]] int plen = 0;
-    u32x4 pr[NP];
+    u32x4 pr[Path::kPieces];
     [[maybe_unused]] auto request_path = [&](int first) {
-        const int total = min(plen - first, L::kPath) * PR;
         const char *xb = reinterpret_cast<const char *>(R.x + (uint64_t)(uint32_t)(b * R.pn) * (uint32_t)R.x_sn + (size_t)h * P + p0);
         const char *Bp = reinterpret_cast<const char *>(R.Bm + (uint64_t)(uint32_t)(b * R.pn) * (uint32_t)R.b_sn + (size_t)g * S);
-        const uint32_t t = fresh(tid);
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {                // (clamped: the last piece again past the end)
-            const uint32_t idx = min(q * 256 + t, (uint32_t)total - 1), c = idx % PR, node = lds_at<unsigned char>(base + L::node + first + idx / PR);
-            pr[q] = *reinterpret_cast<const u32x4 *>(c < PX ? xb + (uint32_t)(node * (int)R.x_sn + c * 8) * 2u
-                                                            : Bp + (uint32_t)(node * (int)R.b_sn + (c - PX) * 8) * 2u);
-        }
+        Path::request(pr, R, xb, Bp, base + L::node + first, plen - first, fresh(tid));
     };
-    [[maybe_unused]] auto stage_path = [&](int first) {
-        const int total = min(plen - first, L::kPath) * PR;
-        const uint32_t t = fresh(tid);
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            const uint32_t idx = min(q * 256 + t, (uint32_t)total - 1), c = idx % PR, at = idx / PR;
-            lds_at<u32x4>(base + L::rows + (c < PX ? at * kPC + c * 8 : L::kPath * kPC + at * S + (c - PX) * 8) * 2) = pr[q];
-        }
-    };
+    [[maybe_unused]] auto stage_path = [&](int first) { Path::stage(pr, base + L::rows, plen - first, fresh(tid)); };
     if constexpr (RP) {
         plen = __builtin_amdgcn_readfirstlane(lds_at<int>(base + L::flags + 12));
         if (plen > 0) request_path(0);
@@ -286,13 +259,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
     if constexpr (RP) {
         const uint32_t ft = fresh(tid), l = ft & 15, kj = (ft & 63) >> 4, prow = (ft >> 6) * 16;
         const float dec = lds_at<float>(base + L::flags + 16);
-        floatx4 hv[kCols][kCW];                       // [column block][tile]
-#pragma unroll
-        for (int q = 0; q < NHR; ++q)
-#pragma unroll
-            for (int e = 0; e < kCW; ++e)
-                hv[q / 4][e][q % 4] = dec * (sizeof(HT) == 4 ? __uint_as_float(hr[q][e % 4])
-                                             : (e & 1) ? bf16_hi(hr[q][e / 2]) : bf16_lo(hr[q][e / 2]));
+        typename Tiles::Values hv;
+        Tiles::widen(hv, hr, dec);
         for (int first = 0; first < plen; first += L::kPath) {
             if (first > 0) {                          // longer paths: the next rows, a round trip for fifteen
                 request_path(first);
@@ -300,57 +268,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
                 stage_path(first);
                 __syncthreads();
             }
-            // four path nodes a turn: lane group kj holds node j of them, its weight (0 past the end of the path), its x
-            // at row l of the wave's rows (operand A) and weight * B at the lane's columns (operand B)
-            const int nl = min(plen - first, L::kPath);
-            for (int j0 = 0; j0 < nl; j0 += 4) {
-                const bool on = j0 + kj < nl;
-                const int j = min(j0 + kj, nl - 1);
-                const float cf_j = lds_at<float>(base + L::weight + (first + j) * 4);
-                const uint32_t xw = lds_at<unsigned short>(base + L::rows + (j * kPC + prow + l) * 2);
-                const float av = on ? __uint_as_float(xw << 16) : 0.f;
-#pragma unroll
-                for (int c = 0; c < kCols; ++c) {
-                    uint32_t bw[kCW / 2];
-#pragma unroll
-                    for (int w = 0; w < kCW / 2; w += 2) {
-                        const u32x2 v = lds_at<u32x2>(base + L::rows + (L::kPath * kPC + j * S + (c * 16 + l) * kCW + 2 * w) * 2);
-                        bw[w] = v.x;
-                        bw[w + 1] = v.y;
-                    }
-#pragma unroll
-                    for (int e = 0; e < kCW; ++e) {
-                        const float bv = on ? cf_j * ((e & 1) ? bf16_hi(bw[e / 2]) : bf16_lo(bw[e / 2])) : 0.f;
-                        hv[c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, hv[c][e], 0, 0, 0);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
+            Tiles::template advance<true>(hv, base + L::rows, L::kPath, base + L::weight + first * 4, min(plen - first, L::kPath), prow, l, kj);
         }
-        // the replayed state, written once (never read again by this kernel); a bf16 state is rounded once: the value
-        // written back is the operand
         const auto ho = make_store_rsrc(reinterpret_cast<HT *>(R.h_out) + (uint64_t)(uint32_t)bh * (uint32_t)(P * S) + (uint32_t)(p0 * S), (uint32_t)(kPC * S * sizeof(HT)));
-        const uint32_t wt = fresh(tid), wl = wt & 15, wrow = (wt >> 6) * 16 + ((wt & 63) >> 4) * 4;
-#pragma unroll
-        for (int q = 0; q < NHR; ++q) {
-            const uint32_t row = wrow + q % 4, col = (q / 4 * 16 + wl) * kCW;
-            uint32_t w[kCW / 2];
-#pragma unroll
-            for (int e = 0; e < kCW; e += 2) w[e / 2] = pack2(hv[q / 4][e][q % 4], hv[q / 4][e + 1][q % 4]);
-            const uint32_t dst = (uint32_t)(row * S + col) * (uint32_t)sizeof(HT);
-            const uint32_t op = base + L::tile + piece_at<S>(row, col / 8);
-            if constexpr (sizeof(HT) == 4)
-                buffer_store_through16(ho, dst, make_uint4(__float_as_uint(hv[q / 4][0][q % 4]), __float_as_uint(hv[q / 4][1][q % 4]),
-                                                           __float_as_uint(hv[q / 4][2][q % 4]), __float_as_uint(hv[q / 4][3][q % 4])));
-            if constexpr (kCW == 8) {
-                buffer_store_through16(ho, dst, make_uint4(w[0], w[1], w[2], w[3]));
-                lds_at<u32x4>(op) = u32x4{w[0], w[1], w[2], w[3]};
-            } else {
-                if constexpr (sizeof(HT) == 2)
-                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{w[0], w[1]}, ho, (int)dst, 0, 1 | 2 | 16);
-                lds_at<u32x2>(op + (col & 4) * 2) = u32x2{w[0], w[1]};
-            }
-        }
+        const uint32_t wt = fresh(tid);
+        Tiles::store(hv, ho, base + L::tile, (wt >> 6) * 16 + ((wt & 63) >> 4) * 4, wt & 15);
         if (bad) {                                    // (uniform) the state is replayed, the outputs are zeros
             bf16_t *yb = y + (uint64_t)(uint32_t)(b * n) * (uint32_t)(H.d * P) + (uint32_t)(h * P + p0);
             for (int i = (int)tid / 8; i < n; i += 32)
@@ -358,18 +280,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
             return;
         }
     } else {
-        const uint32_t ft = fresh(tid);
-#pragma unroll
-        for (int q = 0; q < NH; ++q) {
-            if constexpr (sizeof(HT) == 4) {
-                const uint32_t e = (q * 256 + ft) * 4;
-                lds_at<u32x2>(base + L::tile + piece_at<S>(e / S, e % S / 8) + (e & 4) * 2) =
-                    u32x2{pack2(__uint_as_float(hr[q].x), __uint_as_float(hr[q].y)), pack2(__uint_as_float(hr[q].z), __uint_as_float(hr[q].w))};
-            } else {                                  // a bf16 state is the operand as it comes
-                const uint32_t e = (q * 256 + ft) * 8;
-                lds_at<u32x4>(base + L::tile + piece_at<S>(e / S, e % S / 8)) = hr[q];
-            }
-        }
+        stage_state<S, 256, HT>(hr, base + L::tile, fresh(tid));
     }
     __builtin_amdgcn_sched_barrier(0);
     {
@@ -424,29 +335,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
             if (kk + kAhead < NK) bo[kk % kAhead] = lds_at<bf16x8>(b_at ^ ((kk + kAhead) << 5));
             __builtin_amdgcn_sched_barrier(0);
         }
-        // bit 8(r/4) + r%4 of `word` <-> Gt's register r
         const uint32_t word = lds_at<uint32_t>(base + L::mask + J * 256 + i * 4) >> (4 * lh), u_at = fresh(base + L::u + 16 * lh + J * (kRB * 4));
         u32x4 m[2];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const f32x4 u = lds_at<f32x4>(u_at + 8 * q * 4);
-            float v[4];
-            f32x4 f;
-            if (wide) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) f[e] = __builtin_amdgcn_exp2f(s2_i - u[e]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) f[e] = e_i * u[e];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e)               // bitwise select: an overflow under a cleared mask bit never reaches M
-                v[e] = __uint_as_float(__float_as_uint(gt[4 * q + e] * f[e]) & bit_as_mask(word, 8 * q + e));
-            m[q / 2][2 * (q % 2)] = pack2(v[0], v[1]);
-            m[q / 2][2 * (q % 2) + 1] = pack2(v[2], v[3]);
-            // (formed here: the compiler would put all of this off to the end, behind the branches, and keep f until then)
-            asm volatile("" : "+v"(m[q / 2][2 * (q % 2)]), "+v"(m[q / 2][2 * (q % 2) + 1]));
-        }
+        weigh(m, gt, word, u_at, s2_i, e_i, wide);
         const uint32_t x_at = fresh(x_lane + J * (kRB * 64));
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
