@@ -15,6 +15,7 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <memory>
 #include <vector>
 
 #include "../../include/stree.h"
@@ -56,24 +57,37 @@ struct Owned {
     Owned(const Owned &) = delete;
     ~Owned() { Py_DECREF(o); }
 };
-// A tensor that is read, and results made like it, without a detour through Python: no subclass, whose methods may be
-// somebody's own, and nobody listens to what is called on tensors.
-bool plain(PyObject *o) { return THPVariable_CheckExact(o) && !at::impl::torch_function_mode_enabled(); }
+// The arguments of a call, and whether somebody listens to what is called on tensors (asked for once a call: it costs as much
+// as reading a size).
+struct Arg {
+    PyObject *o;
+    bool heard;
+    operator PyObject *() const { return o; }
+    // A tensor that is read, and results made like it, without a detour through Python: no subclass, whose methods may be
+    // somebody's own.
+    bool plain() const { return THPVariable_CheckExact(o) && !heard; }
+};
+struct Args {
+    PyObject *const *v;
+    bool heard;
+    Arg operator[](int i) const { return {v[i], heard}; }
+    Arg none() const { return {Py_None, heard}; }
+};
 
 // An array argument: a plain tensor, or whatever its Python attributes say it is (shape, stride(), dtype, is_contiguous(),
 // numel(), element_size(), data_ptr()).
 class Array {
   public:
-    explicit Array(PyObject *object) : o(object), t(plain(object) ? &THPVariable_Unpack(object) : nullptr) {}
+    explicit Array(Arg a) : o(a.o), t(a.plain() ? &THPVariable_Unpack(a.o) : nullptr) {}
     at::IntArrayRef sizes() const {
         if (t) return t->sizes();
-        if (!known_size) size_ = numbers(Owned(PyObject_GetAttrString(o, "shape")).o), known_size = true;
-        return size_;
+        if (!size_) size_ = numbers(Owned(PyObject_GetAttrString(o, "shape")).o);
+        return *size_;
     }
     at::IntArrayRef strides() const {
         if (t) return t->strides();
-        if (!known_stride) stride_ = numbers(Owned(PyObject_CallMethod(o, "stride", nullptr)).o), known_stride = true;
-        return stride_;
+        if (!stride_) stride_ = numbers(Owned(PyObject_CallMethod(o, "stride", nullptr)).o);
+        return *stride_;
     }
     int64_t dim() const { return (int64_t)sizes().size(); }
     int64_t size(int64_t i) const {
@@ -100,12 +114,13 @@ class Array {
     bool same_type(const Array &b) const { return type() == b.type() && type() != at::ScalarType::Undefined; }
 
   private:
-    static std::vector<int64_t> numbers(PyObject *sequence) {
+    typedef std::unique_ptr<std::vector<int64_t>> Numbers;
+    static Numbers numbers(PyObject *sequence) {
         const Owned f(PySequence_Fast(sequence, "a sequence of sizes"));
-        std::vector<int64_t> v(PySequence_Fast_GET_SIZE(f.o));
-        for (size_t i = 0; i < v.size(); ++i) {
-            v[i] = PyLong_AsLongLong(PySequence_Fast_GET_ITEM(f.o, (Py_ssize_t)i));
-            if (v[i] == -1 && PyErr_Occurred()) throw Raised{};
+        Numbers v(new std::vector<int64_t>(PySequence_Fast_GET_SIZE(f.o)));
+        for (size_t i = 0; i < v->size(); ++i) {
+            (*v)[i] = PyLong_AsLongLong(PySequence_Fast_GET_ITEM(f.o, (Py_ssize_t)i));
+            if ((*v)[i] == -1 && PyErr_Occurred()) throw Raised{};
         }
         return v;
     }
@@ -116,10 +131,9 @@ class Array {
     }
     PyObject *o;
     const at::Tensor *t;
-    mutable std::vector<int64_t> size_, stride_;
-    mutable bool known_size = false, known_stride = false;
+    mutable Numbers size_, stride_;
 };
-void *pointer(PyObject *o) { return o == Py_None ? nullptr : Array(o).data_ptr(); }
+void *pointer(Arg a) { return a.o == Py_None ? nullptr : a.plain() ? THPVariable_Unpack(a.o).data_ptr() : Array(a).data_ptr(); }
 // An int, or what gives one as an index (numpy's), as far as 64 bits reach: the checks see the whole value.
 int64_t integer(PyObject *o) {
     PyObject *i = PyNumber_Index(o);
@@ -148,15 +162,15 @@ int type_code(const Array &t) {
     raise(PyExc_TypeError, "unsupported dtype");
 }
 // ... of the rows, which are torch's
-int rows_code(PyObject *o) {
-    if (!THPVariable_Check(o)) raise(PyExc_TypeError, "unsupported dtype");
-    return type_code(Array(o));
+int rows_code(Arg a) {
+    if (!a.plain() && !THPVariable_Check(a.o)) raise(PyExc_TypeError, "unsupported dtype");
+    return type_code(Array(a));
 }
 // type of the SSM state from the state tensors of a call (those that are given must agree)
-int state_code(PyObject *h0, PyObject *h_out) {
-    if (h0 == Py_None) return h_out == Py_None ? STREE_F32 : type_code(Array(h_out));
+int state_code(Arg h0, Arg h_out) {
+    if (h0.o == Py_None) return h_out.o == Py_None ? STREE_F32 : type_code(Array(h_out));
     const Array h(h0);
-    require(h_out == Py_None || h_out == h0 || Array(h_out).same_type(h), "h0 and h_out must have the same dtype");
+    require(h_out.o == Py_None || h_out.o == h0.o || Array(h_out).same_type(h), "h0 and h_out must have the same dtype");
     return type_code(h);
 }
 // Element stride between tokens of a [B,N,a,b] view whose last two dims are dense and whose batch stride is N * token
@@ -173,12 +187,12 @@ int64_t token_stride(const Array &t, int64_t nnodes) {
 }
 
 stree_dims make_dims(int64_t batch, int64_t nnodes, int64_t heads, int64_t headdim, int64_t dstate, int64_t groups, int64_t width,
-                     int io, int state, int flags, PyObject *dt_bias) {
+                     int io, int state, int flags, Arg dt_bias) {
     stree_dims d = {};
     d.batch = (int32_t)batch, d.nnodes = (int32_t)nnodes, d.nheads = (int32_t)heads, d.headdim = (int32_t)headdim;
     d.dstate = (int32_t)dstate, d.ngroups = (int32_t)groups, d.conv_width = (int32_t)width;
     d.io_dtype = io, d.state_dtype = state, d.flags = flags;
-    if (dt_bias != Py_None) {
+    if (dt_bias.o != Py_None) {
         const Array b(dt_bias);
         require(b.type() == at::kFloat && b.is_contiguous() && b.numel() == heads, "dt_bias must be fp32 [H], contiguous");
         d.flags |= STREE_FLAG_DT_SOFTPLUS;
@@ -190,13 +204,16 @@ stree_dims make_dims(int64_t batch, int64_t nnodes, int64_t heads, int64_t headd
 // A result: `given`, or what torch.empty_like(o) makes (through Python where something there may want to see it).
 struct Result {
     PyObject *o = nullptr;
+    bool heard = false;
     ~Result() { Py_XDECREF(o); }
-    Array t() const { return Array(o); }
-    void *ptr() const { return pointer(o); }
-    bool keep(PyObject *given) {
-        if (given == Py_None) return false;
-        Py_INCREF(given);
-        o = given;
+    Arg arg() const { return {o, heard}; }
+    Array t() const { return Array(arg()); }
+    void *ptr() const { return pointer(arg()); }
+    bool keep(Arg given) {
+        heard = given.heard;
+        if (given.o == Py_None) return false;
+        Py_INCREF(given.o);
+        o = given.o;
         return true;
     }
     void none() { keep_none(); }
@@ -212,32 +229,32 @@ struct Result {
         o = Py_None;
     }
 };
-void like(Result &r, PyObject *given, PyObject *model) {
+void like(Result &r, Arg given, Arg model) {
     if (r.keep(given)) return;
-    if (plain(model)) {
-        r.o = THPVariable_Wrap(at::empty_like(THPVariable_Unpack(model)));
+    if (model.plain()) {
+        r.o = THPVariable_Wrap(at::empty_like(THPVariable_Unpack(model.o)));
     } else {
         PyObject *torch = PyImport_ImportModule("torch");
-        r.o = torch ? PyObject_CallMethod(torch, "empty_like", "O", model) : nullptr;
+        r.o = torch ? PyObject_CallMethod(torch, "empty_like", "O", model.o) : nullptr;
         Py_XDECREF(torch);
     }
     if (!r.o) throw Raised{};
 }
 // ... what model.new_empty(size) makes, in the type of `typed` (fp32 where that is None)
-void sized(Result &r, PyObject *given, PyObject *model, std::initializer_list<int64_t> size, PyObject *typed) {
+void sized(Result &r, Arg given, Arg model, std::initializer_list<int64_t> size, Arg typed) {
     if (r.keep(given)) return;
-    const auto type = typed == Py_None ? at::kFloat : Array(typed).type();
-    if (plain(model) && type != at::ScalarType::Undefined) {
-        r.o = THPVariable_Wrap(at::empty(at::IntArrayRef(size), THPVariable_Unpack(model).options().dtype(type).requires_grad(false)));
+    const auto type = typed.o == Py_None ? at::kFloat : Array(typed).type();
+    if (model.plain() && type != at::ScalarType::Undefined) {
+        r.o = THPVariable_Wrap(at::empty(at::IntArrayRef(size), THPVariable_Unpack(model.o).options().dtype(type).requires_grad(false)));
     } else {
         PyObject *torch = PyImport_ImportModule("torch"), *dtype = nullptr, *shape = nullptr, *kw = nullptr, *args = nullptr, *f = nullptr;
-        if (torch) dtype = typed == Py_None ? PyObject_GetAttrString(torch, "float32") : PyObject_GetAttrString(typed, "dtype");
+        if (torch) dtype = typed.o == Py_None ? PyObject_GetAttrString(torch, "float32") : PyObject_GetAttrString(typed.o, "dtype");
         shape = PyTuple_New((Py_ssize_t)size.size());
         Py_ssize_t i = 0;
         for (int64_t n : size) PyTuple_SET_ITEM(shape, i++, PyLong_FromLongLong(n));
         if (dtype) kw = Py_BuildValue("{s:O}", "dtype", dtype);
         args = Py_BuildValue("(O)", shape);
-        if (kw) f = PyObject_GetAttrString(model, "new_empty");
+        if (kw) f = PyObject_GetAttrString(model.o, "new_empty");
         if (f) r.o = PyObject_Call(f, args, kw);
         Py_XDECREF(f), Py_XDECREF(args), Py_XDECREF(kw), Py_XDECREF(shape), Py_XDECREF(dtype), Py_XDECREF(torch);
     }
@@ -268,7 +285,7 @@ PyObject *pair(Result &a, Result &b) {
     return t;
 }
 
-PyObject *conv(PyObject *const *a) {
+PyObject *conv(const Args &a) {
     enum { parent, xbc_pre, conv_state, conv_w, conv_b, nheads, headdim, dstate, ngroups, silu, out, status };
     const Array x(a[xbc_pre]), w(a[conv_w]);
     dimensions(x, 3);
@@ -278,7 +295,7 @@ PyObject *conv(PyObject *const *a) {
     require(x.is_contiguous() && Array(a[conv_state]).is_contiguous() && w.is_contiguous(), "contiguous rows");
     Result y;
     like(y, a[out], a[xbc_pre]);
-    const stree_dims d = make_dims(B, N, H, P, S, G, W, rows_code(a[xbc_pre]), STREE_F32, truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0, Py_None);
+    const stree_dims d = make_dims(B, N, H, P, S, G, W, rows_code(a[xbc_pre]), STREE_F32, truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0, a.none());
     const auto p0 = (const int32_t *)pointer(a[parent]);
     const void *p1 = pointer(a[xbc_pre]), *p2 = pointer(a[conv_state]), *p3 = pointer(a[conv_w]), *p4 = pointer(a[conv_b]);
     void *p5 = y.ptr(), *st = stream();
@@ -287,7 +304,7 @@ PyObject *conv(PyObject *const *a) {
     return y.release();
 }
 
-PyObject *ssd(PyObject *const *a) {
+PyObject *ssd(const Args &a) {
     enum { parent, x, dt, A, Bm, Cm, D, h0, out, status, force_fma, general_mfma, dt_bias };
     const Array tx(a[x]), tb(a[Bm]), tc(a[Cm]);
     dimensions(tx, 4);
@@ -295,7 +312,7 @@ PyObject *ssd(PyObject *const *a) {
     const int64_t B = tx.size(0), N = tx.size(1), H = tx.size(2), P = tx.size(3), G = tb.size(2), S = tb.size(3);
     Result y;
     sized(y, a[out], a[x], {B, N, H, P}, a[x]);
-    stree_dims d = make_dims(B, N, H, P, S, G, 0, rows_code(a[x]), state_code(a[h0], Py_None),
+    stree_dims d = make_dims(B, N, H, P, S, G, 0, rows_code(a[x]), state_code(a[h0], a.none()),
                              (truth(a[force_fma]) ? STREE_FLAG_FORCE_FMA : 0) | (truth(a[general_mfma]) ? STREE_FLAG_GENERAL_MFMA : 0), a[dt_bias]);
     d.x_stride_n = token_stride(tx, N), d.b_stride_n = token_stride(tb, N), d.c_stride_n = token_stride(tc, N);
     const Array td(a[dt]);
@@ -309,7 +326,7 @@ PyObject *ssd(PyObject *const *a) {
     return y.release();
 }
 
-PyObject *commit(PyObject *const *a) {
+PyObject *commit(const Args &a) {
     enum { parent, accepted, x, dt, A, Bm, h0, h_out, xbc_pre, conv_state, conv_state_out, status, dims, dt_bias };
     Result h, cs;
     stree_dims d;
@@ -324,7 +341,7 @@ PyObject *commit(PyObject *const *a) {
         for (int i = 0; i < 4; ++i) shape[i] = integer(PySequence_Fast_GET_ITEM(s.o, i));
         like(cs, a[conv_state_out], a[conv_state]);
         d = make_dims(tp.size(0), tp.size(1), shape[0], shape[1], shape[2], shape[3], Array(a[conv_state]).size(1) + 1,
-                      rows_code(a[xbc_pre]), STREE_F32, 0, Py_None);
+                      rows_code(a[xbc_pre]), STREE_F32, 0, a.none());
         h.none();
         const auto p0 = (const int32_t *)pointer(a[parent]), p1 = (const int32_t *)pointer(a[accepted]);
         const void *p2 = pointer(a[xbc_pre]), *p3 = pointer(a[conv_state]);
@@ -347,7 +364,7 @@ PyObject *commit(PyObject *const *a) {
     } else if (!cs.keep(a[conv_state_out])) {
         cs.none();
     }
-    d = make_dims(B, N, H, P, S, G, W, rows_code(a[x]), state_code(a[h0], h.o), 0, a[dt_bias]);
+    d = make_dims(B, N, H, P, S, G, W, rows_code(a[x]), state_code(a[h0], h.arg()), 0, a[dt_bias]);
     d.x_stride_n = token_stride(tx, N), d.b_stride_n = token_stride(tb, N);
     const auto p0 = (const int32_t *)pointer(a[parent]), p1 = (const int32_t *)pointer(a[accepted]);
     const void *p2 = pointer(a[x]), *p5 = pointer(a[Bm]), *p6 = pointer(a[h0]), *p8 = pointer(a[xbc_pre]), *p9 = pointer(a[conv_state]);
@@ -358,7 +375,7 @@ PyObject *commit(PyObject *const *a) {
     return pair(h, cs);
 }
 
-PyObject *ssd_replay(PyObject *const *a) {
+PyObject *ssd_replay(const Args &a) {
     enum { pparent, paccepted, px, pdt, pBm, parent, x, dt, A, Bm, Cm, D, h0, h_out, out, status, rstatus, force_fma, dt_bias };
     const Array tx(a[x]), tb(a[Bm]), tc(a[Cm]), tpx(a[px]), tpb(a[pBm]);
     const Array tpd(a[pdt]), td(a[dt]), th(a[h0]);
@@ -371,7 +388,7 @@ PyObject *ssd_replay(PyObject *const *a) {
     Result y, h;
     sized(y, a[out], a[x], {B, N, H, P}, a[x]);
     like(h, a[h_out], a[h0]);
-    stree_dims d = make_dims(B, N, H, P, S, G, 0, rows_code(a[x]), state_code(a[h0], h.o), truth(a[force_fma]) ? STREE_FLAG_FORCE_FMA : 0, a[dt_bias]);
+    stree_dims d = make_dims(B, N, H, P, S, G, 0, rows_code(a[x]), state_code(a[h0], h.arg()), truth(a[force_fma]) ? STREE_FLAG_FORCE_FMA : 0, a[dt_bias]);
     d.x_stride_n = token_stride(tx, N), d.b_stride_n = token_stride(tb, N), d.c_stride_n = token_stride(tc, N);
     stree_replay r = {};
     r.nnodes = (int32_t)Np, r.parent = (const int32_t *)Array(a[pparent]).data_ptr();
@@ -386,7 +403,7 @@ PyObject *ssd_replay(PyObject *const *a) {
     return pair(y, h);
 }
 
-PyObject *conv_replay(PyObject *const *a) {
+PyObject *conv_replay(const Args &a) {
     enum { pparent, paccepted, pxbc_pre, parent, xbc_pre, conv_state, conv_w, conv_b, nheads, headdim, dstate, ngroups, silu, out,
            conv_state_out, status, rstatus };
     const Array x(a[xbc_pre]), w(a[conv_w]), px(a[pxbc_pre]), cs(a[conv_state]);
@@ -400,7 +417,7 @@ PyObject *conv_replay(PyObject *const *a) {
     like(y, a[out], a[xbc_pre]);
     like(c, a[conv_state_out], a[conv_state]);
     require(c.t().data_ptr() != cs.data_ptr(), "conv_state_out must not be conv_state");
-    const stree_dims d = make_dims(B, N, H, P, S, G, W, rows_code(a[xbc_pre]), STREE_F32, truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0, Py_None);
+    const stree_dims d = make_dims(B, N, H, P, S, G, W, rows_code(a[xbc_pre]), STREE_F32, truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0, a.none());
     stree_replay r = {};
     r.nnodes = (int32_t)Np, r.parent = (const int32_t *)Array(a[pparent]).data_ptr();
     r.accepted = (const int32_t *)Array(a[paccepted]).data_ptr();
@@ -412,7 +429,7 @@ PyObject *conv_replay(PyObject *const *a) {
     return pair(y, c);
 }
 
-PyObject *step(PyObject *const *a) {
+PyObject *step(const Args &a) {
     enum { pparent, paccepted, pxbc_pre, pxbc_out, pdt, parent, xbc_pre, conv_state, conv_w, conv_b, dt, A, D, h0, nheads, headdim, dstate,
            ngroups, silu, xbc_out, conv_state_out, h_out, out, status, rstatus, force_fma, dt_bias };
     const Array x(a[xbc_pre]), w(a[conv_w]), px(a[pxbc_pre]), po(a[pxbc_out]);
@@ -431,7 +448,7 @@ PyObject *step(PyObject *const *a) {
     sized(y, a[out], a[xbc_pre], {B, N, H, P}, a[xbc_pre]);
     require(xo.t().is_contiguous() && y.t().is_contiguous() && h.t().is_contiguous(), "dense results");
     require(c.t().data_ptr() != cs.data_ptr(), "conv_state_out must not be conv_state");
-    const stree_dims d = make_dims(B, N, H, P, S, G, W, rows_code(a[xbc_pre]), state_code(a[h0], h.o),
+    const stree_dims d = make_dims(B, N, H, P, S, G, W, rows_code(a[xbc_pre]), state_code(a[h0], h.arg()),
                                    (truth(a[silu]) ? STREE_FLAG_CONV_SILU : 0) | (truth(a[force_fma]) ? STREE_FLAG_FORCE_FMA : 0), a[dt_bias]);
     stree_replay r = {};
     r.nnodes = (int32_t)Np, r.parent = (const int32_t *)Array(a[pparent]).data_ptr();
@@ -451,7 +468,7 @@ PyObject *step(PyObject *const *a) {
     return PyTuple_Pack(4, y.o, h.o, xo.o, c.o);
 }
 
-PyObject *gate(PyObject *const *a) {
+PyObject *gate(const Args &a) {
     enum { y, z, norm_w, ngroups, eps, out };
     const Array ty(a[y]), tz(a[z]), tw(a[norm_w]);
     dimensions(ty, 4);
@@ -459,7 +476,7 @@ PyObject *gate(PyObject *const *a) {
     require(ty.is_contiguous() && tz.sizes() == ty.sizes() && tz.same_type(ty) && tw.numel() == H * P, "y, z and norm_w agree");
     Result o;
     like(o, a[out], a[y]);
-    const stree_dims d = make_dims(B, N, H, P, 1, integer(a[ngroups]), 0, rows_code(a[y]), STREE_F32, 0, Py_None);
+    const stree_dims d = make_dims(B, N, H, P, 1, integer(a[ngroups]), 0, rows_code(a[y]), STREE_F32, 0, a.none());
     const int64_t zs = token_stride(tz, N);
     const float e = (float)PyFloat_AsDouble(a[eps]);
     if (PyErr_Occurred()) throw Raised{};
@@ -469,7 +486,7 @@ PyObject *gate(PyObject *const *a) {
     return o.release();
 }
 
-PyObject *linear(PyObject *const *a) {
+PyObject *linear(const Args &a) {
     enum { x, dt, A, Bm, Cm, D, h0, want_y, out, h_out, dt_bias };
     const Array tx(a[x]), tb(a[Bm]), td(a[dt]);
     dimensions(tx, 4);
@@ -481,7 +498,7 @@ PyObject *linear(PyObject *const *a) {
     if (wanted) sized(y, a[out], a[x], {B, T, H, P}, a[x]);
     else y.none();
     sized(h, a[h_out], a[x], {B, H, P, S}, a[h0]);
-    stree_dims d = make_dims(B, T, H, P, S, G, 0, rows_code(a[x]), state_code(a[h0], h.o), 0, a[dt_bias]);
+    stree_dims d = make_dims(B, T, H, P, S, G, 0, rows_code(a[x]), state_code(a[h0], h.arg()), 0, a[dt_bias]);
     d.x_stride_n = token_stride(tx, T), d.b_stride_n = token_stride(tb, T);
     d.c_stride_n = a[Cm] == Py_None ? 0 : token_stride(Array(a[Cm]), T);
     const void *p0 = pointer(a[x]), *p3 = pointer(a[Bm]), *p4 = pointer(a[Cm]), *p6 = pointer(a[h0]);
@@ -491,7 +508,7 @@ PyObject *linear(PyObject *const *a) {
     return pair(y, h);
 }
 
-template <PyObject *(*F)(PyObject *const *), int kArgs>
+template <PyObject *(*F)(const Args &), int kArgs>
 PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     if (n != kArgs) {
@@ -499,7 +516,7 @@ PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
         return nullptr;
     }
     try {
-        return F(args);
+        return F(Args{args, at::impl::torch_function_mode_enabled()});
     } catch (const Raised &) {
         return nullptr;
     }

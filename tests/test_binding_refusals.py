@@ -181,7 +181,7 @@ def _native_order():
         text = f.read()
     order = {}
     for name, function, count in re.findall(r'STREE_METHOD\("(\w+)", (\w+), (\d+)\)', text):
-        body = re.search(r"PyObject \*%s\(PyObject \*const \*a\) \{\s*enum \{([^}]*)\}" % function, text).group(1)
+        body = re.search(r"PyObject \*%s\(const Args &a\) \{\s*enum \{([^}]*)\}" % function, text).group(1)
         order["stree_" + name] = ([SHORT.get(n, n) for n in re.findall(r"\w+", body)], int(count))
     return order
 
