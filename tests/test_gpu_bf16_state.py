@@ -29,15 +29,15 @@ def _inputs(seed, B, N, H, P, S, G):
 
 
 SCAN_CASES = [
-    (3, 64, 4, 64, 128, 1, {}),                         # persistent kernel, one node block
+    (3, 64, 4, 64, 128, 1, {}),                         # at most 64 nodes, a workgroup per head
     (2, 37, 4, 128, 128, 2, {}),
     (2, 20, 4, 64, 64, 1, {}),
-    (2, 128, 4, 64, 128, 1, {}),                        # persistent kernel over node blocks
+    (2, 128, 4, 64, 128, 1, {}),                        # 65 to 256 nodes, waves of 32 nodes
     (2, 200, 4, 64, 64, 2, {}),
-    (2, 200, 4, 64, 128, 1, {"general_mfma": True}),    # one workgroup per (sequence, head)
+    (2, 200, 4, 64, 128, 1, {"general_mfma": True}),    # the general MFMA kernel
     (2, 50, 3, 32, 64, 1, {}),
     (2, 150, 2, 128, 128, 1, {}),
-    (2, 64, 3, 64, 256, 1, {}),                         # dstate 256 on the persistent kernels
+    (2, 64, 3, 64, 256, 1, {}),                         # dstate 256
     (2, 180, 3, 64, 256, 1, {}),
     (2, 90, 3, 64, 128, 1, {"force_fma": True}),        # fp32 FMA kernel
     (2, 30, 3, 24, 40, 1, {}),                          # (a shape only the FMA kernel takes)
@@ -85,7 +85,7 @@ def test_commit_into_a_bf16_state(st, oracle, B, N, H, P, S, G):
 @pytest.mark.parametrize("Np,N,P,S", [(64, 64, 64, 128), (23, 50, 64, 64), (40, 33, 128, 128), (100, 40, 64, 128),
                                       (30, 130, 64, 128), (50, 60, 64, 256), (40, 140, 64, 256)])
 def test_replay_and_step_with_a_bf16_state(st, oracle, Np, N, P, S):
-    """Fused replay + scan (one kernel when both trees have at most 64 nodes, otherwise two): the state it
+    """Replay + scan (one kernel when both trees have at most 64 nodes or this one 65 to 128, otherwise two): the state it
     writes is the oracle's commit within one rounding, and y is the scan FROM THAT ROUNDED STATE (the value
     written back is the value scanned from).  The step in one call equals the two fused calls bit for bit."""
     B, H, G, W = 3, 4, 1, 4
@@ -199,7 +199,7 @@ def test_bf16_state_must_start_on_a_16_byte_boundary(st):
 @pytest.mark.parametrize("Np,N", [(50, 64), (90, 140)])
 def test_bf16_state_together_with_the_in_kernel_step_size(st, oracle, Np, N):
     """Both variants at once (raw dt + bias, state in bf16) through the fused replay + scan: one kernel for
-    trees of at most 64 nodes, commit followed by the scan kernel of larger trees otherwise."""
+    trees of at most 64 nodes, commit followed by the scan for one of more than 128."""
     B, H, P, S, G = 2, 4, 64, 128, 1
     io = "bf16"
     rng = np.random.default_rng(9950 + N)

@@ -1,6 +1,6 @@
-"""GPU parity of the persistent tree-scan kernel for trees of 65 .. 256 nodes (several node blocks
-per unit, several units per workgroup) against the CPU oracle, and against the
-one-workgroup-per-unit MFMA kernel that it replaces for these shapes."""
+"""GPU parity of the tree-scan kernel for trees of 65 .. 256 nodes (a workgroup per head whose waves own
+blocks of 32 nodes) against the CPU oracle, and against the general MFMA kernel that it replaces for
+these shapes."""
 import numpy as np
 import pytest
 
@@ -10,12 +10,12 @@ from test_gpu_parity import _rand, _run_ssd, _trees, st  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
 
-# (B, N, H, P, S, G): one and several units per workgroup run (the grid stops at 512 workgroups),
-# runs that cross a sequence and a group boundary, ragged last blocks, every head shape the kernel takes
+# (B, N, H, P, S, G): heads of one and of several groups, more of them than are resident at once, ragged
+# last blocks, every head shape the kernel takes
 SHAPES = [(3, 65, 2, 64, 128, 1), (2, 100, 6, 64, 128, 3), (3, 128, 4, 64, 64, 2), (2, 129, 3, 64, 128, 1),
           (2, 192, 4, 64, 128, 2), (3, 255, 2, 64, 64, 1), (2, 256, 8, 64, 128, 8),
           (9, 70, 64, 64, 128, 4), (5, 130, 120, 64, 128, 1),
-          # the wide tiles (one workgroup per CU): dstate 256, headdim 128; more units than workgroups
+          # dstate 256, headdim 128 (two workgroups a head)
           (2, 100, 3, 64, 256, 1), (2, 256, 4, 64, 256, 2), (3, 129, 2, 128, 128, 1), (2, 250, 4, 128, 128, 2),
           (5, 70, 60, 128, 128, 2)]
 
@@ -29,8 +29,8 @@ def test_blocks_kernel_against_oracle(st, oracle, B, N, H, P, S, G):
     got = _run_ssd(st, "bf16", parent, x, dt, A, Bm, Cm, D, h0)
     for b in range(B):
         assert_parity(got[b], want[b], TOL["bf16"], f"blocks kernel B={B} N={N} H={H} b={b}", kind="y")
-    # the one-workgroup-per-unit kernel forms the same products; its decay weights come from expf
-    # instead of exp2, so an operand may round to the neighbouring bf16 value
+    # the general kernel forms the same products; its decay weights come from expf instead of exp2 or a
+    # product of two factors, so an operand may round to the neighbouring bf16 value
     other = _run_ssd(st, "bf16", parent, x, dt, A, Bm, Cm, D, h0, general_mfma=True)
     assert_parity(got, other.astype(np.float64), TOL["bf16"], "blocks kernel vs general MFMA kernel", kind="y")
 

@@ -109,9 +109,8 @@ def test_tree_conv_width_3_bf16(st, oracle):
 
 
 def test_fused_replay_scan_long_runs_against_oracle(st, oracle):
-    """Batch 33 x 80 heads: 2640 units on 512 workgroups, runs of 5 and 6 units that cross sequences,
-    and a unit count that does not divide over the eight XCDs -- against the oracle's commit followed
-    by its path-unrolled scan (not against another GPU kernel)."""
+    """Batch 33 x 80 heads: 2640 heads, twice as many as are resident at once, the state requested late -- against
+    the oracle's commit followed by its path-unrolled scan (not against another GPU kernel)."""
     io, B, N, H, P, S, G = "bf16", 33, 64, 80, 64, 128, 1
     rng = np.random.default_rng(933)
     parent = np.stack([synth.gen_tree(N, int(rng.integers(4, 9)), 4, rng) for _ in range(B)]).astype(np.int32)

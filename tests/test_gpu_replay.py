@@ -37,8 +37,8 @@ def _run(st, io, pp, acc, prev, p, cur, A, D, h_io=None, **kw):
     return to_host(y), to_host(h)
 
 
-# single-pass kernel shapes (both trees of at most 64 nodes, bf16, MFMA head shapes), several
-# units per workgroup, and shapes that take the two-kernel route
+# single-pass kernel shapes (both trees of at most 64 nodes, or this one 65 to 128; bf16, MFMA head shapes; a workgroup
+# per head and, with 1280 heads, the persistent kernel) and shapes that take the two-kernel route
 SHAPES = [("bf16", 5, 40, 64, 6, 64, 128, 2), ("bf16", 3, 64, 30, 4, 64, 64, 1), ("bf16", 2, 20, 64, 3, 128, 128, 1),
           ("bf16", 16, 33, 57, 80, 64, 128, 1), ("bf16", 2, 100, 64, 4, 64, 128, 1), ("bf16", 2, 30, 130, 4, 64, 128, 2),
           ("f32", 2, 25, 31, 3, 24, 20, 1), ("bf16", 4, 64, 64, 6, 64, 256, 2), ("bf16", 3, 17, 40, 3, 64, 256, 1)]
@@ -214,8 +214,7 @@ def test_conv_replay_matches_commit_then_conv(st, oracle, io, W, N, Np):
 
 @pytest.mark.parametrize("B", [33, 96])
 def test_fused_kernel_equals_commit_then_scan_at_large_batches(st, B):
-    """Runs of 6 to 15 units per workgroup, and a unit count that does not divide over the eight
-    XCDs: the fused kernel against stree_commit_state followed by stree_tree_ssd on the same
+    """Two and six rounds of workgroups, the state requested late: the fused kernel against stree_commit_state followed by stree_tree_ssd on the same
     device inputs (the replay arithmetic is the same chain of fp32 FMAs in path order in both)."""
     import torch
     N, H, P, S, G = 64, 80, 64, 128, 1

@@ -87,7 +87,7 @@ def _same(a, b, what):
         assert torch.equal(uh, vh), f"{what}: {nm} differs from the two-call sequence"
 
 
-# several units per workgroup run, runs that cross a sequence or a group boundary, ragged node
+# heads of several sequences and groups, more of them than are resident at once, ragged node
 # counts, previous tree of another size
 STEP_SHAPES = [(3, 64, 64, 5, 64, 128, 1), (2, 37, 50, 4, 64, 128, 2), (4, 1, 13, 3, 64, 64, 1),
                (2, 64, 1, 2, 128, 128, 1), (20, 20, 64, 80, 64, 128, 1), (3, 64, 64, 6, 64, 128, 3)]

@@ -28,11 +28,11 @@ def _raw(seed, B, N, H):
 
 SCAN_CASES = [
     # io, B, N, H, P, S, G, route
-    ("bf16", 3, 64, 4, 64, 128, 1, {}),                         # persistent kernel, one node block
+    ("bf16", 3, 64, 4, 64, 128, 1, {}),                         # at most 64 nodes, a workgroup per head
     ("bf16", 2, 37, 4, 128, 128, 2, {}),
-    ("bf16", 2, 128, 4, 64, 128, 1, {}),                        # persistent kernel over node blocks
+    ("bf16", 2, 128, 4, 64, 128, 1, {}),                        # 65 to 256 nodes, waves of 32 nodes
     ("bf16", 2, 200, 4, 64, 64, 2, {}),
-    ("bf16", 2, 200, 4, 64, 128, 1, {"general_mfma": True}),    # one workgroup per (sequence, head)
+    ("bf16", 2, 200, 4, 64, 128, 1, {"general_mfma": True}),    # the general MFMA kernel
     ("bf16", 2, 50, 3, 32, 64, 1, {}),
     ("bf16", 2, 90, 3, 64, 128, 1, {"force_fma": True}),        # fp32 FMA kernel, bf16 storage
     ("f32", 2, 15, 4, 64, 64, 1, {}),                           # fp32 path
@@ -65,7 +65,7 @@ def test_commit_takes_softplus_of_raw_dt(st, oracle, io, B, N, H, P, S, G):
 
 @pytest.mark.parametrize("Np,N", [(64, 64), (23, 50), (100, 40), (30, 130)])
 def test_replay_and_step_take_softplus_of_raw_dt(st, oracle, Np, N):
-    """The fused replay + scan (both trees within 64 nodes: one kernel; otherwise two), and the whole step in
+    """The fused replay + scan (one kernel for both trees within 64 nodes or this one of 65 to 128; otherwise two), and the whole step in
     one call, which must equal the two fused calls bit for bit."""
     B, H, P, S, G, W = 3, 4, 64, 128, 1, 4
     io = "bf16"

@@ -87,6 +87,11 @@ def test_unit_kernel_replay_at_the_lines_between_its_forms(st, oracle, B, N, H, 
     _replay(st, oracle, B, N, 21, H, P, S, 1, state, 190 + B + N)
 
 
+def test_persistent_replay_of_several_groups(st, oracle):
+    """Runs of two and three heads that cross groups and sequences (512 workgroups for 1072 heads in 4 groups)."""
+    _replay(st, oracle, 67, 60, 21, 16, 64, 128, 4, "f32", 990)
+
+
 @pytest.mark.parametrize("B,N,H,S", [(65, 49, 16, 128), (64, 49, 16, 128), (65, 48, 16, 128), (106, 50, 16, 64), (107, 50, 16, 64),
                                        (49, 57, 16, 128), (49, 56, 16, 128), (81, 45, 16, 128), (81, 44, 16, 128), (69, 57, 16, 64)])
 def test_unit_kernel_scan_at_the_lines_between_its_forms(st, oracle, B, N, H, S):
@@ -96,7 +101,8 @@ def test_unit_kernel_scan_at_the_lines_between_its_forms(st, oracle, B, N, H, S)
     assert_parity(_run_ssd(st, "bf16", parent, x, dt, A, Bm, Cm, D, h0), want, TOL["bf16"], f"scan B={B} N={N} S={S}", kind="y")
 
 
-@pytest.mark.parametrize("B,N,H", [(65, 57, 16), (65, 56, 16), (80, 64, 16), (81, 64, 16), (65, 53, 16), (65, 52, 16), (81, 59, 16), (81, 58, 16)])
+@pytest.mark.parametrize("B,N,H", [(65, 57, 16), (65, 56, 16), (80, 64, 16), (81, 64, 16), (65, 53, 16), (65, 52, 16), (81, 59, 16), (81, 58, 16),
+                                   (165, 61, 16)])
 def test_scan_of_a_bf16_state_at_the_lines_between_its_forms(st, oracle, B, N, H):
     parent = _trees(260 + B, B, N)
     x, dt, A, Bm, Cm, D, h0 = _rand(261 + B + N, "bf16", B, N, H, 64, 128, 1)
