@@ -17,14 +17,14 @@
 // resident on a CU.  The state, half of all bytes, is requested last and used last: it streams in while the products are
 // formed, and nothing small waits behind it.  Operands read from memory as a product wants them (a lane its own row, 32
 // bytes of 32 rows an instruction) cost an L1 look-up a row: 27 us for 4 x 256 nodes where whole rows through LDS took 24.
-// Before, persistent workgroups of alternating roles with two barriers per pair of 64-node blocks (fp32 state, cold):
-// 8 x 128 nodes x 80 heads 19.8 -> 14.5 us, 16 x 128 29.9 -> 22.2, 16 x 81 28.5 -> 18.7, 4 x 256 x 128 heads 33 -> 19.1,
-// 16 x 256 x 80 70 -> 42; 16 x 128 x 40 heads of 128 42 -> 23; 16 x 128 x 32 heads, S = 256, 24 -> 18.
+// Before, persistent workgroups of alternating roles with two barriers per pair of 64-node blocks (fp32 state, rotating inputs):
+// 8 x 128 nodes x 80 heads 19.4 -> 13.7 us, 16 x 128 29.0 -> 21.9, 16 x 81 27.2 -> 18.1, 4 x 256 x 128 heads 32 -> 18.6,
+// 16 x 256 x 80 70 -> 41; 16 x 128 x 40 heads of 128 41 -> 22; 16 x 128 x 32 heads, S = 256, 24 -> 17.
 //
 // RP: the commit of the previous tree (Alg. 1: replay at the start of the next iteration) on the state while it passes
 // through the registers, for trees of at most 128 nodes; the path is worked out beside the tree's index, its rows are
 // fetched ahead of the state.  As a kernel of its own in front of the scan the commit read and wrote the state once more
-// than needed: replay + scan of 16 x 81 nodes x 80 heads 48.3 -> 28 us, 1 x 81 19.7 -> 10.1, 32 x 100 90.7 -> 52.3 us.
+// than needed: replay + scan of 16 x 81 nodes x 80 heads 46.4 -> 26.8 us, 1 x 81 19.6 -> 10.1, 32 x 100 90 -> 49 us.
 #include "common.hpp"
 #include "launch.hpp"
 #include "tiles.hpp"

@@ -20,8 +20,8 @@
 // state is advanced and done with before B is requested; five workgroups where four take 59 us for 64 x 49 nodes, 57);
 // two chains, of the tree and of the path, on two waves at once; divisions by arguments as multiplications.
 // Before, persistent workgroups of eight waves with alternating roles, replay + scan, 80 heads, S = 128: 1 x 15 nodes
-// 7.5 -> 6.5 us, 4 x 29 11.0 -> 8.9, 16 x 16 21.3 -> 20.2, 64 x 64 87.5 -> 78.8, 64 chains of 64 155 -> 99; bf16 state, 64 x
-// 49 nodes 74 -> 56; 40 heads of 128, 16 x 40 27.3 -> 23.5; scan alone, 1 x 15 nodes 5.5 -> 4.4.
+// 7.8 -> 6.7 us, 4 x 29 11.0 -> 8.9, 16 x 16 21.5 -> 20.3, 64 x 64 86 -> 78, 64 chains of 64 158 -> 93; bf16 state, 64 x
+// 49 nodes 66 -> 51; 40 heads of 128, 16 x 40 26.7 -> 22.8; scan alone, 1 x 15 nodes 5.6 -> 4.5.
 #include "common.hpp"
 #include "launch.hpp"
 #include "tiles.hpp"
