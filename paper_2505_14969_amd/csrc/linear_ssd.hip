@@ -840,13 +840,19 @@ __global__ __launch_bounds__(64 * NSEG, 2) void linear_state_kernel(
         __syncthreads();                              // (and the tiles are dead)
         float later = 0.f;
         for (int k = seg + 1; k < NSEG; ++k) later += sums[k];
+        // (in one factor; where steps grow the state so much that it is infinite, in one a segment: a state of zeros stays one)
         const float share = __builtin_amdgcn_exp2f(later);
+        const bool beyond = share > 3.4e38f;
+#pragma unroll 1
+        for (int k = beyond ? seg + 1 : NSEG - 1; k < NSEG; ++k) {
+            const float factor = beyond ? __builtin_amdgcn_exp2f(sums[k]) : share;
 #pragma unroll
-        for (int n = 0; n < NC; ++n)
+            for (int n = 0; n < NC; ++n)
 #pragma unroll
-            for (int st = 0; st < ST; ++st)
+                for (int st = 0; st < ST; ++st)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) hacc[n][st][e] *= share;
+                    for (int e = 0; e < 16; ++e) hacc[n][st][e] *= factor;
+        }
         constexpr int kSlot = NC * ST * 4 * 64;
         f32x4 *slots = reinterpret_cast<f32x4 *>(lds) + lane;
 #pragma unroll 1

@@ -38,3 +38,16 @@ def test_state_only(st, oracle, B, T, H, P, S, G, state):
     _, want = oracle.linear_scan(x, dt, A, Bm, Cm, None, None)
     _, h = st.stree_linear_ssd(*args, want_y=False)
     assert_parity(to_host(h), want, 1e-4, f"state after {T} tokens from zero", kind="state")
+
+
+@pytest.mark.parametrize("B,T,H,P,S", [(1, 512, 4, 64, 64), (1, 512, 129, 64, 64), (1, 640, 260, 64, 128)])
+def test_state_of_zeros_behind_steps_that_grow(st, oracle, B, T, H, P, S):
+    """Steps with A > 0 whose growth over all later segments is beyond fp32's range, from a state of zeros: nothing grows
+    until x comes, in the last segment."""
+    x, dt, A, Bm, _, _, _ = _rand(6400 + H, "bf16", B, T, H, P, S, 1)
+    x[:, :T - 128] = 0.0
+    dt[:] = 0.5
+    A[:] = 0.55                                          # 0.4 bits a token: 2^51 a segment of 128, 2^152 for three
+    _, want = oracle.linear_scan(x, dt, A, Bm, Bm, None, None)
+    _, h = st.stree_linear_ssd(to_dev(x, "bf16"), to_dev(dt), to_dev(A), to_dev(Bm, "bf16"), want_y=False)
+    assert_parity(to_host(h), want, 1e-4, f"state behind {T - 128} empty tokens", kind="state")
